@@ -801,6 +801,22 @@ def test_gemm_small_raw_code_kernel(qg, oracle, N, K, bits, group, M, splits):
     assert err <= TOL_BF16, err
 
 
+@pytest.mark.parametrize("N,K,bits,group,M", [
+    (25600, 2304, 4, 64, 40),        # units dealt evenly over the workgroups: blocks that two or three of them share
+    (25600, 2304, 2, 32, 100),       # ... two blocks of rows
+    (8333, 1216, 3, 64, 65),         # K ends inside a step and inside a unit; ragged N and M, a block of one row
+    (130, 64, 3, 64, 2),             # less than one step
+    (200, 1536, 2, 256, 33),         # groups of two steps of 128 k
+    (200, 1536, 3, 768, 17),         # ... of six
+    (70, 272, 4, 16, 31),            # eight groups per step, K ends inside a step
+])
+def test_gemm_small_raw_code_units(qg, oracle, N, K, bits, group, M):
+    _announce("gemm raw codes, units", N, K, bits, group, M)
+    W, X = synth.small_case(4600 + N + M, N, K, 0.02, True, m=M)
+    err = _gemm_case(qg, oracle, W, X, bits, group)
+    assert err <= TOL_BF16, err
+
+
 @pytest.mark.parametrize("tuning", [(0, 0, 0), (1, 4096, 0), (3, 8192, 0), (8, 65536, 0)])
 @pytest.mark.parametrize("N,K,group,M", [(200, 1024, 128, 16), (130, 512, 16, 7), (70, 1408, 32, 1), (300, 2304, 64, 13),
                                          (64, 11008, 128, 16), (1000, 128, 128, 9)])
