@@ -62,10 +62,69 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float4 *__restrict_
     }
 }
 
+// Least and greatest of three.
+__device__ inline float min3(float a, float b, float c)
+{
+    float r;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ inline float max3(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+template <int CTRL>
+__device__ inline float dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
+// Least lo and greatest hi of a team of neighbouring lanes, in all of them: exchanges inside a row of 16
+// lanes on the vector ALU (pairs, quads, mirrored halves and rows: once a quad agrees, its mirror
+// image is its partner), rows by lane exchanges; nothing goes through LDS.
+template <int TEAM>
+__device__ inline void team_range(float &lo, float &hi)
+{
+#define QG_TEAM_STEP(C) { const float l = dpp<C>(lo), h = dpp<C>(hi); lo = l < lo ? l : lo; hi = h > hi ? h : hi; }
+    if constexpr (TEAM >= 2) QG_TEAM_STEP(0xb1)          // quad_perm [1, 0, 3, 2]
+    if constexpr (TEAM >= 4) QG_TEAM_STEP(0x4e)          // quad_perm [2, 3, 0, 1]
+    if constexpr (TEAM >= 8) QG_TEAM_STEP(0x141)         // row_half_mirror
+    if constexpr (TEAM >= 16) QG_TEAM_STEP(0x140)        // row_mirror
+#undef QG_TEAM_STEP
+    if constexpr (TEAM >= 32) {
+        const auto l = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(lo), false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(hi), __float_as_uint(hi), false, false);
+        const float l0 = __uint_as_float(l[0]), l1 = __uint_as_float(l[1]), h0 = __uint_as_float(h[0]), h1 = __uint_as_float(h[1]);
+        lo = l0 < l1 ? l0 : l1;
+        hi = h0 > h1 ? h0 : h1;
+    }
+    if constexpr (TEAM >= 64) {
+        const auto l = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(lo), false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(hi), __float_as_uint(hi), false, false);
+        const float l0 = __uint_as_float(l[0]), l1 = __uint_as_float(l[1]), h0 = __uint_as_float(h[0]), h1 = __uint_as_float(h[1]);
+        lo = l0 < l1 ? l0 : l1;
+        hi = h0 > h1 ? h0 : h1;
+    }
+}
+
 // The same for groups of 4 * R * TEAM weights (TEAM a power of two <= 64): every lane keeps its
 // R float4 in registers, so W is read once, and handles U groups whose loads are all issued
 // before the first is reduced.  Teams of one wavefront work on neighbouring groups, so each
 // load instruction reads 1 KB of consecutive weights.
+//
+// The vector ALU is as close to the bound as memory is (a correctly rounded division is a dozen
+// instructions; with one per weight the kernel issued 38 per weight: 70 of the 84 us of 13824 x 5120
+// g64), so the codes come from a product with the reciprocal, and the division is made only where it
+// could round the other way.  With s the group's scale and |w| <= (2^b - 1) s, t = fl(w * rcp(s)) is off
+// the true quotient by less than 16 * 2^-22 (rcp: one unit in the last place; one rounding), the
+// correctly rounded quotient by less than 16 * 2^-24; both round to the same integer unless a
+// half-integer lies between them, that is within 5e-6 of t.  Lanes that see |t - rint(t)| > 0.49999, or
+// a scale whose reciprocal is near the ends of the range, divide (one weight in 50 000 otherwise).
+// By itself, W rotated: 13824 x 5120 g64 83.6 -> 68-70 us (5.1 TB/s of the bytes in and out, the rate of a
+// large copy), 11008 x 4096 g128 48 -> 40 us.
 template <int TEAM, int R, int U>
 __global__ __launch_bounds__(256) void quantize_regs(const float4 *__restrict__ W, int64_t total_groups,
                                                      int qmax, uint32_t *__restrict__ q4,
@@ -92,26 +151,42 @@ __global__ __launch_bounds__(256) void quantize_regs(const float4 *__restrict__ 
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const float4 a = v[u][r];
-            lo = a.x < lo ? a.x : lo;  hi = a.x > hi ? a.x : hi;
-            lo = a.y < lo ? a.y : lo;  hi = a.y > hi ? a.y : hi;
-            lo = a.z < lo ? a.z : lo;  hi = a.z > hi ? a.z : hi;
-            lo = a.w < lo ? a.w : lo;  hi = a.w > hi ? a.w : hi;
+            lo = min3(min3(lo, a.x, a.y), a.z, a.w);
+            hi = max3(max3(hi, a.x, a.y), a.z, a.w);
         }
-#pragma unroll
-        for (int off = TEAM / 2; off >= 1; off >>= 1) {
-            const float ol = __shfl_xor(lo, off);
-            const float oh = __shfl_xor(hi, off);
-            lo = ol < lo ? ol : lo;
-            hi = oh > hi ? oh : hi;
-        }
+        team_range<TEAM>(lo, hi);
         const float range = hi - lo;
-        float scale = 1.0f;
-        int zero = 0;
-        if (range != 0.0f) {
-            scale = range / (float)qmax;
-            zero = (int)rintf(-lo / scale);
-            zero = zero < 0 ? 0 : (zero > qmax ? qmax : zero);
+        const bool some = range != 0.0f;
+        const float scale = some ? range / (float)qmax : 1.0f;       // s = (hi - lo) / (2^b - 1)
+        const float inv = __builtin_amdgcn_rcpf(scale);
+        // z = rint(-lo / s) and the codes' rint(w / s), from products with the reciprocal
+        const float tz = -lo * inv;
+        float rz = rintf(tz);
+        float worst = fabsf(tz - rz);
+        float rq[R][4];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float w[4] = {v[u][r].x, v[u][r].y, v[u][r].z, v[u][r].w};
+            float off[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float t = w[j] * inv;
+                rq[r][j] = rintf(t);
+                off[j] = fabsf(t - rq[r][j]);
+            }
+            worst = max3(max3(worst, off[0], off[1]), off[2], off[3]);
         }
+        if (!(worst <= 0.49999f && scale >= 1e-30f && scale <= 1e30f)) {
+            rz = rintf(-lo / scale);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float w[4] = {v[u][r].x, v[u][r].y, v[u][r].z, v[u][r].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) rq[r][j] = rintf(w[j] / scale);
+            }
+        }
+        int zero = some ? (int)rz : 0;
+        zero = zero < 0 ? 0 : (zero > qmax ? qmax : zero);
         if (g >= total_groups) continue;
         if (lane == 0) {
             s[g] = scale;
@@ -119,11 +194,10 @@ __global__ __launch_bounds__(256) void quantize_regs(const float4 *__restrict__ 
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float w[4] = {v[u][r].x, v[u][r].y, v[u][r].z, v[u][r].w};
             uint32_t packed = 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                int c = (int)rintf(w[j] / scale) + zero;
+                int c = (int)rq[r][j] + zero;              // ties to even, integer add of z
                 c = c < 0 ? 0 : (c > qmax ? qmax : c);
                 packed |= (uint32_t)c << (8 * j);
             }
@@ -136,7 +210,7 @@ template <int TEAM, int R>
 int launch_regs(const float *W, int64_t groups, int qmax, uint8_t *q, float *s, uint8_t *z,
                 hipStream_t stream)
 {
-    constexpr int U = R >= 8 ? 1 : R >= 4 ? 2 : 4;
+    constexpr int U = R >= 4 ? 1 : 2;        // (8192 x 8192 g32: 1 group per team 61.9 us, 2 58.0, 4 62.7)
     const int64_t threads = (groups + U - 1) / U * TEAM;
     const int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffff) return QG_ERR_SHAPE;

@@ -45,6 +45,36 @@ QUANT_CASES = [  # N, K, bits, group, std, outliers
 ]
 
 
+@pytest.mark.parametrize("group", [16, 32, 64, 128, 256, 512, 1024, 2048, 4096, 48])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_quantize_at_the_rounding_boundaries(qg, oracle, bits, group):
+    # Weights whose quotient by the scale is a half-integer, or a few units in the last place beside one
+    # (where a product with the reciprocal may round the other way than the division), at scales over
+    # the whole range of fp32, down to those with no finite reciprocal.
+    _announce("quantize boundaries", bits, group)
+    rng = np.random.default_rng(900 + bits + group)
+    qmax = (1 << bits) - 1
+    scales = np.float32([2e-45, 1e-41, 3e-39, 1.5e-38, 9e-31, 1.1e-30, 0.02, 0.3333333, 1.0, 7.1, 9e29, 1.1e30, 1e36, 1.5e37])
+    rows = []
+    for s in scales:
+        s = np.float32(s)
+        z = int(rng.integers(0, qmax + 1))
+        half = (rng.integers(0, qmax, group) - z + 0.5).astype(np.float32)
+        w = (half * s).astype(np.float32)
+        steps = rng.integers(-4, 5, group)
+        bits32 = w.view(np.int32)
+        w = np.where((bits32 & 0x7fffffff) > 8, bits32 + steps, bits32).astype(np.int32).view(np.float32)
+        w[0], w[1] = np.float32(-z) * s, np.float32(qmax - z) * s          # fixes range and scale
+        rows.append(w)
+    W = np.stack(rows).astype(np.float32)
+    assert np.all(np.isfinite(W))
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    q, s, z = qg.qg_quantize(dev(W), bits, group)
+    assert np.array_equal(host(s).view(np.uint32), s0.view(np.uint32))
+    assert np.array_equal(host(z), z0)
+    assert np.array_equal(host(q), q0)
+
+
 @pytest.mark.parametrize("N,K,bits,group,std,outliers", QUANT_CASES)
 def test_quantize_bit_exact(qg, oracle, N, K, bits, group, std, outliers):
     _announce("quantize", N, K, bits, group)
