@@ -100,16 +100,95 @@ struct RepackArgs {
     const char *src;
     char *dst;
     size_t w_codes, w_scales, w_zeros;      // section offsets of the wide blob
+    size_t total;                           // bytes of the narrow blob
     long tiles64, tiles16, steps, wsteps, ngroups, zwords;
     int loads, gps, zbits, zb;
     int meta_zeros, code_bytes, rec_bytes;
     uint32_t flip;                          // what every code word is XORed with on its way (either way)
 };
 
-// One thread per 16-byte piece of codes, per scale and per zero word of the blob that is written
-// (the narrow records' zero words, or the wide blob's).
-template <bool TO_NARROW>
-__global__ void repack_narrow(const RepackArgs A)
+// wide -> narrow: one workgroup per record, which it writes whole (a record has no padding; the last
+// workgroup clears the blob's tail), every load of a thread ahead of its first store.  Bound by memory: the
+// bytes of both blobs once each.  (One thread per piece with 64-bit divisions to find its record, behind
+// a kernel that cleared the destination, took 20.9 us on 13824 x 5120 3-bit g64 by the profiler, 6.7 of
+// them the clearing; 63 MB.)
+template <int LOADS, int GPS>
+__global__ __launch_bounds__(256) void wide_to_narrow(const RepackArgs A)
+{
+    const unsigned wsteps = (unsigned)A.wsteps, r = blockIdx.x;
+    char *rec = A.dst + (size_t)r * A.rec_bytes;
+    if (r == (unsigned)A.tiles16 * wsteps) {
+        const size_t at = threadIdx.x * 4;
+        if ((size_t)r * A.rec_bytes + at < A.total) *(uint32_t *)(rec + at) = 0u;
+        return;
+    }
+    const unsigned T = r / wsteps, w = r - T * wsteps;
+    const size_t tile = T / 4;
+    const unsigned base64 = T % 4 * NW_OUT;
+    // thread's pieces of codes and its scales: element i = (load or group) * 64 + lane
+    constexpr int PIECES = (LOADS * QG_WAVE + 255) / 256, SCALES = (GPS * QG_WAVE + 255) / 256;
+    uint4 v[PIECES];
+    float sc[SCALES];
+#pragma unroll
+    for (int j = 0; j < PIECES; ++j) {
+        const int i = j * 256 + threadIdx.x, lane = i % QG_WAVE;
+        const size_t t = NW_SLICES * (size_t)w + (lane >> 4);
+        v[j] = make_uint4(0u, 0u, 0u, 0u);       // (a padded step meets zero scales: what its codes read as is immaterial)
+        if (i < LOADS * QG_WAVE && t < (size_t)A.steps) {
+            v[j] = ((const uint4 *)(A.src + A.w_codes))[((tile * A.steps + t) * LOADS + i / QG_WAVE) * QG_WAVE + base64 + (lane & 15)];
+            v[j].x ^= A.flip; v[j].y ^= A.flip; v[j].z ^= A.flip; v[j].w ^= A.flip;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < SCALES; ++j) {
+        const int i = j * 256 + threadIdx.x, lane = i % QG_WAVE;
+        const size_t t = NW_SLICES * (size_t)w + (lane >> 4);
+        sc[j] = 0.0f;
+        if (i < GPS * QG_WAVE && t < (size_t)A.steps)
+            sc[j] = ((const float *)(A.src + A.w_scales))[(tile * A.ngroups + t * GPS + i / QG_WAVE) * QG_WAVE + base64 + (lane & 15)];
+    }
+    // zero words: the groups of a step share one word of the wide blob (GPS divides the groups of a word)
+    uint32_t zeros = 0;
+    if ((int)threadIdx.x < 2 * A.zb) {
+        const int zper = 32 / A.zbits, lpd = 32 / A.zb;
+        const uint32_t mask = A.zb == 32 ? ~0u : (1u << A.zb) - 1u;
+        for (int li = 0; li < lpd; ++li) {
+            const int lane = threadIdx.x * lpd + li;
+            const size_t t = NW_SLICES * (size_t)w + (lane >> 4);
+            if (t >= (size_t)A.steps) continue;
+            const size_t g = t * GPS;
+            const uint32_t zw = ((const uint32_t *)(A.src + A.w_zeros))[(tile * A.zwords + g / zper) * QG_WAVE + base64 + (lane & 15)];
+            zeros |= ((zw >> (A.zbits * (int)(g % zper))) & mask) << (li * A.zb);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < PIECES; ++j) {
+        const int i = j * 256 + threadIdx.x;
+        if (i < LOADS * QG_WAVE) ((uint4 *)rec)[i] = v[j];
+    }
+#pragma unroll
+    for (int j = 0; j < SCALES; ++j) {
+        const int i = j * 256 + threadIdx.x;
+        if (i < GPS * QG_WAVE) ((float *)(rec + A.code_bytes))[i] = sc[j];
+    }
+    if ((int)threadIdx.x < 2 * A.zb) ((uint32_t *)(rec + A.code_bytes + A.meta_zeros))[threadIdx.x] = zeros;
+}
+
+template <int LOADS>
+void launch_wide_to_narrow(const RepackArgs &A, unsigned grid, hipStream_t st)
+{
+    switch (A.gps) {
+    case 1: hipLaunchKernelGGL((wide_to_narrow<LOADS, 1>), dim3(grid), dim3(256), 0, st, A); break;
+    case 2: hipLaunchKernelGGL((wide_to_narrow<LOADS, 2>), dim3(grid), dim3(256), 0, st, A); break;
+    case 4: hipLaunchKernelGGL((wide_to_narrow<LOADS, 4>), dim3(grid), dim3(256), 0, st, A); break;
+    case 8: hipLaunchKernelGGL((wide_to_narrow<LOADS, 8>), dim3(grid), dim3(256), 0, st, A); break;
+    default: hipLaunchKernelGGL((wide_to_narrow<LOADS, 16>), dim3(grid), dim3(256), 0, st, A); break;
+    }
+}
+
+// narrow -> wide: one thread per 16-byte piece of codes, per scale and per zero word of the wide blob
+// (cleared before: its padding, and the outputs past the last tile of 16, are written by nothing else).
+__global__ void narrow_to_wide(const RepackArgs A)
 {
     const size_t recs = (size_t)A.tiles16 * A.wsteps;
     const size_t per_rec = (size_t)(A.loads + A.gps) * QG_WAVE;
@@ -123,69 +202,37 @@ __global__ void repack_narrow(const RepackArgs A)
         const int lane = i % QG_WAVE;
         const long t = NW_SLICES * w + (lane >> 4), tile = T / 4;
         const int lane64 = (int)(T % 4) * NW_OUT + (lane & 15);
-        const bool real = t < A.steps;
+        if (t >= A.steps) return;
         const size_t codes_at = r * A.rec_bytes, meta_at = codes_at + A.code_bytes;
         if (i < A.loads * QG_WAVE) {
             const int ld = i / QG_WAVE;
-            const size_t wide = ((size_t)(tile * A.steps + (real ? t : 0)) * A.loads + ld) * QG_WAVE + lane64;
-            if (TO_NARROW) {
-                uint4 v = make_uint4(0u, 0u, 0u, 0u);       // (a padded step meets zero scales: what its codes read as is immaterial)
-                if (real) {
-                    v = ((const uint4 *)(A.src + A.w_codes))[wide];
-                    v.x ^= A.flip; v.y ^= A.flip; v.z ^= A.flip; v.w ^= A.flip;
-                }
-                ((uint4 *)(A.dst + codes_at))[ld * QG_WAVE + lane] = v;
-            } else if (real) {
-                uint4 v = ((const uint4 *)(A.src + codes_at))[ld * QG_WAVE + lane];
-                v.x ^= A.flip; v.y ^= A.flip; v.z ^= A.flip; v.w ^= A.flip;
-                ((uint4 *)(A.dst + A.w_codes))[wide] = v;
-            }
+            uint4 v = ((const uint4 *)(A.src + codes_at))[ld * QG_WAVE + lane];
+            v.x ^= A.flip; v.y ^= A.flip; v.z ^= A.flip; v.w ^= A.flip;
+            ((uint4 *)(A.dst + A.w_codes))[((size_t)(tile * A.steps + t) * A.loads + ld) * QG_WAVE + lane64] = v;
         } else {
             const int gs = i / QG_WAVE - A.loads;
-            const size_t wide = (size_t)(tile * A.ngroups + (real ? t * A.gps + gs : 0)) * QG_WAVE + lane64;
-            if (TO_NARROW) ((float *)(A.dst + meta_at))[gs * QG_WAVE + lane] = real ? ((const float *)(A.src + A.w_scales))[wide] : 0.0f;
-            else if (real) ((float *)(A.dst + A.w_scales))[wide] = ((const float *)(A.src + meta_at))[gs * QG_WAVE + lane];
+            ((float *)(A.dst + A.w_scales))[(size_t)(tile * A.ngroups + t * A.gps + gs) * QG_WAVE + lane64] =
+                ((const float *)(A.src + meta_at))[gs * QG_WAVE + lane];
         }
         return;
     }
     e -= recs * per_rec;
-    if (TO_NARROW) {
-        const int words = 2 * A.zb;                                 // zero words of a record
-        if (e >= recs * words) return;
-        const size_t r = e / words;
-        const int d = (int)(e % words);
-        const long w = (long)(r % A.wsteps), T = (long)(r / A.wsteps);
-        uint32_t val = 0;
-        for (int li = 0; li < lpd; ++li) {
-            const int lane = d * lpd + li;
-            const long t = NW_SLICES * w + (lane >> 4);
-            if (t >= A.steps) continue;
-            const int lane64 = (int)(T % 4) * NW_OUT + (lane & 15);
-            for (int gs = 0; gs < A.gps; ++gs) {
-                const long g = t * A.gps + gs;
-                const uint32_t zw = ((const uint32_t *)(A.src + A.w_zeros))[(size_t)((T / 4) * A.zwords + g / zper) * QG_WAVE + lane64];
-                val |= ((zw >> (A.zbits * (int)(g % zper))) & zmask) << (li * A.zb + gs * A.zbits);
-            }
+    if (e >= (size_t)A.tiles64 * A.zwords * QG_WAVE) return;
+    const int lane64 = (int)(e % QG_WAVE);
+    const long zw = (long)((e / QG_WAVE) % A.zwords), tile = (long)(e / QG_WAVE / A.zwords);
+    const long T = tile * 4 + lane64 / NW_OUT;
+    uint32_t val = 0;
+    if (T < A.tiles16)
+        for (int f = 0; f < zper; ++f) {
+            const long g = zw * zper + f;
+            if (g >= A.ngroups) break;
+            const long t = g / A.gps;
+            const int gs = (int)(g % A.gps), lane = (int)(t % NW_SLICES) * NW_OUT + lane64 % NW_OUT;
+            const size_t meta_at = ((size_t)T * A.wsteps + t / NW_SLICES) * A.rec_bytes + A.code_bytes;
+            const uint32_t word = ((const uint32_t *)(A.src + meta_at + A.meta_zeros))[lane / lpd];
+            val |= ((word >> ((lane % lpd) * A.zb + gs * A.zbits)) & zmask) << (A.zbits * f);
         }
-        ((uint32_t *)(A.dst + r * A.rec_bytes + A.code_bytes + A.meta_zeros))[d] = val;
-    } else {
-        if (e >= (size_t)A.tiles64 * A.zwords * QG_WAVE) return;
-        const int lane64 = (int)(e % QG_WAVE);
-        const long zw = (long)((e / QG_WAVE) % A.zwords), tile = (long)(e / QG_WAVE / A.zwords);
-        const long T = tile * 4 + lane64 / NW_OUT;
-        uint32_t val = 0;
-        if (T < A.tiles16)
-            for (int f = 0; f < zper; ++f) {
-                const long g = zw * zper + f;
-                if (g >= A.ngroups) break;
-                const long t = g / A.gps;
-                const int gs = (int)(g % A.gps), lane = (int)(t % NW_SLICES) * NW_OUT + lane64 % NW_OUT;
-                const size_t meta_at = ((size_t)T * A.wsteps + t / NW_SLICES) * A.rec_bytes + A.code_bytes;
-                const uint32_t word = ((const uint32_t *)(A.src + meta_at + A.meta_zeros))[lane / lpd];
-                val |= ((word >> ((lane % lpd) * A.zb + gs * A.zbits)) & zmask) << (A.zbits * f);
-            }
-        ((uint32_t *)(A.dst + A.w_zeros))[e] = val;
-    }
+    ((uint32_t *)(A.dst + A.w_zeros))[e] = val;
 }
 
 __global__ void zero_bytes16(uint4 *p, size_t n)
@@ -562,17 +609,20 @@ int repack(const void *src, void *dst, int64_t N, int64_t K, int bits, int group
     A.meta_zeros = L.meta_zeros; A.code_bytes = L.code_bytes; A.rec_bytes = L.rec_bytes;
     A.loads = L.loads; A.gps = L.gps;
     A.flip = bits == 4 ? 0x80808080u : 0u;
-    const size_t elements = (size_t)L.tiles16 * L.wsteps * (L.loads + L.gps) * QG_WAVE +
-                            (to_narrow ? (size_t)L.tiles16 * L.wsteps * 2 * L.zb : (size_t)L.wide.tiles * L.wide.zwords * QG_WAVE);
+    A.total = L.total;
+    const size_t recs = (size_t)L.tiles16 * L.wsteps;
+    if (to_narrow) {
+        if (recs + 1 > 0x7fffffffu) return QG_ERR_SHAPE;
+        if (L.loads == 4) launch_wide_to_narrow<4>(A, (unsigned)recs + 1, st);
+        else launch_wide_to_narrow<6>(A, (unsigned)recs + 1, st);
+        return qg_launch_status();
+    }
+    const size_t elements = recs * (L.loads + L.gps) * QG_WAVE + (size_t)L.wide.tiles * L.wide.zwords * QG_WAVE;
     if ((elements + 255) / 256 > 0x7fffffffu) return QG_ERR_SHAPE;
-    const unsigned blocks = (unsigned)((elements + 255) / 256);
-    // the destination is cleared first: the padding of its records or sections, and (wide) the
-    // outputs past the last tile of 16, are written by nothing else
-    const size_t n16 = (to_narrow ? L.total : L.wide.total) / 16;
+    const size_t n16 = L.wide.total / 16;
     hipLaunchKernelGGL(zero_bytes16, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st, (uint4 *)dst, n16);
     if (qg_launch_status() != QG_OK) return QG_ERR_DEVICE;
-    if (to_narrow) hipLaunchKernelGGL(repack_narrow<true>, dim3(blocks), dim3(256), 0, st, A);
-    else hipLaunchKernelGGL(repack_narrow<false>, dim3(blocks), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(narrow_to_wide, dim3((unsigned)((elements + 255) / 256)), dim3(256), 0, st, A);
     return qg_launch_status();
 }
 }  // namespace

@@ -161,16 +161,15 @@ template <int FB> constexpr int span_of() { return FB == 3 ? 512 : 256; }
 //   per tile:   P [tile][word][lane]         (TILED = true; lanes past N hold zero words)
 // `words` = words per row.  Each wavefront of the workgroup takes a quarter of the block's runs.
 template <int FB, bool TILED>
-__global__ __launch_bounds__(PK_THREADS) void stream_pack(const uint8_t *__restrict__ v, int64_t N,
+__device__ inline void stream_pack(int64_t block, uint8_t *lds, const uint8_t *__restrict__ v, int64_t N,
                                                           int64_t cols, int64_t words, int spans,
                                                           bool wide, uint32_t *__restrict__ P)
 {
     using R = Run<FB>;
     constexpr int SPAN = span_of<FB>(), PITCH = SPAN + 16;
     constexpr int RUNS = SPAN / R::CODES / 4;            // per wavefront
-    __shared__ __align__(16) uint8_t lds[QG_WAVE * PITCH];
-    const int64_t tile = blockIdx.x / spans;
-    const int span = blockIdx.x % spans;
+    const int64_t tile = block / spans;
+    const int span = block % spans;
     rows_to_lds<SPAN>(v, N, cols, tile * QG_WAVE, (int64_t)span * SPAN, wide, lds);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -201,16 +200,15 @@ __global__ __launch_bounds__(PK_THREADS) void stream_pack(const uint8_t *__restr
 }
 
 template <int FB, bool TILED>
-__global__ __launch_bounds__(PK_THREADS) void stream_unpack(const uint32_t *__restrict__ P, int64_t N,
+__device__ inline void stream_unpack(int64_t block, uint8_t *lds, const uint32_t *__restrict__ P, int64_t N,
                                                             int64_t cols, int64_t words, int spans,
                                                             bool wide, uint8_t *__restrict__ v)
 {
     using R = Run<FB>;
     constexpr int SPAN = span_of<FB>(), PITCH = SPAN + 16;
     constexpr int RUNS = SPAN / R::CODES / 4;
-    __shared__ __align__(16) uint8_t lds[QG_WAVE * PITCH];
-    const int64_t tile = blockIdx.x / spans;
-    const int span = blockIdx.x % spans;
+    const int64_t tile = block / spans;
+    const int span = block % spans;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t n = tile * QG_WAVE + lane;
     if (TILED || n < N) {
@@ -272,7 +270,7 @@ __device__ inline void cell_unpack(const uint32_t *w, uint32_t *d)
 // q [N][K] -> codes uint4 [tile][unit][plane][lane].  A workgroup takes one tile and
 // 4 * UPW consecutive units; a wavefront UPW of them, lane = output.
 template <int BITS>
-__global__ __launch_bounds__(PK_THREADS) void device_pack_codes(const uint8_t *__restrict__ q, int64_t N,
+__device__ inline void device_pack_codes(int64_t block, uint8_t *lds, const uint8_t *__restrict__ q, int64_t N,
                                                                 int64_t K, int64_t units, int spans,
                                                                 bool wide, uint4 *__restrict__ out)
 {
@@ -281,9 +279,8 @@ __global__ __launch_bounds__(PK_THREADS) void device_pack_codes(const uint8_t *_
     constexpr int UNIT = 4 * CELL;
     constexpr int SPAN = span_of<BITS>(), PITCH = SPAN + 16;
     constexpr int UPW = SPAN / UNIT / 4;
-    __shared__ __align__(16) uint8_t lds[QG_WAVE * PITCH];
-    const int64_t tile = blockIdx.x / spans;
-    const int span = blockIdx.x % spans;
+    const int64_t tile = block / spans;
+    const int span = block % spans;
     rows_to_lds<SPAN>(q, N, K, tile * QG_WAVE, (int64_t)span * SPAN, wide, lds);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -318,7 +315,7 @@ __global__ __launch_bounds__(PK_THREADS) void device_pack_codes(const uint8_t *_
 }
 
 template <int BITS>
-__global__ __launch_bounds__(PK_THREADS) void device_unpack_codes(const uint4 *__restrict__ in, int64_t N,
+__device__ inline void device_unpack_codes(int64_t block, uint8_t *lds, const uint4 *__restrict__ in, int64_t N,
                                                                   int64_t K, int64_t units, int spans,
                                                                   bool wide, uint8_t *__restrict__ q)
 {
@@ -327,9 +324,8 @@ __global__ __launch_bounds__(PK_THREADS) void device_unpack_codes(const uint4 *_
     constexpr int UNIT = 4 * CELL;
     constexpr int SPAN = span_of<BITS>(), PITCH = SPAN + 16;
     constexpr int UPW = SPAN / UNIT / 4;
-    __shared__ __align__(16) uint8_t lds[QG_WAVE * PITCH];
-    const int64_t tile = blockIdx.x / spans;
-    const int span = blockIdx.x % spans;
+    const int64_t tile = block / spans;
+    const int span = block % spans;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int u = 0; u < UPW; ++u) {
@@ -366,12 +362,12 @@ __global__ __launch_bounds__(PK_THREADS) void device_unpack_codes(const uint4 *_
 // s [N][G] (row-major)  <->  canonical St [G][N]  or  per tile sd [tile][G][lane] (lanes past
 // N hold 0).  A workgroup moves 64 outputs x 64 groups through LDS.
 template <bool TILED>
-__global__ __launch_bounds__(PK_THREADS) void scales_pack(const float *__restrict__ s, int64_t N, int64_t G,
+__device__ inline void scales_pack(int64_t block, uint8_t *lds, const float *__restrict__ s, int64_t N, int64_t G,
                                                           int spans, float *__restrict__ out)
 {
-    __shared__ float lds[QG_WAVE][QG_WAVE + 1];
-    const int64_t tile = blockIdx.x / spans;
-    const int64_t g0 = (int64_t)(blockIdx.x % spans) * QG_WAVE;
+    float (*image)[QG_WAVE + 1] = (float (*)[QG_WAVE + 1])lds;
+    const int64_t tile = block / spans;
+    const int64_t g0 = (int64_t)(block % spans) * QG_WAVE;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float val[QG_WAVE / 4];                    // all loads of the thread before the first store
 #pragma unroll
@@ -380,7 +376,7 @@ __global__ __launch_bounds__(PK_THREADS) void scales_pack(const float *__restric
         val[j] = (n < N && g < G) ? s[n * G + g] : 0.0f;
     }
 #pragma unroll
-    for (int j = 0; j < QG_WAVE / 4; ++j) lds[wave + 4 * j][lane] = val[j];
+    for (int j = 0; j < QG_WAVE / 4; ++j) image[wave + 4 * j][lane] = val[j];
     __syncthreads();
     const int64_t n = tile * QG_WAVE + lane;
 #pragma unroll
@@ -388,18 +384,18 @@ __global__ __launch_bounds__(PK_THREADS) void scales_pack(const float *__restric
         const int c = wave + 4 * j;
         const int64_t g = g0 + c;
         if (g >= G) break;
-        if (TILED) out[(tile * G + g) * QG_WAVE + lane] = lds[lane][c];
-        else if (n < N) out[g * N + n] = lds[lane][c];
+        if (TILED) out[(tile * G + g) * QG_WAVE + lane] = image[lane][c];
+        else if (n < N) out[g * N + n] = image[lane][c];
     }
 }
 
 template <bool TILED>
-__global__ __launch_bounds__(PK_THREADS) void scales_unpack(const float *__restrict__ in, int64_t N, int64_t G,
+__device__ inline void scales_unpack(int64_t block, uint8_t *lds, const float *__restrict__ in, int64_t N, int64_t G,
                                                             int spans, float *__restrict__ s)
 {
-    __shared__ float lds[QG_WAVE][QG_WAVE + 1];
-    const int64_t tile = blockIdx.x / spans;
-    const int64_t g0 = (int64_t)(blockIdx.x % spans) * QG_WAVE;
+    float (*image)[QG_WAVE + 1] = (float (*)[QG_WAVE + 1])lds;
+    const int64_t tile = block / spans;
+    const int64_t g0 = (int64_t)(block % spans) * QG_WAVE;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t nl = tile * QG_WAVE + lane;
     float val[QG_WAVE / 4];
@@ -410,11 +406,11 @@ __global__ __launch_bounds__(PK_THREADS) void scales_unpack(const float *__restr
         if (g < G && (TILED || nl < N)) val[j] = in[TILED ? (tile * G + g) * QG_WAVE + lane : g * N + nl];
     }
 #pragma unroll
-    for (int j = 0; j < QG_WAVE / 4; ++j) lds[lane][wave + 4 * j] = val[j];
+    for (int j = 0; j < QG_WAVE / 4; ++j) image[lane][wave + 4 * j] = val[j];
     __syncthreads();
     for (int r = wave; r < QG_WAVE; r += 4) {
         const int64_t n = tile * QG_WAVE + r, g = g0 + lane;
-        if (n < N && g < G) s[n * G + g] = lds[r][lane];
+        if (n < N && g < G) s[n * G + g] = image[r][lane];
     }
 }
 
@@ -426,62 +422,57 @@ inline unsigned grid_for(int64_t tiles, int64_t spans)
     return tiles * spans > 0x7fffffff ? 0u : (unsigned)(tiles * spans);
 }
 
-// stream_pack / stream_unpack for a [N][cols] byte matrix with `fb`-bit fields
-template <bool TILED>
-int launch_stream(bool pack, int fb, const void *bytes, int64_t N, int64_t cols, int64_t words,
-                  const void *packed, hipStream_t st)
+// ------------------------------------------------------------------ one launch per call
+//
+// The three sections of a blob are independent, and two of them are small: as launches of their own the
+// scales and zero-points took 3.9-5.6 us each behind the codes' (11008 x 4096 4-bit g128 unpack 12.6 + 5.1 +
+// 3.9 us by the profiler).  Here a call is one grid: first the workgroups of the small sections, whose
+// round trips then run beside the codes, then the codes'.
+struct ConvertArgs {
+    void *q, *s, *z;
+    char *packed;
+    size_t codes_off, scales_off, zeros_off;
+    int64_t N, K, G, code_words, zero_words;   // code_words: units (device layout) or words per row (canonical)
+    int code_spans, scale_spans, zero_spans;   // workgroups per tile of 64 outputs
+    unsigned scale_blocks, zero_blocks;
+    bool q_wide, z_wide;                       // 16-byte pieces (rows_to_lds)
+};
+
+// ZB: bits per stored zero-point
+template <int BITS, int ZB, bool DEVICE, bool PACK>
+__global__ __launch_bounds__(PK_THREADS) void convert_blob(const ConvertArgs A)
 {
-    const int64_t tiles = ceil_div(N, QG_WAVE);
-    const int spans = (int)ceil_div(cols, fb == 3 ? span_of<3>() : span_of<4>());
-    const unsigned grid = grid_for(tiles, spans);
-    if (!grid) return QG_ERR_SHAPE;
-    const bool wide = cols % 16 == 0 && qg_aligned16(bytes);
-    const uint8_t *vin = (const uint8_t *)bytes;
-    uint8_t *vout = (uint8_t *)bytes;
-    const uint32_t *pin = (const uint32_t *)packed;
-    uint32_t *pout = (uint32_t *)packed;
-#define QG_STREAM(FB)                                                                                   \
-    if (pack) hipLaunchKernelGGL((stream_pack<FB, TILED>), dim3(grid), dim3(PK_THREADS), 0, st, vin, N, \
-                                 cols, words, spans, wide, pout);                                       \
-    else hipLaunchKernelGGL((stream_unpack<FB, TILED>), dim3(grid), dim3(PK_THREADS), 0, st, pin, N,    \
-                            cols, words, spans, wide, vout)
-    if (fb == 4) { QG_STREAM(4); }
-    else if (fb == 2) { QG_STREAM(2); }
-    else { QG_STREAM(3); }
-#undef QG_STREAM
-    return QG_OK;
+    constexpr int CODES_LDS = QG_WAVE * (span_of<BITS>() + 16), ZEROS_LDS = QG_WAVE * (span_of<ZB>() + 16);
+    constexpr int SCALES_LDS = QG_WAVE * (QG_WAVE + 1) * 4;
+    constexpr int LDS = CODES_LDS > ZEROS_LDS ? (CODES_LDS > SCALES_LDS ? CODES_LDS : SCALES_LDS)
+                                              : (ZEROS_LDS > SCALES_LDS ? ZEROS_LDS : SCALES_LDS);
+    __shared__ __align__(16) uint8_t lds[LDS];
+    const unsigned block = blockIdx.x;
+    if (block < A.scale_blocks) {
+        float *out = (float *)(A.packed + A.scales_off);
+        if constexpr (PACK) scales_pack<DEVICE>(block, lds, (const float *)A.s, A.N, A.G, A.scale_spans, out);
+        else scales_unpack<DEVICE>(block, lds, out, A.N, A.G, A.scale_spans, (float *)A.s);
+    } else if (block < A.scale_blocks + A.zero_blocks) {
+        const int64_t at = block - A.scale_blocks;
+        uint32_t *out = (uint32_t *)(A.packed + A.zeros_off);
+        if constexpr (PACK) stream_pack<ZB, DEVICE>(at, lds, (const uint8_t *)A.z, A.N, A.G, A.zero_words, A.zero_spans, A.z_wide, out);
+        else stream_unpack<ZB, DEVICE>(at, lds, out, A.N, A.G, A.zero_words, A.zero_spans, A.z_wide, (uint8_t *)A.z);
+    } else {
+        const int64_t at = block - A.scale_blocks - A.zero_blocks;
+        char *out = A.packed + A.codes_off;
+        if constexpr (DEVICE && PACK) device_pack_codes<BITS>(at, lds, (const uint8_t *)A.q, A.N, A.K, A.code_words, A.code_spans, A.q_wide, (uint4 *)out);
+        else if constexpr (DEVICE) device_unpack_codes<BITS>(at, lds, (const uint4 *)out, A.N, A.K, A.code_words, A.code_spans, A.q_wide, (uint8_t *)A.q);
+        else if constexpr (PACK) stream_pack<BITS, false>(at, lds, (const uint8_t *)A.q, A.N, A.K, A.code_words, A.code_spans, A.q_wide, (uint32_t *)out);
+        else stream_unpack<BITS, false>(at, lds, (const uint32_t *)out, A.N, A.K, A.code_words, A.code_spans, A.q_wide, (uint8_t *)A.q);
+    }
 }
 
-template <bool TILED>
-int launch_scales(bool pack, const float *s, int64_t N, int64_t G, const float *packed, hipStream_t st)
+template <int BITS, bool DEVICE>
+void launch_convert(bool pack, const ConvertArgs &A, unsigned grid, hipStream_t st)
 {
-    const int spans = (int)ceil_div(G, QG_WAVE);
-    const unsigned grid = grid_for(ceil_div(N, QG_WAVE), spans);
-    if (!grid) return QG_ERR_SHAPE;
-    if (pack) hipLaunchKernelGGL(scales_pack<TILED>, dim3(grid), dim3(PK_THREADS), 0, st, s, N, G, spans,
-                                 (float *)packed);
-    else hipLaunchKernelGGL(scales_unpack<TILED>, dim3(grid), dim3(PK_THREADS), 0, st, packed, N, G, spans,
-                            (float *)s);
-    return QG_OK;
-}
-
-int launch_device_codes(bool pack, const QgLayout &L, const void *q, const void *codes, hipStream_t st)
-{
-    const int span_units = (L.bits == 3 ? span_of<3>() : span_of<4>()) / L.unit;
-    const int spans = (int)ceil_div(L.units, span_units);
-    const unsigned grid = grid_for(L.tiles, spans);
-    if (!grid) return QG_ERR_SHAPE;
-    const bool wide = L.K % 16 == 0 && qg_aligned16(q);
-#define QG_CODES(B)                                                                                      \
-    if (pack) hipLaunchKernelGGL(device_pack_codes<B>, dim3(grid), dim3(PK_THREADS), 0, st,              \
-                                 (const uint8_t *)q, L.N, L.K, L.units, spans, wide, (uint4 *)codes);    \
-    else hipLaunchKernelGGL(device_unpack_codes<B>, dim3(grid), dim3(PK_THREADS), 0, st,                 \
-                            (const uint4 *)codes, L.N, L.K, L.units, spans, wide, (uint8_t *)q)
-    if (L.bits == 4) { QG_CODES(4); }
-    else if (L.bits == 2) { QG_CODES(2); }
-    else { QG_CODES(3); }
-#undef QG_CODES
-    return QG_OK;
+    constexpr int ZB = !DEVICE ? BITS : BITS == 2 ? 2 : 4;
+    if (pack) hipLaunchKernelGGL((convert_blob<BITS, ZB, DEVICE, true>), dim3(grid), dim3(PK_THREADS), 0, st, A);
+    else hipLaunchKernelGGL((convert_blob<BITS, ZB, DEVICE, false>), dim3(grid), dim3(PK_THREADS), 0, st, A);
 }
 
 // both directions of qg_pack / qg_unpack: the same three sections either way
@@ -494,25 +485,47 @@ int convert(bool pack, const void *q, const void *s, const void *z, int64_t N, i
     if (rc != QG_OK) return rc;
     if (!q || !s || !z || !packed) return QG_ERR_NULL;
     if (!qg_aligned16(packed)) return QG_ERR_ALIGN;
-    const char *base = (const char *)packed;
-
+    ConvertArgs A;
+    A.q = const_cast<void *>(q);
+    A.s = const_cast<void *>(s);
+    A.z = const_cast<void *>(z);
+    A.packed = (char *)const_cast<void *>(packed);
+    A.N = N;
+    A.K = K;
+    A.G = L.ngroups;
+    A.q_wide = K % 16 == 0 && qg_aligned16(q);
+    A.z_wide = L.ngroups % 16 == 0 && qg_aligned16(z);
+    const int code_span = bits == 3 ? span_of<3>() : span_of<4>();
+    A.scale_spans = (int)ceil_div(L.ngroups, QG_WAVE);
+    int zero_bits;
     if (layout == QG_LAYOUT_CANONICAL) {
         QgCanonical C;
         rc = qg_make_canonical(N, K, bits, group, &C);
         if (rc != QG_OK) return rc;
-        rc = launch_stream<false>(pack, bits, q, N, K, C.code_words, base + C.codes_off, st);
-        if (rc == QG_OK) rc = launch_scales<false>(pack, (const float *)s, N, C.ngroups,
-                                                   (const float *)(base + C.scales_off), st);
-        if (rc == QG_OK) rc = launch_stream<false>(pack, bits, z, N, C.ngroups, C.zero_words,
-                                                   base + C.zeros_off, st);
+        A.codes_off = C.codes_off; A.scales_off = C.scales_off; A.zeros_off = C.zeros_off;
+        A.code_words = C.code_words;
+        A.zero_words = C.zero_words;
+        A.code_spans = (int)ceil_div(K, code_span);
+        zero_bits = bits;
     } else {
-        rc = launch_device_codes(pack, L, q, base + L.codes_off, st);
-        if (rc == QG_OK) rc = launch_scales<true>(pack, (const float *)s, N, L.ngroups,
-                                                  (const float *)(base + L.scales_off), st);
-        if (rc == QG_OK) rc = launch_stream<true>(pack, L.zbits, z, N, L.ngroups, L.zwords,
-                                                  base + L.zeros_off, st);
+        A.codes_off = L.codes_off; A.scales_off = L.scales_off; A.zeros_off = L.zeros_off;
+        A.code_words = L.units;
+        A.zero_words = L.zwords;
+        A.code_spans = (int)ceil_div(L.units, code_span / L.unit);
+        zero_bits = L.zbits;
     }
-    return rc == QG_OK ? qg_launch_status() : rc;
+    A.zero_spans = (int)ceil_div(L.ngroups, zero_bits == 3 ? span_of<3>() : span_of<4>());
+    // HIP's grid holds each section (as before) and their sum
+    if (!grid_for(L.tiles, A.code_spans) || !grid_for(L.tiles, A.scale_spans) || !grid_for(L.tiles, A.zero_spans)) return QG_ERR_SHAPE;
+    const unsigned grid = grid_for(L.tiles, (int64_t)A.code_spans + A.scale_spans + A.zero_spans);
+    if (!grid) return QG_ERR_SHAPE;
+    A.scale_blocks = (unsigned)(L.tiles * A.scale_spans);
+    A.zero_blocks = (unsigned)(L.tiles * A.zero_spans);
+    const bool device = layout == QG_LAYOUT_DEVICE;
+    if (bits == 4) device ? launch_convert<4, true>(pack, A, grid, st) : launch_convert<4, false>(pack, A, grid, st);
+    else if (bits == 2) device ? launch_convert<2, true>(pack, A, grid, st) : launch_convert<2, false>(pack, A, grid, st);
+    else device ? launch_convert<3, true>(pack, A, grid, st) : launch_convert<3, false>(pack, A, grid, st);
+    return qg_launch_status();
 }
 
 }  // namespace
