@@ -1264,6 +1264,9 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
 // where xhat comes out of one more matrix instruction per operand (X times a column of ones),
 // so it sits in the same registers as T.  Each wavefront converts the X rows of its own step
 // and keeps them in its own LDS region, one 16-byte operand piece per (row, cell).
+// Bound by what a compute unit can load: 8 KB of X per 4 KB of codes (11008 x 4096 at 16 rows 11.2 -> 11.0
+// us, 22016 x 8192 38.9 -> 34.6, 8192 x 8192 g64 19.2 -> 18.2 with the operands below, which need no lane
+// exchange of code words, and X in one register set: 168-184 registers instead of 208-232).
 // ---------------------------------------------------------------------------------------
 template <int CPG>
 __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvArgs A)
@@ -1305,8 +1308,8 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
         uint4 v[L];
         float s[GPS];
         uint32_t zw[ZW];
-        float4 x[XL][2];       // pieces (row, cell) = (4 j + lane / 16, lane % 16): 8 consecutive k of X
     };
+    float4 x[XL][2];           // pieces (row, cell) = (4 j + lane / 16, lane % 16): 8 consecutive k of X
     // groups of four rows with no real row are not loaded; other rows past M read row M - 1
     // again; both are cleared on their way into LDS
     const int xrow0 = lane >> 4, xcell = lane & 15;
@@ -1317,19 +1320,21 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
         for (int g = 0; g < GPS; ++g) r.s[g] = scales[(size_t)(step * GPS + g) * QG_WAVE];
 #pragma unroll
         for (int w = 0; w < ZW; ++w) r.zw[w] = zeros[(size_t)((step * GPS) / ZPER + w) * QG_WAVE];
+    };
+    auto fetch_x = [&](int step) {
 #pragma unroll
         for (int j = 0; j < XL; ++j) {
             if (4 * j >= M) continue;                    // uniform
             int m = 4 * j + xrow0;
             m = m < M ? m : M - 1;
             const float4 *src = (const float4 *)(P.x + (size_t)m * P.K + (size_t)step * S + xcell * 8);
-            r.x[j][0] = src[0];
-            r.x[j][1] = src[1];
+            x[j][0] = src[0];
+            x[j][1] = src[1];
         }
     };
     // X of one step into LDS: per piece the eight values in the order the unpacked codes have
     // inside an operand (register j = codes j and j + 4)
-    auto stage = [&](const Regs &r) {
+    auto stage = [&]() {
 #pragma unroll
         for (int j = 0; j < XL; ++j) {
             const int m = 4 * j + xrow0;
@@ -1339,7 +1344,7 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
                 *(lds_u128 *)(xs + m * PITCH + xcell * 8) = o.q;
                 continue;
             }
-            const float4 a = r.x[j][0], b = r.x[j][1];
+            const float4 a = x[j][0], b = x[j][1];
             const float keep = m < M ? 1.0f : 0.0f;
             mma_floatx2 t2;
             t2[0] = a.x * keep; t2[1] = b.x * keep;
@@ -1354,36 +1359,41 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
         }
     };
 
-    // A operand: row = lane % 32 (rows 16-31 are zero), half = lane / 32 = which cell of the pair
+    // A operands.  A lane's B operand is a cell of its own output, so lanes l and l + 32 hold the same k of
+    // two outputs; with the 16 rows of X against lanes 0-31 in rows 0-15 of A and once more against lanes
+    // 32-63 in rows 16-31 (zeros elsewhere), one instruction multiplies a cell of all 64 outputs with 16
+    // rows, and neither the code words nor the scales have to change lanes.  For xhat: 16 k in rows 0-15.
     const int row = lane & 31, half = lane >> 5;
-    const lds_u16 *abase = row < 16 ? xs + row * PITCH + half * 8 : zero_row + half * 8;
+    const lds_u16 *abase = (row < 16) == (half == 0) ? xs + (row & 15) * PITCH : zero_row;
+    const lds_u16 *xbase = xs + (row & 15) * PITCH + half * 8;
     const MmaConst mc = mma_constants<4>();
     MmaOperand ones;
 #pragma unroll
     for (int j = 0; j < 4; ++j) ones.r[j] = 0x3f803f80u;     // two bf16 1.0
 
-    // results of this wavefront: rows 8 (i / 4) + 4 half + i % 4 (i < 8) of outputs lane % 32 (P)
-    // and 32 + lane % 32 (Q) of the tile
+    // results of this wavefront: rows 8 (i / 4) + 4 half + i % 4 (i < 8) of outputs lane % 32 (yp)
+    // and 32 + lane % 32 (yq) of the tile
     float yp[8], yq[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) { yp[i] = 0.0f; yq[i] = 0.0f; }
 
     auto compute = [&](const Regs &r, int step) {
-        mma_floatx16 accP, accQ, accX;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) { accP[i] = 0.0f; accQ[i] = 0.0f; accX[i] = 0.0f; }
+        const mma_floatx16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        mma_floatx16 acc, accX;
 #pragma unroll
         for (int cp = 0; cp < CELLS / 2; ++cp) {
             const int c0 = 2 * cp, u = c0 >> 2, j = c0 & 3;
-            const auto sw = __builtin_amdgcn_permlane32_swap(word_of(r.v[u], j), word_of(r.v[u], j + 1), false, false);
-            uint32_t wp[1] = {sw[0]}, wq[1] = {sw[1]};
-            MmaOperand bp[1], bq[1], a;
-            mma_unpack<4>(wp, mc, bp);
-            mma_unpack<4>(wq, mc, bq);
-            a.q = *(const lds_u128 *)(abase + cp * 16);
-            accP = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, bp[0].v, accP, 0, 0, 0);
-            accQ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, bq[0].v, accQ, 0, 0, 0);
-            accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, ones.v, accX, 0, 0, 0);
+            const bool starts = c0 % CPG == 0;
+            uint32_t w0[1] = {word_of(r.v[u], j)}, w1[1] = {word_of(r.v[u], j + 1)};
+            MmaOperand b0[1], b1[1], a0, a1, ax;
+            mma_unpack<4>(w0, mc, b0);
+            mma_unpack<4>(w1, mc, b1);
+            a0.q = *(const lds_u128 *)(abase + cp * 16);
+            a1.q = *(const lds_u128 *)(abase + cp * 16 + 8);
+            ax.q = *(const lds_u128 *)(xbase + cp * 16);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0.v, b0[0].v, starts ? zero16 : acc, 0, 0, 0);
+            accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ax.v, ones.v, starts ? zero16 : accX, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1.v, b1[0].v, acc, 0, 0, 0);
             if ((2 * cp + 2) % CPG == 0) {
                 const int gs = (2 * cp + 2) / CPG - 1;
                 const int gabs = step * GPS + gs;
@@ -1397,29 +1407,33 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
                 const float zP = __uint_as_float(zz[0]), zQ = __uint_as_float(zz[1]);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    yp[i] += fmaf(sP, accP[i], zP * accX[i]);
-                    yq[i] += fmaf(sQ, accQ[i], zQ * accX[i]);
+                    yp[i] += fmaf(sP, acc[i], zP * accX[i]);
+                    yq[i] += fmaf(sQ, acc[8 + i], zQ * accX[i]);
                 }
-#pragma unroll
-                for (int i = 0; i < 16; ++i) { accP[i] = 0.0f; accQ[i] = 0.0f; accX[i] = 0.0f; }
             }
         }
     };
 
-    // two register buffers used alternately; the rows of X of a step are converted into the
-    // wavefront's LDS region right before the step is computed
+    // two register buffers for the weights used alternately; the rows of X of a step are converted into
+    // the wavefront's LDS region right before the step is computed, those of the next step requested
+    // as soon as their registers are free
     const int last = s1 - 1;
     Regs ra, rb;
+    fetch_x(s0);
     fetch(s0, ra);
     for (int s = s0; s < s1; s += 2) {
         const int sb = s + 1 < last ? s + 1 : last;
         const int sc = s + 2 < last ? s + 2 : last;
         fetch(sb, rb);
-        stage(ra);
+        stage();
+        fetch_x(sb);
+        __builtin_amdgcn_sched_barrier(0);
         compute(ra, s);
         if (s + 1 >= s1) break;                       // odd number of steps
         fetch(sc, ra);
-        stage(rb);
+        stage();
+        fetch_x(sc);
+        __builtin_amdgcn_sched_barrier(0);
         compute(rb, sb);
     }
 
@@ -1889,7 +1903,10 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
     // wavefronts per team, at most (measured: 12 is best for the 4-bit vector-ALU kernel with
     // groups inside a step, 8 for the 2- and 3-bit ones, which hold more registers per wavefront)
     int cap = t_cur.wpb > 0 ? t_cur.wpb : (bits_all == 4 ? 12 : 8);
-    if (rows > 0 && cap > 8) cap = 8;          // gemm_rows16 is built for at most 8 wavefronts
+    if (rows > 0 && cap > 8) cap = 8;          // gemm_rows16 is built for at most 8 wavefronts;
+    // ... with more tiles than compute units teams of 4, two of which share a unit, leave no second round
+    // (22016 x 8192 4-bit, 16 rows, 344 tiles: 34.6 against 37.6 us; 216 tiles: 13.6 against 12.6)
+    if (rows > 0 && t_cur.wpb == 0 && L[0].tiles > qg_compute_units()) cap = 4;
     if (mma) {                                 // the matrix-core kernels are built for at most 8 wavefronts;
         if (cap > 8) cap = 8;                  // measured: teams of 4 are best for them ...
         if (t_cur.wpb == 0) cap = 4;
