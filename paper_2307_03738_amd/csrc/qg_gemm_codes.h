@@ -27,14 +27,16 @@
 // bank conflicts, since an operand is read as it lies), and every load of unit u + 1 is issued between
 // the matrix instructions of unit u.  The units of all blocks of outputs and rows are dealt evenly over
 // one workgroup per compute unit, wherever the borders fall: with a whole number of K ranges per block
-// the 22016 x 8192 matrix at 128 rows ran 172 workgroups on 256 units.
+// the 22016 x 8192 matrix at 128 rows ran 172 workgroups on 256 compute units.
 //
 // What bounds it: the vector ALU and the matrix core together.  Per 16 k x 64 outputs x 64 rows there
 // are 4 matrix instructions (32 cycles each) and, at groups of 32 k, 32 multiply-adds of the fold plus
-// 16-20 instructions of unpacking (4 cycles each); two wavefronts per SIMD share both.  Measured (us per
-// call, passes in sequence, four rotated matrices; before: iterations of KW layout steps, activations
-// through registers, whole K ranges per block): 22016 x 8192 2-bit g32 M = 128 104.7 -> 83.0, 13824 x
-// 5120 3-bit g64 M = 37 27.1 -> 22.2, 4096 x 11008 4-bit g128 M = 128 28.1 -> 26.8.
+// 16-20 instructions of unpacking (4 cycles each); two wavefronts per SIMD share both.  On short problems the
+// launches around it count as much: prepare_x and, where many parts of a sum are better, add_parts.
+// Measured (us per call, passes in sequence, four rotated matrices; before: iterations of KW layout steps,
+// activations through registers, whole K ranges per block, always a kernel that adds the ranges): 22016 x
+// 8192 2-bit g32 M = 128 104.4 -> 76.0, 13824 x 5120 3-bit g64 M = 37 27.2 -> 22.5, M = 128 43.0 -> 35, 4096 x
+// 11008 4-bit g128 M = 128 28.1 -> 26.1.
 #pragma once
 
 #include "qg_common.h"
@@ -43,7 +45,9 @@
 struct QgCodesArgs {
     const char *codes, *scales, *zeros;
     const char *Xop;           // A operands (prepare_x)
-    float *Y, *partial;        // partial results [segment][M][pitch]
+    float *Y;
+    char *partial;             // partial results [segment][tile][band of 8 rows][outputs 0-31, 32-63][lane][4 rows]
+    uint32_t *arrived;         // [tile][block of rows]: workgroups whose part of the sum is there (prepare_x clears it)
     int M, N, tiles;
     uint32_t tile_codes, tile_scales, tile_zeros;      // bytes of one tile's codes, scales, zero words
     int steps_padded;          // steps of 128 k rounded up to a multiple of 4: what prepare_x has written
@@ -53,7 +57,7 @@ struct QgCodesArgs {
     int ranges;                // > 0: every block's units are cut into this many ranges, one workgroup each
     int quota;                 // units per workgroup
     int total;                 // units of the launch = blocks * units
-    int pitch;                 // tiles * 64
+    int fused;                 // parts of a sum are added here (else by add_parts)
 };
 
 struct QgPrepArgs {
@@ -61,6 +65,8 @@ struct QgPrepArgs {
     char *Xop;
     int M, K, steps_padded;
     int groupk;                // k one xhat covers: the group, or a step for groups of several steps
+    uint32_t *arrived;         // counters the product kernel finds at zero
+    int counters;
 };
 
 // What a launch would run, for the search that prices candidates before it times them.
@@ -71,6 +77,7 @@ struct QgKernelInfo {
 };
 
 constexpr size_t QG_LDS_BYTES = 160u << 10;
+constexpr int QG_MAX_SEGMENTS = 8;             // parts the sum of an element of Y is cut into, at most
 
 // gps: groups per step of 128 k, 0 for groups of several steps.  A operands per step and block of 32 rows:
 constexpr int qg_codes_seq(int gps) { return 8 + (gps > 0 ? gps : 1); }
@@ -79,11 +86,19 @@ constexpr size_t qg_codes_lds(int gps, int mb, int tn, int kw)
 {
     return (size_t)2 * mb * kw * qg_codes_seq(gps) * 1024 + (size_t)(kw - 1) * tn * 32 * 256;
 }
+// k-slices of a workgroup of eight wavefronts: as many as LDS holds, up to 4 at 32 rows and 2 at 64 (4 there, with half
+// of the tiles, halves the partial sums but doubles the A operands' traffic: 13824 x 5120 3-bit M = 37 25.2
+// against 22.2 us, 4096 x 11008 4-bit M = 128 29.1 against 27.3; 1 doubles the partial sums: 22.5, 31.0)
+constexpr int qg_codes_kw(int gps, int mb)
+{
+    const int kw = mb == 1 ? 4 : 2;
+    return qg_codes_lds(gps, mb, 8 / kw, kw) > QG_LDS_BYTES ? kw / 2 : kw;
+}
 
 // One per bit width.  query: fill it instead of launching.
-int qg_codes_launch_b2(int gps, int mb, int tn, int kw, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query);
-int qg_codes_launch_b3(int gps, int mb, int tn, int kw, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query);
-int qg_codes_launch_b4(int gps, int mb, int tn, int kw, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query);
+int qg_codes_launch_b2(int gps, int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query);
+int qg_codes_launch_b3(int gps, int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query);
+int qg_codes_launch_b4(int gps, int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query);
 void qg_codes_prepare_b2(const QgPrepArgs &P, int rows_padded, hipStream_t st);
 void qg_codes_prepare_b3(const QgPrepArgs &P, int rows_padded, hipStream_t st);
 void qg_codes_prepare_b4(const QgPrepArgs &P, int rows_padded, hipStream_t st);
@@ -104,6 +119,7 @@ __global__ __launch_bounds__(256) void prepare_x(const QgPrepArgs A)
     constexpr float UP = BITS == 3 ? 8.0f : 4.0f;
     const int m = blockIdx.y;
     const int item = blockIdx.x * 256 + threadIdx.x;
+    for (int i = (m * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < A.counters; i += gridDim.x * gridDim.y * 256) A.arrived[i] = 0u;
     const int items = A.steps_padded * S / OCT;
     const bool live = item < items;                         // the last block of a row may overhang
     const int k0 = (live ? item : items - 1) * OCT;
@@ -185,7 +201,9 @@ __device__ inline rsrc_t buffer_of(const void *base, uint32_t bytes)
     return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000);
 }
 
-template <int BITS, int GPS_, int MB, int TN, int KW>
+// FUSED: parts of a sum are added by the workgroup that comes last (an instance of its own: the code for it costs
+// the others 3 %).
+template <int BITS, int GPS_, int MB, int TN, int KW, bool FUSED>
 __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs A)
 {
     using F = Fmt<BITS>;
@@ -294,13 +312,19 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     float sc[2][2];                           // SHORT: [outputs 0-31, 32-63][group parity]
     uint32_t held = ~0u;                      // LONG: that group
     auto reset = [&]() {
+        // (an opaque zero: the accumulators must not be cleared ahead of the sums over parts, which want
+        // their registers)
+        float zero;
+        asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
 #pragma unroll
-        for (int k = 0; k < NT; ++k) acc[k] = zero16;
+        for (int k = 0; k < NT; ++k)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[k][i] = zero;
 #pragma unroll
         for (int k = 0; k < 2 * MB; ++k)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) y[k][i] = 0.0f;
-        sP = sQ = sc[0][0] = sc[0][1] = sc[1][0] = sc[1][1] = 0.0f;
+            for (int i = 0; i < 16; ++i) y[k][i] = zero;
+        sP = sQ = sc[0][0] = sc[0][1] = sc[1][0] = sc[1][1] = zero;
         held = ~0u;
     };
     auto fold = [&](int k) {
@@ -560,9 +584,8 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
                     }
                 }
             }
-            if (kw > 0) return;
         }
-        const int tb = b >> A.zshift, m0 = (b - (tb << A.zshift)) * ROWS;
+        const int tb = b >> A.zshift, z = b - (tb << A.zshift), m0 = z * ROWS;
         const int tile = tb * TN + tn;
         int seg, nseg;
         if (A.ranges > 0) {
@@ -573,38 +596,102 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
             seg = blockIdx.x - first;
             nseg = ((b + 1) * A.units - 1) / A.quota - first + 1;
         }
-        if (tile < A.tiles) {
-            // Register i of an accumulator is row 8 (i / 4) + 4 half + i % 4 of its block: bands of eight
-            // rows, four registers each.  A band that lies inside M in a tile that lies inside N is
-            // stored without a test per lane (both conditions are the same for the whole wavefront).
-            const int pitch = nseg > 1 ? A.pitch : A.N;
-            const int n0 = tile * QG_WAVE + row;
-            float *out = (nseg > 1 ? A.partial + (size_t)seg * A.M * pitch : A.Y) + (size_t)(m0 + 4 * half) * pitch + n0;
-            const int rows_left = A.M - m0;
-            const bool whole_tile = (tile + 1) * QG_WAVE <= pitch;
+        // Register i of an accumulator is row 8 (i / 4) + 4 half + i % 4 of its block: bands of eight rows,
+        // a quad of registers each.  Stores quad (4 rows x 32 outputs, lane = row half and output) to Y.
+        const int rows_left = A.M - m0;
+        const int n0 = tile * QG_WAVE + row;
+        const bool whole_tile = (tile + 1) * QG_WAVE <= A.N;
+        auto store_y = [&](int r0, int pq, const float *v) {
+            float *o = A.Y + (size_t)(m0 + r0 + 4 * half) * A.N + n0 + 32 * pq;
+            if (whole_tile && r0 + 8 <= rows_left) {           // uniform: no test per lane
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+                for (int j = 0; j < 4; ++j) o[(size_t)j * A.N] = v[j];
+            } else {
 #pragma unroll
-                for (int band = 0; band < 4; ++band) {
-                    const int r0 = mb * 32 + 8 * band;
-                    if (r0 >= rows_left) break;
-                    if (whole_tile && r0 + 8 <= rows_left) {
+                for (int j = 0; j < 4; ++j)
+                    if (r0 + 4 * half + j < rows_left && n0 + 32 * pq < A.N) o[(size_t)j * A.N] = v[j];
+            }
+        };
+        constexpr int QUADS = 8 * MB;                          // quad 8 mb + 2 band + pq of a tile
+        if (nseg == 1) {
+            if (kw > 0 || tile >= A.tiles) return;
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            float *o = out + (size_t)(r0 + j) * pitch;
-                            o[0] = y[2 * mb][4 * band + j];
-                            o[32] = y[2 * mb + 1][4 * band + j];
-                        }
-                    } else {
+            for (int qd = 0; qd < QUADS; ++qd) {
+                const int r0 = 8 * (qd / 2), k = 2 * (qd / 8) + qd % 2;
+                if (r0 < rows_left) store_y(r0, qd % 2, &y[k][4 * ((qd / 2) % 4)]);
+            }
+            return;
+        }
+        // A part of the sum, for add_parts or (fused) for the workgroup that comes last: every workgroup
+        // writes its part and counts itself in; the one that finds the others there adds all parts in
+        // the order of K (so the bits do not depend on who it is) and stores Y.  Those parts are written
+        // and read past the caches of the chip's dies (sc1), and written before they are counted
+        // (s_waitcnt); nobody waits for anybody.
+        constexpr int SC1 = 16;
+        const int bands = (A.M + 7) / 8;
+        auto part_of = [&](int sg) {
+            const int mine = (rows_left + 7) / 8;
+            return buffer_of(A.partial + (((size_t)sg * A.tiles + tile) * bands + m0 / 8) * 2048, (mine < 4 * MB ? mine : 4 * MB) * 2048);
+        };
+        auto quad_of = [&](int qd) {
+            const float *v = &y[2 * (qd / 8) + qd % 2][4 * ((qd / 2) % 4)];
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            return u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+        };
+        if constexpr (!FUSED) {
+            if (kw > 0 || tile >= A.tiles) return;
+            const rsrc_t part = part_of(seg);
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const bool in_m = r0 + 4 * half + j < rows_left;
-                            float *o = out + (size_t)(r0 + j) * pitch;
-                            if (in_m && n0 < pitch) o[0] = y[2 * mb][4 * band + j];
-                            if (in_m && n0 + 32 < pitch) o[32] = y[2 * mb + 1][4 * band + j];
-                        }
-                    }
+            for (int qd = 0; qd < QUADS; ++qd)                 // (bands past M fall outside the buffer and are dropped)
+                __builtin_amdgcn_raw_buffer_store_b128(quad_of(qd), part, lane16 + qd * 1024, 0, 0);
+            return;
+        } else {
+        bool last = false;
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        if (kw == 0 && tile < A.tiles) {
+            const rsrc_t part = part_of(seg);
+#pragma unroll
+            for (int qd = 0; qd < QUADS; ++qd) __builtin_amdgcn_raw_buffer_store_b128(quad_of(qd), part, lane16 + qd * 1024, 0, SC1);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            uint32_t before = 0;
+            if (lane == 0)
+                before = __hip_atomic_fetch_add(A.arrived + ((size_t)tile << A.zshift) + z, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = (int)__builtin_amdgcn_readfirstlane(before) + 1 == nseg;
+        }
+        if constexpr (KW > 1) {
+            // the k-slices' wavefronts share the adding: slice 0 tells them
+            uint32_t *flag = (uint32_t *)(smem + 2 * CHUNK * 1024) + tn * (32 * 64);
+            if (kw == 0 && lane == 0) *flag = last;
+            __syncthreads();
+            last = __builtin_amdgcn_readfirstlane(*flag) != 0;
+        }
+        if (!last || tile >= A.tiles) return;
+        constexpr int SHARE = QUADS / KW, AT_ONCE = SHARE < 2 ? SHARE : 2;
+        static_assert(QUADS % KW == 0 && SHARE % AT_ONCE == 0, "quads per wavefront");
+        for (int q0 = kw * SHARE; q0 < (kw + 1) * SHARE; q0 += AT_ONCE) {
+            u32x4 v[AT_ONCE][QG_MAX_SEGMENTS];
+#pragma unroll
+            for (int sg = 0; sg < QG_MAX_SEGMENTS; ++sg)
+                if (sg < nseg) {
+                    const rsrc_t part = part_of(sg);
+#pragma unroll
+                    for (int i = 0; i < AT_ONCE; ++i) v[i][sg] = __builtin_amdgcn_raw_buffer_load_b128(part, lane16, (q0 + i) * 1024, SC1);
                 }
+#pragma unroll
+            for (int i = 0; i < AT_ONCE; ++i) {
+                float t[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) t[j] = __uint_as_float(v[i][0][j]);
+#pragma unroll
+                for (int sg = 1; sg < QG_MAX_SEGMENTS; ++sg)
+                    if (sg < nseg) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) t[j] += __uint_as_float(v[i][sg][j]);
+                    }
+                const int r0 = 8 * ((q0 + i) / 2);
+                if (r0 < rows_left) store_y(r0, (q0 + i) % 2, t);
+            }
+        }
         }
     };
 
@@ -655,12 +742,12 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no copy into LDS outlives the workgroup
 }
 
-template <int BITS, int GPS, int MB, int TN, int KW>
+template <int BITS, int GPS, int MB, int TN, int KW, bool FUSED>
 int codes_launch(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
     if constexpr (qg_codes_lds(GPS, MB, TN, KW) <= QG_LDS_BYTES) {
         constexpr size_t lds = qg_codes_lds(GPS, MB, TN, KW);
-        const void *f = (const void *)gemm_codes<BITS, GPS, MB, TN, KW>;
+        const void *f = (const void *)gemm_codes<BITS, GPS, MB, TN, KW, FUSED>;
         if (query) {
             *query = {f, TN * KW * 64, lds};
             return QG_OK;
@@ -673,7 +760,7 @@ int codes_launch(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelI
             }
             prepared = true;
         }
-        hipLaunchKernelGGL((gemm_codes<BITS, GPS, MB, TN, KW>), dim3((unsigned)workgroups), dim3(TN * KW * 64), lds, st, A);
+        hipLaunchKernelGGL((gemm_codes<BITS, GPS, MB, TN, KW, FUSED>), dim3((unsigned)workgroups), dim3(TN * KW * 64), lds, st, A);
         return QG_OK;
     } else {
         return QG_ERR_UNSUPPORTED;
@@ -681,32 +768,28 @@ int codes_launch(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelI
 }
 
 template <int BITS, int GPS>
-int codes_launch_shape(int mb, int tn, int kw, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
+int codes_launch_shape(int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
-#define QG_CODES_SHAPE(M_, T_, K_) \
-    if (mb == M_ && tn == T_ && kw == K_) return codes_launch<BITS, GPS, M_, T_, K_>(A, workgroups, st, query)
-    QG_CODES_SHAPE(1, 8, 1);
-    QG_CODES_SHAPE(1, 4, 2);
-    QG_CODES_SHAPE(1, 2, 4);
-    QG_CODES_SHAPE(2, 8, 1);
-    QG_CODES_SHAPE(2, 4, 2);
-    QG_CODES_SHAPE(2, 2, 4);
-#undef QG_CODES_SHAPE
-    return QG_ERR_UNSUPPORTED;
+    constexpr int K1 = qg_codes_kw(GPS, 1), K2 = qg_codes_kw(GPS, 2);
+    if (mb == 1)
+        return A.fused ? codes_launch<BITS, GPS, 1, 8 / K1, K1, true>(A, workgroups, st, query)
+                       : codes_launch<BITS, GPS, 1, 8 / K1, K1, false>(A, workgroups, st, query);
+    return A.fused ? codes_launch<BITS, GPS, 2, 8 / K2, K2, true>(A, workgroups, st, query)
+                   : codes_launch<BITS, GPS, 2, 8 / K2, K2, false>(A, workgroups, st, query);
 }
 
 template <int BITS>
-int codes_launch_any(int gps, int mb, int tn, int kw, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
+int codes_launch_any(int gps, int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
     switch (gps) {
-    case 0: return codes_launch_shape<BITS, 0>(mb, tn, kw, A, workgroups, st, query);
-    case 1: return codes_launch_shape<BITS, 1>(mb, tn, kw, A, workgroups, st, query);
-    case 2: return codes_launch_shape<BITS, 2>(mb, tn, kw, A, workgroups, st, query);
+    case 0: return codes_launch_shape<BITS, 0>(mb, A, workgroups, st, query);
+    case 1: return codes_launch_shape<BITS, 1>(mb, A, workgroups, st, query);
+    case 2: return codes_launch_shape<BITS, 2>(mb, A, workgroups, st, query);
     case 4:
-        if constexpr (BITS != 3) return codes_launch_shape<BITS, 4>(mb, tn, kw, A, workgroups, st, query);
+        if constexpr (BITS != 3) return codes_launch_shape<BITS, 4>(mb, A, workgroups, st, query);
         return QG_ERR_UNSUPPORTED;
     case 8:
-        if constexpr (BITS == 4) return codes_launch_shape<BITS, 8>(mb, tn, kw, A, workgroups, st, query);
+        if constexpr (BITS == 4) return codes_launch_shape<BITS, 8>(mb, A, workgroups, st, query);
         return QG_ERR_UNSUPPORTED;
     default: return QG_ERR_UNSUPPORTED;
     }

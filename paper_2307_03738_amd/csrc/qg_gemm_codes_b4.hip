@@ -2,9 +2,9 @@
 #define QG_CODES_KERNELS
 #include "qg_gemm_codes.h"
 
-int qg_codes_launch_b4(int gps, int mb, int tn, int kw, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
+int qg_codes_launch_b4(int gps, int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
-    return codes_launch_any<4>(gps, mb, tn, kw, A, workgroups, st, query);
+    return codes_launch_any<4>(gps, mb, A, workgroups, st, query);
 }
 
 void qg_codes_prepare_b4(const QgPrepArgs &P, int rows_padded, hipStream_t st) { codes_prepare<4>(P, rows_padded, st); }

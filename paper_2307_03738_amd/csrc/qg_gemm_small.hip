@@ -625,42 +625,43 @@ __global__ void add_splits(const float *__restrict__ partial, int splits, size_t
     Y[i] = t;
 }
 
-// The same for the raw-code kernel, whose blocks of outputs and rows have `ranges` partial results each or,
-// with ranges == 0, as many as workgroups their units fell to (one: the workgroup has stored Y itself).
-__global__ __launch_bounds__(256) void add_ranges(const float *__restrict__ partial, int pitch, int N, int M, int tn, int rows,
-                                                  int zshift, int units, int ranges, int quota, float *__restrict__ Y)
+// The same for the raw-code kernel (parts as it writes them: quads of 4 rows x 32 outputs, lane = row half and
+// output).  A block of outputs and rows has `ranges` parts or, with ranges == 0, as many as workgroups its
+// units fell to (one: that workgroup has stored Y itself).
+__global__ __launch_bounds__(256) void add_parts(const char *__restrict__ partial, int tiles, int N, int M, int tn, int rows,
+                                                 int zshift, int units, int ranges, int quota, float *__restrict__ Y)
 {
-    const int n = (blockIdx.x * 256 + threadIdx.x) * 4;
-    const int m = blockIdx.y;
-    if (n >= pitch) return;
+    const int bands = (M + 7) / 8;
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6);        // (tile, band, pq)
+    const int lane = threadIdx.x & 63;
+    if (q >= tiles * bands * 2) return;
+    const int pq = q & 1, band = (q >> 1) % bands, tile = (q >> 1) / bands;
     int count = ranges;
     if (ranges == 0) {
-        const int b = (n / (QG_WAVE * tn) << zshift) + m / rows;
+        const int b = (tile / tn << zshift) + band * 8 / rows;
         count = ((b + 1) * units - 1) / quota - b * units / quota + 1;
         if (count == 1) return;
     }
     const float4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    float4 v[MAX_SPLITS];
+    float4 v[QG_MAX_SEGMENTS];
 #pragma unroll
-    for (int s = 0; s < MAX_SPLITS; ++s)
-        v[s] = s < count ? *(const float4 *)(partial + ((size_t)s * M + m) * pitch + n) : zero;
+    for (int s = 0; s < QG_MAX_SEGMENTS; ++s)
+        v[s] = s < count ? *(const float4 *)(partial + (((size_t)s * tiles + tile) * bands + band) * 2048 + pq * 1024 + lane * 16) : zero;
     float4 t = v[0];
 #pragma unroll
-    for (int s = 1; s < MAX_SPLITS; ++s) {           // the missing ones add +0.0
+    for (int s = 1; s < QG_MAX_SEGMENTS; ++s) {           // the missing ones add +0.0
         t.x += v[s].x;
         t.y += v[s].y;
         t.z += v[s].z;
         t.w += v[s].w;
     }
+    const int n = tile * QG_WAVE + 32 * pq + (lane & 31), m = band * 8 + 4 * (lane >> 5);
+    if (n >= N) return;
     float *o = Y + (size_t)m * N + n;
-    if ((N & 3) == 0) {
-        if (n < N) *(float4 *)o = t;
-    } else {
-        if (n < N) o[0] = t.x;
-        if (n + 1 < N) o[1] = t.y;
-        if (n + 2 < N) o[2] = t.z;
-        if (n + 3 < N) o[3] = t.w;
-    }
+    if (m < M) o[0] = t.x;
+    if (m + 1 < M) o[(size_t)N] = t.y;
+    if (m + 2 < M) o[(size_t)2 * N] = t.z;
+    if (m + 3 < M) o[(size_t)3 * N] = t.w;
 }
 
 bool fast_path(const QgLayout &L)
@@ -785,9 +786,9 @@ int codes_gps(const QgLayout &L)       // groups per step of 128 k, 0: groups of
     return L.group >= least && KC % L.group == 0 ? KC / L.group : -1;
 }
 
-// Workspace of the raw-code path: A operands, partial results of the K ranges.
+// Workspace of the raw-code path: A operands, counters, partial results of the K ranges.
 struct CodesSpace {
-    size_t partial_off, total;
+    size_t arrived_off, partial_off, total;
     int rows_padded, steps_padded, groupk;
 };
 CodesSpace codes_space(const QgLayout &L, int gps, int M)
@@ -797,8 +798,9 @@ CodesSpace codes_space(const QgLayout &L, int gps, int M)
     W.rows_padded = (M + rows_per_block - 1) / rows_per_block * rows_per_block;
     W.steps_padded = (int)((L.K + 4 * KC - 1) / (4 * KC) * 4);
     W.groupk = L.group > KC ? KC : L.group;
-    W.partial_off = (size_t)W.rows_padded / 32 * W.steps_padded * qg_codes_seq(gps) * 1024;
-    W.total = qg_round_up(W.partial_off + (size_t)MAX_SPLITS * M * L.tiles * QG_WAVE * sizeof(float), QG_SECTION_ALIGN);
+    W.arrived_off = (size_t)W.rows_padded / 32 * W.steps_padded * qg_codes_seq(gps) * 1024;
+    W.partial_off = qg_round_up(W.arrived_off + (size_t)L.tiles * 2 * sizeof(uint32_t), QG_SECTION_ALIGN);
+    W.total = qg_round_up(W.partial_off + (size_t)QG_MAX_SEGMENTS * L.tiles * ((M + 7) / 8) * 2048, QG_SECTION_ALIGN);
     return W;
 }
 
@@ -806,8 +808,31 @@ CodesSpace codes_space(const QgLayout &L, int gps, int M)
 // steps; `ranges` K ranges per block of outputs and rows (one workgroup each), or, with ranges == 0,
 // `quota` consecutive units per workgroup whatever blocks they fall into.
 struct CodesPlan {
-    int mb, tn, kw, zshift, blocks, units, ranges, quota, workgroups;
+    int mb, tn, kw, zshift, blocks, units, ranges, quota, workgroups, parts;
+    bool fused;
 };
+
+// Cuts into at most `most` parts per block, one workgroup per compute unit at most where that is possible (a
+// workgroup takes half of a unit's registers or more, so one more would wait for a second round).
+void codes_cut(CodesPlan &P, int most, int cus, bool exactly)
+{
+    int ranges = exactly ? most : cus / P.blocks < most ? cus / P.blocks : most;
+    if (ranges < 1) ranges = 1;
+    if (ranges > P.units) ranges = P.units;
+    P.quota = (P.units + ranges - 1) / ranges;
+    P.ranges = P.parts = (P.units + P.quota - 1) / P.quota;
+    P.workgroups = P.blocks * P.ranges;
+    if (exactly) return;
+    const int even = (int)(((int64_t)P.blocks * P.units + cus - 1) / cus);
+    const int parts = (P.units + even - 2) / even + 1;          // of a block that begins at the end of a quota
+    if (even < P.quota && parts <= most) {
+        P.quota = even;
+        P.ranges = 0;
+        P.parts = parts;
+        P.workgroups = (P.blocks * P.units + even - 1) / even;
+    }
+}
+
 CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
 {
     CodesPlan P;
@@ -815,27 +840,36 @@ CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
     P.zshift = M > 64 ? 1 : 0;
     const int zblocks = 1 << P.zshift;
     const int cus = qg_compute_units();
-    P.kw = P.mb == 1 ? 4 : 2;
-    if (qg_codes_lds(gps, P.mb, 8 / P.kw, P.kw) > QG_LDS_BYTES) P.kw /= 2;
+    P.kw = qg_codes_kw(gps, P.mb);
     P.tn = 8 / P.kw;
     P.blocks = (int)((L.tiles + P.tn - 1) / P.tn) * zblocks;
     P.units = (int)(((L.K + KC - 1) / KC + P.kw - 1) / P.kw);
-    int ranges = knob_splits ? knob_splits : cus / P.blocks;
-    if (ranges < 1) ranges = 1;
-    if (ranges > MAX_SPLITS) ranges = MAX_SPLITS;
-    if (ranges > P.units) ranges = P.units;
-    P.quota = (P.units + ranges - 1) / ranges;
-    P.ranges = (P.units + P.quota - 1) / P.quota;
-    P.workgroups = P.blocks * P.ranges;
-    if (!knob_splits) {
-        const int even = (int)(((int64_t)P.blocks * P.units + cus - 1) / cus);
-        if (even < P.quota && (P.units + even - 1) / even + 1 <= MAX_SPLITS) {
-            P.quota = even;
-            P.ranges = 0;
-            P.workgroups = (P.blocks * P.units + even - 1) / even;
+    // Two or three parts are added by the workgroup that comes last, more by a kernel of their own.  More parts
+    // shorten a workgroup's units (1.0-2.0 us each at 32 rows, 1.8-2.4 at 64, more for small groups), but adding two costs
+    // about 1 us, three 3.5 (the last workgroup alone reads them all), a kernel 5 and its launch.  us per call, two
+    // or three parts | up to eight and a kernel: 11008 x 4096 4-bit M = 128 27.2 | 31.5, M = 20 15.3 |
+    // 17.2, 13824 x 5120 3-bit M = 100 34.0 | 38.0, M = 48 26.1 | 23.7, 4096 x 11008 4-bit M = 128 37.9 | 27.9,
+    // 8192 x 8192 2-bit g32 M = 20 19.1-21.5 | 17.5.
+    if (knob_splits) {
+        codes_cut(P, knob_splits, cus, true);
+        P.fused = P.parts > 1 && P.parts <= 3;
+        return P;
+    }
+    const double unit_us = P.mb == 1 ? (gps >= 4 ? 2.0 : gps == 2 ? 1.3 : 1.0) : (gps >= 4 ? 2.4 : gps == 2 ? 2.0 : 1.8);
+    const double add_us[] = {0.0, 0.0, 1.0, 3.5};
+    CodesPlan best = P;
+    double least = 0.0;
+    for (int most = 1; most <= 4; ++most) {
+        CodesPlan c = P;
+        codes_cut(c, most < 4 ? most : QG_MAX_SEGMENTS, cus, false);
+        c.fused = most < 4 && c.parts > 1;
+        const double us = c.quota * unit_us + (most < 4 ? add_us[c.parts] : 5.5);
+        if (most == 1 || us < least) {
+            best = c;
+            least = us;
         }
     }
-    return P;
+    return best;
 }
 }  // namespace
 
@@ -887,13 +921,14 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     if (!qg_aligned16(workspace)) return QG_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
 
-    // The raw-code kernel: every layout it takes that the 4-bit kernels below do not (2 and 3
-    // bits, 4-bit groups of 16), and whatever shape 13 sends it.  (Measured on the 7B shapes at 4
-    // bits, group 128: within 0-20 % of the dequantizing kernels, behind mostly by the launch of
-    // prepare_x; at 2 and 3 bits 2-15 times ahead of one GEMV per row.)
+    // The raw-code kernel: every layout it takes that the 4-bit kernels below do not (2 and 3 bits, 4-bit
+    // groups of 16), whatever shape 13 sends it, and the larger 4-bit matrices (in tile-steps of 64 outputs x
+    // 128 k), where it is ahead of the dequantizing kernels; us per call, raw codes | dequantizing:
+    // 11008 x 4096 (5504) M = 20 15.3 | 16.9, M = 32 15.3 | 18.1, M = 64 23.4 | 20.0; 4096 x 11008 M = 32 15.4 |
+    // 15.8, M = 64 22.8 | 23.3; 22016 x 8192 (22016) M = 32 33.0 | 54.1, M = 64 45.4 | 63.3; 4096 x 4096 (2048)
+    // M = 32 12.4 | 11.5, M = 128 19.5 | 18.1.
     const int gps = codes_gps(L);
-    // (... and, measured, 3-6 % ahead of them beyond 64 rows on the larger 7B shapes)
-    const bool large = M > 64 && L.tiles * L.steps >= 4096;
+    const bool large = M > 16 && L.tiles * L.steps >= (M > 32 && M <= 64 ? 8192 : 4096);
     if (gps >= 0 && M > 1 && (knob_shape == NSHAPES + 1 || (knob_shape == 0 && (!fast_path(L) || large)))) {
         const CodesPlan C = codes_plan(L, gps, M, knob_splits);
         const CodesSpace W = codes_space(L, gps, M);
@@ -905,6 +940,8 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         P.K = (int)K;
         P.steps_padded = W.steps_padded;
         P.groupk = W.groupk;
+        P.arrived = (uint32_t *)(ws + W.arrived_off);
+        P.counters = C.fused ? (int)L.tiles << C.zshift : 0;
         QgCodesArgs A;
         const char *base = (const char *)packed;
         A.codes = base + L.codes_off;
@@ -915,7 +952,8 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         A.tile_zeros = (uint32_t)(L.zwords * QG_WAVE * 4);
         A.Xop = ws;
         A.Y = Y;
-        A.partial = (float *)(ws + W.partial_off);
+        A.partial = ws + W.partial_off;
+        A.arrived = (uint32_t *)(ws + W.arrived_off);
         A.M = M;
         A.N = (int)N;
         A.tiles = (int)L.tiles;
@@ -926,11 +964,11 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         A.ranges = C.ranges;
         A.quota = C.quota;
         A.total = C.blocks * C.units;
-        A.pitch = (int)L.tiles * QG_WAVE;
+        A.fused = C.fused;
         auto main_kernel = [&](KernelInfo *query) {
-            return bits == 4 ? qg_codes_launch_b4(gps, C.mb, C.tn, C.kw, A, C.workgroups, st, query)
-                 : bits == 2 ? qg_codes_launch_b2(gps, C.mb, C.tn, C.kw, A, C.workgroups, st, query)
-                             : qg_codes_launch_b3(gps, C.mb, C.tn, C.kw, A, C.workgroups, st, query);
+            return bits == 4 ? qg_codes_launch_b4(gps, C.mb, A, C.workgroups, st, query)
+                 : bits == 2 ? qg_codes_launch_b2(gps, C.mb, A, C.workgroups, st, query)
+                             : qg_codes_launch_b3(gps, C.mb, A, C.workgroups, st, query);
         };
         // (the instance is looked up before anything is enqueued: a layout without one is an error
         // that leaves nothing behind)
@@ -938,7 +976,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         const int have = main_kernel(&info);
         if (have != QG_OK) return have;
         if (price) {
-            *price = {0, NSHAPES, C.ranges, (long)C.workgroups, C.quota, C.ranges != 1 ? 3 : 2, info};
+            *price = {0, NSHAPES, C.ranges, (long)C.workgroups, C.quota, C.ranges != 1 && !C.fused ? 3 : 2, info};
             return QG_OK;
         }
         if (bits == 4) qg_codes_prepare_b4(P, W.rows_padded, st);
@@ -948,9 +986,9 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         const int r = main_kernel(nullptr);
         if (r != QG_OK) return r;
         if (qg_launch_status() != QG_OK) return QG_ERR_DEVICE;
-        if (C.ranges != 1) {
-            const unsigned quads = (unsigned)(L.tiles * (QG_WAVE / 4));
-            hipLaunchKernelGGL(add_ranges, dim3((quads + 255) / 256, (unsigned)M), dim3(256), 0, st, A.partial, A.pitch, (int)N, M,
+        if (C.ranges != 1 && !C.fused) {
+            const int64_t quads = L.tiles * ((M + 7) / 8) * 2;
+            hipLaunchKernelGGL(add_parts, dim3((unsigned)((quads + 3) / 4)), dim3(256), 0, st, A.partial, (int)L.tiles, (int)N, M,
                                C.tn, 32 * C.mb, C.zshift, C.units, C.ranges, C.quota, Y);
         }
         return qg_launch_status();
