@@ -851,7 +851,9 @@ CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
     // 17.2, 13824 x 5120 3-bit M = 100 34.0 | 38.0, M = 48 26.1 | 23.7, 4096 x 11008 4-bit M = 128 37.9 | 27.9,
     // 8192 x 8192 2-bit g32 M = 20 19.1-21.5 | 17.5.
     if (knob_splits) {
-        codes_cut(P, knob_splits, cus, true);
+        // (a count that would need more workgroups than compute units is dealt evenly over those, as the
+        // built-in choice would, so that the launch-shape search meets that plan too)
+        codes_cut(P, knob_splits, cus, knob_splits == 1 || (int64_t)P.blocks * knob_splits <= cus);
         P.fused = P.parts > 1 && P.parts <= 3;
         return P;
     }
