@@ -27,8 +27,9 @@
 // computed.  K may also be cut into `splits` ranges handled by different workgroups; their
 // fp32 partial results are added by a second small kernel in a fixed order.
 //
-// Other bit widths and group sizes take the fp32 GEMV kernel once per activation row, up to
-// 16 rows per launch.
+// The other widths, 4-bit groups of 16 and the larger 4-bit products take the kernel on raw codes
+// (qg_gemm_codes.h); what neither takes runs the fp32 GEMV kernel once per activation row, up to 16
+// rows per launch.
 #include <mutex>
 #include <type_traits>
 

@@ -831,6 +831,42 @@ def test_gemm_small_raw_code_kernel(qg, oracle, N, K, bits, group, M, splits):
     assert err <= TOL_BF16, err
 
 
+@pytest.mark.parametrize("splits", [1, 2, 3, 8])       # no parts; parts added by the last workgroup; by a kernel
+@pytest.mark.parametrize("N,K,bits,group,M", [(300, 2304, 4, 128, 40), (200, 4096, 2, 32, 100), (130, 3072, 3, 64, 9)])
+def test_gemm_small_replayed_from_a_graph(qg, oracle, N, K, bits, group, M, splits):
+    # a captured call, replayed with eager calls and synchronizations in between: the counters of the
+    # parts are cleared by every call, and every replay gives the bits of the eager call
+    _announce("gemm in a graph", N, K, bits, group, M, splits)
+    W, X = synth.small_case(4800 + N + splits, N, K, 0.02, True, m=M)
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    norms = oracle.row_norms(q0, s0, z0, group)
+    blob = qg.qg_pack(*qg.qg_quantize(dev(W), bits, group), bits, group)
+    ws = qg.new_workspace(qg.qg_workspace_bytes(N, K, bits, group, M))
+    x, y = dev(X), torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    qg.qg_set_gemm_tuning(splits, 13)
+    try:
+        qg.qg_gemm_small(blob, N, K, bits, group, x, y, ws)          # the kernels are loaded before the capture
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            qg.qg_gemm_small(blob, N, K, bits, group, x, y, ws)
+        for replay in range(4):
+            Xr = (X * np.float32(replay + 1)).astype(np.float32)
+            x.copy_(dev(Xr))
+            y.fill_(7.0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            replayed = host(y).copy()
+            eager = host(qg.qg_gemm_small(blob, N, K, bits, group, x, None, ws))
+            torch.cuda.synchronize()
+            assert np.array_equal(replayed, eager), replay
+            err = scaled_error(replayed, oracle.matmul_small(q0, s0, z0, group, Xr), norms, Xr)
+            assert err <= gemm_model_bound(K), (replay, err)
+    finally:
+        qg.qg_set_gemm_tuning(0, 0)
+
+
 @pytest.mark.parametrize("N,K,bits,group,M", [
     (25600, 2304, 4, 64, 40),        # units dealt evenly over the workgroups: blocks that two or three of them share
     (25600, 2304, 2, 32, 100),       # ... two blocks of rows
