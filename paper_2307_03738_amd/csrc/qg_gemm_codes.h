@@ -249,24 +249,32 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     };
     // Where the next unit's data are (all scalar).  Reads past a tile's codes, scales or zero words (a
     // k-slice past K; the last step of a K that ends inside it) return zeros; the activations there are
-    // zeros too.
+    // zeros too.  A buffer checks the lane's offset against its size and leaves the scalar offset of the
+    // instruction out, so the buffers of a unit begin at its step and end with the tile's section (a step
+    // past it: size 0).
+    const char *codes_t, *scales_t, *zeros_t;
     rsrc_t codes_n, scales_n, zeros_n, x_n;
-    uint32_t at_codes, at_scales, at_zeros, at_x;
+    uint32_t at_x;
     const uint32_t x_row_block = (uint32_t)A.steps_padded * (SEQ * 1024);
     auto aim_block = [&](int nb) {
         const int tb = nb >> A.zshift, z = nb - (tb << A.zshift);
         int tile = tb * TN + tn;
         tile = tile < A.tiles ? tile : A.tiles - 1;
-        codes_n = buffer_of(A.codes + (size_t)tile * A.tile_codes, A.tile_codes);
-        scales_n = buffer_of(A.scales + (size_t)tile * A.tile_scales, A.tile_scales);
-        zeros_n = buffer_of(A.zeros + (size_t)tile * A.tile_zeros, A.tile_zeros);
+        codes_t = A.codes + (size_t)tile * A.tile_codes;
+        scales_t = A.scales + (size_t)tile * A.tile_scales;
+        zeros_t = A.zeros + (size_t)tile * A.tile_zeros;
         x_n = buffer_of(A.Xop + (size_t)z * MB * x_row_block, MB * x_row_block);
+    };
+    auto rest_of = [&](const char *section, uint32_t bytes, uint32_t at) {
+        at = at < bytes ? at : bytes;
+        return buffer_of(section + at, bytes - at);
     };
     auto aim = [&](int nit) {
         const uint32_t step = nit * KW + kw;
-        at_codes = step * (L * 1024);
-        at_scales = (LONG ? __umulhi(step, A.group_magic) : step * GPS) * 256;
-        at_zeros = (LONG ? __umulhi(step, A.group_magic) : step * GPS) / ZPER * 256;      // a step's groups share one zero word
+        const uint32_t g = LONG ? __umulhi(step, A.group_magic) : step * GPS;
+        codes_n = rest_of(codes_t, A.tile_codes, step * (L * 1024));
+        scales_n = rest_of(scales_t, A.tile_scales, g * 256);
+        zeros_n = rest_of(zeros_t, A.tile_zeros, g / ZPER * 256);                         // a step's groups share one zero word
         at_x = nit * (KW * SEQ * 1024);
     };
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
@@ -284,12 +292,12 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     auto request = [&](int t, StepRegs &r, int stage) {
         if (t < L) {
             typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(codes_n, lane16 + t * 1024, at_codes, 0);
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(codes_n, lane16 + t * 1024, 0, 0);
             r.v[t] = make_uint4(v[0], v[1], v[2], v[3]);
         } else if (t == L) {
-            r.zw = __builtin_amdgcn_raw_buffer_load_b32(zeros_n, lane4, at_zeros, 0);
+            r.zw = __builtin_amdgcn_raw_buffer_load_b32(zeros_n, lane4, 0, 0);
         } else if (t < NLOAD) {
-            r.s[t - L - 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(scales_n, lane4 + (t - L - 1) * 256, at_scales, 0));
+            r.s[t - L - 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(scales_n, lane4 + (t - L - 1) * 256, 0, 0));
         } else if (t < NLOAD + NDMA) {
             const int j = t - NLOAD;
             const int p = j * NW + wave < CHUNK ? j * NW + wave : CHUNK - 1;
@@ -672,7 +680,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
                 if (sg < nseg) {
                     const rsrc_t part = part_of(sg);
 #pragma unroll
-                    for (int i = 0; i < AT_ONCE; ++i) v[i][sg] = __builtin_amdgcn_raw_buffer_load_b128(part, lane16, (q0 + i) * 1024, SC1);
+                    for (int i = 0; i < AT_ONCE; ++i) v[i][sg] = __builtin_amdgcn_raw_buffer_load_b128(part, lane16 + (q0 + i) * 1024, 0, SC1);
                 }
 #pragma unroll
             for (int i = 0; i < AT_ONCE; ++i) {

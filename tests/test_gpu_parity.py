@@ -883,6 +883,36 @@ def test_gemm_small_raw_code_units(qg, oracle, N, K, bits, group, M):
     assert err <= TOL_BF16, err
 
 
+@pytest.mark.parametrize("bits,group,K,M", [
+    (4, 128, 1152, 20), (4, 384, 1152, 9), (4, 64, 1408, 40), (4, 16, 1200, 100), (3, 64, 1216, 20), (3, 128, 1152, 70),
+    (3, 768, 2304, 17), (2, 32, 1184, 9), (2, 64, 1344, 40), (2, 256, 1280, 20)])
+@pytest.mark.parametrize("behind", ["zero-points", "another tile"])
+def test_gemm_small_raw_codes_end_with_their_tile(qg, oracle, bits, group, K, M, behind):
+    # K leaves k-slices past its end, and groups past its end in the last step.  What lies behind the tile's
+    # scales must not come in, since it would come in times zero: with every zero-point at the top of its
+    # range the zero words behind the last tile's scales are NaN (2 and 4 bits), and another tile's scales
+    # may be anything.
+    _announce("gemm raw codes, end of a tile", bits, group, K, M, behind)
+    rng = np.random.default_rng(4700 + bits + group + M)
+    N, top = (64 if behind == "zero-points" else 192), (1 << bits) - 1
+    q = rng.integers(0, top + 1, (N, K), dtype=np.uint8)
+    s = rng.uniform(0.01, 0.02, (N, K // group)).astype(np.float32)
+    z = np.full((N, K // group), top, np.uint8)
+    s[64:128:2], s[65:128:2] = np.inf, np.nan
+    good = [n for n in range(N) if not 64 <= n < 128]
+    X = rng.standard_normal((M, K)).astype(np.float32)
+    blob = qg.qg_pack(dev(q), dev(s), dev(z), bits, group)
+    qg.qg_set_gemm_tuning(0, 13)
+    try:
+        Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X)))[:, good]
+    finally:
+        qg.qg_set_gemm_tuning(0, 0)
+    assert np.all(np.isfinite(Y))
+    q, s, z = q[good], s[good], z[good]
+    err = scaled_error(Y, oracle.matmul_small(q, s, z, group, X), oracle.row_norms(q, s, z, group), X)
+    assert err <= gemm_model_bound(K), err
+
+
 @pytest.mark.parametrize("tuning", [(0, 0, 0), (1, 4096, 0), (3, 8192, 0), (8, 65536, 0)])
 @pytest.mark.parametrize("N,K,group,M", [(200, 1024, 128, 16), (130, 512, 16, 7), (70, 1408, 32, 1), (300, 2304, 64, 13),
                                          (64, 11008, 128, 16), (1000, 128, 128, 9)])
