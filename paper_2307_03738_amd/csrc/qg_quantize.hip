@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float4 *__restrict_
     }
 }
 
-// Least and greatest of three.
+// Least and greatest of three; NaNs of either kind are passed over (numbers_past_nans).
 __device__ inline float min3(float a, float b, float c)
 {
     float r;
@@ -74,6 +74,15 @@ __device__ inline float max3(float a, float b, float c)
     float r;
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
+}
+
+// The IEEE bit of the wavefront's mode off: with it on, a minimum that meets a signalling NaN is that NaN made
+// quiet, and the next minimum drops it with everything it had seen, so one such weight spoiled the range
+// of its group.  Off, a NaN of either kind is passed over, as a comparison would (making every weight quiet
+// first would be one more instruction for each).
+__device__ inline void numbers_past_nans()
+{
+    __builtin_amdgcn_s_setreg(1 | 9 << 6, 0);           // hwreg(MODE, 9, 1)
 }
 
 template <int CTRL>
@@ -135,6 +144,7 @@ __global__ __launch_bounds__(256) void quantize_regs(const float4 *__restrict__ 
     const int64_t teams = (int64_t)gridDim.x * blockDim.x / TEAM;
     const int64_t team = tid / TEAM;
     const int lane = (int)(tid % TEAM);
+    numbers_past_nans();
 
     float4 v[U][R];
 #pragma unroll

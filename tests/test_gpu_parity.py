@@ -108,6 +108,30 @@ def test_quantize_special_values_bit_exact(qg, oracle):
         assert np.array_equal(host(z), z0), bits
 
 
+@pytest.mark.parametrize("group", [16, 32, 64, 128, 256, 1024, 4096, 48])
+@pytest.mark.parametrize("pattern", [0x7fc00000, 0xffc00001, 0x7f800001, 0xffbfffff, 0x7f800000, 0xff800000])
+def test_quantize_not_a_number_and_infinity(qg, oracle, group, pattern):
+    # one weight of every other group is a quiet or signalling NaN or an infinity, at every place of a
+    # lane's four: a NaN is passed over in the range and its code is the zero-point, every other value is as
+    # the oracle's
+    _announce("quantize special pattern", group, hex(pattern))
+    rng = np.random.default_rng(950 + group)
+    N = 16
+    W = (rng.standard_normal((N, 2 * group)) * 0.02).astype(np.float32)
+    at = (rng.integers(0, group // 4, N) * 4 + np.arange(N) % 4).astype(np.int64)
+    W.view(np.uint32)[np.arange(N), at] = pattern
+    for bits in (2, 3, 4):
+        if group % {2: 16, 3: 32, 4: 8}[bits]:
+            continue
+        q0, s0, z0 = oracle.quantize(W, bits, group)
+        q, s, z = (host(t) for t in qg.qg_quantize(dev(W), bits, group))
+        assert np.array_equal(s.view(np.uint32), s0.view(np.uint32)), bits
+        assert np.array_equal(z, z0), bits
+        if np.isnan(np.uint32(pattern).view(np.float32)):
+            q0[np.arange(N), at] = z0[:, 0]
+        assert np.array_equal(q, q0), bits
+
+
 # ------------------------------------------------------------------ pack / unpack (bit-exact)
 
 PACK_CASES = [(512, 512, 4, 64), (200, 768, 4, 128), (130, 640, 3, 64), (77, 512, 2, 32),
