@@ -304,7 +304,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
             const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + (stage * CHUNK + p) * 1024);
             const uint32_t from = __builtin_amdgcn_readfirstlane(at_x + piece_at[j]);
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane16), "s"(x_n), "s"(from)
-                         : "memory");
+                         : "memory", "m0");
         }
     };
 
