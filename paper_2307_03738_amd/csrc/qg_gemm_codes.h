@@ -78,6 +78,7 @@ struct QgKernelInfo {
 
 constexpr size_t QG_LDS_BYTES = 160u << 10;
 constexpr int QG_MAX_SEGMENTS = 8;             // parts the sum of an element of Y is cut into, at most
+constexpr int QG_FUSED_SEGMENTS = 3;           // ... and are added by the workgroup that comes last, at most
 
 // gps: groups per step of 128 k, 0 for groups of several steps.  A operands per step and block of 32 rows:
 constexpr int qg_codes_seq(int gps) { return 8 + (gps > 0 ? gps : 1); }
@@ -674,9 +675,9 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         constexpr int SHARE = QUADS / KW, AT_ONCE = SHARE < 2 ? SHARE : 2;
         static_assert(QUADS % KW == 0 && SHARE % AT_ONCE == 0, "quads per wavefront");
         for (int q0 = kw * SHARE; q0 < (kw + 1) * SHARE; q0 += AT_ONCE) {
-            u32x4 v[AT_ONCE][QG_MAX_SEGMENTS];
+            u32x4 v[AT_ONCE][QG_FUSED_SEGMENTS];
 #pragma unroll
-            for (int sg = 0; sg < QG_MAX_SEGMENTS; ++sg)
+            for (int sg = 0; sg < QG_FUSED_SEGMENTS; ++sg)
                 if (sg < nseg) {
                     const rsrc_t part = part_of(sg);
 #pragma unroll
@@ -688,7 +689,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
 #pragma unroll
                 for (int j = 0; j < 4; ++j) t[j] = __uint_as_float(v[i][0][j]);
 #pragma unroll
-                for (int sg = 1; sg < QG_MAX_SEGMENTS; ++sg)
+                for (int sg = 1; sg < QG_FUSED_SEGMENTS; ++sg)
                     if (sg < nseg) {
 #pragma unroll
                         for (int j = 0; j < 4; ++j) t[j] += __uint_as_float(v[i][sg][j]);

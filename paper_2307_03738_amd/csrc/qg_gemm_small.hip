@@ -855,18 +855,18 @@ CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
         // (a count that would need more workgroups than compute units is dealt evenly over those, as the
         // built-in choice would, so that the launch-shape search meets that plan too)
         codes_cut(P, knob_splits, cus, knob_splits == 1 || (int64_t)P.blocks * knob_splits <= cus);
-        P.fused = P.parts > 1 && P.parts <= 3;
+        P.fused = P.parts > 1 && P.parts <= QG_FUSED_SEGMENTS;
         return P;
     }
     const double unit_us = P.mb == 1 ? (gps >= 4 ? 2.0 : gps == 2 ? 1.3 : 1.0) : (gps >= 4 ? 2.4 : gps == 2 ? 2.0 : 1.8);
     const double add_us[] = {0.0, 0.0, 1.0, 3.5};
     CodesPlan best = P;
     double least = 0.0;
-    for (int most = 1; most <= 4; ++most) {
+    for (int most = 1; most <= QG_FUSED_SEGMENTS + 1; ++most) {
         CodesPlan c = P;
-        codes_cut(c, most < 4 ? most : QG_MAX_SEGMENTS, cus, false);
-        c.fused = most < 4 && c.parts > 1;
-        const double us = c.quota * unit_us + (most < 4 ? add_us[c.parts] : 5.5);
+        codes_cut(c, most <= QG_FUSED_SEGMENTS ? most : QG_MAX_SEGMENTS, cus, false);
+        c.fused = most <= QG_FUSED_SEGMENTS && c.parts > 1;
+        const double us = c.quota * unit_us + (most <= QG_FUSED_SEGMENTS ? add_us[c.parts] : 5.5);
         if (most == 1 || us < least) {
             best = c;
             least = us;
