@@ -628,14 +628,17 @@ __global__ void add_splits(const float *__restrict__ partial, int splits, size_t
 
 // The same for the raw-code kernel (parts as it writes them: quads of 4 rows x 32 outputs, lane = row half and
 // output).  A block of outputs and rows has `ranges` parts or, with ranges == 0, as many as workgroups its
-// units fell to (one: that workgroup has stored Y itself).
-__global__ __launch_bounds__(256) void add_parts(const char *__restrict__ partial, int tiles, int N, int M, int tn, int rows,
-                                                 int zshift, int units, int ranges, int quota, float *__restrict__ Y)
+// units fell to (one: that workgroup has stored Y itself).  A workgroup is one wavefront and a quarter of a quad,
+// one element per lane: what bounds it is the way of the parts from the other dies, so the more
+// wavefronts ask at once the better (a call with eight parts, us, against 16 bytes per lane and four
+// wavefronts per workgroup: 2048 x 2048 M = 24 10.1 -> 9.3, 4096 x 4096 M = 24 11.5 -> 10.8, 8192 x 8192 M = 24
+// 16.1 -> 15.6).
+__global__ __launch_bounds__(64) void add_parts(const char *__restrict__ partial, int tiles, int N, int M, int tn, int rows,
+                                                int zshift, int units, int ranges, int quota, float *__restrict__ Y)
 {
     const int bands = (M + 7) / 8;
-    const int q = blockIdx.x * 4 + (threadIdx.x >> 6);        // (tile, band, pq)
-    const int lane = threadIdx.x & 63;
-    if (q >= tiles * bands * 2) return;
+    const int q = blockIdx.x / 4;                             // (tile, band, pq)
+    const int at = blockIdx.x % 4 * 64 + threadIdx.x;         // element of the quad
     const int pq = q & 1, band = (q >> 1) % bands, tile = (q >> 1) / bands;
     int count = ranges;
     if (ranges == 0) {
@@ -643,26 +646,15 @@ __global__ __launch_bounds__(256) void add_parts(const char *__restrict__ partia
         count = ((b + 1) * units - 1) / quota - b * units / quota + 1;
         if (count == 1) return;
     }
-    const float4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    float4 v[QG_MAX_SEGMENTS];
+    float v[QG_MAX_SEGMENTS];
 #pragma unroll
     for (int s = 0; s < QG_MAX_SEGMENTS; ++s)
-        v[s] = s < count ? *(const float4 *)(partial + (((size_t)s * tiles + tile) * bands + band) * 2048 + pq * 1024 + lane * 16) : zero;
-    float4 t = v[0];
+        v[s] = s < count ? *(const float *)(partial + (((size_t)s * tiles + tile) * bands + band) * 2048 + pq * 1024 + at * 4) : 0.0f;
+    float t = v[0];
 #pragma unroll
-    for (int s = 1; s < QG_MAX_SEGMENTS; ++s) {           // the missing ones add +0.0
-        t.x += v[s].x;
-        t.y += v[s].y;
-        t.z += v[s].z;
-        t.w += v[s].w;
-    }
-    const int n = tile * QG_WAVE + 32 * pq + (lane & 31), m = band * 8 + 4 * (lane >> 5);
-    if (n >= N) return;
-    float *o = Y + (size_t)m * N + n;
-    if (m < M) o[0] = t.x;
-    if (m + 1 < M) o[(size_t)N] = t.y;
-    if (m + 2 < M) o[(size_t)2 * N] = t.z;
-    if (m + 3 < M) o[(size_t)3 * N] = t.w;
+    for (int s = 1; s < QG_MAX_SEGMENTS; ++s) t += v[s];      // the missing ones add +0.0
+    const int lane = at / 4, n = tile * QG_WAVE + 32 * pq + (lane & 31), m = band * 8 + 4 * (lane >> 5) + at % 4;
+    if (n < N && m < M) Y[(size_t)m * N + n] = t;
 }
 
 bool fast_path(const QgLayout &L)
@@ -991,7 +983,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         if (qg_launch_status() != QG_OK) return QG_ERR_DEVICE;
         if (C.ranges != 1 && !C.fused) {
             const int64_t quads = L.tiles * ((M + 7) / 8) * 2;
-            hipLaunchKernelGGL(add_parts, dim3((unsigned)((quads + 3) / 4)), dim3(256), 0, st, A.partial, (int)L.tiles, (int)N, M,
+            hipLaunchKernelGGL(add_parts, dim3((unsigned)quads * 4u), dim3(64), 0, st, A.partial, (int)L.tiles, (int)N, M,
                                C.tn, 32 * C.mb, C.zshift, C.units, C.ranges, C.quota, Y);
         }
         return qg_launch_status();
