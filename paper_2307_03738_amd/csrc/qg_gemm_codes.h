@@ -58,6 +58,7 @@ struct QgCodesArgs {
     int quota;                 // units per workgroup
     int total;                 // units of the launch = blocks * units
     int fused;                 // parts of a sum are added here (else by add_parts)
+    int kw;                    // k-slices of a workgroup
 };
 
 struct QgPrepArgs {
@@ -82,19 +83,24 @@ constexpr int QG_FUSED_SEGMENTS = 3;           // ... and are added by the workg
 
 // gps: groups per step of 128 k, 0 for groups of several steps.  A operands per step and block of 32 rows:
 constexpr int qg_codes_seq(int gps) { return 8 + (gps > 0 ? gps : 1); }
-// LDS of an instance: two units of A operands, and 32 rows of the accumulators of k-slices 1 ... KW-1
+// LDS of an instance: two units of A operands, and 32 rows of the accumulators of k-slices 1 ... KW-1; where
+// those do not fit beside the operands (groups of 16 with four slices) they lie over the unit just multiplied
+constexpr size_t qg_codes_stages(int gps, int mb, int kw) { return (size_t)2 * mb * kw * qg_codes_seq(gps) * 1024; }
+constexpr bool qg_codes_slices_apart(int gps, int mb, int tn, int kw)
+{
+    return qg_codes_stages(gps, mb, kw) + (size_t)(kw - 1) * tn * 32 * 256 <= QG_LDS_BYTES;
+}
 constexpr size_t qg_codes_lds(int gps, int mb, int tn, int kw)
 {
-    return (size_t)2 * mb * kw * qg_codes_seq(gps) * 1024 + (size_t)(kw - 1) * tn * 32 * 256;
+    return qg_codes_stages(gps, mb, kw) + (qg_codes_slices_apart(gps, mb, tn, kw) ? (size_t)(kw - 1) * tn * 32 * 256 : 0);
 }
-// k-slices of a workgroup of eight wavefronts: as many as LDS holds, up to 4 at 32 rows and 2 at 64 (4 there, with half
-// of the tiles, halves the partial sums but doubles the A operands' traffic: 13824 x 5120 3-bit M = 37 25.2
-// against 22.2 us, 4096 x 11008 4-bit M = 128 29.1 against 27.3; 1 doubles the partial sums: 22.5, 31.0)
-constexpr int qg_codes_kw(int gps, int mb)
-{
-    const int kw = mb == 1 ? 4 : 2;
-    return qg_codes_lds(gps, mb, 8 / kw, kw) > QG_LDS_BYTES ? kw / 2 : kw;
-}
+// k-slices of a workgroup of eight wavefronts: 4 at 32 rows and 2 at 64 (4 there, with half of the tiles, halves
+// the partial sums but doubles the A operands' traffic: 13824 x 5120 3-bit M = 37 25.2 against 22.2 us, 4096 x
+// 11008 4-bit M = 128 29.1 against 27.3; 1 doubles the partial sums: 22.5, 31.0).  Groups of 16 at 32
+// rows, with two A operands for every 16 k, are bound by that traffic as soon as there are tiles enough for
+// every compute unit: 2 there (22016 x 8192 M = 2 40.6 against 45.4 us, 8192 x 8192 18.7 against 20.2), 4 below
+// (1500 x 20480 29.4 against 20.2, 4096 x 11008 21.1 against 17.9, 512 x 512 9.2 against 8.1).
+constexpr int qg_codes_kw(int gps, int mb, bool many_tiles) { return mb == 1 && !(gps == 8 && many_tiles) ? 4 : 2; }
 
 // One per bit width.  query: fill it instead of launching.
 int qg_codes_launch_b2(int gps, int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query);
@@ -558,6 +564,9 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
             }
     };
 
+    int stage = 0;                                         // of the A operands of the next unit
+    constexpr bool APART = qg_codes_slices_apart(GPS_, MB, TN, KW);
+    auto slices_at = [&]() { return APART ? 2 * CHUNK * 1024 : (stage ^ 1) * CHUNK * 1024; };
     // End of a block's units in this workgroup: the whole sum to Y, a part of it to this part's place
     // among the partial results.
     auto finish = [&]() {
@@ -571,7 +580,8 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         if constexpr (KW > 1) {
             // k-slices 1 .. KW-1 hand their results to slice 0 of the same tile, which adds them in
             // slice order, 32 rows at a time
-            float *red = (float *)(smem + 2 * CHUNK * 1024) + lane;
+            if constexpr (!APART) __syncthreads();           // every wavefront has read the unit's operands
+            float *red = (float *)(smem + slices_at()) + lane;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 if (mb > 0) __syncthreads();
@@ -666,7 +676,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         }
         if constexpr (KW > 1) {
             // the k-slices' wavefronts share the adding: slice 0 tells them
-            uint32_t *flag = (uint32_t *)(smem + 2 * CHUNK * 1024) + tn * (32 * 64);
+            uint32_t *flag = (uint32_t *)(smem + slices_at()) + tn * (32 * 64);
             if (kw == 0 && lane == 0) *flag = last;
             __syncthreads();
             last = __builtin_amdgcn_readfirstlane(*flag) != 0;
@@ -714,7 +724,6 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         asm volatile("" : "+v"(r.zw));
         __syncthreads();
     };
-    int stage = 0;
     auto unit = [&](StepRegs &use, StepRegs &req) {
         arrive(use);
         const uint32_t step = it * KW + kw;
@@ -751,37 +760,40 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
 template <int BITS, int GPS, int MB, int TN, int KW, bool FUSED>
 int codes_launch(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
-    if constexpr (qg_codes_lds(GPS, MB, TN, KW) <= QG_LDS_BYTES) {
-        constexpr size_t lds = qg_codes_lds(GPS, MB, TN, KW);
-        const void *f = (const void *)gemm_codes<BITS, GPS, MB, TN, KW, FUSED>;
-        if (query) {
-            *query = {f, TN * KW * 64, lds};
-            return QG_OK;
-        }
-        static bool prepared = false;              // dynamic LDS above 64 KB has to be asked for once
-        if (!prepared) {
-            if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-                (void)hipGetLastError();
-                return QG_ERR_DEVICE;
-            }
-            prepared = true;
-        }
-        hipLaunchKernelGGL((gemm_codes<BITS, GPS, MB, TN, KW, FUSED>), dim3((unsigned)workgroups), dim3(TN * KW * 64), lds, st, A);
+    static_assert(qg_codes_lds(GPS, MB, TN, KW) <= QG_LDS_BYTES, "LDS of a workgroup");
+    static_assert(qg_codes_slices_apart(GPS, MB, TN, KW) || (KW - 1) * TN * 32 * 256 <= qg_codes_stages(GPS, MB, KW) / 2, "slices in a stage");
+    constexpr size_t lds = qg_codes_lds(GPS, MB, TN, KW);
+    const void *f = (const void *)gemm_codes<BITS, GPS, MB, TN, KW, FUSED>;
+    if (query) {
+        *query = {f, TN * KW * 64, lds};
         return QG_OK;
-    } else {
-        return QG_ERR_UNSUPPORTED;
     }
+    static bool prepared = false;              // dynamic LDS above 64 KB has to be asked for once
+    if (!prepared) {
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+            (void)hipGetLastError();
+            return QG_ERR_DEVICE;
+        }
+        prepared = true;
+    }
+    hipLaunchKernelGGL((gemm_codes<BITS, GPS, MB, TN, KW, FUSED>), dim3((unsigned)workgroups), dim3(TN * KW * 64), lds, st, A);
+    return QG_OK;
+}
+
+template <int BITS, int GPS, int MB, int KW>
+int codes_launch_fused(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
+{
+    return A.fused ? codes_launch<BITS, GPS, MB, 8 / KW, KW, true>(A, workgroups, st, query)
+                   : codes_launch<BITS, GPS, MB, 8 / KW, KW, false>(A, workgroups, st, query);
 }
 
 template <int BITS, int GPS>
 int codes_launch_shape(int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
-    constexpr int K1 = qg_codes_kw(GPS, 1), K2 = qg_codes_kw(GPS, 2);
-    if (mb == 1)
-        return A.fused ? codes_launch<BITS, GPS, 1, 8 / K1, K1, true>(A, workgroups, st, query)
-                       : codes_launch<BITS, GPS, 1, 8 / K1, K1, false>(A, workgroups, st, query);
-    return A.fused ? codes_launch<BITS, GPS, 2, 8 / K2, K2, true>(A, workgroups, st, query)
-                   : codes_launch<BITS, GPS, 2, 8 / K2, K2, false>(A, workgroups, st, query);
+    constexpr int FEW = qg_codes_kw(GPS, 1, false), MANY = qg_codes_kw(GPS, 1, true);
+    if (mb == 2) return codes_launch_fused<BITS, GPS, 2, qg_codes_kw(GPS, 2, true)>(A, workgroups, st, query);
+    return A.kw == FEW ? codes_launch_fused<BITS, GPS, 1, FEW>(A, workgroups, st, query)
+                       : codes_launch_fused<BITS, GPS, 1, MANY>(A, workgroups, st, query);
 }
 
 template <int BITS>

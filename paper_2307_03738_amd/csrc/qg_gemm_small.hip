@@ -803,6 +803,7 @@ CodesSpace codes_space(const QgLayout &L, int gps, int M)
 struct CodesPlan {
     int mb, tn, kw, zshift, blocks, units, ranges, quota, workgroups, parts;
     bool fused;
+    double us;                 // what it costs (codes_cost_us)
 };
 
 // Cuts into at most `most` parts per block, one workgroup per compute unit at most where that is possible (a
@@ -826,6 +827,29 @@ void codes_cut(CodesPlan &P, int most, int cus, bool exactly)
     }
 }
 
+// Estimate of a call: a straight line through 9000 cuts of 18 matrices from 512 x 512 to 30000 x 4096 at 2, 3
+// and 4 bits, groups of 16, 32, 64, 128 and one per output, 2 ... 128 rows (root mean square of what it is off: 4
+// %).  A unit has a time of its own, by rows and groups per step, and one on a full chip for the weights it reads.
+// Two or three parts are added by the workgroup that comes last, which alone reads them all; more by
+// a kernel, which the whole chip shares; an evenly dealt workgroup ends a block of outputs in the middle
+// of its units as well as at their end.
+// (A table that went by the groups per step alone and took the adding for 1 us at two parts put 5120 x 5120 3-bit g64
+// M = 16 on 80 workgroups, 14.0 -> 15.3 us, and 4096 x 4096 3-bit M = 8 on 64, 10.6 -> 13.0; now 11.9 and 9.7.)
+double codes_cost_us(const QgLayout &L, int gps, int M, const CodesPlan &P, int cus)
+{
+    static constexpr double UNIT_US[2][5] = {{1.0, 1.05, 1.2, 1.45, 2.0}, {1.35, 1.4, 1.65, 2.15, 3.2}};
+    const double unit = UNIT_US[P.mb - 1][gps == 0 ? 0 : gps == 1 ? 1 : gps == 2 ? 2 : gps == 4 ? 3 : 4];
+    const double weights = L.bits == 4 ? 0.5 : L.bits == 3 ? 0.35 : 0.1;
+    const int rounds = (P.workgroups + cus - 1) / cus;
+    double us = (P.mb == 1 ? 6.0 : 7.3) + rounds * P.quota * (unit + weights * (rounds > 1 ? 1.0 : (double)P.workgroups / cus));
+    if (P.ranges == 0) us += 1.4;
+    if (P.parts > 1) {
+        const double mb = 4e-6 * P.parts * M * (double)L.N;
+        us += P.fused ? (P.mb == 1 ? 1.5 : 4.6) + 0.3 * mb : 1.5 + 0.5 * mb;
+    }
+    return us;
+}
+
 CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
 {
     CodesPlan P;
@@ -833,36 +857,19 @@ CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
     P.zshift = M > 64 ? 1 : 0;
     const int zblocks = 1 << P.zshift;
     const int cus = qg_compute_units();
-    P.kw = qg_codes_kw(gps, P.mb);
+    P.kw = qg_codes_kw(gps, P.mb, (L.tiles + 3) / 4 * QG_MAX_SEGMENTS >= cus);
     P.tn = 8 / P.kw;
     P.blocks = (int)((L.tiles + P.tn - 1) / P.tn) * zblocks;
     P.units = (int)(((L.K + KC - 1) / KC + P.kw - 1) / P.kw);
-    // Two or three parts are added by the workgroup that comes last, more by a kernel of their own.  More parts
-    // shorten a workgroup's units (1.0-2.0 us each at 32 rows, 1.8-2.4 at 64, more for small groups), but adding two costs
-    // about 1 us, three 3.5 (the last workgroup alone reads them all), a kernel 5 and its launch.  us per call, two
-    // or three parts | up to eight and a kernel: 11008 x 4096 4-bit M = 128 27.2 | 31.5, M = 20 15.3 |
-    // 17.2, 13824 x 5120 3-bit M = 100 34.0 | 38.0, M = 48 26.1 | 23.7, 4096 x 11008 4-bit M = 128 37.9 | 27.9,
-    // 8192 x 8192 2-bit g32 M = 20 19.1-21.5 | 17.5.
-    if (knob_splits) {
-        // (a count that would need more workgroups than compute units is dealt evenly over those, as the
-        // built-in choice would, so that the launch-shape search meets that plan too)
-        codes_cut(P, knob_splits, cus, knob_splits == 1 || (int64_t)P.blocks * knob_splits <= cus);
-        P.fused = P.parts > 1 && P.parts <= QG_FUSED_SEGMENTS;
-        return P;
-    }
-    const double unit_us = P.mb == 1 ? (gps >= 4 ? 2.0 : gps == 2 ? 1.3 : 1.0) : (gps >= 4 ? 2.4 : gps == 2 ? 2.0 : 1.8);
-    const double add_us[] = {0.0, 0.0, 1.0, 3.5};
+    // The best of the cuts into at most 1 ... 8 parts by what they cost; a forced count (the search's, too) takes
+    // the one cut.  A count that would need more workgroups than compute units is dealt evenly over those.
     CodesPlan best = P;
-    double least = 0.0;
-    for (int most = 1; most <= QG_FUSED_SEGMENTS + 1; ++most) {
+    for (int most = knob_splits ? knob_splits : 1; most <= (knob_splits ? knob_splits : QG_MAX_SEGMENTS); ++most) {
         CodesPlan c = P;
-        codes_cut(c, most <= QG_FUSED_SEGMENTS ? most : QG_MAX_SEGMENTS, cus, false);
-        c.fused = most <= QG_FUSED_SEGMENTS && c.parts > 1;
-        const double us = c.quota * unit_us + (most <= QG_FUSED_SEGMENTS ? add_us[c.parts] : 5.5);
-        if (most == 1 || us < least) {
-            best = c;
-            least = us;
-        }
+        codes_cut(c, most, cus, most == 1 || (int64_t)P.blocks * most <= cus);
+        c.fused = c.parts > 1 && c.parts <= QG_FUSED_SEGMENTS;
+        c.us = codes_cost_us(L, gps, M, c, cus);
+        if (most == 1 || knob_splits || c.us < best.us) best = c;
     }
     return best;
 }
@@ -960,6 +967,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         A.quota = C.quota;
         A.total = C.blocks * C.units;
         A.fused = C.fused;
+        A.kw = C.kw;
         auto main_kernel = [&](KernelInfo *query) {
             return bits == 4 ? qg_codes_launch_b4(gps, C.mb, A, C.workgroups, st, query)
                  : bits == 2 ? qg_codes_launch_b2(gps, C.mb, A, C.workgroups, st, query)

@@ -1,0 +1,68 @@
+"""What libqg would launch, without a GPU: the library on tests/hip_stub.c in a process of its own."""
+import ctypes
+import json
+import os
+import re
+import subprocess
+import sys
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+class CodesArgs(ctypes.Structure):
+    """Arguments of the raw-code product kernel (QgCodesArgs)."""
+    _fields_ = [(n, ctypes.c_void_p) for n in ("codes", "scales", "zeros", "Xop", "Y", "partial", "arrived")] + \
+        [(n, ctypes.c_int32) for n in ("M", "N", "tiles", "tile_codes", "tile_scales", "tile_zeros", "steps_padded",
+                                       "group_magic", "zshift", "units", "ranges", "quota", "total", "fused", "kw")]
+
+
+def _run(stub_path, lib_path, calls):
+    stub = ctypes.CDLL(stub_path, mode=ctypes.RTLD_GLOBAL)
+    L = ctypes.CDLL(lib_path)
+    stub.stub_name.restype = ctypes.c_char_p
+    stub.stub_args.restype = ctypes.c_void_p
+    i64, i32, vp = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p
+    L.qg_workspace_bytes.restype = ctypes.c_size_t
+    L.qg_workspace_bytes.argtypes = [i64, i64, i32, i32, i32]
+    L.qg_gemm_small.argtypes = [vp, i64, i64, i32, i32, vp, i32, vp, vp, ctypes.c_size_t, vp]
+    out = []
+    for c in calls:
+        stub.stub_clear()
+        stub.stub_device(c.get("device", 0))
+        N, K, bits, group, M = c["problem"]
+        assert L.qg_set_gemm_tuning(c.get("splits", 0), c.get("shape", 0)) == 0
+        size = L.qg_workspace_bytes(N, K, bits, group, M)
+        status = L.qg_gemm_small(1 << 20, N, K, bits, group, 1 << 20, M, 1 << 20, 1 << 20, size, None)
+        kernels = []
+        for i in range(stub.stub_launches()):
+            shape = (ctypes.c_uint32 * 5)()
+            stub.stub_shape(i, shape)
+            mangled = stub.stub_name(i).decode()
+            # _ZN12_GLOBAL__N_1<length><name>I...: the length says where the name ends
+            length, rest = re.match(r"_ZN12_GLOBAL__N_1(\d\d?)(\D.*)", mangled).groups()
+            name, tail = rest[:int(length)], rest[int(length):]
+            k = {"name": name, "template": [int(v) for v in re.findall(r"L[ib](\d+)E", tail)], "grid": list(shape[:3]),
+                 "block": shape[3], "lds": shape[4]}
+            if name == "gemm_codes":
+                a = CodesArgs.from_address(stub.stub_args(i))
+                k["args"] = {f: getattr(a, f) for f, _ in CodesArgs._fields_}
+            kernels.append(k)
+        out.append({"status": status, "kernels": kernels, "limits": stub.stub_limits()})
+    return out
+
+
+def launches(tmp_path, calls):
+    """calls: dicts with problem = (N, K, bits, group, M) of qg_gemm_small and, optionally, splits and shape
+    (qg_set_gemm_tuning) and device.  Returns per call its status and the kernels it launches."""
+    from paper_2307_03738_amd import build
+    stub = os.path.join(str(tmp_path), "hip_stub.so")
+    subprocess.run(["gcc", "-O1", "-w", "-shared", "-fPIC", os.path.join(HERE, "hip_stub.c"), "-o", stub], check=True)
+    done = subprocess.run([sys.executable, os.path.abspath(__file__), stub, os.environ.get("QG_LIBRARY", build.OUT)],
+                          input=json.dumps(calls), capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0, done.stderr
+    return json.loads(done.stdout)
+
+
+if __name__ == "__main__":
+    json.dump(_run(sys.argv[1], sys.argv[2], json.load(sys.stdin)), sys.stdout)

@@ -1,0 +1,26 @@
+"""Launch plans of qg_gemm_small, looked at without a GPU (tests/launches.py; 256 compute units)."""
+import pytest
+
+from tests.launches import launches
+
+
+@pytest.fixture(scope="module")
+def tmp(tmp_path_factory):
+    return tmp_path_factory.mktemp("hip_stub")
+
+
+def _product(result):
+    """The raw-code product of a call and the kernels around it."""
+    assert result["status"] == 0
+    k, = [k for k in result["kernels"] if k["name"] == "gemm_codes"]
+    return k, [k["name"] for k in result["kernels"]]
+
+
+# Few tiles and a K long enough to be cut: the product takes the compute units that parts of K can fill, whatever
+# adding the parts costs (with 64 to 80 of the 256 these were slower than before they shared A operands in LDS)
+@pytest.mark.parametrize("problem,workgroups", [
+    ((5120, 5120, 3, 64, 16), 200), ((4096, 4096, 3, 64, 8), 256), ((4096, 4096, 3, 4096, 8), 128),
+    ((8192, 8192, 2, 128, 16), 250), ((1500, 20480, 4, 16, 8), 96), ((4096, 11008, 4, 16, 24), 250)])
+def test_short_products_fill_the_chip(tmp, problem, workgroups):
+    k, _ = _product(launches(tmp, [{"problem": problem}])[0])
+    assert k["grid"][0] >= workgroups
