@@ -926,11 +926,18 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     // The raw-code kernel: every layout it takes that the 4-bit kernels below do not (2 and 3 bits, 4-bit
     // groups of 16), whatever shape 13 sends it, and the larger 4-bit matrices (in tile-steps of 64 outputs x
     // 128 k), where it is ahead of the dequantizing kernels; us per call, raw codes | dequantizing:
-    // 11008 x 4096 (5504) M = 20 15.3 | 16.9, M = 32 15.3 | 18.1, M = 64 23.4 | 20.0; 4096 x 11008 M = 32 15.4 |
-    // 15.8, M = 64 22.8 | 23.3; 22016 x 8192 (22016) M = 32 33.0 | 54.1, M = 64 45.4 | 63.3; 4096 x 4096 (2048)
-    // M = 32 12.4 | 11.5, M = 128 19.5 | 18.1.
+    //                            M = 24, g128, g32             M = 40, g128, g32
+    //   5120 x 5120    (3200)  12.6 | 12.2  13.8 | 12.8      16.8 | 15.2  19.2 | 15.4
+    //   4096 x 11008   (5504)  14.3 | 15.3  16.2 | 16.0      19.8 | 22.4  24.4 | 23.4
+    //   11008 x 4096   (5504)  14.0 | 17.2  16.0 | 17.9      19.4 | 18.7  21.9 | 18.9
+    //   8192 x 8192    (8192)  15.7 | 17.8  18.0 | 18.8      20.7 | 21.2  23.6 | 22.4
+    //   13824 x 5120   (8640)  16.4 | 22.8  18.7 | 23.7      20.6 | 29.9  24.7 | 30.5
+    //   5120 x 13824   (8640)  17.4 | 24.7  19.8 | 25.9      21.6 | 26.3  27.4 | 27.6
+    // so at 33 ... 64 rows the line lies higher, and above 8192 for groups of 32, whose fold is as much work as their matrix
+    // instructions.
     const int gps = codes_gps(L);
-    const bool large = M > 16 && L.tiles * L.steps >= (M > 32 && M <= 64 ? 8192 : 4096);
+    const int from = M > 32 && M <= 64 ? (gps >= 4 ? 8448 : 8192) : 4096;
+    const bool large = M > 16 && L.tiles * L.steps >= from;
     if (gps >= 0 && M > 1 && (knob_shape == NSHAPES + 1 || (knob_shape == 0 && (!fast_path(L) || large)))) {
         const CodesPlan C = codes_plan(L, gps, M, knob_splits);
         const CodesSpace W = codes_space(L, gps, M);

@@ -24,3 +24,13 @@ def _product(result):
 def test_short_products_fill_the_chip(tmp, problem, workgroups):
     k, _ = _product(launches(tmp, [{"problem": problem}])[0])
     assert k["grid"][0] >= workgroups
+
+
+# 4 bits, where both kernel families take the layout: the faster one as measured, by rows, size and group
+@pytest.mark.parametrize("problem,raw", [
+    ((8192, 8192, 4, 32, 33), False), ((8192, 8192, 4, 32, 64), False), ((8192, 8192, 4, 64, 40), True),
+    ((8192, 8192, 4, 128, 64), True), ((8192, 8192, 4, 32, 32), True), ((8192, 8192, 4, 32, 65), True),
+    ((13824, 5120, 4, 32, 40), True), ((5120, 5120, 4, 32, 24), False)])
+def test_kernel_family_of_4_bit_products(tmp, problem, raw):
+    names = [k["name"] for k in launches(tmp, [{"problem": problem}])[0]["kernels"]]
+    assert ("gemm_codes" in names) == raw, names
