@@ -39,6 +39,8 @@
 // 11008 4-bit g128 M = 128 28.1 -> 26.1.
 #pragma once
 
+#include <atomic>
+
 #include "qg_common.h"
 #include "qg_mma.h"
 
@@ -768,13 +770,17 @@ int codes_launch(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelI
         *query = {f, TN * KW * 64, lds};
         return QG_OK;
     }
-    static bool prepared = false;              // dynamic LDS above 64 KB has to be asked for once
-    if (!prepared) {
+    // dynamic LDS above 64 KB has to be asked for, once per device (devices past the table: every time;
+    // two threads at once ask twice)
+    static std::atomic<bool> prepared[64];
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
+    if (dev < 0 || !prepared[dev].load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
             (void)hipGetLastError();
             return QG_ERR_DEVICE;
         }
-        prepared = true;
+        if (dev >= 0) prepared[dev].store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL((gemm_codes<BITS, GPS, MB, TN, KW, FUSED>), dim3((unsigned)workgroups), dim3(TN * KW * 64), lds, st, A);
     return QG_OK;

@@ -34,3 +34,12 @@ def test_short_products_fill_the_chip(tmp, problem, workgroups):
 def test_kernel_family_of_4_bit_products(tmp, problem, raw):
     names = [k["name"] for k in launches(tmp, [{"problem": problem}])[0]["kernels"]]
     assert ("gemm_codes" in names) == raw, names
+
+
+def test_large_lds_is_asked_for_on_every_device(tmp):
+    # ... and once: further calls on a device ask no more
+    call = {"problem": (4096, 4096, 2, 64, 100)}
+    results = launches(tmp, [dict(call, device=d) for d in (0, 1, 0, 1, 70, 70)])
+    assert [r["status"] for r in results] == [0] * 6
+    assert all(_product(r)[0]["lds"] > 65536 for r in results)
+    assert [r["limits"] for r in results] == [1, 2, 2, 2, 3, 4]
