@@ -133,7 +133,14 @@ def qg_cell(bits: int) -> int:
 
 
 @functools.lru_cache(maxsize=1024)
+def _packed_bytes(N: int, K: int, bits: int, group: int, layout: int) -> int:
+    return int(lib().qg_packed_bytes(N, K, bits, group, layout))
+
+
 def qg_packed_bytes(N: int, K: int, bits: int, group: int, layout: int = QG_LAYOUT_DEVICE) -> int:
+    # remembered for plain ints alone: 512.0 is equal to 512 and refused, an array or tensor of one number may change
+    if type(N) is type(K) is type(bits) is type(group) is type(layout) is int:
+        return _packed_bytes(N, K, bits, group, layout)
     return int(lib().qg_packed_bytes(N, K, bits, group, layout))
 
 

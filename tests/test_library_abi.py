@@ -59,6 +59,20 @@ def test_canonical_bytes_follow_the_memory_formula(qg, oracle, N, K, bits, group
     assert dev <= got * 1.02 + 3 * 256 + 64 * 3 * 1024
 
 
+def test_packed_bytes_answers_for_the_arguments_of_the_call(qg):
+    # whatever was asked before: a float is refused, a number held in a tensor or array may have changed
+    import numpy as np
+    import torch
+    small, large = qg.qg_packed_bytes(512, 512, 4, 64), qg.qg_packed_bytes(1024, 512, 4, 64)
+    with pytest.raises(ctypes.ArgumentError):
+        qg.qg_packed_bytes(512.0, 512, 4, 64)
+    for held in (torch.tensor(512), np.array(512)):
+        assert qg.qg_packed_bytes(held, 512, 4, 64) == small
+        held[()] = 1024
+        assert qg.qg_packed_bytes(held, 512, 4, 64) == large
+    assert qg.qg_packed_bytes(np.int64(512), 512, 4, 64) == small
+
+
 def test_bad_shapes_are_rejected_without_a_gpu(qg):
     assert qg.qg_packed_bytes(64, 100, 4, 32) == 0          # K % G != 0
     assert qg.qg_packed_bytes(64, 96, 4, 12) == 0           # G not a multiple of the 4-bit cell
