@@ -266,7 +266,9 @@ int qg_gemv_autotune(const qg_gemv_desc *descs /* HOST */, int count, int sets,
 int qg_gemv_autotune_report(float *us /* HOST */, int capacity, int *timed, int *dropped);
 
 /* Same for qg_gemm_small: splits in 1..8 = number of K ranges handled by different
- * workgroups (clamped to what the shape allows); shape in 1..12 = workgroup shape (how many
+ * workgroups (clamped to what the shape allows; on the raw-code kernel, a count that would take more
+ * workgroups than compute units is the most parts of a sum, and the units of K are dealt evenly over the
+ * compute units instead of in whole ranges); shape in 1..12 = workgroup shape (how many
  * rows, tiles and K slices the wavefronts of a workgroup cover, and which of the two kernels;
  * ignored if it does not fit M),
  * shape = -1: the kernel for up to 16 rows whatever the number of tiles; shape = 13: the
@@ -276,11 +278,11 @@ int qg_set_gemm_tuning(int splits, int shape);
 /* The launch-shape search of qg_gemm_small for one problem (N, K, bits, group, M) -- Section 3,
  * Algorithm 4 with the resource model of eqs. (3)-(5), on this machine's terms.  The 120
  * candidates are the 15 values of `shape` above (0, -1, 1..13) x 1..8 K ranges.  Each is planned
- * without being launched and priced: registers per lane and LDS per workgroup of its kernel
- * instance give the workgroups the chip holds at once and so the rounds the launch needs; a round
- * costs a workgroup's fixed time (3.3 us) plus its iterations (2 us each), every further kernel
- * of the call 3 us.  Candidates the planner maps to a plan already seen are skipped, candidates
- * priced above 1.5 times the cheapest are dropped, the others run the product `repeats` times,
+ * without being launched and priced: raw-code cuts as the built-in choice prices them, the dequantizing
+ * kernels by the registers per lane and LDS per workgroup of the instance, which give the workgroups the chip
+ * holds at once and so the rounds the launch needs; a round costs a workgroup's fixed time (3.3 us) plus
+ * its iterations (2 us each), every further kernel of the call 3 us.  Candidates the planner maps to a plan already seen are skipped, candidates
+ * priced above 1.5 times the cheapest are dropped (never the built-in choice), the others run the product `repeats` times,
  * rotating over the `sets` packed buffers in packed_sets (HOST array of DEVICE pointers, same
  * matrix shape; different buffers keep a cache from serving the weights).  WAITS for the GPU,
  * records the fastest for later qg_gemm_small calls on the same (N, K, bits, group, M) (used

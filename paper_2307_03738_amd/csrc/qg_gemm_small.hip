@@ -906,6 +906,7 @@ struct GemmPrice {
     long iterations;           // barrier-to-barrier iterations one workgroup runs one after the other
     int launches;              // kernels the call enqueues
     KernelInfo kernel;
+    double us;                 // family 0: what the plan says it costs
 };
 
 // Checks, plans and (price == NULL) enqueues one product; knob_*: as qg_set_gemm_tuning.
@@ -986,7 +987,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         const int have = main_kernel(&info);
         if (have != QG_OK) return have;
         if (price) {
-            *price = {0, NSHAPES, C.ranges, (long)C.workgroups, C.quota, C.ranges != 1 && !C.fused ? 3 : 2, info};
+            *price = {0, NSHAPES, C.ranges, (long)C.workgroups, C.quota, C.ranges != 1 && !C.fused ? 3 : 2, info, C.us};
             return QG_OK;
         }
         if (bits == 4) qg_codes_prepare_b4(P, W.rows_padded, st);
@@ -1009,7 +1010,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     // to cover the chip (measured: ahead from about 128 tiles; shape -1 forces it).
     if (M <= 16 && (knob_shape == 0 ? L.tiles >= 128 : knob_shape < 0)) {
         const int r = qg_gemm_rows16(packed, N, K, bits, group, X, M, Y, workspace, stream, price != nullptr);
-        if (r == QG_OK && price) *price = {1, -1, 1, (long)L.tiles, 0, 1, {nullptr, 0, 0}};
+        if (r == QG_OK && price) *price = {1, -1, 1, (long)L.tiles, 0, 1, {nullptr, 0, 0}, 0.0};
         if (r != QG_ERR_UNSUPPORTED) return r;
     }
 
@@ -1036,7 +1037,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
                                         : qg_gemv_grouped(d, rows, workspace, workspace_bytes, stream);
                 if (r != QG_OK) return r;
             }
-        if (price) *price = {2, -1, 1, 0, 0, (M + QG_MAX_GROUPED - 1) / QG_MAX_GROUPED, {nullptr, 0, 0}};
+        if (price) *price = {2, -1, 1, 0, 0, (M + QG_MAX_GROUPED - 1) / QG_MAX_GROUPED, {nullptr, 0, 0}, 0.0};
         return QG_OK;
     }
 
@@ -1091,7 +1092,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         launch_shape(shape, A, grid, st, &info);
         // (gemm_wide_b4 runs two steps per iteration)
         *price = {3, shape, splits, (long)blocks_x * splits * zblocks, sps / (SHAPES[shape].wide ? 2 : kw) + 1,
-                  splits > 1 ? 2 : 1, info};
+                  splits > 1 ? 2 : 1, info, 0.0};
         return QG_OK;
     }
     launch_shape(shape, A, grid, st);
@@ -1125,22 +1126,26 @@ extern "C" int qg_gemm_small(const void *packed, int64_t N, int64_t K, int bits,
 // (Section 3, Algorithm 4, with the resource model of eqs. (3)-(5)) for this call.  Candidates
 // are (kernel family / workgroup shape) x (number of K ranges).  Each is planned without being
 // launched (a shape that does not fit the problem falls back to the built-in one, and a plan
-// seen before is not tried again) and priced: the registers per lane and the LDS per workgroup of its kernel instance
-// give the workgroups the chip holds at once, hence the rounds the launch needs; a round costs
-// a workgroup's fixed time plus its iterations, and every further kernel of the call a launch.
-// Candidates priced above 1.5 times the cheapest are dropped, the others timed.
+// seen before is not tried again) and priced: a raw-code cut as the built-in plan prices it, the dequantizing
+// kernels by the registers per lane and the LDS per workgroup of the instance, which give the workgroups the
+// chip holds at once, hence the rounds the launch needs; a round costs a workgroup's fixed time plus its
+// iterations, and every further kernel of the call a launch.
+// Candidates priced above 1.5 times the cheapest are dropped, except the plan of the built-in choice, so that
+// the search never records a slower one; the others are timed.
 namespace {
 constexpr int GT_SHAPES = NSHAPES + 3;           // 0 (built-in choice), -1 (gemm_rows16), 1 ... NSHAPES, NSHAPES + 1 (raw codes)
 constexpr int GT_CANDIDATES = GT_SHAPES * MAX_SPLITS;
 constexpr int gt_shape(int c) { return c / MAX_SPLITS == 0 ? 0 : c / MAX_SPLITS == 1 ? -1 : c / MAX_SPLITS - 1; }
 float g_gt_us[GT_CANDIDATES];                    // -1: dropped by the price, -2: same plan as an earlier candidate
 int g_gt_timed = 0, g_gt_dropped = 0;
-// measured on this machine: a workgroup's time outside its loop (first loads, reduction across
-// k-slices, output), one barrier-to-barrier iteration (a memory round trip), one more kernel in a call
+// the dequantizing kernels, measured on this machine: a workgroup's time outside its loop (first loads, reduction across
+// k-slices, output), one barrier-to-barrier iteration (a memory round trip), one more kernel in a call (the
+// raw-code kernel has a unit's time by rows and groups, codes_cost_us, half to one and a half of that iteration)
 constexpr double GT_FIXED_US = 3.3, GT_ITERATION_US = 2.0, GT_LAUNCH_US = 3.0;
 
 double gemm_price_us(const GemmPrice &p)
 {
+    if (p.family == 0) return p.us;
     if (p.family == 1 || p.family == 2) return 0.0;          // no model: always timed
     int resident = 1;
     hipFuncAttributes attr;
@@ -1177,6 +1182,9 @@ extern "C" int qg_gemm_autotune(const void *const *packed_sets, int sets, int64_
     GemmPrice plan[GT_CANDIDATES];
     double price[GT_CANDIDATES], cheapest = -1.0;
     bool valid[GT_CANDIDATES];
+    GemmPrice own;                                       // of the built-in choice
+    const bool have_own = gemm_small(packed_sets[0], N, K, bits, group, X, M, Y, workspace, workspace_bytes, stream, 0, 0, &own) == QG_OK;
+    auto same_plan = [](const GemmPrice &a, const GemmPrice &b) { return a.family == b.family && a.shape == b.shape && a.splits == b.splits; };
     for (int c = 0; c < GT_CANDIDATES; ++c) {
         const int sh = gt_shape(c), sp = 1 + c % MAX_SPLITS;
         const int rc = gemm_small(packed_sets[0], N, K, bits, group, X, M, Y, workspace, workspace_bytes, stream, sp, sh, &plan[c]);
@@ -1184,8 +1192,7 @@ extern "C" int qg_gemm_autotune(const void *const *packed_sets, int sets, int64_
         if (rc != QG_OK) return rc;
         valid[c] = true;
         for (int e = 0; e < c && valid[c]; ++e)          // a knob the planner did not follow: seen already
-            if (valid[e] && plan[e].family == plan[c].family && plan[e].shape == plan[c].shape && plan[e].splits == plan[c].splits)
-                valid[c] = false;
+            if (valid[e] && same_plan(plan[e], plan[c])) valid[c] = false;
         if (!valid[c]) continue;
         price[c] = gemm_price_us(plan[c]);
         if (price[c] > 0.0 && (cheapest < 0.0 || price[c] < cheapest)) cheapest = price[c];
@@ -1201,7 +1208,7 @@ extern "C" int qg_gemm_autotune(const void *const *packed_sets, int sets, int64_
     for (int c = 0; c < GT_CANDIDATES && rc == QG_OK; ++c) {
         g_gt_us[c] = -2.0f;
         if (!valid[c]) continue;
-        if (price[c] > 1.5 * cheapest && cheapest > 0.0) {
+        if (price[c] > 1.5 * cheapest && cheapest > 0.0 && !(have_own && same_plan(plan[c], own))) {
             g_gt_us[c] = -1.0f;
             ++g_gt_dropped;
             continue;

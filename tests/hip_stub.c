@@ -70,7 +70,7 @@ int hipFuncSetAttribute(const void *f, int attribute, int value)
 int hipGetLastError(void) { const int e = error; error = 0; return e; }
 int hipGetDevice(int *d) { *d = device; return 0; }
 int hipDeviceGetAttribute(int *v, int attribute, int d) { *v = 256; return 0; }      /* compute units: all that is asked for */
-int hipFuncGetAttributes(void *a, const void *f) { return 1; }
+int hipFuncGetAttributes(void *a, const void *f) { memset(a, 0, 56); return 0; }     /* hipFuncAttributes */
 int hipGetSymbolAddress(void **p, const void *s) { return 1; }
 int hipEventCreate(void **e) { *e = &call; return 0; }
 int hipEventDestroy(void *e) { return 0; }

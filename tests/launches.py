@@ -25,6 +25,7 @@ def _run(stub_path, lib_path, calls):
     i64, i32, vp = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p
     L.qg_workspace_bytes.restype = ctypes.c_size_t
     L.qg_workspace_bytes.argtypes = [i64, i64, i32, i32, i32]
+    L.qg_gemm_autotune.argtypes = [ctypes.POINTER(vp), i32, i64, i64, i32, i32, vp, i32, vp, vp, ctypes.c_size_t, vp, i32, vp, vp, vp]
     L.qg_gemm_small.argtypes = [vp, i64, i64, i32, i32, vp, i32, vp, vp, ctypes.c_size_t, vp]
     out = []
     for c in calls:
@@ -33,6 +34,13 @@ def _run(stub_path, lib_path, calls):
         N, K, bits, group, M = c["problem"]
         assert L.qg_set_gemm_tuning(c.get("splits", 0), c.get("shape", 0)) == 0
         size = L.qg_workspace_bytes(N, K, bits, group, M)
+        if c.get("search"):
+            blobs, us, timed = (vp * 1)(1 << 20), (ctypes.c_float * 120)(), (ctypes.c_int * 2)()
+            status = L.qg_gemm_autotune(blobs, 1, N, K, bits, group, 1 << 20, M, 1 << 20, 1 << 20, size, None, 1, None, None, None)
+            L.qg_gemm_autotune_report(us, 120, timed, None)
+            L.qg_clear_tuning()
+            out.append({"status": status, "us": list(us)})
+            continue
         status = L.qg_gemm_small(1 << 20, N, K, bits, group, 1 << 20, M, 1 << 20, 1 << 20, size, None)
         kernels = []
         for i in range(stub.stub_launches()):
@@ -54,7 +62,8 @@ def _run(stub_path, lib_path, calls):
 
 def launches(tmp_path, calls):
     """calls: dicts with problem = (N, K, bits, group, M) of qg_gemm_small and, optionally, splits and shape
-    (qg_set_gemm_tuning) and device.  Returns per call its status and the kernels it launches."""
+    (qg_set_gemm_tuning) and device, or search = True for qg_gemm_autotune.  Returns per call its status and
+    the kernels it launches, or the times of the search's candidates (-1: not timed)."""
     from paper_2307_03738_amd import build
     stub = os.path.join(str(tmp_path), "hip_stub.so")
     subprocess.run(["gcc", "-O1", "-w", "-shared", "-fPIC", os.path.join(HERE, "hip_stub.c"), "-o", stub], check=True)

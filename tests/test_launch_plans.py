@@ -43,3 +43,16 @@ def test_large_lds_is_asked_for_on_every_device(tmp):
     assert [r["status"] for r in results] == [0] * 6
     assert all(_product(r)[0]["lds"] > 65536 for r in results)
     assert [r["limits"] for r in results] == [1, 2, 2, 2, 3, 4]
+
+
+@pytest.mark.parametrize("problem", [(4096, 11008, 4, 128, 128), (18000, 2048, 4, 128, 100), (13824, 5120, 4, 64, 48),
+                                     (8192, 8192, 4, 32, 40), (5120, 5120, 3, 64, 16)])
+def test_search_times_the_built_in_plan(tmp, problem):
+    def plan(result):
+        return [(k["name"], k["template"], k["grid"], k.get("args", {}).get("quota")) for k in result["kernels"]]
+
+    results = launches(tmp, [{"problem": problem}] + [{"problem": problem, "splits": s} for s in range(1, 9)] +
+                       [{"problem": problem, "search": True}])
+    same = [s for s in range(1, 9) if plan(results[s]) == plan(results[0])]
+    assert same and results[9]["status"] == 0
+    assert results[9]["us"][same[0] - 1] >= 0          # shape 0 (built-in kernel), that many ranges
