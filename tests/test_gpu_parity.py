@@ -891,19 +891,38 @@ def test_gemm_small_replayed_from_a_graph(qg, oracle, N, K, bits, group, M, spli
         qg.qg_set_gemm_tuning(0, 0)
 
 
-@pytest.mark.parametrize("N,K,bits,group,M", [
-    (25600, 2304, 4, 64, 40),        # units dealt evenly over the workgroups: blocks that two or three of them share
-    (25600, 2304, 2, 32, 100),       # ... two blocks of rows
-    (8333, 1216, 3, 64, 65),         # K ends inside a step and inside a unit; ragged N and M, a block of one row
-    (130, 64, 3, 64, 2),             # less than one step
-    (200, 1536, 2, 256, 33),         # groups of two steps of 128 k
-    (200, 1536, 3, 768, 17),         # ... of six
-    (70, 272, 4, 16, 31),            # eight groups per step, K ends inside a step
-])
-def test_gemm_small_raw_code_units(qg, oracle, N, K, bits, group, M):
-    _announce("gemm raw codes, units", N, K, bits, group, M)
+# N, K, bits, group, M, K ranges asked for, and the cut that gives (tests/test_launch_plans.py looks): units dealt
+# evenly over the workgroups, parts of a sum at most, added by the last workgroup (1) or a kernel (0), blocks of rows
+UNIT_CASES = [
+    (25600, 2304, 4, 64, 40, 3, (True, 3, 1, 1)),       # blocks that two or three workgroups share
+    (25600, 2304, 2, 32, 100, 2, (True, 2, 1, 2)),      # ... two blocks of rows
+    (12790, 2304, 4, 64, 101, 3, (True, 3, 1, 2)),      # ... three workgroups, ragged N and M
+    (12750, 4480, 3, 64, 30, 3, (True, 3, 1, 1)),       # ... 32 rows, K ends inside a unit
+    (6630, 4480, 2, 128, 25, 8, (True, 5, 0, 1)),       # dealt, parts added by the kernel: 32 rows
+    (13300, 2272, 2, 32, 40, 8, (True, 5, 0, 1)),       # ... 64 rows
+    (5590, 2752, 3, 64, 99, 8, (True, 6, 0, 2)),        # ... two blocks of rows, ragged N, M and K
+    (9517, 14720, 3, 128, 96, 8, (True, 5, 0, 2)),
+    (1500, 2560, 4, 16, 23, 5, (False, 5, 0, 1)),       # whole ranges; slices added over the unit just multiplied
+    (700, 1280, 4, 16, 32, 3, (False, 3, 1, 1)),        # ... and parts by the last workgroup
+    (17000, 1088, 4, 16, 9, 3, (False, 3, 1, 1)),    # groups of 16 on many tiles: two slices
+    (40000, 256, 3, 64, 66, 0, (False, 1, 0, 2)),       # more blocks than compute units
+    (8333, 1216, 3, 64, 65, 0, None),        # K ends inside a step and inside a unit; ragged N and M, a block of one row
+    (130, 64, 3, 64, 2, 0, None),            # less than one step
+    (200, 1536, 2, 256, 33, 0, None),        # groups of two steps of 128 k
+    (200, 1536, 3, 768, 17, 0, None),        # ... of six
+    (70, 272, 4, 16, 31, 0, None),           # eight groups per step, K ends inside a step
+]
+
+
+@pytest.mark.parametrize("N,K,bits,group,M,splits,cut", UNIT_CASES)
+def test_gemm_small_raw_code_units(qg, oracle, N, K, bits, group, M, splits, cut):
+    _announce("gemm raw codes, units", N, K, bits, group, M, splits)
     W, X = synth.small_case(4600 + N + M, N, K, 0.02, True, m=M)
-    err = _gemm_case(qg, oracle, W, X, bits, group)
+    qg.qg_set_gemm_tuning(splits, 13)
+    try:
+        err = _gemm_case(qg, oracle, W, X, bits, group)
+    finally:
+        qg.qg_set_gemm_tuning(0, 0)
     assert err <= TOL_BF16, err
 
 

@@ -2,6 +2,7 @@
 import pytest
 
 from tests.launches import launches
+from tests.test_gpu_parity import UNIT_CASES
 
 
 @pytest.fixture(scope="module")
@@ -56,3 +57,14 @@ def test_search_times_the_built_in_plan(tmp, problem):
     same = [s for s in range(1, 9) if plan(results[s]) == plan(results[0])]
     assert same and results[9]["status"] == 0
     assert results[9]["us"][same[0] - 1] >= 0          # shape 0 (built-in kernel), that many ranges
+
+
+# The GPU test of the cuts of K takes the cuts it names
+@pytest.mark.parametrize("case", [c for c in UNIT_CASES if c[6] is not None])
+def test_unit_cases_are_cut_as_stated(tmp, case):
+    *problem, splits, (dealt, parts, fused, row_blocks) = case
+    k, names = _product(launches(tmp, [{"problem": problem, "splits": splits, "shape": 13}])[0])
+    a = k["args"]
+    most = a["ranges"] or (a["units"] + a["quota"] - 2) // a["quota"] + 1
+    assert (a["ranges"] == 0, most, a["fused"], 1 << a["zshift"]) == (dealt, parts, fused, row_blocks)
+    assert ("add_parts" in names) == (parts > 1 and not fused)
