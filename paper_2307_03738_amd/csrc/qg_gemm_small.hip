@@ -830,11 +830,13 @@ void codes_cut(CodesPlan &P, int most, int cus, bool exactly)
 // Estimate of a call: a straight line through 9000 cuts of 18 matrices from 512 x 512 to 30000 x 4096 at 2, 3
 // and 4 bits, groups of 16, 32, 64, 128 and one per output, 2 ... 128 rows (root mean square of what it is off: 4
 // %).  A unit has a time of its own, by rows and groups per step, and one on a full chip for the weights it reads.
-// Two or three parts are added by the workgroup that comes last, which alone reads them all; more by
-// a kernel, which the whole chip shares; an evenly dealt workgroup ends a block of outputs in the middle
-// of its units as well as at their end.
+// Parts are added by a kernel, which the whole chip shares, or, if they are two or three, by the workgroup that
+// comes last, which alone reads them all: at up to 32 rows that is never the slower way, at 64 from 8 MB of
+// parts (two of them) or 11 (three) on (kernel minus last workgroup, us: -3 below 2 MB, +2 at 12 MB of two
+// parts).  An evenly dealt workgroup ends a block of outputs in the middle of its units as well as at
+// their end.
 // (A table that went by the groups per step alone and took the adding for 1 us at two parts put 5120 x 5120 3-bit g64
-// M = 16 on 80 workgroups, 14.0 -> 15.3 us, and 4096 x 4096 3-bit M = 8 on 64, 10.6 -> 13.0; now 11.9 and 9.7.)
+// M = 16 on 80 workgroups, 14.0 -> 15.3 us, and 4096 x 4096 3-bit M = 8 on 64, 10.6 -> 13.0; now 11.9 and 10.3.)
 double codes_cost_us(const QgLayout &L, int gps, int M, const CodesPlan &P, int cus)
 {
     static constexpr double UNIT_US[2][5] = {{1.0, 1.05, 1.2, 1.45, 2.0}, {1.35, 1.4, 1.65, 2.15, 3.2}};
@@ -845,7 +847,7 @@ double codes_cost_us(const QgLayout &L, int gps, int M, const CodesPlan &P, int 
     if (P.ranges == 0) us += 1.4;
     if (P.parts > 1) {
         const double mb = 4e-6 * P.parts * M * (double)L.N;
-        us += P.fused ? (P.mb == 1 ? 1.5 : 4.6) + 0.3 * mb : 1.5 + 0.5 * mb;
+        us += !P.fused ? 1.5 + 0.5 * mb : P.mb == 1 ? 1.5 + 0.3 * mb : 4.6 + 0.1 * (P.parts - 1) * mb;
     }
     return us;
 }
@@ -867,8 +869,14 @@ CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
     for (int most = knob_splits ? knob_splits : 1; most <= (knob_splits ? knob_splits : QG_MAX_SEGMENTS); ++most) {
         CodesPlan c = P;
         codes_cut(c, most, cus, most == 1 || (int64_t)P.blocks * most <= cus);
-        c.fused = c.parts > 1 && c.parts <= QG_FUSED_SEGMENTS;
+        c.fused = false;
         c.us = codes_cost_us(L, gps, M, c, cus);
+        if (c.parts > 1 && c.parts <= QG_FUSED_SEGMENTS) {
+            CodesPlan f = c;
+            f.fused = true;
+            f.us = codes_cost_us(L, gps, M, f, cus);
+            if (f.us <= c.us) c = f;
+        }
         if (most == 1 || knob_splits || c.us < best.us) best = c;
     }
     return best;

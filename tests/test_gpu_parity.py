@@ -855,8 +855,9 @@ def test_gemm_small_raw_code_kernel(qg, oracle, N, K, bits, group, M, splits):
     assert err <= TOL_BF16, err
 
 
-@pytest.mark.parametrize("splits", [1, 2, 3, 8])       # no parts; parts added by the last workgroup; by a kernel
-@pytest.mark.parametrize("N,K,bits,group,M", [(300, 2304, 4, 128, 40), (200, 4096, 2, 32, 100), (130, 3072, 3, 64, 9)])
+# no parts; parts added by a kernel, or (2 and 3 of them, at 9 rows or many outputs) by the last workgroup
+@pytest.mark.parametrize("splits", [1, 2, 3, 8])
+@pytest.mark.parametrize("N,K,bits,group,M", [(300, 2304, 4, 128, 40), (200, 4096, 2, 32, 100), (130, 3072, 3, 64, 9), (12300, 768, 2, 32, 100)])
 def test_gemm_small_replayed_from_a_graph(qg, oracle, N, K, bits, group, M, splits):
     # a captured call, replayed with eager calls and synchronizations in between: the counters of the
     # parts are cleared by every call, and every replay gives the bits of the eager call

@@ -68,3 +68,12 @@ def test_unit_cases_are_cut_as_stated(tmp, case):
     most = a["ranges"] or (a["units"] + a["quota"] - 2) // a["quota"] + 1
     assert (a["ranges"] == 0, most, a["fused"], 1 << a["zshift"]) == (dealt, parts, fused, row_blocks)
     assert ("add_parts" in names) == (parts > 1 and not fused)
+
+
+@pytest.mark.parametrize("problem,splits,last_workgroup", [
+    ((1088, 704, 4, 32, 64), 3, False), ((4096, 4096, 4, 128, 64), 2, False), ((12300, 768, 2, 32, 100), 2, True),
+    ((22016, 8192, 2, 32, 128), 0, True), ((130, 3072, 3, 64, 9), 2, True), ((130, 3072, 3, 64, 32), 3, True)])
+def test_who_adds_two_or_three_parts(tmp, problem, splits, last_workgroup):
+    # at 64 rows the last workgroup from some megabytes of parts on, at 32 always
+    k, names = _product(launches(tmp, [{"problem": problem, "splits": splits, "shape": 13}])[0])
+    assert (k["args"]["fused"] == 1, "add_parts" not in names) == (last_workgroup, last_workgroup)
