@@ -628,17 +628,20 @@ __global__ void add_splits(const float *__restrict__ partial, int splits, size_t
 
 // The same for the raw-code kernel (parts as it writes them: quads of 4 rows x 32 outputs, lane = row half and
 // output).  A block of outputs and rows has `ranges` parts or, with ranges == 0, as many as workgroups its
-// units fell to (one: that workgroup has stored Y itself).  A workgroup is one wavefront and a quarter of a quad,
-// one element per lane: what bounds it is the way of the parts from the other dies, so the more
-// wavefronts ask at once the better (a call with eight parts, us, against 16 bytes per lane and four
-// wavefronts per workgroup: 2048 x 2048 M = 24 10.1 -> 9.3, 4096 x 4096 M = 24 11.5 -> 10.8, 8192 x 8192 M = 24
-// 16.1 -> 15.6).
+// units fell to (one: that workgroup has stored Y itself).  A workgroup is one wavefront of W elements per lane.
+// What bounds it is the way of the parts from the other dies, so as long as the chip has room the more wavefronts
+// ask at once the better; two elements per lane keep whole lines of Y together.  A call with eight parts, us, with
+// four elements per lane and four wavefronts per workgroup | two | one: 2048 x 2048 M = 24 10.1 | 10.2 | 9.3, 4096 x 4096
+// M = 24 11.5 | 11.0 | 10.8, M = 128 23.5 | 22.2 | 22.5, 8192 x 8192 M = 128 32.0 | 30.6 | 31.6.
+template <int W>
 __global__ __launch_bounds__(64) void add_parts(const char *__restrict__ partial, int tiles, int N, int M, int tn, int rows,
                                                 int zshift, int units, int ranges, int quota, float *__restrict__ Y)
 {
+    typedef float vec __attribute__((ext_vector_type(W)));
+    constexpr int WAVES = 4 / W;                              // per quad
     const int bands = (M + 7) / 8;
-    const int q = blockIdx.x / 4;                             // (tile, band, pq)
-    const int at = blockIdx.x % 4 * 64 + threadIdx.x;         // element of the quad
+    const int q = blockIdx.x / WAVES;                         // (tile, band, pq)
+    const int at = (blockIdx.x % WAVES * 64 + threadIdx.x) * W;       // element of the quad
     const int pq = q & 1, band = (q >> 1) % bands, tile = (q >> 1) / bands;
     int count = ranges;
     if (ranges == 0) {
@@ -646,15 +649,18 @@ __global__ __launch_bounds__(64) void add_parts(const char *__restrict__ partial
         count = ((b + 1) * units - 1) / quota - b * units / quota + 1;
         if (count == 1) return;
     }
-    float v[QG_MAX_SEGMENTS];
+    vec v[QG_MAX_SEGMENTS];
 #pragma unroll
     for (int s = 0; s < QG_MAX_SEGMENTS; ++s)
-        v[s] = s < count ? *(const float *)(partial + (((size_t)s * tiles + tile) * bands + band) * 2048 + pq * 1024 + at * 4) : 0.0f;
-    float t = v[0];
+        v[s] = s < count ? *(const vec *)(partial + (((size_t)s * tiles + tile) * bands + band) * 2048 + pq * 1024 + at * 4) : (vec)0.0f;
+    vec t = v[0];
 #pragma unroll
     for (int s = 1; s < QG_MAX_SEGMENTS; ++s) t += v[s];      // the missing ones add +0.0
     const int lane = at / 4, n = tile * QG_WAVE + 32 * pq + (lane & 31), m = band * 8 + 4 * (lane >> 5) + at % 4;
-    if (n < N && m < M) Y[(size_t)m * N + n] = t;
+    if (n >= N) return;
+#pragma unroll
+    for (int j = 0; j < W; ++j)
+        if (m + j < M) Y[(size_t)(m + j) * N + n] = t[j];
 }
 
 bool fast_path(const QgLayout &L)
@@ -1007,8 +1013,9 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         if (qg_launch_status() != QG_OK) return QG_ERR_DEVICE;
         if (C.ranges != 1 && !C.fused) {
             const int64_t quads = L.tiles * ((M + 7) / 8) * 2;
-            hipLaunchKernelGGL(add_parts, dim3((unsigned)quads * 4u), dim3(64), 0, st, A.partial, (int)L.tiles, (int)N, M,
-                               C.tn, 32 * C.mb, C.zshift, C.units, C.ranges, C.quota, Y);
+            const int waves = quads * 4 <= 4096 ? 4 : 2;                 // per quad: up to about 16 wavefronts per compute unit
+            hipLaunchKernelGGL(waves == 4 ? add_parts<1> : add_parts<2>, dim3((unsigned)(quads * waves)), dim3(64), 0, st, A.partial,
+                               (int)L.tiles, (int)N, M, C.tn, 32 * C.mb, C.zshift, C.units, C.ranges, C.quota, Y);
         }
         return qg_launch_status();
     }
