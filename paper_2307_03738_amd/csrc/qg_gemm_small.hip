@@ -813,19 +813,19 @@ struct CodesPlan {
 };
 
 // Cuts into at most `most` parts per block, one workgroup per compute unit at most where that is possible (a
-// workgroup takes half of a unit's registers or more, so one more would wait for a second round).
-void codes_cut(CodesPlan &P, int most, int cus, bool exactly)
+// workgroup takes half of a unit's registers or more, so one more would wait for a second round): whole ranges
+// of K, or, where more workgroups than `room` per block would be needed for them, `even` units per workgroup.
+void codes_cut(CodesPlan &P, int most, int room, int even)
 {
-    int ranges = exactly ? most : cus / P.blocks < most ? cus / P.blocks : most;
+    int ranges = room < most ? room : most;
     if (ranges < 1) ranges = 1;
     if (ranges > P.units) ranges = P.units;
     P.quota = (P.units + ranges - 1) / ranges;
     P.ranges = P.parts = (P.units + P.quota - 1) / P.quota;
     P.workgroups = P.blocks * P.ranges;
-    if (exactly) return;
-    const int even = (int)(((int64_t)P.blocks * P.units + cus - 1) / cus);
+    if (most <= room || even >= P.quota) return;
     const int parts = (P.units + even - 2) / even + 1;          // of a block that begins at the end of a quota
-    if (even < P.quota && parts <= most) {
+    if (parts <= most) {
         P.quota = even;
         P.ranges = 0;
         P.parts = parts;
@@ -843,19 +843,47 @@ void codes_cut(CodesPlan &P, int most, int cus, bool exactly)
 // their end.
 // (A table that went by the groups per step alone and took the adding for 1 us at two parts put 5120 x 5120 3-bit g64
 // M = 16 on 80 workgroups, 14.0 -> 15.3 us, and 4096 x 4096 3-bit M = 8 on 64, 10.6 -> 13.0; now 11.9 and 10.3.)
-double codes_cost_us(const QgLayout &L, int gps, int M, const CodesPlan &P, int cus)
+struct CodesCost {
+    double call, unit, weights;        // of a call, of a unit, of a unit on a full chip for its weights
+    double last_workgroup, last_workgroup_mb, part_mb;
+    int cus;
+    bool by_parts;                     // the last workgroup's time per MB grows with the parts
+};
+CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus)
 {
     static constexpr double UNIT_US[2][5] = {{1.0, 1.05, 1.2, 1.45, 2.0}, {1.35, 1.4, 1.65, 2.15, 3.2}};
-    const double unit = UNIT_US[P.mb - 1][gps == 0 ? 0 : gps == 1 ? 1 : gps == 2 ? 2 : gps == 4 ? 3 : 4];
-    const double weights = L.bits == 4 ? 0.5 : L.bits == 3 ? 0.35 : 0.1;
-    const int rounds = (P.workgroups + cus - 1) / cus;
-    double us = (P.mb == 1 ? 6.0 : 7.3) + rounds * P.quota * (unit + weights * (rounds > 1 ? 1.0 : (double)P.workgroups / cus));
-    if (P.ranges == 0) us += 1.4;
-    if (P.parts > 1) {
-        const double mb = 4e-6 * P.parts * M * (double)L.N;
-        us += !P.fused ? 1.5 + 0.5 * mb : P.mb == 1 ? 1.5 + 0.3 * mb : 4.6 + 0.1 * (P.parts - 1) * mb;
+    CodesCost C;
+    C.call = mb == 1 ? 6.0 : 7.3;
+    C.unit = UNIT_US[mb - 1][gps == 0 ? 0 : gps == 1 ? 1 : gps == 2 ? 2 : gps == 4 ? 3 : 4];
+    C.weights = L.bits == 4 ? 0.5 : L.bits == 3 ? 0.35 : 0.1;
+    C.last_workgroup = mb == 1 ? 1.5 : 4.6;
+    C.last_workgroup_mb = mb == 1 ? 0.3 : 0.1;
+    C.by_parts = mb == 2;
+    C.part_mb = 4e-6 * M * (double)L.N;
+    C.cus = cus;
+    return C;
+}
+// Sets P.us and, with it, who adds the parts.
+void codes_price(CodesPlan &P, const CodesCost &C)
+{
+    P.us = C.call;
+    if (P.workgroups <= C.cus) {
+        P.us += P.quota * (C.unit + C.weights * P.workgroups / C.cus);
+    } else {
+        P.us += (P.workgroups + C.cus - 1) / C.cus * P.quota * (C.unit + C.weights);
     }
-    return us;
+    if (P.ranges == 0) P.us += 1.4;
+    P.fused = false;
+    if (P.parts > 1) {
+        const double mb = P.parts * C.part_mb;
+        double add = 1.5 + 0.5 * mb;
+        if (P.parts <= QG_FUSED_SEGMENTS) {
+            const double last = C.last_workgroup + C.last_workgroup_mb * (C.by_parts ? P.parts - 1 : 1) * mb;
+            P.fused = last <= add;
+            if (P.fused) add = last;
+        }
+        P.us += add;
+    }
 }
 
 CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
@@ -871,19 +899,23 @@ CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
     P.units = (int)(((L.K + KC - 1) / KC + P.kw - 1) / P.kw);
     // The best of the cuts into at most 1 ... 8 parts by what they cost; a forced count (the search's, too) takes
     // the one cut.  A count that would need more workgroups than compute units is dealt evenly over those.
-    CodesPlan best = P;
-    for (int most = knob_splits ? knob_splits : 1; most <= (knob_splits ? knob_splits : QG_MAX_SEGMENTS); ++most) {
+    const CodesCost cost = codes_cost(L, gps, M, P.mb, cus);
+    const int room = cus / P.blocks > 1 ? cus / P.blocks : 1;
+    const int even = (int)(((int64_t)P.blocks * P.units + cus - 1) / cus);
+    if (knob_splits) {
+        codes_cut(P, knob_splits, room, even);
+        codes_price(P, cost);
+        return P;
+    }
+    CodesPlan best = P, last = P;
+    last.quota = last.ranges = -1;
+    for (int most = 1; most <= QG_MAX_SEGMENTS && most <= P.units; ++most) {
         CodesPlan c = P;
-        codes_cut(c, most, cus, most == 1 || (int64_t)P.blocks * most <= cus);
-        c.fused = false;
-        c.us = codes_cost_us(L, gps, M, c, cus);
-        if (c.parts > 1 && c.parts <= QG_FUSED_SEGMENTS) {
-            CodesPlan f = c;
-            f.fused = true;
-            f.us = codes_cost_us(L, gps, M, f, cus);
-            if (f.us <= c.us) c = f;
-        }
-        if (most == 1 || knob_splits || c.us < best.us) best = c;
+        codes_cut(c, most, room, even);
+        if (c.quota == last.quota && c.ranges == last.ranges) continue;        // (priced already)
+        codes_price(c, cost);
+        if (most == 1 || c.us < best.us) best = c;
+        last = c;
     }
     return best;
 }
