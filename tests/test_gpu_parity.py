@@ -927,6 +927,30 @@ def test_gemm_small_raw_code_units(qg, oracle, N, K, bits, group, M, splits, cut
     assert err <= TOL_BF16, err
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("bits,group,M", [(4, 128, 20), (4, 16, 40), (3, 64, 40), (2, 32, 9), (2, 512, 100)])
+def test_gemm_small_raw_codes_non_finite_activations(qg, bits, group, M, value):
+    # one such value in X makes its row of Y NaN and leaves the others as they are
+    _announce("gemm raw codes, non-finite X", bits, group, M, value)
+    rng = np.random.default_rng(4900 + bits + M)
+    N, K = 130, 1024
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    X = rng.standard_normal((M, K)).astype(np.float32)
+    blob = qg.qg_pack(*qg.qg_quantize(dev(W), bits, group), bits, group)
+    qg.qg_set_gemm_tuning(0, 13)
+    try:
+        plain = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X)))
+        for m, k in ((0, 0), (M - 1, K - 1), (M // 2, 37), (3, 70)):
+            Xv = X.copy()
+            Xv[m, k] = value
+            Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(Xv)))
+            assert np.all(np.isnan(Y[m])), (m, k)
+            rest = np.arange(M) != m
+            assert np.array_equal(Y[rest], plain[rest]), (m, k)
+    finally:
+        qg.qg_set_gemm_tuning(0, 0)
+
+
 @pytest.mark.parametrize("bits,group,K,M", [
     (4, 128, 1152, 20), (4, 384, 1152, 9), (4, 64, 1408, 40), (4, 16, 1200, 100), (3, 64, 1216, 20), (3, 128, 1152, 70),
     (3, 768, 2304, 17), (2, 32, 1184, 9), (2, 64, 1344, 40), (2, 256, 1280, 20)])
