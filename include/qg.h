@@ -177,7 +177,7 @@ int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group
  *     matrix instruction as exact bf16 integers, X is rounded to bf16, and scale and zero-point
  *     are applied in fp32 once per group and element of Y (eq. (2)); X is converted by a
  *     kernel of its own first, so a call enqueues two or three kernels.  (The sums of (2^7 + q) x over a
- *     group, or 128 k of it, are fp32: |x| up to 10^34.)
+ *     group, or 128 k of it, are fp32: |x| up to 10^34; NaN and infinity in X come out as NaN.)
  * Where both apply (4 bits) the second is used for 17 ... 32 and more than 64 rows on matrices of 4096
  * tile-steps or more (64 outputs x 128 k each) and for 33 ... 64 rows from 8192 on (groups of 32: from
  * 8448), where it measured faster, else the first; qg_set_gemm_tuning and qg_gemm_autotune choose otherwise.

@@ -25,9 +25,10 @@
 // workgroup is TN tiles x KW k-slices of wavefronts that share the A operands of a unit (KW steps) in
 // LDS.  The operands go there straight from memory (buffer_load ... lds: no registers, no stores, no
 // bank conflicts, since an operand is read as it lies), and every load of unit u + 1 is issued between
-// the matrix instructions of unit u.  The units of all blocks of outputs and rows are dealt evenly over
-// one workgroup per compute unit, wherever the borders fall: with a whole number of K ranges per block
-// the 22016 x 8192 matrix at 128 rows ran 172 workgroups on 256 compute units.
+// the matrix instructions of unit u.  The units of the blocks of outputs and rows are cut into whole ranges of K
+// or, where those would leave compute units idle, dealt evenly over one workgroup per compute unit, wherever the
+// borders fall (22016 x 8192 at 128 rows: 172 workgroups with whole ranges, 251 dealt); with more blocks than
+// compute units a workgroup takes a block.
 //
 // What bounds it: the vector ALU and the matrix core together.  Per 16 k x 64 outputs x 64 rows there
 // are 4 matrix instructions (32 cycles each) and, at groups of 32 k, 32 multiply-adds of the fold plus
@@ -35,8 +36,8 @@
 // launches around it count as much: prepare_x and, where many parts of a sum are better, add_parts.
 // Measured (us per call, passes in sequence, four rotated matrices; before: iterations of KW layout steps,
 // activations through registers, whole K ranges per block, always a kernel that adds the ranges): 22016 x
-// 8192 2-bit g32 M = 128 104.4 -> 76.0, 13824 x 5120 3-bit g64 M = 37 27.2 -> 22.5, M = 128 43.0 -> 35, 4096 x
-// 11008 4-bit g128 M = 128 28.1 -> 26.1.
+// 8192 2-bit g32 M = 128 104.4 -> 76, 13824 x 5120 3-bit g64 M = 37 27.0 -> 22.1, 4096 x 11008 4-bit g128 M = 128
+// 28.2 -> 24.9.  Figures further down are differences that one choice made at the time it was taken.
 #pragma once
 
 #include <atomic>
@@ -97,8 +98,9 @@ constexpr size_t qg_codes_lds(int gps, int mb, int tn, int kw)
     return qg_codes_stages(gps, mb, kw) + (qg_codes_slices_apart(gps, mb, tn, kw) ? (size_t)(kw - 1) * tn * 32 * 256 : 0);
 }
 // k-slices of a workgroup of eight wavefronts: 4 at 32 rows and 2 at 64 (4 there, with half of the tiles, halves
-// the partial sums but doubles the A operands' traffic: 13824 x 5120 3-bit M = 37 25.2 against 22.2 us, 4096 x
-// 11008 4-bit M = 128 29.1 against 27.3; 1 doubles the partial sums: 22.5, 31.0).  Groups of 16 at 32
+// the partial sums but doubles the A operands' traffic: 13824 x 5120 3-bit M = 37 +3.0 us, 4096 x
+// 11008 4-bit M = 128 +1.8; 1 doubles the partial sums: +0.3, +3.7; 2 at 32 rows: 4096 x 4096 +0.4, 4096 x 11008 +1.5 to
+// 2, but 8192 x 22016 -1 to -1.5).  Groups of 16 at 32
 // rows, with two A operands for every 16 k, are bound by that traffic as soon as there are tiles enough for
 // every compute unit: 2 there (22016 x 8192 M = 2 40.6 against 45.4 us, 8192 x 8192 18.7 against 20.2), 4 below
 // (1500 x 20480 29.4 against 20.2, 4096 x 11008 21.1 against 17.9, 512 x 512 9.2 against 8.1).
@@ -118,7 +120,7 @@ namespace {
 // One item = OCT consecutive k of one row (a cell at 2 bits, a word of a cell otherwise).  A workgroup takes
 // one step of 32 rows and so writes its A operands whole: with a workgroup per row every 128-byte line of
 // them was put together from eight workgroups' 16-byte pieces on different dies (a call with 128
-// rows 28.0 -> 26.7 us on 4096 x 11008 4-bit, 83.4 -> 81.8 on 22016 x 8192 2-bit).  Consecutive threads take
+// rows: 1.3 us on 4096 x 11008 4-bit, 1.6 on 22016 x 8192 2-bit).  Consecutive threads take
 // consecutive items of a row, so the items of one xhat sit in neighbouring lanes.
 template <int BITS>
 __global__ __launch_bounds__(32 * 128 / (BITS == 2 ? 16 : 8)) void prepare_x(const QgPrepArgs A)
