@@ -5,8 +5,8 @@ PyTorch supplies device memory and the current stream, nothing else.  There is n
 if the library cannot be loaded or a call returns an error, a RuntimeError is raised.
 """
 import ctypes
-import functools
 import os
+import struct
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -132,16 +132,23 @@ def qg_cell(bits: int) -> int:
     return int(lib().qg_cell(bits))
 
 
-@functools.lru_cache(maxsize=1024)
-def _packed_bytes(N: int, K: int, bits: int, group: int, layout: int) -> int:
-    return int(lib().qg_packed_bytes(N, K, bits, group, layout))
+_SIZES = {}        # blob sizes, at most 1024 of them
+_values = struct.Struct("5q").pack
 
 
 def qg_packed_bytes(N: int, K: int, bits: int, group: int, layout: int = QG_LAYOUT_DEVICE) -> int:
-    # remembered for plain ints alone: 512.0 is equal to 512 and refused, an array or tensor of one number may change
-    if type(N) is type(K) is type(bits) is type(group) is type(layout) is int:
-        return _packed_bytes(N, K, bits, group, layout)
-    return int(lib().qg_packed_bytes(N, K, bits, group, layout))
+    # remembered by the values the arguments have now (512.0, which is equal to 512, is refused; a tensor or
+    # array of one number may change); what has none of 64 bits goes to the library as it is
+    try:
+        key = _values(N, K, bits, group, layout)
+    except Exception:
+        return int(lib().qg_packed_bytes(N, K, bits, group, layout))
+    nbytes = _SIZES.get(key)
+    if nbytes is None:
+        if len(_SIZES) >= 1024:
+            _SIZES.clear()
+        nbytes = _SIZES[key] = int(lib().qg_packed_bytes(N, K, bits, group, layout))
+    return nbytes
 
 
 def qg_workspace_bytes(N: int, K: int, bits: int, group: int, M: int = 1) -> int:
@@ -208,8 +215,10 @@ def qg_gemv(packed: torch.Tensor, N: int, K: int, bits: int, group: int, x: torc
         y = torch.empty(N, dtype=torch.float32, device=x.device)
     if workspace is None:
         workspace = new_workspace(qg_workspace_bytes(N, K, bits, group, 1), x.device)
-    _check(lib().qg_gemv(packed.data_ptr(), N, K, bits, group, x.data_ptr(), y.data_ptr(),
-                         workspace.data_ptr(), workspace.numel(), _stream()), "qg_gemv")
+    rc = (_LIB or lib()).qg_gemv(packed.data_ptr(), N, K, bits, group, x.data_ptr(), y.data_ptr(),
+                                 workspace.data_ptr(), workspace.numel(), _stream())
+    if rc != 0:
+        _check(rc, "qg_gemv")
     return y
 
 
@@ -358,8 +367,10 @@ def qg_gemm_small(packed: torch.Tensor, N: int, K: int, bits: int, group: int, X
         Y = torch.empty((M, N), dtype=torch.float32, device=X.device)
     if workspace is None:
         workspace = new_workspace(qg_workspace_bytes(N, K, bits, group, M), X.device)
-    _check(lib().qg_gemm_small(packed.data_ptr(), N, K, bits, group, X.data_ptr(), M, Y.data_ptr(),
-                               workspace.data_ptr(), workspace.numel(), _stream()), "qg_gemm_small")
+    rc = (_LIB or lib()).qg_gemm_small(packed.data_ptr(), N, K, bits, group, X.data_ptr(), M, Y.data_ptr(),
+                                       workspace.data_ptr(), workspace.numel(), _stream())
+    if rc != 0:
+        _check(rc, "qg_gemm_small")
     return Y
 
 
