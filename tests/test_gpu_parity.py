@@ -396,6 +396,46 @@ def test_gemv_stacked_projections_equal_separate_ones(qg, oracle, H, K, bits, gr
     assert scaled_error(ys, y3.astype(np.float64), norms, x) <= 2e-6           # two fp32 summation orders apart at most
 
 
+@pytest.mark.parametrize("bits,group,K", [
+    # K ends inside its last step of 128 (4 bits) or 256 k: one group of it, all but one, one group in all
+    (4, 16, 16), (4, 16, 1040), (4, 16, 2032), (4, 32, 32), (4, 32, 1056), (4, 32, 4192), (4, 64, 64), (4, 64, 4160),
+    (3, 32, 32), (3, 32, 4160), (3, 32, 2016), (3, 64, 64), (3, 64, 4160), (3, 64, 2240), (3, 128, 128), (3, 128, 4224),
+    (2, 16, 16), (2, 16, 1040), (2, 16, 2032), (2, 32, 32), (2, 32, 4128), (2, 64, 64), (2, 64, 4288), (2, 128, 128), (2, 128, 4224)])
+@pytest.mark.parametrize("N", [1, 130])
+def test_gemv_k_ending_inside_a_step(qg, oracle, N, K, bits, group):
+    # the last step reads nothing of x past K (NaNs lie there) and closes no group past the last, in one wavefront
+    # as in a K cut over wavefronts and workgroups; also as the gated pair and beside a K of whole steps
+    _announce("gemv ragged K", N, K, bits, group)
+    W, x = synth.small_case(N + K + bits, N, K, 0.02, True)
+    for tuning in ((0, 0, 0), (1, 4096, 0), (3, 4096, 4), (8, 65536, 0)):
+        assert _gemv_case(qg, oracle, W, x, bits, group, tuning) <= TOL_FP32, tuning
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    y_ref, norms = oracle.matvec(q0, s0, z0, group, x), oracle.row_norms(q0, s0, z0, group)
+    blob = qg.qg_pack(dev(q0), dev(s0), dev(z0), bits, group)
+    behind = torch.full((K + 512,), float("nan"), device="cuda")
+    behind[:K] = dev(x)
+    y = qg.qg_gemv(blob, N, K, bits, group, behind[:K])
+    assert qg.qg_last_gemv_kernel().endswith(", ragged>")
+    assert scaled_error(host(y), y_ref, norms, x) <= TOL_FP32
+    W2, x2 = synth.small_case(N + K, 70, 1024, 0.02, True)
+    q2, s2, z2 = oracle.quantize(W2, bits, group)
+    problems = [dict(packed=blob, N=N, K=K, bits=bits, group=group, x=behind[:K], y=torch.empty(N, device="cuda")),
+                dict(packed=qg.qg_pack(dev(q2), dev(s2), dev(z2), bits, group), N=70, K=1024, bits=bits, group=group,
+                     x=dev(x2), y=torch.empty(70, device="cuda"))]
+    ya, yb = (host(t) for t in qg.qg_gemv_grouped(problems))
+    assert np.array_equal(ya, host(y))
+    assert scaled_error(yb, oracle.matvec(q2, s2, z2, group, x2), oracle.row_norms(q2, s2, z2, group), x2) <= TOL_FP32
+    if N > 1:
+        W3, _ = synth.small_case(K, 128, K, 0.02, True)
+        q3, s3, z3 = oracle.quantize(W3, bits, group)
+        h = host(qg.qg_gemv_swiglu(qg.qg_pack(dev(q3), dev(s3), dev(z3), bits, group), 64, K, bits, group, behind[:K]))
+        g, u = np.split(oracle.matvec(q3, s3, z3, group, x), 2)
+        # what an error of TOL_FP32 * |row| * |x| in each product may do to h (test_gemv_swiglu_matches_oracle)
+        eg, eu = np.split(TOL_FP32 * oracle.row_norms(q3, s3, z3, group) * np.linalg.norm(x.astype(np.float64)), 2)
+        ref = oracle.swiglu(g, u)
+        assert np.all(np.abs(h - ref) <= 1.1 * eg * (np.abs(u) + eu) + np.abs(g) * eu + 1e-6 * np.abs(ref))
+
+
 @pytest.mark.parametrize("tuning", [(1, 4096, 1), (2, 4096, 1), (4, 8192, 1), (8, 4096, 1), (16, 4096, 1), (4, 65536, 1),
                                     (1, 4096, 2), (3, 8192, 2), (8, 4096, 2), (16, 4096, 2), (4, 65536, 2),
                                     (1, 4096, 3), (3, 8192, 3), (8, 4096, 3), (4, 65536, 3),
