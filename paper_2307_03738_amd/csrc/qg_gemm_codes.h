@@ -28,16 +28,18 @@
 // the matrix instructions of unit u.  The units of the blocks of outputs and rows are cut into whole ranges of K
 // or, where those would leave compute units idle, dealt evenly over one workgroup per compute unit, wherever the
 // borders fall (22016 x 8192 at 128 rows: 172 workgroups with whole ranges, 251 dealt); with more blocks than
-// compute units a workgroup takes a block.
+// compute units a workgroup takes a block.  More than 32 rows go in blocks of 64 or of 32 (codes_plan says when); several
+// blocks of 32 rows of the same tiles sit in one die's workgroups, so that its L2 serves their weights.
 //
-// What bounds it: the vector ALU and the matrix core together.  Per 16 k x 64 outputs x 64 rows there
-// are 4 matrix instructions (32 cycles each) and, at groups of 32 k, 32 multiply-adds of the fold plus
-// 16-20 instructions of unpacking (4 cycles each); two wavefronts per SIMD share both.  On short problems the
+// What bounds it: the issue of a SIMD.  A matrix instruction takes 12 cycles of it (measured: n multiply-adds behind
+// each make max(34, 12 + 4 n) cycles, whether one wavefront runs on the SIMD or two).  Per 16 k x 64 outputs x 64 rows
+// there are 4 matrix instructions and, at groups of 32 k, 32 multiply-adds of the fold plus 16-20 instructions of
+// unpacking (4 cycles each): 2350 cycles per step of 128 k, 2-bit g32, of 2800 measured.  On short problems the
 // launches around it count as much: prepare_x and, where many parts of a sum are better, add_parts.
 // Measured (us per call, passes in sequence, four rotated matrices; before: iterations of KW layout steps,
 // activations through registers, whole K ranges per block, always a kernel that adds the ranges): 22016 x
-// 8192 2-bit g32 M = 128 104.4 -> 76, 13824 x 5120 3-bit g64 M = 37 27.0 -> 22.1, 4096 x 11008 4-bit g128 M = 128
-// 28.2 -> 24.9.  Figures further down are differences that one choice made at the time it was taken.
+// 8192 2-bit g32 M = 128 104.4 -> 76, 13824 x 5120 3-bit g64 M = 37 27.0 -> 22.1 (in blocks of 32 rows 20.0), 4096 x 11008
+// 4-bit g128 M = 128 28.2 -> 24.9.  Figures further down are differences that one choice made at the time it was taken.
 #pragma once
 
 #include <atomic>
@@ -55,13 +57,15 @@ struct QgCodesArgs {
     uint32_t tile_codes, tile_scales, tile_zeros;      // bytes of one tile's codes, scales, zero words
     int steps_padded;          // steps of 128 k rounded up to a multiple of 4: what prepare_x has written
     uint32_t group_magic;      // groups of several steps: 2^32 / steps per group, rounded up
-    int zshift;                // log2 of the blocks of 32 * MB rows
+    int zshift;                // log2 of zblocks, if that is no three
     int units;                 // units (KW steps) in K
     int ranges;                // > 0: every block's units are cut into this many ranges, one workgroup each
     int quota;                 // units per workgroup
     int total;                 // units of the launch = blocks * units
     int fused;                 // parts of a sum are added here (else by add_parts)
     int kw;                    // k-slices of a workgroup
+    int zblocks;               // blocks of 32 * MB rows: 1 ... 4
+    int per_die;               // the workgroups of a die take neighbouring units: row blocks of a tile share its weights in L2
 };
 
 struct QgPrepArgs {
@@ -239,14 +243,19 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     const uint32_t lane4 = lane * 4, lane16 = lane * 16;
 
     // this workgroup's units [u, u1) in the order (block of outputs, block of rows, unit of K)
+    int wg = blockIdx.x;
+    if (A.per_die) {                                     // workgroup i of the grid runs on die i % 8
+        const int die = wg & 7, more = gridDim.x & 7;
+        wg = die * (gridDim.x >> 3) + (die < more ? die : more) + (wg >> 3);
+    }
     int u, u1, b;
     if (A.ranges > 0) {
-        b = __builtin_amdgcn_readfirstlane(blockIdx.x / A.ranges);
-        u = b * A.units + (blockIdx.x - b * A.ranges) * A.quota;
+        b = __builtin_amdgcn_readfirstlane(wg / A.ranges);
+        u = b * A.units + (wg - b * A.ranges) * A.quota;
         u1 = u + A.quota;
         u1 = u1 < (b + 1) * A.units ? u1 : (b + 1) * A.units;
     } else {
-        u = blockIdx.x * A.quota;
+        u = wg * A.quota;
         u1 = u + A.quota;
         u1 = u1 < A.total ? u1 : A.total;
         b = __builtin_amdgcn_readfirstlane(u / A.units);
@@ -267,8 +276,9 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     rsrc_t codes_n, scales_n, zeros_n, x_n;
     uint32_t at_x;
     const uint32_t x_row_block = (uint32_t)A.steps_padded * (SEQ * 1024);
+    auto tiles_of = [&](int nb) { return A.zblocks == 3 ? (int)__umulhi((uint32_t)nb, 0x55555556u) : nb >> A.zshift; };
     auto aim_block = [&](int nb) {
-        const int tb = nb >> A.zshift, z = nb - (tb << A.zshift);
+        const int tb = tiles_of(nb), z = nb - tb * A.zblocks;
         int tile = tb * TN + tn;
         tile = tile < A.tiles ? tile : A.tiles - 1;
         codes_t = A.codes + (size_t)tile * A.tile_codes;
@@ -605,15 +615,15 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
                 }
             }
         }
-        const int tb = b >> A.zshift, z = b - (tb << A.zshift), m0 = z * ROWS;
+        const int tb = tiles_of(b), z = b - tb * A.zblocks, m0 = z * ROWS;
         const int tile = tb * TN + tn;
         int seg, nseg;
         if (A.ranges > 0) {
-            seg = blockIdx.x - b * A.ranges;
+            seg = wg - b * A.ranges;
             nseg = A.ranges;
         } else {
             const int first = b * A.units / A.quota;
-            seg = blockIdx.x - first;
+            seg = wg - first;
             nseg = ((b + 1) * A.units - 1) / A.quota - first + 1;
         }
         // Register i of an accumulator is row 8 (i / 4) + 4 half + i % 4 of its block: bands of eight rows,
@@ -675,7 +685,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             uint32_t before = 0;
             if (lane == 0)
-                before = __hip_atomic_fetch_add(A.arrived + ((size_t)tile << A.zshift) + z, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                before = __hip_atomic_fetch_add(A.arrived + (size_t)tile * A.zblocks + z, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             last = (int)__builtin_amdgcn_readfirstlane(before) + 1 == nseg;
         }
         if constexpr (KW > 1) {

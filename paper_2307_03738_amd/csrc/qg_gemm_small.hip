@@ -635,7 +635,7 @@ __global__ void add_splits(const float *__restrict__ partial, int splits, size_t
 // M = 24 11.5 | 11.0 | 10.8, M = 128 23.5 | 22.2 | 22.5, 8192 x 8192 M = 128 32.0 | 30.6 | 31.6.
 template <int W>
 __global__ __launch_bounds__(64) void add_parts(const char *__restrict__ partial, int tiles, int N, int M, int tn, int rows,
-                                                int zshift, int units, int ranges, int quota, float *__restrict__ Y)
+                                                int zblocks, int units, int ranges, int quota, float *__restrict__ Y)
 {
     typedef float vec __attribute__((ext_vector_type(W)));
     constexpr int WAVES = 4 / W;                              // per quad
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(64) void add_parts(const char *__restrict__ partial
     const int pq = q & 1, band = (q >> 1) % bands, tile = (q >> 1) / bands;
     int count = ranges;
     if (ranges == 0) {
-        const int b = (tile / tn << zshift) + band * 8 / rows;
+        const int b = tile / tn * zblocks + band * 8 / rows;
         count = ((b + 1) * units - 1) / quota - b * units / quota + 1;
         if (count == 1) return;
     }
@@ -798,7 +798,7 @@ CodesSpace codes_space(const QgLayout &L, int gps, int M)
     W.steps_padded = (int)((L.K + 4 * KC - 1) / (4 * KC) * 4);
     W.groupk = L.group > KC ? KC : L.group;
     W.arrived_off = (size_t)W.rows_padded / 32 * W.steps_padded * qg_codes_seq(gps) * 1024;
-    W.partial_off = qg_round_up(W.arrived_off + (size_t)L.tiles * 2 * sizeof(uint32_t), QG_SECTION_ALIGN);
+    W.partial_off = qg_round_up(W.arrived_off + (size_t)L.tiles * 4 * sizeof(uint32_t), QG_SECTION_ALIGN);
     W.total = qg_round_up(W.partial_off + (size_t)QG_MAX_SEGMENTS * L.tiles * ((M + 7) / 8) * 2048, QG_SECTION_ALIGN);
     return W;
 }
@@ -807,7 +807,7 @@ CodesSpace codes_space(const QgLayout &L, int gps, int M)
 // steps; `ranges` K ranges per block of outputs and rows (one workgroup each), or, with ranges == 0,
 // `quota` consecutive units per workgroup whatever blocks they fall into.
 struct CodesPlan {
-    int mb, tn, kw, zshift, blocks, units, ranges, quota, workgroups, parts;
+    int mb, tn, kw, zblocks, blocks, units, ranges, quota, workgroups, parts;
     bool fused;
     double us;                 // what it costs (codes_cost_us)
 };
@@ -833,34 +833,48 @@ void codes_cut(CodesPlan &P, int most, int room, int even)
     }
 }
 
-// Estimate of a call: a straight line through 9000 cuts of 18 matrices from 512 x 512 to 30000 x 4096 at 2, 3
-// and 4 bits, groups of 16, 32, 64, 128 and one per output, 2 ... 128 rows (root mean square of what it is off: 4
-// %).  A unit has a time of its own, by rows and groups per step, and one on a full chip for the weights it reads.
+// Estimate of a call: straight lines through measured cuts of 2, 3 and 4 bits, groups of 16, 32, 64, 128 and one
+// per output.  Up to 32 rows: 9000 cuts of 18 matrices from 512 x 512 to 30000 x 4096 (root mean square of what it is
+// off: 4 %); more: 10000 cuts of 29 matrices, with blocks of 32 rows (5 %) and of 64 (4 %).  A unit has a time of its
+// own, by rows and groups per step, and one on a full chip for the weights it reads.
 // Parts are added by a kernel, which the whole chip shares, or, if they are two or three, by the workgroup that
-// comes last, which alone reads them all: at up to 32 rows that is never the slower way, at 64 from 8 MB of
+// comes last, which alone reads them all: at 32 rows that is never the slower way, at 64 from 8 MB of
 // parts (two of them) or 11 (three) on (kernel minus last workgroup, us: -3 below 2 MB, +2 at 12 MB of two
-// parts).  An evenly dealt workgroup ends a block of outputs in the middle of its units as well as at
-// their end.
+// parts).  An evenly dealt workgroup ends a block of outputs in the middle of its units as well as at their end.
 // (A table that went by the groups per step alone and took the adding for 1 us at two parts put 5120 x 5120 3-bit g64
 // M = 16 on 80 workgroups, 14.0 -> 15.3 us, and 4096 x 4096 3-bit M = 8 on 64, 10.6 -> 13.0; now 11.9 and 10.3.)
 struct CodesCost {
     double call, unit, weights;        // of a call, of a unit, of a unit on a full chip for its weights
-    double last_workgroup, last_workgroup_mb, part_mb;
+    double dealt;                      // of a call whose units are dealt evenly
+    double last, last_mb, kernel, kernel_mb;       // adding, by the last workgroup and by a kernel, per MB of parts
+    double last_workgroup, last_workgroup_mb, part_mb;      // (who adds: the last workgroup against 1.5 + 0.5 per MB)
     int cus;
     bool by_parts;                     // the last workgroup's time per MB grows with the parts
 };
 CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus)
 {
-    static constexpr double UNIT_US[2][5] = {{1.0, 1.05, 1.2, 1.45, 2.0}, {1.35, 1.4, 1.65, 2.15, 3.2}};
+    static constexpr double UNIT_US[3][5] = {{1.0, 1.05, 1.2, 1.45, 2.0}, {1.0, 1.02, 1.18, 1.45, 2.0}, {1.36, 1.38, 1.65, 2.15, 3.2}};
     CodesCost C;
-    C.call = mb == 1 ? 6.0 : 7.3;
-    C.unit = UNIT_US[mb - 1][gps == 0 ? 0 : gps == 1 ? 1 : gps == 2 ? 2 : gps == 4 ? 3 : 4];
-    C.weights = L.bits == 4 ? 0.5 : L.bits == 3 ? 0.35 : 0.1;
-    C.last_workgroup = mb == 1 ? 1.5 : 4.6;
-    C.last_workgroup_mb = mb == 1 ? 0.3 : 0.1;
-    C.by_parts = mb == 2;
     C.part_mb = 4e-6 * M * (double)L.N;
     C.cus = cus;
+    C.by_parts = mb == 2;
+    C.last_workgroup = mb == 1 ? 1.5 : 4.6;
+    C.last_workgroup_mb = mb == 1 ? 0.3 : 0.1;
+    C.unit = UNIT_US[M <= 32 ? 0 : mb][gps == 0 ? 0 : gps == 1 ? 1 : gps == 2 ? 2 : gps == 4 ? 3 : 4];
+    if (M <= 32) {
+        C.call = 6.0;
+        C.weights = L.bits == 4 ? 0.5 : L.bits == 3 ? 0.35 : 0.1;
+        C.dealt = 1.4;
+        C.last = 1.5, C.last_mb = 0.3, C.kernel = 1.5, C.kernel_mb = 0.5;
+        return C;
+    }
+    // (32 rows of X converted, and Y written)
+    const double converted = 1e-5 * ((M + 31) / 32) * (double)L.K;
+    C.call = mb == 1 ? 7.3 + 6.3 * converted + 0.26 * C.part_mb : 7.7 + 3.0 * converted + 0.16 * C.part_mb;
+    C.weights = L.bits == 4 ? (mb == 1 ? 0.3 : 0.28) : L.bits == 3 ? 0.14 : 0.0;
+    C.dealt = 0.0;
+    C.last = mb == 1 ? 1.65 : 3.7, C.last_mb = mb == 1 ? 0.06 : 0.3;
+    C.kernel = mb == 1 ? 1.4 : 1.7, C.kernel_mb = mb == 1 ? 0.55 : 0.42;
     return C;
 }
 // Sets P.us and, with it, who adds the parts.
@@ -872,36 +886,33 @@ void codes_price(CodesPlan &P, const CodesCost &C)
     } else {
         P.us += (P.workgroups + C.cus - 1) / C.cus * P.quota * (C.unit + C.weights);
     }
-    if (P.ranges == 0) P.us += 1.4;
+    if (P.ranges == 0) P.us += C.dealt;
     P.fused = false;
     if (P.parts > 1) {
         const double mb = P.parts * C.part_mb;
-        double add = 1.5 + 0.5 * mb;
-        if (P.parts <= QG_FUSED_SEGMENTS) {
-            const double last = C.last_workgroup + C.last_workgroup_mb * (C.by_parts ? P.parts - 1 : 1) * mb;
-            P.fused = last <= add;
-            if (P.fused) add = last;
-        }
-        P.us += add;
+        if (P.parts <= QG_FUSED_SEGMENTS)
+            P.fused = C.last_workgroup + C.last_workgroup_mb * (C.by_parts ? P.parts - 1 : 1) * mb <= 1.5 + 0.5 * mb;
+        P.us += P.fused ? C.last + C.last_mb * mb : C.kernel + C.kernel_mb * mb;
     }
 }
 
-CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
+// The best of the cuts into at most 1 ... 8 parts by what they cost; a forced count (the search's, too) takes the one cut.
+// A count that would need more workgroups than compute units is dealt evenly over those.
+CodesPlan codes_plan_rows(const QgLayout &L, int gps, int M, int mb, int knob_splits)
 {
     CodesPlan P;
-    P.mb = M <= 32 ? 1 : 2;
-    P.zshift = M > 64 ? 1 : 0;
-    const int zblocks = 1 << P.zshift;
+    P.mb = mb;
+    P.zblocks = (M + 32 * mb - 1) / (32 * mb);
     const int cus = qg_compute_units();
     P.kw = qg_codes_kw(gps, P.mb, (L.tiles + 3) / 4 * QG_MAX_SEGMENTS >= cus);
     P.tn = 8 / P.kw;
-    P.blocks = (int)((L.tiles + P.tn - 1) / P.tn) * zblocks;
+    P.blocks = (int)((L.tiles + P.tn - 1) / P.tn) * P.zblocks;
     P.units = (int)(((L.K + KC - 1) / KC + P.kw - 1) / P.kw);
-    // The best of the cuts into at most 1 ... 8 parts by what they cost; a forced count (the search's, too) takes
-    // the one cut.  A count that would need more workgroups than compute units is dealt evenly over those.
     const CodesCost cost = codes_cost(L, gps, M, P.mb, cus);
     const int room = cus / P.blocks > 1 ? cus / P.blocks : 1;
-    const int even = (int)(((int64_t)P.blocks * P.units + cus - 1) / cus);
+    // (several blocks of 32 rows: whole ranges alone, dealt ones no longer share a tile's weights: 8192 x 22016 4-bit
+    // M = 72 115 us against 74 in blocks of 64)
+    const int even = mb == 1 && P.zblocks > 1 ? 1 << 30 : (int)(((int64_t)P.blocks * P.units + cus - 1) / cus);
     if (knob_splits) {
         codes_cut(P, knob_splits, room, even);
         codes_price(P, cost);
@@ -918,6 +929,22 @@ CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits)
         last = c;
     }
     return best;
+}
+
+// More than 32 rows: in blocks of 64, or of 32 where their price is lower.  A block of 64 unpacks a weight once for
+// all of its rows, 1.35 us a unit; a workgroup of blocks of 32 takes half the tiles and twice the k-slices in 1.0 us, so K is
+// cut into a quarter of the parts, which is more wherever tiles are few.  us per call, blocks of 64 | 32: 5120 x 5120 2-bit
+// g32 M = 48 20.1 | 16.3, 4096 x 4096 3-bit g64 M = 64 17.0 | 13.3, 13824 x 5120 3-bit g64 M = 37 21.5 | 20.6; 22016 x 8192
+// 2-bit g32 M = 128 76 | 90.  Over 504 products of 33 ... 128 rows at 2 and 3 bits the choice takes 0.90 of the time of
+// blocks of 64 alone, the best cut of either kind 0.88.
+// A forced count on the kernel asked for by number (shape 13) keeps blocks of 64.
+CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits, bool by_number)
+{
+    if (M <= 32) return codes_plan_rows(L, gps, M, 1, knob_splits);
+    const CodesPlan two = codes_plan_rows(L, gps, M, 2, knob_splits);
+    if (knob_splits && by_number) return two;
+    const CodesPlan one = codes_plan_rows(L, gps, M, 1, knob_splits);
+    return one.us < two.us ? one : two;
 }
 }  // namespace
 
@@ -955,6 +982,61 @@ struct GemmPrice {
     double us;                 // family 0: what the plan says it costs
 };
 
+// The built-in plan of the dequantizing kernels: shape (index into SHAPES), workgroups along N and M, K ranges.
+//   Up to 32 rows: one block of rows, two tiles x four
+// k-slices.  Up to 64 rows: gemm_wide_b4 with four tiles per workgroup.  More: all rows
+// in one wavefront (gemm_wide_b4, every weight dequantized once) when the launch has
+// enough tiles for it, otherwise blocks of 64 rows on the grid's z axis, four tiles x two
+// k-slices (two blocks double the wavefronts of a launch at the price of dequantizing
+// twice, which pays as long as the launch cannot fill the chip).
+struct DequantizingPlan {
+    int shape, kw, tn, zblocks, blocks_x, steps_per_group, sps, splits;
+};
+DequantizingPlan dequantizing_plan(const QgLayout &L, int M, int cus, int knob_splits, int knob_shape)
+{
+    DequantizingPlan P;
+    P.shape = M <= 32 ? 1 : M <= 64 ? 7 : L.tiles >= 128 ? 9 : 5;
+    if (knob_shape > 0 && knob_shape <= NSHAPES) {
+        const Shape &sh = SHAPES[knob_shape - 1];
+        if (sh.wide ? (M > 32 && M <= sh.mb * 32) : ((sh.mb == 1) == (M <= 32))) P.shape = knob_shape - 1;
+    }
+    const int rows_per_block = SHAPES[P.shape].mb * 32;
+    P.zblocks = (M + rows_per_block - 1) / rows_per_block;
+    P.kw = SHAPES[P.shape].kw, P.tn = SHAPES[P.shape].tn;
+    P.blocks_x = (int)((L.tiles + P.tn - 1) / P.tn);
+    P.steps_per_group = L.group > KC ? L.group / KC : 1;
+    // a split is a whole number of workgroup iterations and of groups
+    const int quantum = P.kw / gcd(P.kw, P.steps_per_group) * P.steps_per_group;
+    const int quanta = (int)((L.steps + quantum - 1) / quantum);
+    // about one workgroup per compute unit, each with at least one quantum of work
+    int splits = knob_splits ? knob_splits : (cus + P.blocks_x * P.zblocks - 1) / (P.blocks_x * P.zblocks);
+    if (splits > MAX_SPLITS) splits = MAX_SPLITS;
+    if (splits > quanta) splits = quanta;
+    P.sps = (quanta + splits - 1) / splits * quantum;
+    P.splits = (int)((L.steps + P.sps - 1) / P.sps);
+    return P;
+}
+// What that plan costs: straight lines through 790 products of 28 matrices from 512 x 512 to 22016 x 8192, 17 ... 128 rows
+// (root mean square of what they are off: 12 % up to 32 rows, 9 up to 64, 5 and 14 beyond).
+double dequantizing_us(const QgLayout &L, int M, int cus)
+{
+    const DequantizingPlan P = dequantizing_plan(L, M, cus, 0, 0);
+    struct Line { double call, round, iteration, iteration_full, g32, add, add_mb, y_mb; };
+    static constexpr Line LINES[] = {{3.6, 0.0, 1.99, 0.06, 0.18, 2.3, 0.62, 0.0}, {3.6, 0.0, 2.3, 0.93, 0.05, 2.3, 0.23, 1.25},
+                                     {3.6, 1.4, 2.57, 0.02, 0.11, 2.6, 0.14, 1.8}, {0.0, 0.0, 2.7, 2.5, 0.47, 7.5, 0.17, 1.24}};
+    const Line &l = LINES[P.shape == 1 ? 0 : P.shape == 7 ? 1 : P.shape == 5 ? 2 : 3];
+    const bool wide = SHAPES[P.shape].wide;
+    const int most = P.sps < L.steps ? P.sps : (int)L.steps, iterations = (most + (wide ? 2 : P.kw) - 1) / (wide ? 2 : P.kw);
+    const int64_t workgroups = (int64_t)P.blocks_x * P.zblocks * P.splits;
+    const int capacity = cus * (wide ? 2 : 1);
+    const int rounds = (int)((workgroups + capacity - 1) / capacity);
+    const double full = workgroups < cus ? (double)workgroups / cus : 1.0, y_mb = 4e-6 * M * (double)L.N;
+    double us = l.call + (rounds - 1) * l.round + l.y_mb * y_mb;
+    us += rounds * iterations * (l.iteration + l.iteration_full * full + (L.group <= 32 ? l.g32 : 0.0));
+    if (P.splits > 1) us += l.add + l.add_mb * P.splits * y_mb;
+    return us;
+}
+
 // Checks, plans and (price == NULL) enqueues one product; knob_*: as qg_set_gemm_tuning.
 int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, const float *X, int M,
                float *Y, void *workspace, size_t workspace_bytes, void *stream, int knob_splits,
@@ -982,11 +1064,23 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     //   5120 x 13824   (8640)  17.4 | 24.7  19.8 | 25.9      21.6 | 26.3  27.4 | 27.6
     // so at 33 ... 64 rows the line lies higher, and above 8192 for groups of 32, whose fold is as much work as their matrix
     // instructions.
+    // The other 4-bit matrices of up to 16 rows go to gemm_rows16 where it has tiles enough; whatever else the
+    // dequantizing kernels take goes to the raw-code kernel where its price is the lower one by more than the two are off.  That
+    // is most of all where groups are long: the dequantizing kernels cut K between groups only (1500 x 20480, one group per
+    // output, M = 33 196 -> 19 us; 8192 x 8192 M = 8 37 -> 15), and 33 and more rows of few tiles (1024 x 8192 g128
+    // M = 96 17.6 -> 14.9, 4096 x 4096 M = 128 18.9 -> 15.6).
     const int gps = codes_gps(L);
     const int from = M > 32 && M <= 64 ? (gps >= 4 ? 8448 : 8192) : 4096;
     const bool large = M > 16 && L.tiles * L.steps >= from;
-    if (gps >= 0 && M > 1 && (knob_shape == NSHAPES + 1 || (knob_shape == 0 && (!fast_path(L) || large)))) {
-        const CodesPlan C = codes_plan(L, gps, M, knob_splits);
+    const bool either = fast_path(L) && !large, rows16 = either && M <= 16 && L.tiles >= 128 && L.group <= KC;
+    bool raw = gps >= 0 && M > 1 && (knob_shape == NSHAPES + 1 || (knob_shape == 0 && !rows16));
+    CodesPlan C;
+    if (raw) {
+        C = codes_plan(L, gps, M, knob_splits, knob_shape != 0);
+        if (knob_shape == 0 && either)                    // (by the built-in counts of K ranges, also where one is forced)
+            raw = (knob_splits ? codes_plan(L, gps, M, 0, false) : C).us * 1.08 < dequantizing_us(L, M, qg_compute_units());
+    }
+    if (raw) {
         const CodesSpace W = codes_space(L, gps, M);
         char *ws = (char *)workspace;
         QgPrepArgs P;
@@ -997,7 +1091,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         P.steps_padded = W.steps_padded;
         P.groupk = W.groupk;
         P.arrived = (uint32_t *)(ws + W.arrived_off);
-        P.counters = C.fused ? (int)L.tiles << C.zshift : 0;
+        P.counters = C.fused ? (int)L.tiles * C.zblocks : 0;
         QgCodesArgs A;
         const char *base = (const char *)packed;
         A.codes = base + L.codes_off;
@@ -1015,7 +1109,9 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         A.tiles = (int)L.tiles;
         A.steps_padded = W.steps_padded;
         A.group_magic = gps == 0 ? (uint32_t)(((1ull << 32) + group / KC - 1) / (group / KC)) : 0;
-        A.zshift = C.zshift;
+        A.zshift = C.zblocks == 4 ? 2 : C.zblocks / 2;
+        A.zblocks = C.zblocks;
+        A.per_die = C.mb == 1 && C.zblocks > 1;      // (13824 x 5120 3-bit M = 37 22.6 -> 20.6 us, 4096 x 11008 4-bit M = 128 28.7 -> 26.2)
         A.units = C.units;
         A.ranges = C.ranges;
         A.quota = C.quota;
@@ -1033,7 +1129,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         const int have = main_kernel(&info);
         if (have != QG_OK) return have;
         if (price) {
-            *price = {0, NSHAPES, C.ranges, (long)C.workgroups, C.quota, C.ranges != 1 && !C.fused ? 3 : 2, info, C.us};
+            *price = {0, NSHAPES + (M > 32 && C.mb == 1), C.ranges, (long)C.workgroups, C.quota, C.ranges != 1 && !C.fused ? 3 : 2, info, C.us};
             return QG_OK;
         }
         if (bits == 4) qg_codes_prepare_b4(P, W.rows_padded, st);
@@ -1047,7 +1143,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
             const int64_t quads = L.tiles * ((M + 7) / 8) * 2;
             const int waves = quads * 4 <= 4096 ? 4 : 2;                 // per quad: up to about 16 wavefronts per compute unit
             hipLaunchKernelGGL(waves == 4 ? add_parts<1> : add_parts<2>, dim3((unsigned)(quads * waves)), dim3(64), 0, st, A.partial,
-                               (int)L.tiles, (int)N, M, C.tn, 32 * C.mb, C.zshift, C.units, C.ranges, C.quota, Y);
+                               (int)L.tiles, (int)N, M, C.tn, 32 * C.mb, C.zblocks, C.units, C.ranges, C.quota, Y);
         }
         return qg_launch_status();
     }
@@ -1088,32 +1184,8 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         return QG_OK;
     }
 
-    // Workgroup shape (measured choices).  Up to 32 rows: one block of rows, two tiles x four
-    // k-slices.  Up to 64 rows: gemm_wide_b4 with four tiles per workgroup.  More: all rows
-    // in one wavefront (gemm_wide_b4, every weight dequantized once) when the launch has
-    // enough tiles for it, otherwise blocks of 64 rows on the grid's z axis, four tiles x two
-    // k-slices (two blocks double the wavefronts of a launch at the price of dequantizing
-    // twice, which pays as long as the launch cannot fill the chip).
-    int shape = M <= 32 ? 1 : M <= 64 ? 7 : L.tiles >= 128 ? 9 : 5;
-    if (knob_shape > 0 && knob_shape <= NSHAPES) {
-        const Shape &sh = SHAPES[knob_shape - 1];
-        if (sh.wide ? (M > 32 && M <= sh.mb * 32) : ((sh.mb == 1) == (M <= 32))) shape = knob_shape - 1;
-    }
-    const int rows_per_block = SHAPES[shape].mb * 32;
-    const int zblocks = (M + rows_per_block - 1) / rows_per_block;
-    const int kw = SHAPES[shape].kw, tn = SHAPES[shape].tn;
-    const int blocks_x = (int)((L.tiles + tn - 1) / tn);
-    const int steps_per_group = group > KC ? group / KC : 1;
-    // a split is a whole number of workgroup iterations and of groups
-    const int quantum = kw / gcd(kw, steps_per_group) * steps_per_group;
-    const int quanta = (int)((L.steps + quantum - 1) / quantum);
-    // about one workgroup per compute unit, each with at least one quantum of work
-    const int cus = qg_compute_units();
-    int splits = knob_splits ? knob_splits : (cus + blocks_x * zblocks - 1) / (blocks_x * zblocks);
-    if (splits > MAX_SPLITS) splits = MAX_SPLITS;
-    if (splits > quanta) splits = quanta;
-    const int sps = (quanta + splits - 1) / splits * quantum;
-    splits = (int)((L.steps + sps - 1) / sps);
+    const DequantizingPlan D = dequantizing_plan(L, M, qg_compute_units(), knob_splits, knob_shape);
+    const int splits = D.splits;
 
     GemmArgs A;
     const char *base = (const char *)packed;
@@ -1131,18 +1203,18 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     A.ngroups = (int)L.ngroups;
     A.zwords = (int)L.zwords;
     A.group_shift = group == 32 ? 5 : group == 64 ? 6 : 7;
-    A.steps_per_group = steps_per_group;
-    A.steps_per_split = sps;
-    const dim3 grid((unsigned)blocks_x, (unsigned)splits, (unsigned)zblocks);
+    A.steps_per_group = D.steps_per_group;
+    A.steps_per_split = D.sps;
+    const dim3 grid((unsigned)D.blocks_x, (unsigned)splits, (unsigned)D.zblocks);
     if (price) {
         KernelInfo info = {nullptr, 0, 0};
-        launch_shape(shape, A, grid, st, &info);
+        launch_shape(D.shape, A, grid, st, &info);
         // (gemm_wide_b4 runs two steps per iteration)
-        *price = {3, shape, splits, (long)blocks_x * splits * zblocks, sps / (SHAPES[shape].wide ? 2 : kw) + 1,
+        *price = {3, D.shape, splits, (long)D.blocks_x * splits * D.zblocks, D.sps / (SHAPES[D.shape].wide ? 2 : D.kw) + 1,
                   splits > 1 ? 2 : 1, info, 0.0};
         return QG_OK;
     }
-    launch_shape(shape, A, grid, st);
+    launch_shape(D.shape, A, grid, st);
     if (qg_launch_status() != QG_OK) return QG_ERR_DEVICE;
     if (splits > 1) {
         const size_t count = (size_t)M * N;
