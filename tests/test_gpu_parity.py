@@ -967,6 +967,28 @@ def test_gemm_small_raw_code_units(qg, oracle, N, K, bits, group, M, splits, cut
     assert err <= TOL_BF16, err
 
 
+# More than 32 rows in blocks of 32, as the plan takes them by itself (tests/test_launch_plans.py looks): N, K, bits,
+# group, M, blocks of rows, parts of a sum, added by the last workgroup; a last block of one row and of all
+# 32, ragged N and K, workgroups that are no multiple of the eight dies, a tile block with one real tile
+ROW_BLOCK_CASES = [
+    (130, 1536, 3, 64, 33, 2, 3, 1),
+    (4999, 2240, 2, 64, 64, 2, 3, 1),
+    (9000, 768, 3, 64, 90, 3, 1, 0),
+    (300, 4160, 4, 32, 65, 3, 5, 0),
+    (190, 20480, 2, 128, 40, 2, 8, 0),
+    (1000, 2304, 2, 32, 128, 4, 5, 0),
+    (4096, 5632, 4, 5632, 97, 4, 2, 1),
+]
+
+
+@pytest.mark.parametrize("N,K,bits,group,M,blocks,parts,fused", ROW_BLOCK_CASES)
+def test_gemm_small_blocks_of_32_rows(qg, oracle, N, K, bits, group, M, blocks, parts, fused):
+    _announce("gemm raw codes, blocks of 32 rows", N, K, bits, group, M)
+    W, X = synth.small_case(4700 + N + M, N, K, 0.02, True, m=M)
+    err = _gemm_case(qg, oracle, W, X, bits, group)
+    assert err <= TOL_BF16, err
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
 @pytest.mark.parametrize("bits,group,M", [(4, 128, 20), (4, 16, 40), (3, 64, 40), (2, 32, 9), (2, 512, 100)])
 def test_gemm_small_raw_codes_non_finite_activations(qg, bits, group, M, value):

@@ -2,7 +2,7 @@
 import pytest
 
 from tests.launches import launches
-from tests.test_gpu_parity import UNIT_CASES
+from tests.test_gpu_parity import ROW_BLOCK_CASES, UNIT_CASES
 
 
 @pytest.fixture(scope="module")
@@ -77,3 +77,24 @@ def test_who_adds_two_or_three_parts(tmp, problem, splits, last_workgroup):
     # at 64 rows the last workgroup from some megabytes of parts on, at 32 always
     k, names = _product(launches(tmp, [{"problem": problem, "splits": splits, "shape": 13}])[0])
     assert (k["args"]["fused"] == 1, "add_parts" not in names) == (last_workgroup, last_workgroup)
+
+
+# The GPU test of the blocks of 32 rows takes the cuts it names
+@pytest.mark.parametrize("case", ROW_BLOCK_CASES)
+def test_row_block_cases_are_cut_as_stated(tmp, case):
+    *problem, blocks, parts, fused = case
+    k, names = _product(launches(tmp, [{"problem": problem}])[0])
+    a, (_, _, mb, tn, *_) = k["args"], k["template"]
+    tiles = (problem[0] + 63) // 64
+    assert (mb, a["ranges"], a["fused"], k["grid"][0]) == (1, parts, fused, -(-tiles // tn) * blocks * parts)
+    assert ("add_parts" in names) == (parts > 1 and not fused)
+
+
+# 4 bits below the sizes where raw codes are taken whatever the estimates say: the dequantizing kernels cut K between
+# groups only, so that long groups go to raw codes, the shortest products stay where one launch does
+@pytest.mark.parametrize("problem,raw", [
+    ((1500, 20480, 4, 20480, 33), True), ((4096, 4096, 4, 4096, 24), True), ((1024, 8192, 4, 128, 96), True),
+    ((512, 768, 4, 768, 20), False), ((512, 512, 4, 64, 64), False), ((2048, 2048, 4, 128, 100), False)])
+def test_kernel_family_of_small_4_bit_products(tmp, problem, raw):
+    names = [k["name"] for k in launches(tmp, [{"problem": problem}])[0]["kernels"]]
+    assert ("gemm_codes" in names) == raw, names
