@@ -13,18 +13,32 @@ namespace {
 // banks.
 constexpr int PK_THREADS = 256;
 
+// A 16-byte piece of a row-major matrix that begins anywhere (rows of K / G zero-points are whole numbers of 16
+// bytes by chance only): the memory unit takes loads and stores of any alignment.
+struct __attribute__((packed)) Piece16 {
+    uint32_t w[4];
+};
+struct __attribute__((packed)) Piece4 {
+    uint32_t w;
+};
+
 // rows [r0, r0+64) x columns [c0, c0+SPAN) of v [rows][cols] -> lds; zeros outside the matrix.
-// `wide`: cols % 16 == 0 and v 16-byte aligned, so the block is moved in 16-byte pieces.
+// `wide`: cols % 16 == 0 and v 16-byte aligned, so every piece is whole and aligned.  Otherwise the last piece of a
+// row also loads what follows it, which is masked; only the pieces that would end past the matrix go byte by byte.
+// (Byte by byte throughout that was 64 dependent steps per thread whatever the columns, which outlasted the
+// codes' workgroups: 22 us for the zero-points of 2061 x 4352 4-bit g32, 136 a row.  Calls, us, before | now: unpack 1544
+// x 13888 4-bit g64 13.2 | 8.8, 12185 x 3232 4-bit g32 17.0 | 12.5; quantize + pack + to_narrow of 2410 x 9600 4-bit
+// g128 46.9 | 36.1, 1222 x 4864 2-bit g32 31.5 | 21.3.)
 template <int SPAN>
 __device__ inline void rows_to_lds(const uint8_t *__restrict__ v, int64_t rows, int64_t cols,
                                    int64_t r0, int64_t c0, bool wide, uint8_t *lds)
 {
     constexpr int PITCH = SPAN + 16;
+    // all loads of the thread are issued before the first is stored
+    constexpr int PIECES = SPAN / 16;
+    constexpr int PER = QG_WAVE * PIECES / PK_THREADS;
+    uint4 val[PER];
     if (wide) {
-        // all loads of the thread are issued before the first is stored
-        constexpr int PIECES = SPAN / 16;
-        constexpr int PER = QG_WAVE * PIECES / PK_THREADS;
-        uint4 val[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int i = threadIdx.x + j * PK_THREADS;
@@ -33,17 +47,37 @@ __device__ inline void rows_to_lds(const uint8_t *__restrict__ v, int64_t rows, 
             val[j] = make_uint4(0u, 0u, 0u, 0u);
             if (n < rows && c < cols) val[j] = *(const uint4 *)(v + n * cols + c);
         }
+    } else {
+        const int64_t total = rows * cols;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int i = threadIdx.x + j * PK_THREADS;
-            *(uint4 *)(lds + (i / PIECES) * PITCH + 16 * (i % PIECES)) = val[j];
+            const int r = i / PIECES, p = i % PIECES;
+            const int64_t n = r0 + r, c = c0 + 16 * p, at = n * cols + c;
+            uint32_t w[4] = {0u, 0u, 0u, 0u};
+            if (n < rows && c < cols) {
+                if (at + 16 <= total) {
+                    const Piece16 piece = *(const Piece16 *)(v + at);
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const int64_t left = cols - c - 4 * d;         // bytes of the row from this word on
+                        w[d] = left >= 4 ? piece.w[d] : left <= 0 ? 0u : piece.w[d] & ((1u << (8 * (int)left)) - 1u);
+                    }
+                } else {
+                    for (int e = 0; e < 16 && c + e < cols; ++e) {
+                        const uint32_t byte = (uint32_t)v[at + e] << (8 * (e & 3));
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) w[d] |= d == e / 4 ? byte : 0u;
+                    }
+                }
+            }
+            val[j] = make_uint4(w[0], w[1], w[2], w[3]);
         }
-    } else {
-        for (int i = threadIdx.x; i < QG_WAVE * SPAN; i += PK_THREADS) {
-            const int r = i / SPAN, b = i % SPAN;
-            const int64_t n = r0 + r, c = c0 + b;
-            lds[r * PITCH + b] = (n < rows && c < cols) ? v[n * cols + c] : (uint8_t)0;
-        }
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = threadIdx.x + j * PK_THREADS;
+        *(uint4 *)(lds + (i / PIECES) * PITCH + 16 * (i % PIECES)) = val[j];
     }
 }
 
@@ -53,18 +87,22 @@ __device__ inline void lds_to_rows(uint8_t *__restrict__ v, int64_t rows, int64_
                                    int64_t r0, int64_t c0, bool wide, const uint8_t *lds)
 {
     constexpr int PITCH = SPAN + 16;
-    if (wide) {
-        constexpr int PIECES = SPAN / 16;
-        for (int i = threadIdx.x; i < QG_WAVE * PIECES; i += PK_THREADS) {
-            const int r = i / PIECES, p = i % PIECES;
-            const int64_t n = r0 + r, c = c0 + 16 * p;
-            if (n < rows && c < cols) *(uint4 *)(v + n * cols + c) = *(const uint4 *)(lds + r * PITCH + 16 * p);
-        }
-    } else {
-        for (int i = threadIdx.x; i < QG_WAVE * SPAN; i += PK_THREADS) {
-            const int r = i / SPAN, b = i % SPAN;
-            const int64_t n = r0 + r, c = c0 + b;
-            if (n < rows && c < cols) v[n * cols + c] = lds[r * PITCH + b];
+    constexpr int PIECES = SPAN / 16;
+    for (int i = threadIdx.x; i < QG_WAVE * PIECES; i += PK_THREADS) {
+        const int r = i / PIECES, p = i % PIECES;
+        const int64_t n = r0 + r, c = c0 + 16 * p;
+        if (n >= rows || c >= cols) continue;
+        const uint8_t *src = lds + r * PITCH + 16 * p;
+        uint8_t *dst = v + n * cols + c;
+        if (wide) {
+            *(uint4 *)dst = *(const uint4 *)src;
+        } else if (c + 16 <= cols) {
+            const uint4 whole = *(const uint4 *)src;
+            *(Piece16 *)dst = Piece16{{whole.x, whole.y, whole.z, whole.w}};
+        } else {                                             // a row's end: words, then bytes
+            const int left = (int)(cols - c);
+            for (int e = 0; e + 4 <= left; e += 4) *(Piece4 *)(dst + e) = Piece4{*(const uint32_t *)(src + e)};
+            for (int e = left & ~3; e < left; ++e) dst[e] = src[e];
         }
     }
 }

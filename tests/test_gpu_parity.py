@@ -171,9 +171,39 @@ def test_device_pack_unpack_identity(qg, N, K, bits, group):
     assert np.array_equal(host(s2).view(np.uint32), s.view(np.uint32))
 
 
+@pytest.mark.parametrize("groups", [1, 2, 15, 17, 39, 136, 255, 257, 515])
+@pytest.mark.parametrize("N", [1, 63, 130])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_pack_rows_of_zero_points_of_any_length(qg, oracle, bits, N, groups):
+    """Rows of zero-points that are no whole number of 16-byte pieces: the end of a row, of a block of rows, of
+    the columns a workgroup takes and of the array; nothing is written outside the arrays."""
+    group = 32
+    K = groups * group
+    _announce("ragged zero-points", N, K, bits, group)
+    rng = np.random.default_rng(N + groups + bits)
+    q = rng.integers(0, 1 << bits, (N, K), dtype=np.uint8)
+    z = rng.integers(0, 1 << bits, (N, groups), dtype=np.uint8)
+    s = rng.standard_normal((N, groups)).astype(np.float32)
+    blob = host(qg.qg_pack(dev(q), dev(s), dev(z), bits, group, qg.QG_LAYOUT_CANONICAL))
+    words = oracle.pack_zeros(z, bits).ravel().view(np.uint8)
+    assert np.array_equal(blob[blob.size - words.size:], words)
+    for layout in (qg.QG_LAYOUT_CANONICAL, qg.QG_LAYOUT_DEVICE):
+        blob = qg.qg_pack(dev(q), dev(s), dev(z), bits, group, layout)
+        zd = torch.full((z.size + 64,), 77, dtype=torch.uint8, device="cuda")
+        q2, s2 = torch.empty_like(dev(q)), torch.empty_like(dev(s))
+        rc = qg.lib().qg_unpack(blob.data_ptr(), N, K, bits, group, layout, q2.data_ptr(), s2.data_ptr(),
+                                zd.data_ptr() + 32, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        torch.cuda.synchronize()
+        assert np.array_equal(host(zd)[32:32 + z.size].reshape(N, groups), z)
+        assert (host(zd)[:32] == 77).all() and (host(zd)[32 + z.size:] == 77).all()
+        assert np.array_equal(host(q2), q)
+        assert np.array_equal(host(s2).view(np.uint32), s.view(np.uint32))
+
+
 @pytest.mark.parametrize("bits", [2, 3, 4])
 def test_pack_from_unaligned_arrays(qg, oracle, bits):
-    """Codes and zero-points that do not start on a 16-byte boundary take the byte-wise path."""
+    """Codes and zero-points that do not start on a 16-byte boundary."""
     N, K, group = 75, 512, 32
     _announce("unaligned pack", N, K, bits, group)
     rng = np.random.default_rng(40 + bits)
