@@ -37,8 +37,8 @@ __device__ inline void rows_to_lds(const uint8_t *__restrict__ v, int64_t rows, 
     // all loads of the thread are issued before the first is stored
     constexpr int PIECES = SPAN / 16;
     constexpr int PER = QG_WAVE * PIECES / PK_THREADS;
-    uint4 val[PER];
     if (wide) {
+        uint4 val[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int i = threadIdx.x + j * PK_THREADS;
@@ -47,37 +47,46 @@ __device__ inline void rows_to_lds(const uint8_t *__restrict__ v, int64_t rows, 
             val[j] = make_uint4(0u, 0u, 0u, 0u);
             if (n < rows && c < cols) val[j] = *(const uint4 *)(v + n * cols + c);
         }
-    } else {
-        const int64_t total = rows * cols;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int i = threadIdx.x + j * PK_THREADS;
-            const int r = i / PIECES, p = i % PIECES;
-            const int64_t n = r0 + r, c = c0 + 16 * p, at = n * cols + c;
-            uint32_t w[4] = {0u, 0u, 0u, 0u};
-            if (n < rows && c < cols) {
-                if (at + 16 <= total) {
-                    const Piece16 piece = *(const Piece16 *)(v + at);
+            *(uint4 *)(lds + (i / PIECES) * PITCH + 16 * (i % PIECES)) = val[j];
+        }
+    } else {
+        const int64_t total = rows * cols;
+        Piece16 val[4];
+#pragma unroll 1
+        for (int j0 = 0; j0 < PER; j0 += 4) {
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        const int64_t left = cols - c - 4 * d;         // bytes of the row from this word on
-                        w[d] = left >= 4 ? piece.w[d] : left <= 0 ? 0u : piece.w[d] & ((1u << (8 * (int)left)) - 1u);
-                    }
-                } else {
-                    for (int e = 0; e < 16 && c + e < cols; ++e) {
-                        const uint32_t byte = (uint32_t)v[at + e] << (8 * (e & 3));
+            for (int j = 0; j < 4; ++j) {
+                const int i = threadIdx.x + (j0 + j) * PK_THREADS;
+                const int64_t n = r0 + i / PIECES, c = c0 + 16 * (i % PIECES), at = n * cols + c;
 #pragma unroll
-                        for (int d = 0; d < 4; ++d) w[d] |= d == e / 4 ? byte : 0u;
+                for (int d = 0; d < 4; ++d) val[j].w[d] = 0u;
+                if (n < rows && c < cols) {
+                    if (at + 16 <= total) {
+                        val[j] = *(const Piece16 *)(v + at);
+                    } else {
+                        for (int e = 0; c + e < cols; ++e) {
+                            const uint32_t byte = (uint32_t)v[at + e] << (8 * (e & 3));
+#pragma unroll
+                            for (int d = 0; d < 4; ++d) val[j].w[d] |= d == e / 4 ? byte : 0u;
+                        }
                     }
                 }
             }
-            val[j] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-    }
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int i = threadIdx.x + j * PK_THREADS;
-        *(uint4 *)(lds + (i / PIECES) * PITCH + 16 * (i % PIECES)) = val[j];
+            for (int j = 0; j < 4; ++j) {
+                const int i = threadIdx.x + (j0 + j) * PK_THREADS;
+                const int64_t c = c0 + 16 * (i % PIECES);
+                const int left = cols - c < 16 ? (int)(cols - c) : 16;         // bytes of the row from here on
+                uint32_t w[4];
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    w[d] = left >= 4 * d + 4 ? val[j].w[d] : left <= 4 * d ? 0u : val[j].w[d] & ((1u << (8 * (left - 4 * d))) - 1u);
+                *(uint4 *)(lds + (i / PIECES) * PITCH + 16 * (i % PIECES)) = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        }
     }
 }
 
@@ -88,21 +97,28 @@ __device__ inline void lds_to_rows(uint8_t *__restrict__ v, int64_t rows, int64_
 {
     constexpr int PITCH = SPAN + 16;
     constexpr int PIECES = SPAN / 16;
-    for (int i = threadIdx.x; i < QG_WAVE * PIECES; i += PK_THREADS) {
-        const int r = i / PIECES, p = i % PIECES;
-        const int64_t n = r0 + r, c = c0 + 16 * p;
-        if (n >= rows || c >= cols) continue;
-        const uint8_t *src = lds + r * PITCH + 16 * p;
-        uint8_t *dst = v + n * cols + c;
-        if (wide) {
-            *(uint4 *)dst = *(const uint4 *)src;
-        } else if (c + 16 <= cols) {
-            const uint4 whole = *(const uint4 *)src;
-            *(Piece16 *)dst = Piece16{{whole.x, whole.y, whole.z, whole.w}};
-        } else {                                             // a row's end: words, then bytes
-            const int left = (int)(cols - c);
-            for (int e = 0; e + 4 <= left; e += 4) *(Piece4 *)(dst + e) = Piece4{*(const uint32_t *)(src + e)};
-            for (int e = left & ~3; e < left; ++e) dst[e] = src[e];
+    if (wide) {
+        for (int i = threadIdx.x; i < QG_WAVE * PIECES; i += PK_THREADS) {
+            const int r = i / PIECES, p = i % PIECES;
+            const int64_t n = r0 + r, c = c0 + 16 * p;
+            if (n < rows && c < cols) *(uint4 *)(v + n * cols + c) = *(const uint4 *)(lds + r * PITCH + 16 * p);
+        }
+    } else {
+#pragma unroll 1
+        for (int i = threadIdx.x; i < QG_WAVE * PIECES; i += PK_THREADS) {
+            const int r = i / PIECES, p = i % PIECES;
+            const int64_t n = r0 + r, c = c0 + 16 * p;
+            if (n >= rows || c >= cols) continue;
+            const uint8_t *src = lds + r * PITCH + 16 * p;
+            uint8_t *dst = v + n * cols + c;
+            if (c + 16 <= cols) {
+                const uint4 whole = *(const uint4 *)src;
+                *(Piece16 *)dst = Piece16{{whole.x, whole.y, whole.z, whole.w}};
+            } else {                                         // a row's end: words, then bytes
+                const int left = (int)(cols - c);
+                for (int e = 0; e + 4 <= left; e += 4) *(Piece4 *)(dst + e) = Piece4{*(const uint32_t *)(src + e)};
+                for (int e = left & ~3; e < left; ++e) dst[e] = src[e];
+            }
         }
     }
 }
