@@ -175,8 +175,8 @@ int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group
  *   - any width, G a whole number of pairs of cells up to one step (4 bits: 16 ... 128; 2 bits:
  *     32 ... 256; 3 bits: 64 ... 256) or a multiple of a step, K % 16 == 0: the codes enter the
  *     matrix instruction as exact bf16 integers, X is rounded to bf16, and scale and zero-point
- *     are applied in fp32 once per group and element of Y (eq. (2)); X is converted by a
- *     kernel of its own first, so a call enqueues two or three kernels.  (The sums of (2^7 + q) x over a
+ *     are applied in fp32 once per group and element of Y (eq. (2)); X is converted by the
+ *     product kernel itself or, on larger products, by a kernel of its own first, so a call enqueues one to three kernels.  (The sums of (2^7 + q) x over a
  *     group, or 128 k of it, are fp32: |x| up to 10^34; NaN and infinity in X come out as NaN.)
  * Where both apply (4 bits) the second is used for 17 ... 32 and more than 64 rows on matrices of 4096
  * tile-steps or more (64 outputs x 128 k each) and for 33 ... 64 rows from 8192 on (groups of 32: from

@@ -18,7 +18,12 @@
 // prepare_x converts X once per call into the A operands themselves: for every block of 32 rows and
 // every step of 128 k, SEQ operands of 1 KB -- per group its xhat operand, then its k in sixteens -- each
 // laid out as the 64 lanes of a wavefront read it (row = lane % 32, k-octet = lane / 32).  Rows past M
-// and k past K are zeros, so the product kernel tests neither.
+// and k past K are zeros, so the product kernel tests neither.  Blocks of 32 rows can also make their operands
+// themselves, from X into LDS (SELF): every block of outputs converts X again, but a kernel less is launched, which
+// is 2 us of the caller's time and 2 to 3 us on the GPU, against 0.1 us per unit up to 16 rows and 0.6 beyond (a unit
+// itself 1.1 to 1.6).  So it is taken wherever units per workgroup are few (codes_price): 400 random products of
+// 2 ... 32 rows take 0.80 of the time, 400 of 33 ... 128 rows 0.90; 1192 x 11200 3-bit g64 M = 5 12.4 -> 10.4 us,
+// 1087 x 768 4-bit g128 M = 4 9.0 -> 6.5, 1408 x 3840 2-bit M = 38 11.9 -> 9.6.
 //
 // gemm_codes: a wavefront owns a tile of 64 outputs (device layout, lane = output) and MB blocks of 32
 // rows; one v_permlane32_swap per pair of code words turns "lane = output" into the operand layout.  A
@@ -43,6 +48,7 @@
 #pragma once
 
 #include <atomic>
+#include <type_traits>
 
 #include "qg_common.h"
 #include "qg_mma.h"
@@ -66,6 +72,9 @@ struct QgCodesArgs {
     int kw;                    // k-slices of a workgroup
     int zblocks;               // blocks of 32 * MB rows: 1 ... 4
     int per_die;               // the workgroups of a die take neighbouring units: row blocks of a tile share its weights in L2
+    int self;                  // the A operands are made here, from X
+    int K;
+    const float *X;            // [M][K] fp32
 };
 
 struct QgPrepArgs {
@@ -82,6 +91,13 @@ struct QgKernelInfo {
     const void *kernel;
     int threads;
     size_t lds_dynamic;
+};
+
+// Variants of the product kernel.
+enum {
+    QG_CODES_PREPARED = 0,     // A operands by prepare_x, parts by add_parts
+    QG_CODES_FUSED = 1,        // A operands by prepare_x, parts by the workgroup that comes last
+    QG_CODES_SELF = 2          // A operands by the product kernel itself (blocks of 32 rows), parts by add_parts
 };
 
 constexpr size_t QG_LDS_BYTES = 160u << 10;
@@ -213,12 +229,13 @@ __device__ inline rsrc_t buffer_of(const void *base, uint32_t bytes)
     return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000);
 }
 
-// FUSED: parts of a sum are added by the workgroup that comes last (an instance of its own: the code for it costs
-// the others 3 %).
-template <int BITS, int GPS_, int MB, int TN, int KW, bool FUSED>
+// HOW: QG_CODES_*.  FUSED: parts of a sum are added by the workgroup that comes last (an instance of its own: the code
+// for it costs the others 3 %).
+template <int BITS, int GPS_, int MB, int TN, int KW, int HOW>
 __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs A)
 {
     using F = Fmt<BITS>;
+    constexpr bool FUSED = HOW == QG_CODES_FUSED, SELF = HOW == QG_CODES_SELF;
     constexpr bool LONG = GPS_ == 0;                     // groups of several steps
     constexpr bool SHORT = GPS_ >= 2;                    // groups of 64 k or less: see compute_short
     constexpr int GPS = LONG ? 1 : GPS_;                 // xhat entries per step
@@ -228,12 +245,13 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     constexpr int SEQ = GPS * (GK + 1);                  // A operands per step and row block
     constexpr int ROWS = 32 * MB;
     constexpr int CHUNK = MB * KW * SEQ;                 // KB of A operands per unit
-    constexpr int NDMA = (CHUNK + NW - 1) / NW;          // 1 KB copies per wavefront and unit
+    constexpr int NDMA = SELF ? 0 : (CHUNK + NW - 1) / NW;          // 1 KB copies per wavefront and unit
     constexpr int NLOAD = L + 1 + GPS;                   // weight loads per wavefront and unit
     constexpr int ZPER = 32 / F::ZBITS;
     constexpr int SLOTS = 2 * MB;                        // matrix instructions per A operand index
     static_assert(SEQ == qg_codes_seq(GPS_), "operand count");
     static_assert(NLOAD + NDMA <= SEQ * SLOTS, "a request per slot");
+    static_assert(!SELF || (MB == 1 && NW >= 2 * KW), "a wavefront per 16 rows and step");
     extern __shared__ __attribute__((aligned(16))) char smem[];       // [2][CHUNK KB], then the reduction's
 
     const int lane = threadIdx.x & 63;
@@ -275,6 +293,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     const char *codes_t, *scales_t, *zeros_t;
     rsrc_t codes_n, scales_n, zeros_n, x_n;
     uint32_t at_x;
+    bool x_takes = false;                                // SELF: this wavefront converts a part of the unit's X
     const uint32_t x_row_block = (uint32_t)A.steps_padded * (SEQ * 1024);
     auto tiles_of = [&](int nb) { return A.zblocks == 3 ? (int)__umulhi((uint32_t)nb, 0x55555556u) : nb >> A.zshift; };
     auto aim_block = [&](int nb) {
@@ -284,7 +303,13 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         codes_t = A.codes + (size_t)tile * A.tile_codes;
         scales_t = A.scales + (size_t)tile * A.tile_scales;
         zeros_t = A.zeros + (size_t)tile * A.tile_zeros;
-        x_n = buffer_of(A.Xop + (size_t)z * MB * x_row_block, MB * x_row_block);
+        if constexpr (SELF) {
+            const int rows = A.M - z * 32 < 32 ? A.M - z * 32 : 32;
+            x_n = buffer_of(A.X + (size_t)z * 32 * A.K, (uint32_t)rows * A.K * 4);
+            x_takes = wave < (rows > 16 ? 2 : 1) * KW;
+        } else {
+            x_n = buffer_of(A.Xop + (size_t)z * MB * x_row_block, MB * x_row_block);
+        }
     };
     auto rest_of = [&](const char *section, uint32_t bytes, uint32_t at) {
         at = at < bytes ? at : bytes;
@@ -296,11 +321,11 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         codes_n = rest_of(codes_t, A.tile_codes, step * (L * 1024));
         scales_n = rest_of(scales_t, A.tile_scales, g * 256);
         zeros_n = rest_of(zeros_t, A.tile_zeros, g / ZPER * 256);                         // a step's groups share one zero word
-        at_x = nit * (KW * SEQ * 1024);
+        at_x = SELF ? nit * (KW * 128) : nit * (KW * SEQ * 1024);
     };
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
     // pieces of a unit's A operands this wavefront copies: where they are in memory
-    uint32_t piece_at[NDMA];
+    uint32_t piece_at[NDMA > 0 ? NDMA : 1];
 #pragma unroll
     for (int j = 0; j < NDMA; ++j) {
         int p = j * NW + wave;
@@ -327,6 +352,103 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane16), "s"(x_n), "s"(from)
                          : "memory", "m0");
         }
+    };
+
+    // SELF.  A wavefront takes 16 rows of one step: lane 4 r + i loads items i (OCT consecutive k, as in prepare_x) of
+    // row r of every quarter (2 bits: half) of the step, whole lines of X, while the unit before is multiplied, and
+    // writes them as pieces of the A operands at the end of it.  Rows past M and k past K lie outside the buffer and
+    // come as zeros.  The 16 bytes of row r of an operand's half lie at place r ^ 4 half ^ 8 parity of that half, parity
+    // being bit 1 of the item: the four items and four rows that 16 lanes write then fall on distinct banks.
+    constexpr int OCT = BITS == 2 ? 16 : 8, SUBS = 32 / OCT;          // (a lane's 32 values of a step)
+    constexpr float UP = BITS == 3 ? 8.0f : 4.0f;
+    const int x_item = lane & 3, x_row = (wave / KW & 1) * 16 + (lane >> 2);
+    uint4 xr[SELF ? 8 : 1];
+    bool x_loaded = false;
+    auto load_x = [&]() {
+        x_loaded = x_takes;
+        if (!x_loaded) return;
+        const uint32_t from = (uint32_t)x_row * A.K * 4;
+#pragma unroll
+        for (int s = 0; s < SUBS; ++s) {
+            const uint32_t k = at_x + wave % KW * 128 + (4 * s + x_item) * OCT;
+            const uint32_t at = k < (uint32_t)A.K ? from + k * 4 : 0x40000000u;      // (past every buffer of 32 rows)
+#pragma unroll
+            for (int i = 0; i < OCT / 4; ++i) {
+                typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(x_n, at + 16 * i, 0, 0);
+                xr[s * (OCT / 4) + i] = make_uint4(v[0], v[1], v[2], v[3]);
+            }
+        }
+    };
+    auto quad_add = [](float v, auto ctrl) {
+        return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    auto store_x = [&](int stage) {
+        if (!x_loaded) return;
+        const int xhalf = x_item & 1, par = x_item >> 1;
+        char *to = smem + (stage * CHUNK + wave % KW * SEQ) * 1024 + xhalf * 512;
+        const int place = (x_row ^ (4 * xhalf)) * 16;
+        constexpr int PAIRS = SUBS * 4 * OCT / 16 / GK;               // xhats of the step
+        static_assert(PAIRS == GPS, "xhats");
+        float sum0 = 0.0f, sum1 = 0.0f;
+#pragma unroll
+        for (int s = 0; s < SUBS; ++s) {
+            float t[OCT];                                             // in operand order
+#pragma unroll
+            for (int e = 0; e < OCT; ++e) {
+                const bool up = BITS == 3 ? (e & 7) >= 4 : BITS == 2 && (e & 1);
+                t[mma_slot<BITS>(e)] = __uint_as_float(word_of(xr[s * (OCT / 4) + e / 4], e & 3)) * (up ? 1.0f / UP : 1.0f);
+            }
+#pragma unroll
+            for (int o = 0; o < OCT / 8; ++o) {
+                MmaOperand piece;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const mma_floatx2 t2 = {t[8 * o + 2 * j], t[8 * o + 2 * j + 1]};
+                    const mma_bf16x2 hb = __builtin_convertvector(t2, mma_bf16x2);      // round to nearest even
+                    piece.r[j] = *(const uint32_t *)&hb;
+                    // 2 and 3 bits: the registers of codes taken one field up
+                    const bool up = BITS == 3 ? (j & 1) != 0 : BITS == 2 && (j & 1);
+                    const float pair = __uint_as_float(piece.r[j] << 16) + __uint_as_float(piece.r[j] & 0xffff0000u);
+                    if (up) sum1 += pair; else sum0 += pair;
+                }
+                // the lane's piece: sixteen c of the step, c = c0 at parity 0
+                const int c0 = BITS == 2 ? 4 * s + o : 2 * s;
+                const int next = BITS == 2 ? 2 : 1;                   // ... and c0 + next at parity 1
+                const int at0 = c0 / GK * (GK + 1) + 1 + c0 % GK, at1 = (c0 + next) / GK * (GK + 1) + 1 + (c0 + next) % GK;
+                *(lds_u128 *)(to + at0 * 1024 + par * ((at1 - at0) * 1024) + (place ^ (128 * par))) = piece.q;
+            }
+            constexpr int SUB16 = 4 * OCT / 16;                       // sixteens of k the four lanes hold
+            if ((s + 1) * SUB16 % GK == 0) {
+                // xhat of a group: over the four lanes, or over two of them where they hold two groups
+                sum0 = quad_add(sum0, std::integral_constant<int, 0xb1>());
+                sum1 = quad_add(sum1, std::integral_constant<int, 0xb1>());
+                if constexpr (GK >= SUB16) {
+                    sum0 = quad_add(sum0, std::integral_constant<int, 0x4e>());
+                    sum1 = quad_add(sum1, std::integral_constant<int, 0x4e>());
+                }
+                float rest = xhalf ? (BITS == 4 ? 0.0f : sum1 * UP) : sum0;
+                uint32_t part[3];
+#pragma unroll
+                for (int p3 = 0; p3 < 3; ++p3) {
+                    const mma_floatx2 t2 = {rest, 0.0f};
+                    const mma_bf16x2 hb = __builtin_convertvector(t2, mma_bf16x2);
+                    part[p3] = *(const uint32_t *)&hb & 0xffffu;
+                    rest -= __uint_as_float(part[p3] << 16);
+                }
+                const int grp = ((s + 1) * SUB16 - 1) / GK;           // GK < SUB16: of parity 1
+                if (GK < SUB16) *(lds_u128 *)(to + ((grp - 1) + par) * ((GK + 1) * 1024) + place) = make_uint4(part[0] | (part[1] << 16), part[2], 0u, 0u);
+                else if (par == 0) *(lds_u128 *)(to + grp * ((GK + 1) * 1024) + place) = make_uint4(part[0] | (part[1] << 16), part[2], 0u, 0u);
+                sum0 = sum1 = 0.0f;
+            }
+        }
+    };
+    // where lane (row, half) finds its piece of an operand: the xhats and sixteens of parity 0, those of parity 1
+    const uint32_t a_at0 = SELF ? half * 512 + (row ^ (4 * half)) * 16 : lane16, a_at1 = SELF ? a_at0 ^ 128 : lane16;
+    auto a_at = [&](int q) {
+        const int c = q / (GK + 1) * GK + q % (GK + 1) - 1;
+        const bool odd = q % (GK + 1) != 0 && (BITS == 2 ? (c >> 1) & 1 : c & 1);
+        return (odd ? a_at1 : a_at0) + q * 1024;
     };
 
     // ---- accumulators ----
@@ -369,7 +491,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     // and, where a group starts, preceded by the fold of the group that ended.  Every slot is fenced, so
     // that the order written here is the order issued.
     auto compute = [&](const StepRegs &r, uint32_t step, int stage, StepRegs &req) {
-        const char *xs = smem + (stage * CHUNK + kw * SEQ) * 1024 + lane16;
+        const char *xs = smem + (stage * CHUNK + kw * SEQ) * 1024;
         const uint32_t g = LONG ? __umulhi(step, A.group_magic) : step * GPS;             // first group of the step
         const uint32_t zw = r.zw >> (F::ZBITS * (g % ZPER));
         const auto zsw = __builtin_amdgcn_permlane32_swap(zw, zw, false, false);
@@ -428,7 +550,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         };
         auto read_a = [&](int q, MmaOperand *a) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) a[mb].q = *(const lds_u128 *)(xs + (mb * KW * SEQ + q) * 1024);
+            for (int mb = 0; mb < MB; ++mb) a[mb].q = *(const lds_u128 *)(xs + mb * KW * SEQ * 1024 + a_at(q));
         };
         read_a(0, aN);
         if constexpr (LONG) {
@@ -482,7 +604,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     auto compute_short = [&](const StepRegs &r, uint32_t step, int stage, StepRegs &req) {
         constexpr int R = GK + 1;                          // operands of a group: xhat, sixteens of k
         constexpr int PIECES = 2 * GK + 1;                 // pieces of preparation per half of a group
-        const char *xs = smem + (stage * CHUNK + kw * SEQ) * 1024 + lane16;
+        const char *xs = smem + (stage * CHUNK + kw * SEQ) * 1024;
         const uint32_t zw = r.zw >> (F::ZBITS * (step * GPS % ZPER));
         const auto zsw = __builtin_amdgcn_permlane32_swap(zw, zw, false, false);
         MmaOperand bo[2][R], a[MB == 1 ? 2 : 1][MB][R];
@@ -534,7 +656,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         };
         auto read_a = [&](int grp, int mb) {
 #pragma unroll
-            for (int q = 0; q < R; ++q) a[MB == 1 ? grp & 1 : 0][mb][q].q = *(const lds_u128 *)(xs + (mb * KW * SEQ + grp * R + q) * 1024);
+            for (int q = 0; q < R; ++q) a[MB == 1 ? grp & 1 : 0][mb][q].q = *(const lds_u128 *)(xs + mb * KW * SEQ * 1024 + a_at(grp * R + q));
         };
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) read_a(0, mb);
@@ -739,12 +861,16 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         __syncthreads();
     };
     auto unit = [&](StepRegs &use, StepRegs &req) {
+        if constexpr (SELF) store_x(stage);
         arrive(use);
         const uint32_t step = it * KW + kw;
         const bool last = u + 1 >= u1, ends = it + 1 >= A.units;
         const int nit = last ? it : ends ? 0 : it + 1;
         if (ends && !last) aim_block(b + 1);
         aim(nit);
+        if constexpr (SELF) {
+            if (!last) load_x();
+        }
         if constexpr (SHORT) compute_short(use, step, stage, req);
         else compute(use, step, stage, req);
         stage ^= 1;
@@ -763,6 +889,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     aim(it);
 #pragma unroll
     for (int t = 0; t < NLOAD + NDMA; ++t) request(t, ra, 0);
+    if constexpr (SELF) load_x();
     while (u < u1) {
         unit(ra, rb);
         if (u >= u1) break;
@@ -771,13 +898,13 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no copy into LDS outlives the workgroup
 }
 
-template <int BITS, int GPS, int MB, int TN, int KW, bool FUSED>
+template <int BITS, int GPS, int MB, int TN, int KW, int HOW>
 int codes_launch(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
     static_assert(qg_codes_lds(GPS, MB, TN, KW) <= QG_LDS_BYTES, "LDS of a workgroup");
     static_assert(qg_codes_slices_apart(GPS, MB, TN, KW) || (KW - 1) * TN * 32 * 256 <= qg_codes_stages(GPS, MB, KW) / 2, "slices in a stage");
     constexpr size_t lds = qg_codes_lds(GPS, MB, TN, KW);
-    const void *f = (const void *)gemm_codes<BITS, GPS, MB, TN, KW, FUSED>;
+    const void *f = (const void *)gemm_codes<BITS, GPS, MB, TN, KW, HOW>;
     if (query) {
         *query = {f, TN * KW * 64, lds};
         return QG_OK;
@@ -794,24 +921,28 @@ int codes_launch(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelI
         }
         if (dev >= 0) prepared[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((gemm_codes<BITS, GPS, MB, TN, KW, FUSED>), dim3((unsigned)workgroups), dim3(TN * KW * 64), lds, st, A);
+    hipLaunchKernelGGL((gemm_codes<BITS, GPS, MB, TN, KW, HOW>), dim3((unsigned)workgroups), dim3(TN * KW * 64), lds, st, A);
     return QG_OK;
 }
 
 template <int BITS, int GPS, int MB, int KW>
-int codes_launch_fused(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
+int codes_launch_how(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
-    return A.fused ? codes_launch<BITS, GPS, MB, 8 / KW, KW, true>(A, workgroups, st, query)
-                   : codes_launch<BITS, GPS, MB, 8 / KW, KW, false>(A, workgroups, st, query);
+    if (A.self) {
+        if constexpr (MB == 1 && GPS <= 4) return codes_launch<BITS, GPS, MB, 8 / KW, KW, QG_CODES_SELF>(A, workgroups, st, query);
+        return QG_ERR_UNSUPPORTED;
+    }
+    return A.fused ? codes_launch<BITS, GPS, MB, 8 / KW, KW, QG_CODES_FUSED>(A, workgroups, st, query)
+                   : codes_launch<BITS, GPS, MB, 8 / KW, KW, QG_CODES_PREPARED>(A, workgroups, st, query);
 }
 
 template <int BITS, int GPS>
 int codes_launch_shape(int mb, const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
     constexpr int FEW = qg_codes_kw(GPS, 1, false), MANY = qg_codes_kw(GPS, 1, true);
-    if (mb == 2) return codes_launch_fused<BITS, GPS, 2, qg_codes_kw(GPS, 2, true)>(A, workgroups, st, query);
-    return A.kw == FEW ? codes_launch_fused<BITS, GPS, 1, FEW>(A, workgroups, st, query)
-                       : codes_launch_fused<BITS, GPS, 1, MANY>(A, workgroups, st, query);
+    if (mb == 2) return codes_launch_how<BITS, GPS, 2, qg_codes_kw(GPS, 2, true)>(A, workgroups, st, query);
+    return A.kw == FEW ? codes_launch_how<BITS, GPS, 1, FEW>(A, workgroups, st, query)
+                       : codes_launch_how<BITS, GPS, 1, MANY>(A, workgroups, st, query);
 }
 
 template <int BITS>

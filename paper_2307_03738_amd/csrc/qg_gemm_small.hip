@@ -40,6 +40,8 @@
 size_t qg_gemm_workspace_bytes(const QgLayout &L, int M);
 int qg_gemm_rows16(const void *packed, int64_t N, int64_t K, int bits, int group, const float *X,
                    int M, float *Y, void *workspace, void *stream, bool dry);   // qg_gemv.hip
+int qg_gemv_rows(const void *packed, int64_t N, int64_t K, int bits, int group, const float *X, int M, float *Y,
+                 void *stream, bool dry);
 int qg_gemv_grouped_check(const qg_gemv_desc *descs, int count, void *workspace, size_t workspace_bytes);
 
 namespace {
@@ -808,8 +810,9 @@ CodesSpace codes_space(const QgLayout &L, int gps, int M)
 // `quota` consecutive units per workgroup whatever blocks they fall into.
 struct CodesPlan {
     int mb, tn, kw, zblocks, blocks, units, ranges, quota, workgroups, parts;
-    bool fused;
-    double us;                 // what it costs (codes_cost_us)
+    bool fused, self;
+    int kernels;               // of a call
+    double us;                 // what it costs (codes_price)
 };
 
 // Cuts into at most `most` parts per block, one workgroup per compute unit at most where that is possible (a
@@ -848,11 +851,13 @@ struct CodesCost {
     double dealt;                      // of a call whose units are dealt evenly
     double last, last_mb, kernel, kernel_mb;       // adding, by the last workgroup and by a kernel, per MB of parts
     double last_workgroup, last_workgroup_mb, part_mb;      // (who adds: the last workgroup against 1.5 + 0.5 per MB)
+    double self_call, self_unit, self_weights, self_dealt, self_round, self_y_mb, self_kernel, self_kernel_mb;     // (codes_self_us; 0: not taken)
     int cus;
     bool by_parts;                     // the last workgroup's time per MB grows with the parts
 };
-CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus)
+CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus, bool self)
 {
+    static constexpr double SELF_US[2][4] = {{1.14, 1.17, 1.33, 1.64}, {1.80, 1.85, 2.07, 2.46}};
     static constexpr double UNIT_US[3][5] = {{1.0, 1.05, 1.2, 1.45, 2.0}, {1.0, 1.02, 1.18, 1.45, 2.0}, {1.36, 1.38, 1.65, 2.15, 3.2}};
     CodesCost C;
     C.part_mb = 4e-6 * M * (double)L.N;
@@ -861,6 +866,21 @@ CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus)
     C.last_workgroup = mb == 1 ? 1.5 : 4.6;
     C.last_workgroup_mb = mb == 1 ? 0.3 : 0.1;
     C.unit = UNIT_US[M <= 32 ? 0 : mb][gps == 0 ? 0 : gps == 1 ? 1 : gps == 2 ? 2 : gps == 4 ? 3 : 4];
+    C.self_call = 0.0;
+    if (self && mb == 1 && gps <= 4) {
+        C.self_unit = SELF_US[M <= 32 ? 0 : 1][gps == 4 ? 3 : gps];
+        if (M <= 32) {
+            C.self_call = 3.7;
+            C.self_unit += M > 16 ? 0.55 : 0.0;
+            C.self_weights = L.bits == 4 ? 0.31 : L.bits == 3 ? 0.28 : 0.0;
+            C.self_dealt = 2.0, C.self_round = 0.0;
+            C.self_y_mb = 0.24, C.self_kernel = 1.7, C.self_kernel_mb = 0.44;
+        } else {
+            C.self_call = 3.6, C.self_weights = 0.0;
+            C.self_dealt = 0.0, C.self_round = 1.9;
+            C.self_y_mb = 0.12, C.self_kernel = 1.3, C.self_kernel_mb = 0.8;
+        }
+    }
     if (M <= 32) {
         C.call = 6.0;
         C.weights = L.bits == 4 ? 0.5 : L.bits == 3 ? 0.35 : 0.1;
@@ -877,7 +897,26 @@ CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus)
     C.kernel = mb == 1 ? 1.4 : 1.7, C.kernel_mb = mb == 1 ? 0.55 : 0.42;
     return C;
 }
-// Sets P.us and, with it, who adds the parts.
+// What a call takes of the caller's time, whatever its kernels take: a launch is 2.1 us of it.  A call is priced at
+// the longer of the two; between calls that wait for the caller the shorter kernels win.
+double call_us(double kernels_us, int launches)
+{
+    const double host = 2.9 + 2.1 * launches;
+    return (kernels_us > host ? kernels_us : host) + 0.01 * kernels_us;
+}
+// Blocks of 32 rows that make their A operands themselves (gemm_codes, SELF): no prepare_x, but every block of
+// outputs converts X again, so a unit takes longer, hardly so up to 16 rows.  Lines through 1600 cuts of 400 random
+// products of 2 ... 32 rows (2.5 % off) and 1100 of 33 ... 128 (2.9 %).
+double codes_self_us(const CodesPlan &P, const CodesCost &C)
+{
+    const int rounds = (P.workgroups + C.cus - 1) / C.cus;
+    const double full = P.workgroups < C.cus ? (double)P.workgroups / C.cus : 1.0;
+    double us = C.self_call + P.quota * rounds * (C.self_unit + C.self_weights * full) + C.self_round * (rounds - 1) + C.self_y_mb * C.part_mb;
+    if (P.ranges == 0) us += C.self_dealt;
+    if (P.parts > 1) us += C.self_kernel + C.self_kernel_mb * P.parts * C.part_mb;
+    return us;
+}
+// Sets P.us and, with it, who makes the A operands and who adds the parts.
 void codes_price(CodesPlan &P, const CodesCost &C)
 {
     P.us = C.call;
@@ -887,18 +926,30 @@ void codes_price(CodesPlan &P, const CodesCost &C)
         P.us += (P.workgroups + C.cus - 1) / C.cus * P.quota * (C.unit + C.weights);
     }
     if (P.ranges == 0) P.us += C.dealt;
-    P.fused = false;
+    P.fused = P.self = false;
     if (P.parts > 1) {
         const double mb = P.parts * C.part_mb;
         if (P.parts <= QG_FUSED_SEGMENTS)
             P.fused = C.last_workgroup + C.last_workgroup_mb * (C.by_parts ? P.parts - 1 : 1) * mb <= 1.5 + 0.5 * mb;
         P.us += P.fused ? C.last + C.last_mb * mb : C.kernel + C.kernel_mb * mb;
     }
+    P.kernels = P.parts > 1 && !P.fused ? 3 : 2;
+    P.us = call_us(P.us, P.kernels);
+    if (C.self_call > 0.0) {
+        const int kernels = P.parts > 1 ? 2 : 1;
+        const double us = call_us(codes_self_us(P, C), kernels);
+        if (us < P.us) {
+            P.us = us;
+            P.kernels = kernels;
+            P.self = true;
+            P.fused = false;
+        }
+    }
 }
 
 // The best of the cuts into at most 1 ... 8 parts by what they cost; a forced count (the search's, too) takes the one cut.
 // A count that would need more workgroups than compute units is dealt evenly over those.
-CodesPlan codes_plan_rows(const QgLayout &L, int gps, int M, int mb, int knob_splits)
+CodesPlan codes_plan_rows(const QgLayout &L, int gps, int M, int mb, int knob_splits, bool by_number)
 {
     CodesPlan P;
     P.mb = mb;
@@ -908,7 +959,7 @@ CodesPlan codes_plan_rows(const QgLayout &L, int gps, int M, int mb, int knob_sp
     P.tn = 8 / P.kw;
     P.blocks = (int)((L.tiles + P.tn - 1) / P.tn) * P.zblocks;
     P.units = (int)(((L.K + KC - 1) / KC + P.kw - 1) / P.kw);
-    const CodesCost cost = codes_cost(L, gps, M, P.mb, cus);
+    const CodesCost cost = codes_cost(L, gps, M, P.mb, cus, !by_number);
     const int room = cus / P.blocks > 1 ? cus / P.blocks : 1;
     // (several blocks of 32 rows: whole ranges alone, dealt ones no longer share a tile's weights: 8192 x 22016 4-bit
     // M = 72 115 us against 74 in blocks of 64)
@@ -937,13 +988,14 @@ CodesPlan codes_plan_rows(const QgLayout &L, int gps, int M, int mb, int knob_sp
 // g32 M = 48 20.1 | 16.3, 4096 x 4096 3-bit g64 M = 64 17.0 | 13.3, 13824 x 5120 3-bit g64 M = 37 21.5 | 20.6; 22016 x 8192
 // 2-bit g32 M = 128 76 | 90.  Over 504 products of 33 ... 128 rows at 2 and 3 bits the choice takes 0.90 of the time of
 // blocks of 64 alone, the best cut of either kind 0.88.
-// A forced count on the kernel asked for by number (shape 13) keeps blocks of 64.
+// A forced count on the kernel asked for by number (shape 13) keeps blocks of 64, and that kernel's operands come
+// from prepare_x.
 CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits, bool by_number)
 {
-    if (M <= 32) return codes_plan_rows(L, gps, M, 1, knob_splits);
-    const CodesPlan two = codes_plan_rows(L, gps, M, 2, knob_splits);
+    if (M <= 32) return codes_plan_rows(L, gps, M, 1, knob_splits, by_number);
+    const CodesPlan two = codes_plan_rows(L, gps, M, 2, knob_splits, by_number);
     if (knob_splits && by_number) return two;
-    const CodesPlan one = codes_plan_rows(L, gps, M, 1, knob_splits);
+    const CodesPlan one = codes_plan_rows(L, gps, M, 1, knob_splits, by_number);
     return one.us < two.us ? one : two;
 }
 }  // namespace
@@ -1034,7 +1086,7 @@ double dequantizing_us(const QgLayout &L, int M, int cus)
     double us = l.call + (rounds - 1) * l.round + l.y_mb * y_mb;
     us += rounds * iterations * (l.iteration + l.iteration_full * full + (L.group <= 32 ? l.g32 : 0.0));
     if (P.splits > 1) us += l.add + l.add_mb * P.splits * y_mb;
-    return us;
+    return call_us(us, P.splits > 1 ? 2 : 1);
 }
 
 // Checks, plans and (price == NULL) enqueues one product; knob_*: as qg_set_gemm_tuning.
@@ -1117,6 +1169,9 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         A.quota = C.quota;
         A.total = C.blocks * C.units;
         A.fused = C.fused;
+        A.self = C.self;
+        A.X = X;
+        A.K = (int)K;
         A.kw = C.kw;
         auto main_kernel = [&](KernelInfo *query) {
             return bits == 4 ? qg_codes_launch_b4(gps, C.mb, A, C.workgroups, st, query)
@@ -1129,17 +1184,19 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         const int have = main_kernel(&info);
         if (have != QG_OK) return have;
         if (price) {
-            *price = {0, NSHAPES + (M > 32 && C.mb == 1), C.ranges, (long)C.workgroups, C.quota, C.ranges != 1 && !C.fused ? 3 : 2, info, C.us};
+            *price = {0, NSHAPES + (M > 32 && C.mb == 1) + 2 * C.self, C.ranges, (long)C.workgroups, C.quota, C.kernels, info, C.us};
             return QG_OK;
         }
-        if (bits == 4) qg_codes_prepare_b4(P, W.rows_padded, st);
-        else if (bits == 2) qg_codes_prepare_b2(P, W.rows_padded, st);
-        else qg_codes_prepare_b3(P, W.rows_padded, st);
-        if (qg_launch_status() != QG_OK) return QG_ERR_DEVICE;
+        if (!C.self) {
+            if (bits == 4) qg_codes_prepare_b4(P, W.rows_padded, st);
+            else if (bits == 2) qg_codes_prepare_b2(P, W.rows_padded, st);
+            else qg_codes_prepare_b3(P, W.rows_padded, st);
+            if (qg_launch_status() != QG_OK) return QG_ERR_DEVICE;
+        }
         const int r = main_kernel(nullptr);
         if (r != QG_OK) return r;
         if (qg_launch_status() != QG_OK) return QG_ERR_DEVICE;
-        if (C.ranges != 1 && !C.fused) {
+        if (C.parts > 1 && !C.fused) {
             const int64_t quads = L.tiles * ((M + 7) / 8) * 2;
             const int waves = quads * 4 <= 4096 ? 4 : 2;                 // per quad: up to about 16 wavefronts per compute unit
             hipLaunchKernelGGL(waves == 4 ? add_parts<1> : add_parts<2>, dim3((unsigned)(quads * waves)), dim3(64), 0, st, A.partial,

@@ -1919,9 +1919,10 @@ Mul multiplier(int bits, int cpg, Kind kind, size_t code_bytes)
 // y = Y [rows][N]) for gemm_rows16; the caller has checked that the kernel applies.
 // dry: plan and check only -- returns the status the launch would have up to the point where
 // the kernel is enqueued, and enqueues nothing.
+// one_chunk: no K is cut over workgroups, so the launch needs no meeting slots.
 int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const size_t *ws_off,
                  char *workspace, hipStream_t st, const int64_t *gate_rows, float *const *gated,
-                 int rows = 0, bool dry = false, LaunchShape *report = nullptr)
+                 int rows = 0, bool dry = false, LaunchShape *report = nullptr, bool one_chunk = false)
 {
     GemvArgs A;
     A.count = count;
@@ -1989,6 +1990,7 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
             target = share < 4096 ? 4096 : share > most ? most : share;
         }
     }
+    if (one_chunk && mma && t_cur.wpb == 0) cap = 8;
     if (target == 0) {
         target = code_bytes / ((size_t)qg_compute_units() * 24);    // about 24 wavefronts per CU
         if (target < 4096) target = 4096;
@@ -2018,7 +2020,7 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
             bool found = false;
             int64_t best_miss = 0;
             // (the many-row kernel has no reduction across workgroups)
-            for (int64_t chunks = 1; chunks <= (rows > 0 ? 1 : QG_MAX_CHUNKS); chunks *= 2) {
+            for (int64_t chunks = 1; chunks <= (rows > 0 || one_chunk ? 1 : QG_MAX_CHUNKS); chunks *= 2) {
                 for (int64_t team = 1; team <= limit; ++team) {
                     const int64_t spw = (q.items + chunks * team - 1) / (chunks * team);
                     if (spw > q.max_spw) continue;
@@ -2327,6 +2329,25 @@ int qg_gemm_rows16(const void *packed, int64_t N, int64_t K, int bits, int group
     const size_t ws_off = 0;
     t_cur = {g_tune_wpb, g_tune_bytes_per_wave, g_tune_kernel};
     return launch_class(&d, &idx, 1, &ws_off, (char *)workspace, (hipStream_t)stream, nullptr, nullptr, M, dry);
+}
+
+// Y = X What^T for M <= 16 rows as M matrix-vector products in one launch (used by qg_gemm_small): fp32 throughout, and no
+// workspace.  QG_ERR_UNSUPPORTED where no such launch exists (a K too long for one workgroup); the arguments
+// have been checked by the caller.  dry: plan only, nothing enqueued.
+int qg_gemv_rows(const void *packed, int64_t N, int64_t K, int bits, int group, const float *X, int M, float *Y,
+                 void *stream, bool dry)
+{
+    if (M < 1 || M > QG_MAX_GROUPED || K % 16 != 0) return QG_ERR_UNSUPPORTED;       // (rows of X stay 64-byte aligned)
+    qg_gemv_desc d[QG_MAX_GROUPED];
+    int idx[QG_MAX_GROUPED];
+    size_t ws_off[QG_MAX_GROUPED];
+    for (int i = 0; i < M; ++i) {
+        d[i] = {packed, N, K, bits, group, X + (size_t)i * K, Y + (size_t)i * N};
+        idx[i] = i;
+        ws_off[i] = 0;
+    }
+    t_cur = {g_tune_wpb, g_tune_bytes_per_wave, g_tune_kernel};
+    return launch_class(d, idx, M, ws_off, nullptr, (hipStream_t)stream, nullptr, nullptr, 0, dry, nullptr, true);
 }
 
 extern "C" int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group,

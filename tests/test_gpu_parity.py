@@ -1001,13 +1001,13 @@ def test_gemm_small_raw_code_units(qg, oracle, N, K, bits, group, M, splits, cut
 # group, M, blocks of rows, parts of a sum, added by the last workgroup; a last block of one row and of all
 # 32, ragged N and K, workgroups that are no multiple of the eight dies, a tile block with one real tile
 ROW_BLOCK_CASES = [
-    (130, 1536, 3, 64, 33, 2, 3, 1),
     (4999, 2240, 2, 64, 64, 2, 3, 1),
     (9000, 768, 3, 64, 90, 3, 1, 0),
     (300, 4160, 4, 32, 65, 3, 5, 0),
     (190, 20480, 2, 128, 40, 2, 8, 0),
     (1000, 2304, 2, 32, 128, 4, 5, 0),
-    (4096, 5632, 4, 5632, 97, 4, 2, 1),
+    (2500, 16640, 2, 64, 100, 4, 3, 1),
+    (13824, 5120, 3, 64, 37, 2, 1, 0),
 ]
 
 
@@ -1017,6 +1017,45 @@ def test_gemm_small_blocks_of_32_rows(qg, oracle, N, K, bits, group, M, blocks, 
     W, X = synth.small_case(4700 + N + M, N, K, 0.02, True, m=M)
     err = _gemm_case(qg, oracle, W, X, bits, group)
     assert err <= TOL_BF16, err
+
+
+# A operands made by the product kernel (tests/test_launch_plans.py looks): N, K, bits, group, M, parts of a sum
+# (0: units dealt evenly).  Every # number of groups per step and width; 2 to 16 rows (one wavefront per step converts), 17 and more (two), several
+# blocks of rows with 1 ... 32 in the last; K of less than a step, ending inside a step and inside a unit; one unit
+# and several per workgroup, units dealt evenly
+SELF_CASES = [
+    (300, 2304, 4, 128, 17, 5), (70, 1280, 4, 1280, 32, 3), (260, 1024, 2, 64, 31, 2), (330, 1536, 3, 128, 30, 3),
+    (5005, 16640, 3, 64, 16, 6), (9000, 2304, 2, 64, 24, 3), (130, 416, 4, 32, 60, 1), (8333, 1216, 3, 64, 65, 1),
+    (700, 1280, 2, 32, 128, 3), (12790, 512, 4, 128, 35, 1), (130, 1536, 3, 64, 33, 3), (4096, 5632, 4, 5632, 97, 2),
+    (9000, 1056, 2, 32, 20, 3), (6000, 4160, 4, 64, 30, 5), (1100, 3072, 3, 768, 40, 6), (65, 1024, 2, 512, 64, 2),
+    (16000, 1024, 3, 64, 30, 1), (70, 64, 3, 64, 40, 1), (11000, 10240, 3, 64, 9, 0)]
+
+
+@pytest.mark.parametrize("N,K,bits,group,M,parts", SELF_CASES)
+def test_gemm_small_own_operands(qg, oracle, N, K, bits, group, M, parts):
+    _announce("gemm raw codes, own operands", N, K, bits, group, M)
+    W, X = synth.small_case(5100 + N + M, N, K, 0.02, True, m=M)
+    err = _gemm_case(qg, oracle, W, X, bits, group)
+    assert err <= TOL_BF16, err
+    # the same sums as with operands made ahead, in another order of the xhats (fp32 sums of at most 128 terms, of 128 + q
+    # each: 2^-24 of 128 sum |x| at most per addition, far below the bf16 rounding both share); a value that is
+    # no number stays in its row
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    blob = qg.qg_pack(dev(q0), dev(s0), dev(z0), bits, group)
+    Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X)))
+    qg.qg_set_gemm_tuning(0, 13)
+    try:
+        ahead = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X)))
+    finally:
+        qg.qg_set_gemm_tuning(0, 0)
+    assert np.linalg.norm(Y - ahead) <= 1e-4 * np.linalg.norm(ahead)
+    for value in (np.nan, np.inf):
+        Xv = X.copy()
+        Xv[M // 2, K - 1] = value
+        Yv = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(Xv)))
+        assert np.isnan(Yv[M // 2]).all()
+        others = np.arange(M) != M // 2
+        assert np.array_equal(Yv[others], Y[others])
 
 
 @pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])

@@ -2,7 +2,7 @@
 import pytest
 
 from tests.launches import launches
-from tests.test_gpu_parity import ROW_BLOCK_CASES, UNIT_CASES
+from tests.test_gpu_parity import ROW_BLOCK_CASES, SELF_CASES, UNIT_CASES
 
 
 @pytest.fixture(scope="module")
@@ -79,7 +79,7 @@ def test_who_adds_two_or_three_parts(tmp, problem, splits, last_workgroup):
     assert (k["args"]["fused"] == 1, "add_parts" not in names) == (last_workgroup, last_workgroup)
 
 
-# The GPU test of the blocks of 32 rows takes the cuts it names
+# The GPU tests of the blocks of 32 rows take the cuts they name
 @pytest.mark.parametrize("case", ROW_BLOCK_CASES)
 def test_row_block_cases_are_cut_as_stated(tmp, case):
     *problem, blocks, parts, fused = case
@@ -90,11 +90,19 @@ def test_row_block_cases_are_cut_as_stated(tmp, case):
     assert ("add_parts" in names) == (parts > 1 and not fused)
 
 
+@pytest.mark.parametrize("case", SELF_CASES)
+def test_own_operand_cases_are_cut_as_stated(tmp, case):
+    *problem, parts = case
+    k, names = _product(launches(tmp, [{"problem": problem}])[0])
+    assert (k["template"][2], k["template"][5]) == (1, 2) and k["args"]["ranges"] == parts
+    assert names == ["gemm_codes"] + ["add_parts"] * (parts != 1)
+
+
 # 4 bits below the sizes where raw codes are taken whatever the estimates say: the dequantizing kernels cut K between
-# groups only, so that long groups go to raw codes, the shortest products stay where one launch does
+# groups only, so that long groups go to raw codes, and so do products that take one launch there
 @pytest.mark.parametrize("problem,raw", [
     ((1500, 20480, 4, 20480, 33), True), ((4096, 4096, 4, 4096, 24), True), ((1024, 8192, 4, 128, 96), True),
-    ((512, 768, 4, 768, 20), False), ((512, 512, 4, 64, 64), False), ((2048, 2048, 4, 128, 100), False)])
+    ((512, 768, 4, 768, 20), False), ((512, 512, 4, 64, 64), True), ((2048, 2048, 4, 128, 100), True)])
 def test_kernel_family_of_small_4_bit_products(tmp, problem, raw):
     names = [k["name"] for k in launches(tmp, [{"problem": problem}])[0]["kernels"]]
     assert ("gemm_codes" in names) == raw, names
