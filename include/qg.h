@@ -180,9 +180,10 @@ int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group
  *     group, or 128 k of it, are fp32: |x| up to 10^34; NaN and infinity in X come out as NaN.)
  * Where both apply (4 bits) the second is used for 17 ... 32 and more than 64 rows on matrices of 4096
  * tile-steps or more (64 outputs x 128 k each) and for 33 ... 64 rows from 8192 on (groups of 32: from
- * 8448); below that, and at up to 16 rows on fewer than 128 tiles of 64 outputs or with groups of more than
- * 128, whichever the planner's estimates say is the faster (groups of one per output nearly always the
- * second); else the first.  qg_set_gemm_tuning and qg_gemm_autotune choose otherwise.
+ * 8448); below that whichever the planner's estimates say is the faster (groups of one per output nearly always
+ * the second).  At 2 ... 16 rows its estimates choose between the second way, at 4 bits a kernel on codes without a
+ * split of K over workgroups, and, for small products, qg_gemv's arithmetic (fp32, X not rounded) once per row in one
+ * launch that needs nothing of the workspace.  qg_set_gemm_tuning and qg_gemm_autotune choose otherwise.
  * Every other layout (odd numbers of cells per group, K % 16 != 0 only with M == 1) runs
  * qg_gemv once per row in fp32, 16 rows per launch; with K % 16 != 0 and M > 1 the call returns
  * QG_ERR_UNSUPPORTED.  M == 1 is qg_gemv.

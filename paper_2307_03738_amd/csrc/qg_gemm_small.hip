@@ -30,6 +30,7 @@
 // The other widths, 4-bit groups of 16 and the larger 4-bit products take the kernel on raw codes
 // (qg_gemm_codes.h); what neither takes runs the fp32 GEMV kernel once per activation row, up to 16
 // rows per launch.
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -897,12 +898,13 @@ CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus, bool se
     C.kernel = mb == 1 ? 1.4 : 1.7, C.kernel_mb = mb == 1 ? 0.55 : 0.42;
     return C;
 }
-// What a call takes of the caller's time, whatever its kernels take: a launch is 2.1 us of it.  A call is priced at
-// the longer of the two; between calls that wait for the caller the shorter kernels win.
-double call_us(double kernels_us, int launches)
+// What a call takes of the caller's time, whatever its kernels take: a launch is 2.1 us of it, a problem of a launch 0.03.
+// A call is priced at the longer of the two, and a fifth of its kernels' time: of calls that all wait for the caller the
+// one with the shorter kernels is there first.
+double call_us(double kernels_us, int launches, int problems = 0)
 {
-    const double host = 2.9 + 2.1 * launches;
-    return (kernels_us > host ? kernels_us : host) + 0.01 * kernels_us;
+    const double host = 2.9 + 2.1 * launches + 0.03 * problems;
+    return (kernels_us > host ? kernels_us : host) + 0.2 * kernels_us;
 }
 // Blocks of 32 rows that make their A operands themselves (gemm_codes, SELF): no prepare_x, but every block of
 // outputs converts X again, so a unit takes longer, hardly so up to 16 rows.  Lines through 1600 cuts of 400 random
@@ -1089,6 +1091,27 @@ double dequantizing_us(const QgLayout &L, int M, int cus)
     return call_us(us, P.splits > 1 ? 2 : 1);
 }
 
+// What the product costs as M matrix-vector products in one launch (qg_gemv_rows): teams of eight wavefronts go through
+// K, or the chip through all of the work.  Through 600 products of 2 ... 16 rows (9 % off below 11 us).
+double gemv_rows_us(const QgLayout &L, int M)
+{
+    const double spw = (double)((L.steps + 7) / 8), step = (double)L.unit * L.step_units;
+    const double per_step = L.group < step ? step / L.group : 1.0;
+    const double work = 64e-9 * L.tiles * M * L.steps * step;
+    const double one = ((L.bits == 4 ? 0.61 : 1.03) + 0.07 * per_step) * spw;
+    const double all = ((L.bits == 4 ? 70.0 : L.bits == 3 ? 53.5 : 45.4) + 2.3 * per_step) * work;
+    return 2.3 + sqrt(one * one + all * all);
+}
+// ... and on gemm_rows16: a workgroup per tile (teams of eight wavefronts, of four beyond one tile per compute unit).
+// Through 171 products of 2 ... 16 rows and 48 and more tiles (6 % off).
+double rows16_us(const QgLayout &L, int M, int cus)
+{
+    const int team = L.tiles > cus ? 4 : 8;
+    const double rounds = (double)((L.tiles * team / 8 + cus - 1) / cus), spw = (double)((L.steps + team - 1) / team);
+    const double full = L.tiles < cus ? (double)L.tiles / cus : 1.0;
+    return 3.0 + rounds * spw * (0.96 + 0.023 * M + 0.168 * (128 / L.group) + 0.3 * full);
+}
+
 // Checks, plans and (price == NULL) enqueues one product; knob_*: as qg_set_gemm_tuning.
 int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, const float *X, int M,
                float *Y, void *workspace, size_t workspace_bytes, void *stream, int knob_splits,
@@ -1116,21 +1139,39 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     //   5120 x 13824   (8640)  17.4 | 24.7  19.8 | 25.9      21.6 | 26.3  27.4 | 27.6
     // so at 33 ... 64 rows the line lies higher, and above 8192 for groups of 32, whose fold is as much work as their matrix
     // instructions.
-    // The other 4-bit matrices of up to 16 rows go to gemm_rows16 where it has tiles enough; whatever else the
-    // dequantizing kernels take goes to the raw-code kernel where its price is the lower one by more than the two are off.  That
-    // is most of all where groups are long: the dequantizing kernels cut K between groups only (1500 x 20480, one group per
-    // output, M = 33 196 -> 19 us; 8192 x 8192 M = 8 37 -> 15), and 33 and more rows of few tiles (1024 x 8192 g128
-    // M = 96 17.6 -> 14.9, 4096 x 4096 M = 128 18.9 -> 15.6).
+    // Whatever else of more than 16 rows the dequantizing kernels take goes to the raw-code kernel where its price is the lower
+    // one by more than the two are off.  That is most of all where groups are long: the dequantizing kernels cut K between
+    // groups only (1500 x 20480, one group per output, M = 33 196 -> 19 us; 8192 x 8192 M = 8 37 -> 15), and 33 and more rows
+    // of few tiles (1024 x 8192 g128 M = 96 17.6 -> 14.9, 4096 x 4096 M = 128 18.9 -> 15.6).
+    // Up to 16 rows the cheapest of three is taken: the raw-code kernel; at 4 bits gemm_rows16; and, up to about 60 M
+    // weights times rows, one fp32 matrix-vector product per row, in one launch that takes no more of the caller's time than
+    // one product does.  (500 products of 2 ... 16 rows: 0.80 of the kernels' time of the raw-code kernel and gemm_rows16 from
+    // 128 tiles on; 2045 x 576 4-bit M = 3 7.0 | 3.4 us, 1062 x 640 2-bit M = 5 6.1 | 3.3.  The dequantizing kernels were
+    // the fastest of none.)
     const int gps = codes_gps(L);
     const int from = M > 32 && M <= 64 ? (gps >= 4 ? 8448 : 8192) : 4096;
     const bool large = M > 16 && L.tiles * L.steps >= from;
-    const bool either = fast_path(L) && !large, rows16 = either && M <= 16 && L.tiles >= 128 && L.group <= KC;
-    bool raw = gps >= 0 && M > 1 && (knob_shape == NSHAPES + 1 || (knob_shape == 0 && !rows16));
+    bool raw = gps >= 0 && M > 1 && (knob_shape == NSHAPES + 1 || knob_shape == 0);
+    bool rows16 = M == 1 && knob_shape == 0 && L.tiles >= 128;
     CodesPlan C;
-    if (raw) {
-        C = codes_plan(L, gps, M, knob_splits, knob_shape != 0);
-        if (knob_shape == 0 && either)                    // (by the built-in counts of K ranges, also where one is forced)
-            raw = (knob_splits ? codes_plan(L, gps, M, 0, false) : C).us * 1.08 < dequantizing_us(L, M, qg_compute_units());
+    if (raw) C = codes_plan(L, gps, M, knob_splits, knob_shape != 0);
+    if (raw && knob_shape == 0) {
+        // (by the built-in counts of K ranges, also where one is forced)
+        const double us = (knob_splits ? codes_plan(L, gps, M, 0, false) : C).us;
+        const int cus = qg_compute_units();
+        if (M > 16) {
+            raw = !fast_path(L) || large || us * 1.08 < dequantizing_us(L, M, cus);
+        } else {
+            const double us16 = fast_path(L) && L.group <= KC && L.tiles >= 48 ? call_us(rows16_us(L, M, cus), 1) : us;
+            const double us1 = call_us(1.05 * gemv_rows_us(L, M), 1, M);
+            rows16 = us16 < us && us16 <= us1;
+            if (us1 < us && us1 < us16) {
+                const int r = qg_gemv_rows(packed, N, K, bits, group, X, M, Y, stream, price != nullptr);
+                if (r == QG_OK && price) *price = {2, -1, 1, 0, 0, 1, {nullptr, 0, 0}, 0.0};
+                if (r != QG_ERR_UNSUPPORTED) return r;
+            }
+            raw = !rows16;
+        }
     }
     if (raw) {
         const CodesSpace W = codes_space(L, gps, M);
@@ -1207,8 +1248,8 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
 
     // Up to 16 rows: the barrier-free kernel on the GEMV's launch structure, where it applies.
     // It has one workgroup per tile and no split of K over workgroups, so it needs enough tiles
-    // to cover the chip (measured: ahead from about 128 tiles; shape -1 forces it).
-    if (M <= 16 && (knob_shape == 0 ? L.tiles >= 128 : knob_shape < 0)) {
+    // to cover the chip (shape -1 forces it).
+    if (M <= 16 && (rows16 || knob_shape < 0)) {
         const int r = qg_gemm_rows16(packed, N, K, bits, group, X, M, Y, workspace, stream, price != nullptr);
         if (r == QG_OK && price) *price = {1, -1, 1, (long)L.tiles, 0, 1, {nullptr, 0, 0}, 0.0};
         if (r != QG_ERR_UNSUPPORTED) return r;

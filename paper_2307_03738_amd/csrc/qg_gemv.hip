@@ -1919,7 +1919,7 @@ Mul multiplier(int bits, int cpg, Kind kind, size_t code_bytes)
 // y = Y [rows][N]) for gemm_rows16; the caller has checked that the kernel applies.
 // dry: plan and check only -- returns the status the launch would have up to the point where
 // the kernel is enqueued, and enqueues nothing.
-// one_chunk: no K is cut over workgroups, so the launch needs no meeting slots.
+// one_chunk: the problems are of one shape and no K is cut over workgroups, so the launch needs no meeting slots.
 int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const size_t *ws_off,
                  char *workspace, hipStream_t st, const int64_t *gate_rows, float *const *gated,
                  int rows = 0, bool dry = false, LaunchShape *report = nullptr, bool one_chunk = false)
@@ -1931,6 +1931,11 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
     Plan pl[QG_MAX_GROUPED];
     for (int i = 0; i < count; ++i) {
         const qg_gemv_desc &d = descs[idx[i]];
+        if (one_chunk && i > 0) {
+            L[i] = L[0];
+            pl[i] = pl[0];
+            continue;
+        }
         qg_make_layout(d.N, d.K, d.bits, d.group, &L[i]);
         pl[i] = make_plan(L[i]);
     }
@@ -2010,6 +2015,12 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
     auto plan_all = [&](int limit) -> bool {
         wpb = 1;
         for (int i = 0; i < count; ++i) {
+            if (one_chunk && i > 0) {
+                spw_of[i] = spw_of[0];
+                team_of[i] = team_of[0];
+                chunks_of[i] = 1;
+                continue;
+            }
             const Plan &q = pl[i];
             int64_t want = (int64_t)((target + q.item_bytes / 2) / q.item_bytes);   // items per wavefront
             if (want < 1) want = 1;

@@ -1058,6 +1058,27 @@ def test_gemm_small_own_operands(qg, oracle, N, K, bits, group, M, parts):
         assert np.array_equal(Yv[others], Y[others])
 
 
+# Products of few rows that run as one fp32 matrix-vector product per row (tests/test_launch_plans.py looks): N, K, bits,
+# group, M; K of whole steps, ending inside one and shorter than one, groups of several steps, 16 rows, one cell per group
+ROWS_CASES = [(512, 512, 4, 64, 2), (2045, 576, 4, 64, 3), (1062, 640, 2, 128, 5), (7803, 2432, 2, 32, 2), (65, 64, 4, 32, 16),
+              (300, 2240, 3, 64, 4), (700, 3072, 2, 3072, 6), (200, 1024, 4, 16, 9), (130, 1536, 3, 128, 16), (5000, 256, 2, 64, 7)]
+
+
+@pytest.mark.parametrize("N,K,bits,group,M", ROWS_CASES)
+def test_gemm_small_as_matrix_vector_products(qg, oracle, N, K, bits, group, M):
+    # ... whatever the workspace holds: nothing of it is used
+    _announce("gemm, a matrix-vector product per row", N, K, bits, group, M)
+    W, X = synth.small_case(5200 + N + M, N, K, 0.02, True, m=M)
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    blob = qg.qg_pack(dev(q0), dev(s0), dev(z0), bits, group)
+    Y_ref, norms = oracle.matmul_small(q0, s0, z0, group, X), oracle.row_norms(q0, s0, z0, group)
+    for fill in (0, 0x3c, 0xff):
+        ws = torch.full((qg.qg_workspace_bytes(N, K, bits, group, M),), fill, dtype=torch.uint8, device="cuda")
+        Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X), None, ws))
+        assert scaled_error(Y, Y_ref, norms, X) <= TOL_FP32
+        assert (host(ws) == fill).all()
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
 @pytest.mark.parametrize("bits,group,M", [(4, 128, 20), (4, 16, 40), (3, 64, 40), (2, 32, 9), (2, 512, 100)])
 def test_gemm_small_raw_codes_non_finite_activations(qg, bits, group, M, value):

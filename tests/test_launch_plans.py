@@ -2,7 +2,7 @@
 import pytest
 
 from tests.launches import launches
-from tests.test_gpu_parity import ROW_BLOCK_CASES, SELF_CASES, UNIT_CASES
+from tests.test_gpu_parity import ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
 
 
 @pytest.fixture(scope="module")
@@ -96,6 +96,13 @@ def test_own_operand_cases_are_cut_as_stated(tmp, case):
     k, names = _product(launches(tmp, [{"problem": problem}])[0])
     assert (k["template"][2], k["template"][5]) == (1, 2) and k["args"]["ranges"] == parts
     assert names == ["gemm_codes"] + ["add_parts"] * (parts != 1)
+
+
+@pytest.mark.parametrize("problem,name", [(c, "gemv_mma4i") for c in ROWS_CASES] + [
+    ((11008, 4096, 4, 128, 16), "gemm_rows16"), ((11967, 2048, 4, 128, 4), "gemm_rows16"), ((6000, 1664, 4, 64, 12), "gemm_rows16"),
+    ((16888, 864, 4, 32, 5), "gemm_codes"), ((11295, 1280, 3, 1280, 14), "gemm_codes")])
+def test_one_launch_up_to_16_rows(tmp, problem, name):
+    assert [k["name"] for k in launches(tmp, [{"problem": problem}])[0]["kernels"]] == [name]
 
 
 # 4 bits below the sizes where raw codes are taken whatever the estimates say: the dequantizing kernels cut K between
