@@ -918,6 +918,7 @@ double codes_self_us(const CodesPlan &P, const CodesCost &C)
     if (P.parts > 1) us += C.self_kernel + C.self_kernel_mb * P.parts * C.part_mb;
     return us;
 }
+constexpr double CODES_LEAST_US = 4.8;       // what no plan's kernels are priced below
 // Sets P.us and, with it, who makes the A operands and who adds the parts.
 void codes_price(CodesPlan &P, const CodesCost &C)
 {
@@ -1153,17 +1154,22 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     const bool large = M > 16 && L.tiles * L.steps >= from;
     bool raw = gps >= 0 && M > 1 && (knob_shape == NSHAPES + 1 || knob_shape == 0);
     bool rows16 = M == 1 && knob_shape == 0 && L.tiles >= 128;
+    const int cus = qg_compute_units();
+    double us16 = 1e30, us1 = 1e30;                       // of the other two families up to 16 rows
+    if (raw && knob_shape == 0 && M <= 16) {
+        if (fast_path(L) && L.group <= KC && L.tiles >= 48) us16 = call_us(rows16_us(L, M, cus), 1);
+        us1 = call_us(1.05 * gemv_rows_us(L, M), 1, M);
+    }
     CodesPlan C;
-    if (raw) C = codes_plan(L, gps, M, knob_splits, knob_shape != 0);
+    C.us = call_us(CODES_LEAST_US, 1);
+    bool planned = raw && us1 >= C.us;                    // (else rows of products are the cheaper whatever the plan)
+    if (planned) C = codes_plan(L, gps, M, knob_splits, knob_shape != 0);
     if (raw && knob_shape == 0) {
         // (by the built-in counts of K ranges, also where one is forced)
-        const double us = (knob_splits ? codes_plan(L, gps, M, 0, false) : C).us;
-        const int cus = qg_compute_units();
+        const double us = knob_splits && planned ? codes_plan(L, gps, M, 0, false).us : C.us;
         if (M > 16) {
             raw = !fast_path(L) || large || us * 1.08 < dequantizing_us(L, M, cus);
         } else {
-            const double us16 = fast_path(L) && L.group <= KC && L.tiles >= 48 ? call_us(rows16_us(L, M, cus), 1) : us;
-            const double us1 = call_us(1.05 * gemv_rows_us(L, M), 1, M);
             rows16 = us16 < us && us16 <= us1;
             if (us1 < us && us1 < us16) {
                 const int r = qg_gemv_rows(packed, N, K, bits, group, X, M, Y, stream, price != nullptr);
@@ -1172,6 +1178,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
             }
             raw = !rows16;
         }
+        if (raw && !planned) C = codes_plan(L, gps, M, knob_splits, false);
     }
     if (raw) {
         const CodesSpace W = codes_space(L, gps, M);

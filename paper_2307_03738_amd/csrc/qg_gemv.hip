@@ -1697,7 +1697,12 @@ enum Kind { KIND_STATIC, KIND_RUNTIME, KIND_RAGGED, KIND_GENERIC };
 
 // What the last launch of this thread's process ran (for bench reports): kernel family and
 // template arguments.
-char g_last_kernel[64] = "";
+struct LastKernel {
+    const char *family;
+    int bits, cpg;             // cpg: cells per group, -1: not an argument of the kernel
+    const char *ragged;
+};
+LastKernel g_last_kernel = {nullptr, 0, -1, ""};
 
 // The K-split of one problem: work items along K are steps for the two fast kernels and
 // groups for the generic one; a wavefront takes `spw` consecutive items.
@@ -2029,14 +2034,16 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
             // <= cap wavefronts, take the one whose items per wavefront come closest to `want`;
             // on a tie the fewest workgroups, then the smallest team.
             bool found = false;
-            int64_t best_miss = 0;
+            int32_t best_miss = 0;
+            const int32_t items = (int32_t)q.items;                          // (at most 2^24 groups)
             // (the many-row kernel has no reduction across workgroups)
-            for (int64_t chunks = 1; chunks <= (rows > 0 || one_chunk ? 1 : QG_MAX_CHUNKS); chunks *= 2) {
-                for (int64_t team = 1; team <= limit; ++team) {
-                    const int64_t spw = (q.items + chunks * team - 1) / (chunks * team);
+            for (int32_t chunks = 1; chunks <= (rows > 0 || one_chunk ? 1 : QG_MAX_CHUNKS); chunks *= 2) {
+                for (int32_t team = 1; team <= limit; ++team) {
+                    if ((chunks - 1) * team >= items) break;                 // (a step per wavefront leaves an empty workgroup, and so does every wider team)
+                    const int32_t spw = (items + chunks * team - 1) / (chunks * team);
                     if (spw > q.max_spw) continue;
-                    if ((chunks - 1) * team * spw >= q.items) continue;       // an empty workgroup
-                    const int64_t miss = spw > want ? spw - want : want - spw;
+                    if ((chunks - 1) * team * spw >= items) continue;         // an empty workgroup
+                    const int32_t miss = spw > want ? (int32_t)(spw - want) : (int32_t)(want - spw);
                     if (!found || miss < best_miss) {
                         spw_of[i] = spw;
                         team_of[i] = team;
@@ -2177,15 +2184,21 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
         report->bytes_in_flight = in_flight;
     }
     if (dry) return QG_OK;
-    if (shown_cpg >= 0) snprintf(g_last_kernel, sizeof g_last_kernel, "%s<%d, %d%s>", family, bits, shown_cpg, ragged);
-    else snprintf(g_last_kernel, sizeof g_last_kernel, "%s<%d>", family, bits);
+    g_last_kernel = {family, bits, shown_cpg, ragged};
     launch_kernel(fn, (unsigned)blocks, threads, lds, st, A);
     return qg_launch_status();
 }
 
 }  // namespace
 
-extern "C" const char *qg_last_gemv_kernel(void) { return g_last_kernel; }
+extern "C" const char *qg_last_gemv_kernel(void)
+{
+    static char name[64] = "";
+    const LastKernel k = g_last_kernel;
+    if (k.family && k.cpg >= 0) snprintf(name, sizeof name, "%s<%d, %d%s>", k.family, k.bits, k.cpg, k.ragged);
+    else if (k.family) snprintf(name, sizeof name, "%s<%d>", k.family, k.bits);
+    return name;
+}
 
 extern "C" int qg_set_gemv_tuning(int waves_per_block, int bytes_per_wave, int kernel)
 {
@@ -2252,9 +2265,9 @@ static int gemv_grouped(const qg_gemv_desc *descs, int count, void *workspace, s
     if (count > QG_MAX_GROUPED) return QG_ERR_UNSUPPORTED;
     size_t ws_off[QG_MAX_GROUPED];
     size_t need = 0;
+    QgLayout L[QG_MAX_GROUPED];
     for (int i = 0; i < count; ++i) {
-        QgLayout L;
-        const int rc = qg_make_layout(descs[i].N, descs[i].K, descs[i].bits, descs[i].group, &L);
+        const int rc = qg_make_layout(descs[i].N, descs[i].K, descs[i].bits, descs[i].group, &L[i]);
         if (rc != QG_OK) return rc;
         const bool pair = gate_rows && gate_rows[i] > 0;
         if (!descs[i].packed || !descs[i].x || !(pair ? (const void *)gated[i] : (const void *)descs[i].y))
@@ -2262,28 +2275,28 @@ static int gemv_grouped(const qg_gemv_desc *descs, int count, void *workspace, s
         // x is read with 64-byte scalar loads
         if (!qg_aligned16(descs[i].packed) || ((uintptr_t)descs[i].x & 63u)) return QG_ERR_ALIGN;
         ws_off[i] = need;
-        need += workspace_for(L);
+        need += workspace_for(L[i]);
     }
     if (!workspace || workspace_bytes < need) return QG_ERR_WORKSPACE;
     if (!qg_aligned16(workspace)) return QG_ERR_ALIGN;
     t_cur = tuning_for(descs, count);
+    Kind kind[QG_MAX_GROUPED];
+    for (int i = 0; i < count; ++i) kind[i] = make_plan(L[i]).kind;
 
     // one launch per distinct (bits, kernel kind), and per group size where the kernel has it
     // as a compile-time constant.  Two passes: the first plans every class and launches
-    // nothing, so that an error leaves nothing enqueued; the second launches.
-    for (int pass = 0; pass < (check_only ? 1 : 2); ++pass) {
+    // nothing, so that an error leaves nothing enqueued; the second launches.  A single problem is
+    // one launch, which fails before it is enqueued or not at all, and is planned once.
+    const bool one_pass = check_only || (count == 1 && !report);
+    for (int pass = 0; pass < (one_pass ? 1 : 2); ++pass) {
         bool done[QG_MAX_GROUPED] = {false};
         for (int i = 0; i < count; ++i) {
             if (done[i]) continue;
-            QgLayout Li;
-            qg_make_layout(descs[i].N, descs[i].K, descs[i].bits, descs[i].group, &Li);
             int idx[QG_MAX_GROUPED], n = 0;
             for (int j = i; j < count; ++j) {
                 if (done[j]) continue;
-                QgLayout Lj;
-                qg_make_layout(descs[j].N, descs[j].K, descs[j].bits, descs[j].group, &Lj);
-                const Kind ki = make_plan(Li).kind;
-                if (Lj.bits == Li.bits && make_plan(Lj).kind == ki && ((ki != KIND_STATIC && ki != KIND_RAGGED) || Lj.group == Li.group)) {
+                if (descs[j].bits == descs[i].bits && kind[j] == kind[i] &&
+                    ((kind[i] != KIND_STATIC && kind[i] != KIND_RAGGED) || descs[j].group == descs[i].group)) {
                     idx[n++] = j;
                     done[j] = true;
                 }
@@ -2295,7 +2308,7 @@ static int gemv_grouped(const qg_gemv_desc *descs, int count, void *workspace, s
                 }
             LaunchShape shape;
             const int rc = launch_class(descs, idx, n, ws_off, (char *)workspace, (hipStream_t)stream,
-                                        gate_rows, gated, 0, pass == 0, report ? &shape : nullptr);
+                                        gate_rows, gated, 0, pass == 0 && (check_only || !one_pass), report ? &shape : nullptr);
             if (rc != QG_OK) return rc;
             if (report && pass == 0 && (i == 0 || shape.waves > report->waves)) *report = shape;
         }
