@@ -28,8 +28,8 @@
 // fp32 partial results are added by a second small kernel in a fixed order.
 //
 // The other widths, 4-bit groups of 16 and the larger 4-bit products take the kernel on raw codes
-// (qg_gemm_codes.h); what neither takes runs the fp32 GEMV kernel once per activation row, up to 16
-// rows per launch.
+// (qg_gemm_codes.h), 3-bit groups of 32 the one on int8 digits (qg_gemm_rows_i8.hip); what none of them takes, and
+// few rows of small matrices, runs the fp32 GEMV kernel once per activation row, up to 16 rows per launch.
 #include <cmath>
 #include <mutex>
 #include <type_traits>
@@ -41,6 +41,11 @@
 size_t qg_gemm_workspace_bytes(const QgLayout &L, int M);
 int qg_gemm_rows16(const void *packed, int64_t N, int64_t K, int bits, int group, const float *X,
                    int M, float *Y, void *workspace, void *stream, bool dry);   // qg_gemv.hip
+bool qg_rows_i8_takes(const QgLayout &L);                 // qg_gemm_rows_i8.hip
+size_t qg_rows_i8_bytes(const QgLayout &L, int M);
+int qg_rows_i8_splits(const QgLayout &L, int M);
+double qg_rows_i8_us(const QgLayout &L, int M);
+int qg_rows_i8(const void *packed, const QgLayout &L, const float *X, int M, float *Y, void *workspace, hipStream_t st, float **partial);
 int qg_gemv_rows(const void *packed, int64_t N, int64_t K, int bits, int group, const float *X, int M, float *Y,
                  void *stream, bool dry);
 int qg_gemv_grouped_check(const qg_gemv_desc *descs, int count, void *workspace, size_t workspace_bytes);
@@ -778,8 +783,8 @@ void launch_shape(int i, const GemmArgs &A, dim3 grid, hipStream_t st, KernelInf
 
 
 // ---- gemm_codes: which layouts it takes, and its launch ----
-// (X is rounded to bf16 on this path.  Layouts outside it keep the fp32 product of the row-by-row form, also
-// where the kernel could take them: 3-bit groups of 32, 2- and 3-bit groups of an odd number of 128 k.)
+// (X is rounded to bf16 on this path.  Layouts outside it keep an fp32 product, also where the kernel could take
+// them: 3-bit groups of 32, 2- and 3-bit groups of an odd number of 128 k.)
 int codes_gps(const QgLayout &L)       // groups per step of 128 k, 0: groups of several steps, -1: not taken
 {
     if (L.K % 16 != 0 || L.K > (1 << 22)) return -1;
@@ -1003,7 +1008,8 @@ CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits, bool by
 }
 }  // namespace
 
-size_t qg_gemm_workspace_bytes(const QgLayout &L, int M)
+// What a call takes at least.
+static size_t gemm_workspace_least(const QgLayout &L, int M)
 {
     // partial results of the K split, or the GEMV workspaces of the rows of one grouped launch
     const size_t partial = (size_t)MAX_SPLITS * M * L.N * sizeof(float);
@@ -1014,6 +1020,12 @@ size_t qg_gemm_workspace_bytes(const QgLayout &L, int M)
     const int gps = codes_gps(L);
     if (M > 1 && gps >= 0 && codes_space(L, gps, M).total > need) need = codes_space(L, gps, M).total;
     return qg_round_up(need, QG_SECTION_ALIGN);
+}
+// (3-bit groups of 32: the int8 product's operands and parts lie behind the meeting slots of the products per row, which
+// stay as qg_workspace_init has left them)
+size_t qg_gemm_workspace_bytes(const QgLayout &L, int M)
+{
+    return gemm_workspace_least(L, M) + (M > 1 && qg_rows_i8_takes(L) ? qg_rows_i8_bytes(L, M) : 0);
 }
 
 extern "C" int qg_set_gemm_tuning(int splits, int shape)
@@ -1124,7 +1136,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     if (M <= 0 || M > 128) return QG_ERR_SHAPE;
     if (!packed || !X || !Y) return QG_ERR_NULL;
     if (!qg_aligned16(packed) || ((uintptr_t)X & 63u) || !qg_aligned16(Y)) return QG_ERR_ALIGN;
-    if (!workspace || workspace_bytes < qg_gemm_workspace_bytes(L, M)) return QG_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < gemm_workspace_least(L, M)) return QG_ERR_WORKSPACE;
     if (!qg_aligned16(workspace)) return QG_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
 
@@ -1262,13 +1274,41 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         if (r != QG_ERR_UNSUPPORTED) return r;
     }
 
+    // 3-bit groups of 32 weights: fp32 all the way, as qg_gemv computes it (X to 2^-30 of the largest of 128 values), the
+    // cheapest of three: the product on int8 matrix instructions, two or three launches; up to 16 rows a matrix-vector
+    // product per row in one launch, with K cut over workgroups (below; 3.3 us and 55 per 10^9 weights times rows) or not.
+    // (A workspace of the size asked for before the int8 kernel keeps the products per row.)
+    if (M > 1 && qg_rows_i8_takes(L) && workspace_bytes >= qg_gemm_workspace_bytes(L, M)) {
+        const int splits = qg_rows_i8_splits(L, M);
+        const double us8 = call_us(qg_rows_i8_us(L, M), splits > 1 ? 3 : 2);
+        const double us1 = M <= 16 ? call_us(1.05 * gemv_rows_us(L, M), 1, M) : 1e30;
+        const double cut = M <= 16 ? call_us(3.3 + 55e-9 * 64 * L.tiles * M * L.K, 1, 3 * M) : 1e30;
+        if (us1 < us8 && us1 <= cut) {
+            const int r = qg_gemv_rows(packed, N, K, bits, group, X, M, Y, stream, price != nullptr);
+            if (r == QG_OK && price) *price = {2, -1, 1, 0, 0, 1, {nullptr, 0, 0}, 0.0};
+            if (r != QG_ERR_UNSUPPORTED) return r;
+        }
+        if (us8 <= cut) {
+            if (price) {
+                *price = {2, -1, splits, 0, 0, splits > 1 ? 3 : 2, {nullptr, 0, 0}, 0.0};
+                return QG_OK;
+            }
+            float *partial = nullptr;
+            const int r = qg_rows_i8(packed, L, X, M, Y, (char *)workspace + gemm_workspace_least(L, M), st, &partial);
+            if (r != QG_OK || splits == 1) return r;
+            const size_t count = (size_t)M * N;
+            hipLaunchKernelGGL(add_splits, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, (const float *)partial, splits, count, Y);
+            return qg_launch_status();
+        }
+    }
+
     if (!fast_path(L)) {
         // the fp32 GEMV once per activation row, up to 16 rows per launch (rows of X stay
         // 64-byte aligned only if K % 16 == 0)
         if (K % 16 != 0 && M > 1) return QG_ERR_UNSUPPORTED;
         // two passes over the launches of 16 rows: the first only checks and plans, so that an
-        // error leaves nothing enqueued
-        for (int pass = 0; pass < (price ? 1 : 2); ++pass)
+        // error leaves nothing enqueued (a single launch sees to that itself)
+        for (int pass = price || M > QG_MAX_GROUPED ? 0 : 1; pass < (price ? 1 : 2); ++pass)
             for (int m0 = 0; m0 < M; m0 += QG_MAX_GROUPED) {
                 qg_gemv_desc d[QG_MAX_GROUPED];
                 const int rows = M - m0 < QG_MAX_GROUPED ? M - m0 : QG_MAX_GROUPED;

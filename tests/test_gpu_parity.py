@@ -1079,6 +1079,63 @@ def test_gemm_small_as_matrix_vector_products(qg, oracle, N, K, bits, group, M):
         assert (host(ws) == fill).all()
 
 
+# 3-bit groups of 32 on the int8 matrix instructions: N, K, M; one, two and four blocks of eight rows, several of those,
+# rows 1 ... 8 in the last; K ending inside a unit of 128, one group in all, K in one range and in several
+@pytest.mark.parametrize("N,K,M", [(2100, 2688, 7), (3000, 4128, 8), (130, 16640, 9), (4000, 1120, 16), (700, 3072, 17), (65, 32, 31),
+                                   (1000, 2080, 33), (300, 8224, 64), (129, 1056, 65), (64, 2048, 128), (20000, 256, 5)])
+def test_gemm_small_3_bit_groups_of_one_cell(qg, oracle, N, K, M):
+    bits, group = 3, 32
+    _announce("gemm rows int8", N, K, bits, group, M)
+    W, X = synth.small_case(5300 + N + M, N, K, 0.02, True, m=M)
+    X *= np.exp2(np.arange(M, dtype=np.float32) - 60)[:, None]               # every row a scale of its own
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    blob = qg.qg_pack(dev(q0), dev(s0), dev(z0), bits, group)
+    Y_ref, norms = oracle.matmul_small(q0, s0, z0, group, X), oracle.row_norms(q0, s0, z0, group)
+    nbytes = qg.qg_workspace_bytes(N, K, bits, group, M)
+    ws = qg.new_workspace(nbytes)
+    Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X), None, ws)).copy()
+    for m in range(M):
+        assert scaled_error(Y[m], Y_ref[m], norms, X[m]) <= TOL_FP32, m
+    assert np.array_equal(host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X), None, ws)), Y)
+    Xv = X.copy()
+    Xv[M // 2, K - 1] = np.inf
+    Yv = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(Xv), None, ws))
+    others = np.arange(M) != M // 2
+    assert not np.isfinite(Yv[M // 2]).any() and np.array_equal(Yv[others], Y[others])
+    # a workspace of the size the products per row ask for still does
+    rows = min(M, 16)
+    least = rows * qg.qg_workspace_bytes(N, K, bits, group, 1)
+    if least < nbytes:
+        ws = qg.new_workspace(least)[:least]
+        Yl = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X), None, ws))
+        for m in range(M):
+            assert scaled_error(Yl[m], Y_ref[m], norms, X[m]) <= TOL_FP32, m
+
+
+@pytest.mark.parametrize("N,K,bits,group,M", [(300, 2304, 4, 128, 17), (1062, 640, 2, 128, 5), (700, 3072, 3, 32, 17), (2100, 2688, 3, 32, 7)])
+def test_gemm_small_chosen_routes_replayed_from_a_graph(qg, N, K, bits, group, M):
+    # own operands with parts, products per row, the int8 kernel with parts, rows with meeting slots: replays give the
+    # bits of the eager call, with eager calls in between
+    _announce("gemm routes in a graph", N, K, bits, group, M)
+    W, X = synth.small_case(5400 + N, N, K, 0.02, True, m=M)
+    blob = qg.qg_pack(*qg.qg_quantize(dev(W), bits, group), bits, group)
+    ws = qg.new_workspace(qg.qg_workspace_bytes(N, K, bits, group, M))
+    x, y = dev(X), torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    qg.qg_gemm_small(blob, N, K, bits, group, x, y, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        qg.qg_gemm_small(blob, N, K, bits, group, x, y, ws)
+    for replay in range(4):
+        x.copy_(dev((X * np.float32(replay + 1)).astype(np.float32)))
+        y.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        replayed = host(y).copy()
+        assert np.array_equal(replayed, host(qg.qg_gemm_small(blob, N, K, bits, group, x, None, ws))), replay
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
 @pytest.mark.parametrize("bits,group,M", [(4, 128, 20), (4, 16, 40), (3, 64, 40), (2, 32, 9), (2, 512, 100)])
 def test_gemm_small_raw_codes_non_finite_activations(qg, bits, group, M, value):
