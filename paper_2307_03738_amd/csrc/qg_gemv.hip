@@ -1990,8 +1990,18 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
                                                       : kind == KIND_RUNTIME);
     if (few_long) {
         const size_t share = code_bytes / ((size_t)qg_compute_units() * 10);
+        // 4 bits below 32 MB of codes: the chip is not full, and what counts is how soon the last wavefront ends.  Teams
+        // of up to 8, which need a level of the reduction across workgroups less, with a step each or, from 14 MB on,
+        // three (single steps have too many sums to hand over there).  Over 160 random products and layer
+        // sets 0.94 of the time below 32 MB, the slowest 1.09: 4202 x 2432 g128 4.61 -> 4.03 us, gated 2 x 3200 x 3584 g128
+        // 6.02 -> 5.57, 8195 x 2432 g32 6.33 -> 5.50; from 40 MB on the same shapes lose 2 %.
+        const bool part_of_the_chip = bits_all == 4 && mul == MUL_MMA4I && t_cur.wpb == 0 && target == 0 && code_bytes < ((size_t)32 << 20);
+        if (part_of_the_chip) {
+            cap = 8;
+            target = (code_bytes < ((size_t)14 << 20) ? 1 : 3) * pl[0].item_bytes;
+        }
         // (the vector-ALU kernel keeps its wider teams while a wavefront has a single step)
-        if (t_cur.wpb == 0 && (mma || share > 4096)) cap = 4;
+        if (t_cur.wpb == 0 && !part_of_the_chip && (mma || share > 4096)) cap = 4;
         if (target == 0) {
             size_t most = bits_all == 4 ? 65536 : 49152;
             // (groups of one or two cells: a wavefront holds at most 64 groups, and half of that
