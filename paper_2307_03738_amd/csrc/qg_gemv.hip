@@ -31,6 +31,7 @@
 // gemv_mma (32 x 32 x 16 on bf16).  All share the work distribution and the reductions.
 #include <cstdio>
 #include <mutex>
+#include <type_traits>
 
 #include "qg_common.h"
 #include "qg_mma.h"
@@ -1458,8 +1459,9 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
         compute(rb, sb);
     }
 
-    // team reduction through LDS (each wavefront writes its own region first), then the lead
-    // adds the partial results in wavefront order and stores Y
+    // team reduction through LDS: each wavefront writes its 16 accumulators to its own region, and takes its share of them to
+    // add in wavefront order and store.  (One wavefront adding all: teams of eight 11008 x 4096 M = 16 10.5 -> 10.2 us, 8192 x 8192 g64
+    // 17.95 -> 17.4, 4096 x 4096 M = 12 8.91 -> 8.48; teams of four level: 20000 x 4096 M = 16 16.45 -> 16.5, 22016 x 8192 34.1 -> 34.3.)
     float *mine = (float *)(rows_raw + (size_t)wave * 16 * PITCH);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -1467,23 +1469,22 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
         mine[(8 + i) * QG_WAVE + lane] = yq[i];
     }
     __syncthreads();
-    if (wave != job.lead) return;
-    for (int w = 1; w < job.team; ++w) {
-        const float *other = (const float *)(rows_raw + (size_t)(job.lead + w) * 16 * PITCH);
+    const int team = job.team;
+    auto add_and_store = [&](auto most) {                 // teams of up to `most`: all reads at once, of regions the team has
+        for (int i = wave - job.lead; i < 16; i += team) {
+            const float *from = (const float *)(rows_raw + (size_t)job.lead * 16 * PITCH) + i * QG_WAVE + lane;
+            float part[most];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            yp[i] += other[i * QG_WAVE + lane];
-            yq[i] += other[(8 + i) * QG_WAVE + lane];
+            for (int w = 0; w < most; ++w) part[w] = from[(w < team ? w : 0) * (16 * PITCH / 2)];
+            float sum = part[0];
+#pragma unroll
+            for (int w = 1; w < most; ++w) sum = w < team ? sum + part[w] : sum;
+            const int m = 8 * (i / 4 & 1) + 4 * half + i % 4, n = tile * QG_WAVE + 32 * (i / 8) + (lane & 31);
+            if (m < M && n < P.N) P.y[(size_t)m * P.N + n] = sum;
         }
-    }
-    const int col = lane & 31;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int m = 8 * (i / 4) + 4 * half + (i % 4);
-        const int np = tile * QG_WAVE + col, nq = np + 32;
-        if (m < M && np < P.N) P.y[(size_t)m * P.N + np] = yp[i];
-        if (m < M && nq < P.N) P.y[(size_t)m * P.N + nq] = yq[i];
-    }
+    };
+    if (team > 4) add_and_store(std::integral_constant<int, 8>());
+    else add_and_store(std::integral_constant<int, 4>());
 }
 
 // ---------------------------------------------------------------------------------------
