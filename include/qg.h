@@ -82,7 +82,8 @@ size_t qg_packed_bytes(int64_t N, int64_t K, int bits, int group, int layout);
  * The buffer must be prepared once before its first use with qg_workspace_init (it fills it
  * with the "empty slot" pattern); every qg_gemv call leaves it prepared again.  A buffer
  * belongs to one problem shape and one of the two entry points, and two calls that overlap
- * in time must not share one. */
+ * in time must not share one.  Shape means (N, K, bits, group): a buffer as large as the largest M asks
+ * for serves qg_gemm_small with any M up to it, in any order, unless one of them is 1. */
 size_t qg_workspace_bytes(int64_t N, int64_t K, int bits, int group, int M);
 int qg_workspace_init(void *workspace, size_t bytes, void *stream);
 

@@ -1022,10 +1022,12 @@ static size_t gemm_workspace_least(const QgLayout &L, int M)
     return qg_round_up(need, QG_SECTION_ALIGN);
 }
 // (3-bit groups of 32: the int8 product's operands and parts lie behind the meeting slots of the products per row, which
-// stay as qg_workspace_init has left them)
+// stay as qg_workspace_init has left them: behind those of as many rows as a launch takes, whatever the call's M, so that
+// a buffer large enough for several M serves them in any order)
+static size_t rows_i8_off(const QgLayout &L) { return gemm_workspace_least(L, QG_MAX_GROUPED); }
 size_t qg_gemm_workspace_bytes(const QgLayout &L, int M)
 {
-    return gemm_workspace_least(L, M) + (M > 1 && qg_rows_i8_takes(L) ? qg_rows_i8_bytes(L, M) : 0);
+    return M > 1 && qg_rows_i8_takes(L) ? rows_i8_off(L) + qg_rows_i8_bytes(L, M) : gemm_workspace_least(L, M);
 }
 
 extern "C" int qg_set_gemm_tuning(int splits, int shape)
@@ -1277,7 +1279,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     // 3-bit groups of 32 weights: fp32 all the way, as qg_gemv computes it (X to 2^-30 of the largest of 128 values), the
     // cheapest of three: the product on int8 matrix instructions, two or three launches; up to 16 rows a matrix-vector
     // product per row in one launch, with K cut over workgroups (below; 3.3 us and 55 per 10^9 weights times rows) or not.
-    // (A workspace of the size asked for before the int8 kernel keeps the products per row.)
+    // (A workspace that holds the slots of the call's rows but not the int8 operands keeps the products per row.)
     if (M > 1 && qg_rows_i8_takes(L) && workspace_bytes >= qg_gemm_workspace_bytes(L, M)) {
         const int splits = qg_rows_i8_splits(L, M);
         const double us8 = call_us(qg_rows_i8_us(L, M), splits > 1 ? 3 : 2);
@@ -1294,7 +1296,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
                 return QG_OK;
             }
             float *partial = nullptr;
-            const int r = qg_rows_i8(packed, L, X, M, Y, (char *)workspace + gemm_workspace_least(L, M), st, &partial);
+            const int r = qg_rows_i8(packed, L, X, M, Y, (char *)workspace + rows_i8_off(L), st, &partial);
             if (r != QG_OK || splits == 1) return r;
             const size_t count = (size_t)M * N;
             hipLaunchKernelGGL(add_splits, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, (const float *)partial, splits, count, Y);

@@ -7,7 +7,7 @@
 #include <string.h>
 
 typedef struct { uint32_t x, y, z; } dim3_t;
-enum { MOST = 4096, ARGS = 128, LDS_FREE = 64 << 10 };
+enum { MOST = 4096, ARGS = 4224, LDS_FREE = 64 << 10 };
 
 static struct { const void *f; char name[256]; } known[1024];
 static int n_known;
@@ -57,7 +57,10 @@ int hipLaunchKernel(const void *f, dim3_t g, dim3_t b, void **args, size_t lds, 
     if (k == n_known || n_launch == MOST || lds > (size_t)allowed) return error = 1;
     launch[n_launch].kernel = k; launch[n_launch].device = device;
     launch[n_launch].grid = g; launch[n_launch].block = b; launch[n_launch].lds = lds;
-    if (strstr(known[k].name, "gemm_codes")) memcpy(launch[n_launch].args, args[0], ARGS - 8);
+    /* the argument struct: QgCodesArgs, QgRowsI8Args, GemvArgs */
+    if (strstr(known[k].name, "gemm_codes")) memcpy(launch[n_launch].args, args[0], 120);
+    if (strstr(known[k].name, "gemm_rows_i8")) memcpy(launch[n_launch].args, args[0], 80);
+    if (strstr(known[k].name, "gemv_")) memcpy(launch[n_launch].args, args[3], 4224);
     ++n_launch;
     return 0;
 }

@@ -17,6 +17,26 @@ class CodesArgs(ctypes.Structure):
                                        "group_magic", "zshift", "units", "ranges", "quota", "total", "fused", "kw")]
 
 
+class RowsI8Args(ctypes.Structure):
+    """Arguments of the product on int8 digits (QgRowsI8Args)."""
+    _fields_ = [(n, ctypes.c_void_p) for n in ("codes", "scales", "zeros", "Aop", "inverse", "out")] + \
+        [(n, ctypes.c_int32) for n in ("M", "N", "tiles", "ngroups", "zwords", "units", "units_padded", "per_wave")]
+
+
+class GemvProblem(ctypes.Structure):
+    """One problem of a GEMV launch, up to the meeting slots and the cuts of K."""
+    _fields_ = [(n, ctypes.c_void_p) for n in ("codes", "scales", "zeros", "x", "y", "slots")] + \
+        [(n, ctypes.c_int32) for n in ("N", "K", "tiles", "steps", "ngroups", "zwords", "group", "chunks")] + [("rest", ctypes.c_ubyte * 176)]
+
+
+class GemvArgs(ctypes.Structure):
+    _fields_ = [("count", ctypes.c_int32), ("block_begin", ctypes.c_int32 * 31), ("p", GemvProblem * 16)]
+
+
+WORKSPACE = 1 << 32
+SLOTS_PER_TILE = 33 * 64 * 4           # bytes of meeting slots per tile of 64 outputs
+
+
 def _run(stub_path, lib_path, calls):
     stub = ctypes.CDLL(stub_path, mode=ctypes.RTLD_GLOBAL)
     L = ctypes.CDLL(lib_path)
@@ -33,7 +53,7 @@ def _run(stub_path, lib_path, calls):
         stub.stub_device(c.get("device", 0))
         N, K, bits, group, M = c["problem"]
         assert L.qg_set_gemm_tuning(c.get("splits", 0), c.get("shape", 0)) == 0
-        size = L.qg_workspace_bytes(N, K, bits, group, M)
+        size = c.get("size") or L.qg_workspace_bytes(N, K, bits, group, M)
         if c.get("search"):
             blobs, us, timed = (vp * 1)(1 << 20), (ctypes.c_float * 120)(), (ctypes.c_int * 2)()
             status = L.qg_gemm_autotune(blobs, 1, N, K, bits, group, 1 << 20, M, 1 << 20, 1 << 20, size, None, 1, None, None, None)
@@ -41,7 +61,7 @@ def _run(stub_path, lib_path, calls):
             L.qg_clear_tuning()
             out.append({"status": status, "us": list(us)})
             continue
-        status = L.qg_gemm_small(1 << 20, N, K, bits, group, 1 << 20, M, 1 << 20, 1 << 20, size, None)
+        status = L.qg_gemm_small(1 << 20, N, K, bits, group, 1 << 20, M, 1 << 20, WORKSPACE, size, None)
         kernels = []
         for i in range(stub.stub_launches()):
             shape = (ctypes.c_uint32 * 5)()
@@ -55,14 +75,25 @@ def _run(stub_path, lib_path, calls):
             if name == "gemm_codes":
                 a = CodesArgs.from_address(stub.stub_args(i))
                 k["args"] = {f: getattr(a, f) for f, _ in CodesArgs._fields_}
+            # what a launch writes into the workspace, and the meeting slots it expects empty: [from, to) in it
+            if name == "gemm_rows_i8":
+                a = RowsI8Args.from_address(stub.stub_args(i))
+                blocks = (a.M + 7) // 8
+                writes = [(a.Aop, blocks * a.units * 4096), (a.inverse, blocks * a.units * 32)]
+                if shape[1] > 1:
+                    writes.append((a.out, shape[1] * a.M * a.N * 4))
+                k["writes"] = [(p - WORKSPACE, p - WORKSPACE + n) for p, n in writes]
+            if name.startswith("gemv_"):
+                a = GemvArgs.from_address(stub.stub_args(i))
+                k["slots"] = [(p.slots - WORKSPACE, p.slots - WORKSPACE + p.tiles * SLOTS_PER_TILE) for p in a.p[:a.count] if p.chunks > 1]
             kernels.append(k)
-        out.append({"status": status, "kernels": kernels, "limits": stub.stub_limits()})
+        out.append({"status": status, "kernels": kernels, "limits": stub.stub_limits(), "size": size})
     return out
 
 
 def launches(tmp_path, calls):
     """calls: dicts with problem = (N, K, bits, group, M) of qg_gemm_small and, optionally, splits and shape
-    (qg_set_gemm_tuning) and device, or search = True for qg_gemm_autotune.  Returns per call its status and
+    (qg_set_gemm_tuning), device and the workspace's size, or search = True for qg_gemm_autotune.  Returns per call its status and
     the kernels it launches, or the times of the search's candidates (-1: not timed)."""
     from paper_2307_03738_amd import build
     stub = os.path.join(str(tmp_path), "hip_stub.so")

@@ -1112,6 +1112,26 @@ def test_gemm_small_3_bit_groups_of_one_cell(qg, oracle, N, K, M):
             assert scaled_error(Yl[m], Y_ref[m], norms, X[m]) <= TOL_FP32, m
 
 
+def test_gemm_small_3_bit_groups_of_one_cell_share_a_workspace(qg, oracle):
+    # 8 rows are a product on int8 digits and 16 are matrix-vector products with K cut in two, whose partial sums
+    # meet in the workspace: neither finds what the other leaves there, in a buffer as qg_workspace_bytes asks for
+    # 16 rows and in one that holds the slots of 16 rows alone
+    N, K, bits, group = 4096, 4096, 3, 32
+    W, X = synth.small_case(5350, N, K, 0.02, True, m=16)
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    blob = qg.qg_pack(dev(q0), dev(s0), dev(z0), bits, group)
+    Y_ref, norms = oracle.matmul_small(q0, s0, z0, group, X), oracle.row_norms(q0, s0, z0, group)
+    slots = 16 * qg.qg_workspace_bytes(N, K, bits, group, 1)
+    for size in (qg.qg_workspace_bytes(N, K, bits, group, 16), slots):
+        ws = qg.new_workspace(size)[:size]
+        for M in (8, 16, 8, 16, 2, 16):
+            _announce("gemm rows int8, one workspace", N, K, bits, group, M)
+            Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X[:M].copy()), None, ws))
+            for m in range(M):
+                assert scaled_error(Y[m], Y_ref[m], norms, X[m]) <= TOL_FP32, (size, M, m)
+        assert (host(ws)[:slots] == 0xff).all()
+
+
 @pytest.mark.parametrize("N,K,bits,group,M", [(300, 2304, 4, 128, 17), (1062, 640, 2, 128, 5), (700, 3072, 3, 32, 17), (2100, 2688, 3, 32, 7)])
 def test_gemm_small_chosen_routes_replayed_from_a_graph(qg, N, K, bits, group, M):
     # own operands with parts, products per row, the int8 kernel with parts, rows with meeting slots: replays give the

@@ -113,3 +113,21 @@ def test_one_launch_up_to_16_rows(tmp, problem, name):
 def test_kernel_family_of_small_4_bit_products(tmp, problem, raw):
     names = [k["name"] for k in launches(tmp, [{"problem": problem}])[0]["kernels"]]
     assert ("gemm_codes" in names) == raw, names
+
+
+# 3-bit groups of 32: the rows of a call are products on int8 digits or matrix-vector products whose partial sums meet in the
+# workspace, by M; a buffer of any accepted size serves every M it is large enough for
+@pytest.mark.parametrize("N,K", [(4096, 4096), (4096, 11008), (1000, 2080), (20000, 256)])
+def test_int8_operands_stay_out_of_the_meeting_slots(tmp, N, K):
+    rows = list(range(1, 129))
+    slots = 8448 * ((N + 63) // 64)                                       # of one row (as qg_workspace_bytes asks for M = 1)
+    own = launches(tmp, [{"problem": (N, K, 3, 32, M)} for M in rows])
+    sizes = [16 * slots, 9 * slots] + [own[M - 1]["size"] for M in (1, 2, 8, 15, 16, 17, 40, 128)]
+    assert own[0]["size"] == slots and all(r["status"] == 0 for r in own)
+    for size in sizes:
+        results = [r for r in launches(tmp, [{"problem": (N, K, 3, 32, M), "size": size} for M in rows]) if r["status"] == 0]
+        kernels = [k for r in results for k in r["kernels"]]
+        writes = [w for k in kernels for w in k.get("writes", [])]
+        reads = [s for k in kernels for s in k.get("slots", [])]
+        assert results and all(a >= 0 and b <= size for a, b in writes + reads)
+        assert not reads or all(a >= max(b for _, b in reads) for a, _ in writes)
