@@ -190,7 +190,8 @@ int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group
  * the fixed point keeps its precision while the largest |x| of a run is at least 2^-96.)
  * Every other layout (odd numbers of cells per group, K % 16 != 0 only with M == 1) runs
  * qg_gemv once per row in fp32, 16 rows per launch; with K % 16 != 0 and M > 1 the call returns
- * QG_ERR_UNSUPPORTED.  M == 1 is qg_gemv.
+ * QG_ERR_UNSUPPORTED.  M == 1 is qg_gemv (its arithmetic; at 4 bits its sums may be cut elsewhere), and launches at
+ * most two kernels.
  *   X [M][K] fp32 row-major, 64-byte aligned;  Y [M][N] fp32 row-major (overwritten).
  * workspace: qg_workspace_bytes(N, K, bits, group, M) bytes (converted activations and partial
  * results of a K split; for the row-by-row form, qg_gemv's meeting slots, to be prepared with

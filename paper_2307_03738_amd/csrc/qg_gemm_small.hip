@@ -1142,6 +1142,26 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     if (!qg_aligned16(workspace)) return QG_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
 
+    // One row of a 4-bit layout whose products of more rows leave parts of sums in the workspace (one row of the others is a
+    // GEMV below): qg_gemv's arithmetic, in one launch that cuts no K over workgroups or, where a K is long for one, in a cut
+    // launch, whose meeting slots a fill of 2 us empties first.  (As a bf16 product X was rounded, 1.7e-3 off 64
+    // bits, now 1e-7; us per call 11008 x 4096 8.9 -> 6.7, 512 x 512 4.8 -> 2.6, 512 x 22016, cut, 17.2 -> 8.1.)
+    const int gps = codes_gps(L);
+    if (M == 1 && knob_shape == 0 && bits == 4 && (fast_path(L) || gps >= 0)) {
+        if (call_us(gemv_rows_us(L, 1), 1) <= call_us(5.3 + 55e-9 * 64 * L.tiles * L.K, 2)) {
+            const int r = qg_gemv_rows(packed, N, K, bits, group, X, 1, Y, stream, price != nullptr);
+            if (r == QG_OK && price) *price = {2, -1, 1, 0, 0, 1, {nullptr, 0, 0}, 0.0};
+            if (r != QG_ERR_UNSUPPORTED) return r;
+        }
+        const size_t slots = qg_workspace_bytes(N, K, bits, group, 1);
+        const qg_gemv_desc d = {packed, N, K, bits, group, X, Y};
+        int r = qg_gemv_grouped_check(&d, 1, workspace, slots);
+        if (r == QG_OK && price) *price = {2, -1, 1, 0, 0, 2, {nullptr, 0, 0}, 0.0};
+        if (r != QG_OK || price) return r;
+        r = qg_workspace_init(workspace, slots, stream);
+        return r == QG_OK ? qg_gemv_grouped(&d, 1, workspace, slots, stream) : r;
+    }
+
     // The raw-code kernel: every layout it takes that the 4-bit kernels below do not (2 and 3 bits, 4-bit
     // groups of 16), whatever shape 13 sends it, and the larger 4-bit matrices (in tile-steps of 64 outputs x
     // 128 k), where it is ahead of the dequantizing kernels; us per call, raw codes | dequantizing:
@@ -1163,11 +1183,10 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     // one product does.  (500 products of 2 ... 16 rows: 0.80 of the kernels' time of the raw-code kernel and gemm_rows16 from
     // 128 tiles on; 2045 x 576 4-bit M = 3 7.0 | 3.4 us, 1062 x 640 2-bit M = 5 6.1 | 3.3.  The dequantizing kernels were
     // the fastest of none.)
-    const int gps = codes_gps(L);
     const int from = M > 32 && M <= 64 ? (gps >= 4 ? 8448 : 8192) : 4096;
     const bool large = M > 16 && L.tiles * L.steps >= from;
     bool raw = gps >= 0 && M > 1 && (knob_shape == NSHAPES + 1 || knob_shape == 0);
-    bool rows16 = M == 1 && knob_shape == 0 && L.tiles >= 128;
+    bool rows16 = false;
     const int cus = qg_compute_units();
     double us16 = 1e30, us1 = 1e30;                       // of the other two families up to 16 rows
     if (raw && knob_shape == 0 && M <= 16) {

@@ -1079,6 +1079,29 @@ def test_gemm_small_as_matrix_vector_products(qg, oracle, N, K, bits, group, M):
         assert (host(ws) == fill).all()
 
 
+# One row (tests/test_launch_plans.py looks): N, K, bits, group, whether meeting slots are emptied first; K of one step, long
+# enough to be cut over workgroups, groups of a cell pair and of all of K, ragged outputs, and more than 128 tiles
+M1_CASES = [(64, 128, 4, 32, False), (11008, 4096, 4, 128, False), (4099, 4096, 4, 64, False), (300, 8192, 4, 16, True),
+            (512, 22016, 4, 128, True), (130, 16384, 4, 16384, True), (1000, 1024, 4, 1024, False), (8200, 2048, 4, 16, False),
+            (700, 2048, 3, 64, False), (700, 2048, 2, 32, False)]
+
+
+@pytest.mark.parametrize("N,K,bits,group,filled", M1_CASES)
+def test_gemm_small_one_row(qg, oracle, N, K, bits, group, filled):
+    # fp32 as qg_gemv, at 4 bits whatever the workspace holds
+    _announce("gemm, one row", N, K, bits, group)
+    W, X = synth.small_case(5250 + N, N, K, 0.02, True, m=2)
+    X = X[:1].copy()
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    blob = qg.qg_pack(dev(q0), dev(s0), dev(z0), bits, group)
+    Y_ref, norms = oracle.matmul_small(q0, s0, z0, group, X), oracle.row_norms(q0, s0, z0, group)
+    for fill in (0xff, 0, 0x3c) if bits == 4 else (0xff,):
+        ws = torch.full((qg.qg_workspace_bytes(N, K, bits, group, 1),), fill, dtype=torch.uint8, device="cuda")
+        for again in range(2):
+            Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X), None, ws))
+            assert scaled_error(Y, Y_ref, norms, X) <= TOL_FP32, (fill, again)
+
+
 # 3-bit groups of 32 on the int8 matrix instructions: N, K, M; one, two and four blocks of eight rows, several of those,
 # rows 1 ... 8 in the last; K ending inside a unit of 128, one group in all, K in one range and in several
 @pytest.mark.parametrize("N,K,M", [(2100, 2688, 7), (3000, 4128, 8), (130, 16640, 9), (4000, 1120, 16), (700, 3072, 17), (65, 32, 31),

@@ -2,7 +2,7 @@
 import pytest
 
 from tests.launches import launches
-from tests.test_gpu_parity import ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
+from tests.test_gpu_parity import M1_CASES, ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
 
 
 @pytest.fixture(scope="module")
@@ -103,6 +103,16 @@ def test_own_operand_cases_are_cut_as_stated(tmp, case):
     ((16888, 864, 4, 32, 5), "gemm_codes"), ((11295, 1280, 3, 1280, 14), "gemm_codes")])
 def test_one_launch_up_to_16_rows(tmp, problem, name):
     assert [k["name"] for k in launches(tmp, [{"problem": problem}])[0]["kernels"]] == [name]
+
+
+# One row is a GEMV at every width; at 4 bits, where products of more rows leave other things in the workspace, without
+# meeting slots or with slots emptied first
+@pytest.mark.parametrize("case", M1_CASES)
+def test_one_row_is_a_gemv(tmp, case):
+    *problem, filled = case
+    *before, k = launches(tmp, [{"problem": (*problem, 1)}])[0]["kernels"]
+    assert k["name"].startswith("gemv_") and [b["name"] for b in before] == ["fill_u32"] * filled
+    assert filled or not k["slots"] or problem[2] != 4
 
 
 # 4 bits below the sizes where raw codes are taken whatever the estimates say: the dequantizing kernels cut K between
