@@ -116,7 +116,8 @@ int qg_unpack(const void *packed, int64_t N, int64_t K, int bits, int group, int
  * bits) or 256 k (an error of at most 2^-30 of that largest |x| per term, below the rounding
  * of the fp32 sum it enters; the built-in choice), or as three bf16 parts that add up to x.
  * (The fixed point keeps that precision while the largest |x| of a run is at least 2^-97;
- * NaN and infinity in x reach y through the sum of x of their group.)
+ * NaN and infinity in x reach y through the sum of x of their group: y is not finite, and NaN where K is no
+ * whole number of those runs.)
  *   packed: QG_LAYOUT_DEVICE blob;  x [K] fp32, 64-byte aligned;  y [N] fp32 (overwritten).
  * workspace: qg_workspace_bytes(N, K, bits, group, 1) bytes, 16-byte aligned. */
 int qg_gemv(const void *packed, int64_t N, int64_t K, int bits, int group,
@@ -178,7 +179,7 @@ int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group
  *     matrix instruction as exact bf16 integers, X is rounded to bf16, and scale and zero-point
  *     are applied in fp32 once per group and element of Y (eq. (2)); X is converted by the
  *     product kernel itself or, on larger products, by a kernel of its own first, so a call enqueues one to three kernels.  (The sums of (2^7 + q) x over a
- *     group, or 128 k of it, are fp32: |x| up to 10^34; NaN and infinity in X come out as NaN.)
+ *     group, or 128 k of it, are fp32: |x| up to 10^34.)
  * Where both apply (4 bits) the second is used for 17 ... 32 and more than 64 rows on matrices of 4096
  * tile-steps or more (64 outputs x 128 k each) and for 33 ... 64 rows from 8192 on (groups of 32: from
  * 8448); below that whichever the planner's estimates say is the faster (groups of one per output nearly always
@@ -186,12 +187,13 @@ int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group
  * split of K over workgroups, and, for small products, qg_gemv's arithmetic (fp32, X not rounded) once per row in one
  * launch that needs nothing of the workspace.  qg_set_gemm_tuning and qg_gemm_autotune choose otherwise.
  * 3-bit groups of 32: fp32 throughout, X as 32-bit fixed point relative to the largest |x| of each run of 128 k, on int8
- * matrix instructions (two or three kernels) or, for few rows, as below.  (NaN and infinity in X make their row of Y NaN;
- * the fixed point keeps its precision while the largest |x| of a run is at least 2^-96.)
+ * matrix instructions (two or three kernels) or, for few rows, as below.  (The fixed point keeps its precision while the
+ * largest |x| of a run is at least 2^-96.)
  * Every other layout (odd numbers of cells per group, K % 16 != 0 only with M == 1) runs
  * qg_gemv once per row in fp32, 16 rows per launch; with K % 16 != 0 and M > 1 the call returns
  * QG_ERR_UNSUPPORTED.  M == 1 is qg_gemv (its arithmetic; at 4 bits its sums may be cut elsewhere), and launches at
  * most two kernels.
+ * NaN and infinity in X make their row of Y NaN, except that on dequantized weights an infinity may come out as one.
  *   X [M][K] fp32 row-major, 64-byte aligned;  Y [M][N] fp32 row-major (overwritten).
  * workspace: qg_workspace_bytes(N, K, bits, group, M) bytes (converted activations and partial
  * results of a K split; for the row-by-row form, qg_gemv's meeting slots, to be prepared with

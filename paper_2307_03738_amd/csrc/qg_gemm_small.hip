@@ -48,6 +48,7 @@ double qg_rows_i8_us(const QgLayout &L, int M);
 int qg_rows_i8(const void *packed, const QgLayout &L, const float *X, int M, float *Y, void *workspace, hipStream_t st, float **partial);
 int qg_gemv_rows(const void *packed, int64_t N, int64_t K, int bits, int group, const float *X, int M, float *Y,
                  void *stream, bool dry);
+int qg_gemv_grouped_rows(const qg_gemv_desc *descs, int count, void *workspace, size_t workspace_bytes, void *stream);
 int qg_gemv_grouped_check(const qg_gemv_desc *descs, int count, void *workspace, size_t workspace_bytes);
 
 namespace {
@@ -1159,7 +1160,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         if (r == QG_OK && price) *price = {2, -1, 1, 0, 0, 2, {nullptr, 0, 0}, 0.0};
         if (r != QG_OK || price) return r;
         r = qg_workspace_init(workspace, slots, stream);
-        return r == QG_OK ? qg_gemv_grouped(&d, 1, workspace, slots, stream) : r;
+        return r == QG_OK ? qg_gemv_grouped_rows(&d, 1, workspace, slots, stream) : r;
     }
 
     // The raw-code kernel: every layout it takes that the 4-bit kernels below do not (2 and 3 bits, 4-bit
@@ -1343,7 +1344,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
                     d[i].y = Y + (size_t)(m0 + i) * N;
                 }
                 const int r = pass == 0 ? qg_gemv_grouped_check(d, rows, workspace, workspace_bytes)
-                                        : qg_gemv_grouped(d, rows, workspace, workspace_bytes, stream);
+                                        : qg_gemv_grouped_rows(d, rows, workspace, workspace_bytes, stream);
                 if (r != QG_OK) return r;
             }
         if (price) *price = {2, -1, 1, 0, 0, (M + QG_MAX_GROUPED - 1) / QG_MAX_GROUPED, {nullptr, 0, 0}, 0.0};

@@ -58,7 +58,7 @@ struct alignas(128) GemvProblem {
     int block_begin;       // first block of this problem in the grid
     int pair_tiles;        // > 0: outputs [0, 64 pair_tiles) gate outputs [64 pair_tiles, ...), see emit_output
     float *h;              // gated result (pair_tiles > 0)
-    int rows;              // gemm_rows16 only: activation rows M (x is X [M][K], y is Y [M][N])
+    int rows;              // gemm_rows16: activation rows M (x is X [M][K], y is Y [M][N]); else 1 for a row of a qg_gemm_small call
 };
 
 // Every field of a problem entry in scalar registers at one point: the loads that fetch the
@@ -1119,7 +1119,10 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
         }
     const lds_u8 *abase[2] = {&xs[wave][0][lane & 3][0], &xs[wave][1][lane & 3][0]};
 
-    // Fixed point of the step: |x| scale < 2^30 for the largest |x| of the step.  Returns 1 / scale.
+    // Fixed point of the step: |x| scale < 2^30 for the largest |x| of the step.  Returns 1 / scale, or, where an infinity has to
+    // make y NaN (rows of qg_gemm_small; a K that ends inside a step, as on gemv_generic), a NaN: the sum of the codes would count
+    // the infinity as 2^31 and -z xhat alone would give y its sign.
+    const uint32_t infinite = RAGGED || P.rows > 0 ? 255u : 256u;
     auto stage_x = [&](const D &d, int buf) -> float {
         float m = 0.0f;
 #pragma unroll
@@ -1131,6 +1134,7 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
         m = dpp_max<QG_DPP_BCAST15, 0xa>(m);
         m = dpp_max<QG_DPP_BCAST31, 0xc>(m);
         uint32_t eb = (uint32_t)__builtin_amdgcn_readlane(__float_as_int(m), 63) >> 23;   // biased exponent
+        const bool to_nan = eb >= infinite;
         eb = eb < 30u ? 30u : eb > 254u ? 254u : eb;
         const float scale = __uint_as_float((283u - eb) << 23);                             // 2^(156 - eb)
 #pragma unroll
@@ -1148,7 +1152,7 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
                 xs[wave][buf][3][xpos[i][e]] = (uint8_t)(pat >> 24);
             }
         }
-        return __uint_as_float((eb - 29u) << 23);                                           // 2^(eb - 156)
+        return __uint_as_float(to_nan ? 0x7fc00000u : (eb - 29u) << 23);                    // 2^(eb - 156)
     };
 
     float yacc = 0.0f;
@@ -1926,9 +1930,10 @@ Mul multiplier(int bits, int cpg, Kind kind, size_t code_bytes)
 // dry: plan and check only -- returns the status the launch would have up to the point where
 // the kernel is enqueued, and enqueues nothing.
 // one_chunk: the problems are of one shape and no K is cut over workgroups, so the launch needs no meeting slots.
+// product_rows: the problems are rows of a qg_gemm_small call.
 int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const size_t *ws_off,
                  char *workspace, hipStream_t st, const int64_t *gate_rows, float *const *gated,
-                 int rows = 0, bool dry = false, LaunchShape *report = nullptr, bool one_chunk = false)
+                 int rows = 0, bool dry = false, LaunchShape *report = nullptr, bool one_chunk = false, bool product_rows = false)
 {
     GemvArgs A;
     A.count = count;
@@ -2121,7 +2126,7 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
         P.tiles_per_block = P.chunks > 1 ? 1 : wpb / P.waves_per_tile;
         P.pair_tiles = gate_rows ? (int)(gate_rows[idx[i]] / QG_WAVE) : 0;
         P.h = gated ? gated[idx[i]] : nullptr;
-        P.rows = rows;
+        P.rows = rows > 0 ? rows : product_rows;
         P.block_begin = blocks;
         A.block_begin[i] = blocks;
         const int64_t nb = P.chunks > 1 ? (int64_t)P.tiles * P.chunks
@@ -2277,7 +2282,7 @@ extern "C" int qg_workspace_init(void *workspace, size_t bytes, void *stream)
 // check_only: argument checks and planning, nothing enqueued.
 static int gemv_grouped(const qg_gemv_desc *descs, int count, void *workspace, size_t workspace_bytes,
                         void *stream, const int64_t *gate_rows, float *const *gated, bool check_only = false,
-                        LaunchShape *report = nullptr)       // report: the shape of the call's largest launch
+                        LaunchShape *report = nullptr, bool product_rows = false)       // report: the shape of the call's largest launch
 {
     if (!descs) return QG_ERR_NULL;
     if (count <= 0) return QG_ERR_SHAPE;
@@ -2327,7 +2332,7 @@ static int gemv_grouped(const qg_gemv_desc *descs, int count, void *workspace, s
                 }
             LaunchShape shape;
             const int rc = launch_class(descs, idx, n, ws_off, (char *)workspace, (hipStream_t)stream,
-                                        gate_rows, gated, 0, pass == 0 && (check_only || !one_pass), report ? &shape : nullptr);
+                                        gate_rows, gated, 0, pass == 0 && (check_only || !one_pass), report ? &shape : nullptr, false, product_rows);
             if (rc != QG_OK) return rc;
             if (report && pass == 0 && (i == 0 || shape.waves > report->waves)) *report = shape;
         }
@@ -2346,6 +2351,12 @@ extern "C" int qg_gemv_grouped(const qg_gemv_desc *descs, int count, void *works
 int qg_gemv_grouped_check(const qg_gemv_desc *descs, int count, void *workspace, size_t workspace_bytes)
 {
     return gemv_grouped(descs, count, workspace, workspace_bytes, nullptr, nullptr, nullptr, true);
+}
+
+// The launch for the rows of a product (used by qg_gemm_small).
+int qg_gemv_grouped_rows(const qg_gemv_desc *descs, int count, void *workspace, size_t workspace_bytes, void *stream)
+{
+    return gemv_grouped(descs, count, workspace, workspace_bytes, stream, nullptr, nullptr, false, nullptr, true);
 }
 
 // Y = X What^T for M <= 16 rows on the GEMV's launch structure (used by qg_gemm_small).
@@ -2390,7 +2401,7 @@ int qg_gemv_rows(const void *packed, int64_t N, int64_t K, int bits, int group, 
         ws_off[i] = 0;
     }
     t_cur = {g_tune_wpb, g_tune_bytes_per_wave, g_tune_kernel};
-    return launch_class(d, idx, M, ws_off, nullptr, (hipStream_t)stream, nullptr, nullptr, 0, dry, nullptr, true);
+    return launch_class(d, idx, M, ws_off, nullptr, (hipStream_t)stream, nullptr, nullptr, 0, dry, nullptr, true, true);
 }
 
 extern "C" int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group,

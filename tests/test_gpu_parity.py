@@ -1102,6 +1102,41 @@ def test_gemm_small_one_row(qg, oracle, N, K, bits, group, filled):
             assert scaled_error(Y, Y_ref, norms, X) <= TOL_FP32, (fill, again)
 
 
+# Rows that run as matrix-vector products, in every way they do: one launch without cuts of K, 4 bits and one row with cuts,
+# 3-bit groups of 32 with and without cuts and on int8 digits; groups inside a step, of several, and a K ending inside one
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("N,K,bits,group,M", [
+    (512, 512, 4, 64, 2), (2045, 576, 4, 64, 3), (700, 3072, 2, 3072, 6), (300, 2240, 3, 64, 4), (130, 1536, 3, 128, 16), (1000, 1024, 4, 1024, 1),
+    (512, 22016, 4, 128, 1), (4096, 4096, 3, 32, 16), (1000, 2080, 3, 32, 2), (2100, 2688, 3, 32, 7)])
+def test_gemm_small_non_finite_rows_of_products(qg, N, K, bits, group, M, value):
+    # a value that is no number makes its row NaN, at whichever M, and leaves the others
+    _announce("gemm, products per row", N, K, bits, group, M, value)
+    W, X = synth.small_case(5280 + N + M, N, K, 0.02, True, m=max(M, 2))
+    X = X[:M].copy()
+    blob = qg.qg_pack(*qg.qg_quantize(dev(W), bits, group), bits, group)
+    Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X))).copy()
+    for k in (0, K // 2, K - 1):
+        Xv = X.copy()
+        Xv[M // 2, k] = value
+        Yv = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(Xv)))
+        assert np.isnan(Yv[M // 2]).all(), k
+        others = np.arange(M) != M // 2
+        assert np.array_equal(Yv[others], Y[others])
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("N,K,bits,group", [(130, 4160, 4, 64), (130, 4160, 3, 32), (70, 1040, 2, 16), (130, 64, 3, 64)])
+def test_gemv_k_ending_inside_a_step_non_finite(qg, N, K, bits, group, value):
+    # as where every product of such an x is formed one by one: inf - inf, or 0 inf
+    _announce("gemv ragged K", N, K, bits, group, value)
+    W, x = synth.small_case(5290 + N, N, K, 0.02, True)
+    blob = qg.qg_pack(*qg.qg_quantize(dev(W), bits, group), bits, group)
+    for k in (0, K // 2, K - 1):
+        xv = x.copy()
+        xv[k] = value
+        assert np.isnan(host(qg.qg_gemv(blob, N, K, bits, group, dev(xv)))).all(), k
+
+
 # 3-bit groups of 32 on the int8 matrix instructions: N, K, M; one, two and four blocks of eight rows, several of those,
 # rows 1 ... 8 in the last; K ending inside a unit of 128, one group in all, K in one range and in several
 @pytest.mark.parametrize("N,K,M", [(2100, 2688, 7), (3000, 4128, 8), (130, 16640, 9), (4000, 1120, 16), (700, 3072, 17), (65, 32, 31),
