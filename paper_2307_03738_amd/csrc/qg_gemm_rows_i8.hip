@@ -273,13 +273,15 @@ size_t qg_rows_i8_bytes(const QgLayout &L, int M) { return rows_i8_plan(L, M).to
 int qg_rows_i8_splits(const QgLayout &L, int M) { return rows_i8_plan(L, M).splits; }
 
 // Kernels' time of a call, adding the parts included: a unit's instructions at 1.78 times the time they issue in, as
-// measured from 4096 x 4096 to 10486 x 16608 (29.5, 53.4, 46.0 us for 29.6, 53.1, 46.0).
+// measured from 4096 x 4096 to 10486 x 16608 (29.5, 53.4, 46.0 us for 29.6, 53.1, 46.0), and on a chip that is not full the
+// chain of its blocks of rows, one after the other: 1.6, 2.0 and 3.4 us (100 products of less than a wavefront per
+// SIMD, 64 to 22000 outputs and inputs: 6 % off; as for one block, 1.6, 75 x 1536 M = 18 was priced at 9.4 us for 14.3).
 double qg_rows_i8_us(const QgLayout &L, int M)
 {
     const RowsI8Plan P = rows_i8_plan(L, M);
-    const double unit = P.nb == 1 ? 0.55 : P.nb == 2 ? 0.87 : 1.5;
+    const double unit = P.nb == 1 ? 0.55 : P.nb == 2 ? 0.87 : 1.5, least = P.nb == 1 ? 0.9 : P.nb == 2 ? 1.1 : 1.9;
     const double waves = (double)L.tiles * P.zblocks * P.splits * SLICES / (4.0 * qg_compute_units());
-    const double busy = unit * waves > 0.9 ? unit * waves : 0.9;
+    const double busy = unit * waves > least ? unit * waves : least;
     return 4.6 + 1.78 * P.per_wave * busy + (P.splits > 1 ? 2.0 + 1.5e-6 * P.splits * M * L.N : 0.0);
 }
 

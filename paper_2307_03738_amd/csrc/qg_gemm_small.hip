@@ -1297,17 +1297,26 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     }
 
     // 3-bit groups of 32 weights: fp32 all the way, as qg_gemv computes it (X to 2^-30 of the largest of 128 values), the
-    // cheapest of three: the product on int8 matrix instructions, two or three launches; up to 16 rows a matrix-vector
-    // product per row in one launch, with K cut over workgroups (below; 3.3 us and 55 per 10^9 weights times rows) or not.
-    // (A workspace that holds the slots of the call's rows but not the int8 operands keeps the products per row.)
+    // cheapest of three: the product on int8 matrix instructions, two or three launches; a matrix-vector product per row, 16
+    // rows to a launch, with K cut over workgroups (below; 150 products of 2 ... 16 rows, 9 % off) or not.
+    // (A workspace that holds the slots of the call's rows but not the int8 operands keeps the products per row.  Several
+    // launches of rows take more of the caller's time for each row, and cut ones are planned twice: over 48 products of
+    // 17 ... 40 rows the choice takes 1.01 of the best one's time, always the int8 kernel 1.10: int8 | rows 254 x 1696 M = 18
+    // 17.7 | 7.9 us, 964 x 1344 M = 32 15.8 | 8.6.)
     if (M > 1 && qg_rows_i8_takes(L) && workspace_bytes >= qg_gemm_workspace_bytes(L, M)) {
-        const int splits = qg_rows_i8_splits(L, M);
+        const int splits = qg_rows_i8_splits(L, M), full = M / QG_MAX_GROUPED, rest = M % QG_MAX_GROUPED, calls = full + (rest > 0);
         const double us8 = call_us(qg_rows_i8_us(L, M), splits > 1 ? 3 : 2);
-        const double us1 = M <= 16 ? call_us(1.05 * gemv_rows_us(L, M), 1, M) : 1e30;
-        const double cut = M <= 16 ? call_us(3.3 + 55e-9 * 64 * L.tiles * M * L.K, 1, 3 * M) : 1e30;
+        const double rows_us = (full > 0 ? full * gemv_rows_us(L, QG_MAX_GROUPED) : 0.0) + (rest > 0 ? gemv_rows_us(L, rest) : 0.0);
+        const double us1 = call_us(1.05 * rows_us, calls, calls > 1 ? 2 * M : M);
+        const double cut = call_us(calls * (3.55 + 1.3e-4 * L.K) + 65e-9 * 64 * L.tiles * M * L.K, calls, calls > 1 ? 6 * M : 3 * M);
         if (us1 < us8 && us1 <= cut) {
-            const int r = qg_gemv_rows(packed, N, K, bits, group, X, M, Y, stream, price != nullptr);
-            if (r == QG_OK && price) *price = {2, -1, 1, 0, 0, 1, {nullptr, 0, 0}, 0.0};
+            // (the first pass only plans, so that an error leaves nothing enqueued)
+            int r = QG_OK;
+            for (int pass = price || calls > 1 ? 0 : 1; pass < (price ? 1 : 2) && r == QG_OK; ++pass)
+                for (int m0 = 0; m0 < M && r == QG_OK; m0 += QG_MAX_GROUPED)
+                    r = qg_gemv_rows(packed, N, K, bits, group, X + (size_t)m0 * K, M - m0 < QG_MAX_GROUPED ? M - m0 : QG_MAX_GROUPED,
+                                     Y + (size_t)m0 * N, stream, pass == 0);
+            if (r == QG_OK && price) *price = {2, -1, 1, 0, 0, calls, {nullptr, 0, 0}, 0.0};
             if (r != QG_ERR_UNSUPPORTED) return r;
         }
         if (us8 <= cut) {

@@ -1139,8 +1139,13 @@ def test_gemv_k_ending_inside_a_step_non_finite(qg, N, K, bits, group, value):
 
 # 3-bit groups of 32 on the int8 matrix instructions: N, K, M; one, two and four blocks of eight rows, several of those,
 # rows 1 ... 8 in the last; K ending inside a unit of 128, one group in all, K in one range and in several
-@pytest.mark.parametrize("N,K,M", [(2100, 2688, 7), (3000, 4128, 8), (130, 16640, 9), (4000, 1120, 16), (700, 3072, 17), (65, 32, 31),
-                                   (1000, 2080, 33), (300, 8224, 64), (129, 1056, 65), (64, 2048, 128), (20000, 256, 5)])
+# (I8_CASES: those the int8 kernel takes; tests/test_launch_plans.py looks)
+I8_CASES = [(2500, 11008, 7), (5000, 4128, 8), (4000, 4000, 9), (6000, 4128, 16), (700, 3072, 33), (65, 32, 31), (300, 8224, 64), (129, 1056, 65),
+            (64, 2048, 128)]
+
+
+@pytest.mark.parametrize("N,K,M", [(2100, 2688, 7), (3000, 4128, 8), (130, 16640, 9), (4000, 1120, 16), (700, 3072, 17),
+                                   (1000, 2080, 33), (20000, 256, 5)] + I8_CASES)
 def test_gemm_small_3_bit_groups_of_one_cell(qg, oracle, N, K, M):
     bits, group = 3, 32
     _announce("gemm rows int8", N, K, bits, group, M)
@@ -1170,6 +1175,23 @@ def test_gemm_small_3_bit_groups_of_one_cell(qg, oracle, N, K, M):
             assert scaled_error(Yl[m], Y_ref[m], norms, X[m]) <= TOL_FP32, m
 
 
+# ... and as matrix-vector products in several launches (tests/test_launch_plans.py looks): N, K, bits, group, M, launches; the
+# last one of one row and of 16, K cut over workgroups and not, of whole steps and ending inside one
+MANY_ROWS_CASES = [(254, 1696, 3, 32, 17, 2), (261, 4384, 3, 32, 21, 2), (964, 1344, 3, 32, 32, 2), (75, 1536, 3, 32, 18, 2), (1000, 2080, 3, 32, 33, 3)]
+
+
+@pytest.mark.parametrize("N,K,bits,group,M,calls", MANY_ROWS_CASES)
+def test_gemm_small_3_bit_groups_of_one_cell_in_several_launches(qg, oracle, N, K, bits, group, M, calls):
+    _announce("gemm rows in launches", N, K, bits, group, M)
+    W, X = synth.small_case(5330 + N + M, N, K, 0.02, True, m=M)
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    blob = qg.qg_pack(dev(q0), dev(s0), dev(z0), bits, group)
+    Y_ref, norms = oracle.matmul_small(q0, s0, z0, group, X), oracle.row_norms(q0, s0, z0, group)
+    Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X)))
+    for m in range(M):
+        assert scaled_error(Y[m], Y_ref[m], norms, X[m]) <= TOL_FP32, m
+
+
 def test_gemm_small_3_bit_groups_of_one_cell_share_a_workspace(qg, oracle):
     # 8 rows are a product on int8 digits and 16 are matrix-vector products with K cut in two, whose partial sums
     # meet in the workspace: neither finds what the other leaves there, in a buffer as qg_workspace_bytes asks for
@@ -1190,9 +1212,9 @@ def test_gemm_small_3_bit_groups_of_one_cell_share_a_workspace(qg, oracle):
         assert (host(ws)[:slots] == 0xff).all()
 
 
-@pytest.mark.parametrize("N,K,bits,group,M", [(300, 2304, 4, 128, 17), (1062, 640, 2, 128, 5), (700, 3072, 3, 32, 17), (2100, 2688, 3, 32, 7)])
+@pytest.mark.parametrize("N,K,bits,group,M", [(300, 2304, 4, 128, 17), (1062, 640, 2, 128, 5), (700, 3072, 3, 32, 33), (700, 3072, 3, 32, 17), (2100, 2688, 3, 32, 7)])
 def test_gemm_small_chosen_routes_replayed_from_a_graph(qg, N, K, bits, group, M):
-    # own operands with parts, products per row, the int8 kernel with parts, rows with meeting slots: replays give the
+    # own operands with parts, products per row, the int8 kernel with parts, rows with meeting slots in two launches and one: replays give the
     # bits of the eager call, with eager calls in between
     _announce("gemm routes in a graph", N, K, bits, group, M)
     W, X = synth.small_case(5400 + N, N, K, 0.02, True, m=M)

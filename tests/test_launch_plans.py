@@ -2,7 +2,7 @@
 import pytest
 
 from tests.launches import launches
-from tests.test_gpu_parity import M1_CASES, ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
+from tests.test_gpu_parity import I8_CASES, M1_CASES, MANY_ROWS_CASES, ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
 
 
 @pytest.fixture(scope="module")
@@ -113,6 +113,21 @@ def test_one_row_is_a_gemv(tmp, case):
     *before, k = launches(tmp, [{"problem": (*problem, 1)}])[0]["kernels"]
     assert k["name"].startswith("gemv_") and [b["name"] for b in before] == ["fill_u32"] * filled
     assert filled or not k["slots"] or problem[2] != 4
+
+
+# 3-bit groups of 32, more rows than one launch of matrix-vector products takes: those where the int8 kernel's chain of units
+# is the longer way
+@pytest.mark.parametrize("problem,names", [(c, ["gemv_mma4i"] * launches_) for *c, launches_ in MANY_ROWS_CASES] + [
+    ((4096, 4096, 3, 32, 17), ["prepare_rows_i8", "gemm_rows_i8", "add_splits"]), ((9934, 576, 3, 32, 17), ["prepare_rows_i8", "gemm_rows_i8"])])
+def test_3_bit_groups_of_32_beyond_16_rows(tmp, problem, names):
+    assert [k["name"] for k in launches(tmp, [{"problem": problem}])[0]["kernels"]] == names
+
+
+# The GPU tests of the int8 kernel take it, with one, two and four blocks of eight rows, K in one range and in several
+def test_int8_cases_take_that_kernel(tmp):
+    kernels = [r["kernels"] for r in launches(tmp, [{"problem": (N, K, 3, 32, M)} for N, K, M in I8_CASES])]
+    assert all([k["name"] for k in ks][:2] == ["prepare_rows_i8", "gemm_rows_i8"] for ks in kernels)
+    assert {ks[1]["template"][0] for ks in kernels} == {1, 2, 4} and {len(ks) for ks in kernels} == {2, 3}
 
 
 # 4 bits below the sizes where raw codes are taken whatever the estimates say: the dequantizing kernels cut K between
