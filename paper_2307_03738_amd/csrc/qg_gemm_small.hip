@@ -820,6 +820,7 @@ struct CodesPlan {
     bool fused, self;
     int kernels;               // of a call
     double us;                 // what it costs (codes_price)
+    double cut_us;             // ... as blocks of 64 rows are cut by (codes_cut_us)
 };
 
 // Cuts into at most `most` parts per block, one workgroup per compute unit at most where that is possible (a
@@ -858,6 +859,7 @@ struct CodesCost {
     double dealt;                      // of a call whose units are dealt evenly
     double last, last_mb, kernel, kernel_mb;       // adding, by the last workgroup and by a kernel, per MB of parts
     double last_workgroup, last_workgroup_mb, part_mb;      // (who adds: the last workgroup against 1.5 + 0.5 per MB)
+    double cut_unit, cut_weights;      // (codes_cut_us)
     double self_call, self_unit, self_weights, self_dealt, self_round, self_y_mb, self_kernel, self_kernel_mb;     // (codes_self_us; 0: not taken)
     int cus;
     bool by_parts;                     // the last workgroup's time per MB grows with the parts
@@ -866,6 +868,7 @@ CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus, bool se
 {
     static constexpr double SELF_US[2][4] = {{1.14, 1.17, 1.33, 1.64}, {1.80, 1.85, 2.07, 2.46}};
     static constexpr double UNIT_US[3][5] = {{1.0, 1.05, 1.2, 1.45, 2.0}, {1.0, 1.02, 1.18, 1.45, 2.0}, {1.36, 1.38, 1.65, 2.15, 3.2}};
+    static constexpr double CUT_UNIT_US[5] = {1.35, 1.4, 1.65, 2.15, 3.2};
     CodesCost C;
     C.part_mb = 4e-6 * M * (double)L.N;
     C.cus = cus;
@@ -873,6 +876,8 @@ CodesCost codes_cost(const QgLayout &L, int gps, int M, int mb, int cus, bool se
     C.last_workgroup = mb == 1 ? 1.5 : 4.6;
     C.last_workgroup_mb = mb == 1 ? 0.3 : 0.1;
     C.unit = UNIT_US[M <= 32 ? 0 : mb][gps == 0 ? 0 : gps == 1 ? 1 : gps == 2 ? 2 : gps == 4 ? 3 : 4];
+    C.cut_unit = CUT_UNIT_US[gps == 0 ? 0 : gps == 1 ? 1 : gps == 2 ? 2 : gps == 4 ? 3 : 4];
+    C.cut_weights = L.bits == 4 ? 0.5 : L.bits == 3 ? 0.35 : 0.1;
     C.self_call = 0.0;
     if (self && mb == 1 && gps <= 4) {
         C.self_unit = SELF_US[M <= 32 ? 0 : 1][gps == 4 ? 3 : gps];
@@ -956,6 +961,20 @@ void codes_price(CodesPlan &P, const CodesCost &C)
     }
 }
 
+// By which the cuts of blocks of 64 rows are compared: the line fitted through cuts of 2 ... 128 rows.  (The one above, through
+// cuts of more than 32 rows, tells blocks of 32 from blocks of 64, but takes dealt units for 10 to 16 % less than they
+// need on a long K: 14611 x 6784 2-bit M = 70 34.3 us for 39.1 in dealt units, 36.0 as cut here; 7614 x 20608 3-bit M = 90 52.6
+// for 62.8, 58.2.)
+double codes_cut_us(const CodesPlan &P, const CodesCost &C)
+{
+    const int rounds = (P.workgroups + C.cus - 1) / C.cus;
+    double us = rounds * P.quota * (C.cut_unit + C.cut_weights * (rounds > 1 ? 1.0 : (double)P.workgroups / C.cus));
+    if (P.ranges == 0) us += 1.4;
+    const double mb = P.parts * C.part_mb;
+    if (P.parts > 1) us += P.fused ? C.last_workgroup + C.last_workgroup_mb * (P.parts - 1) * mb : 1.5 + 0.5 * mb;
+    return us;
+}
+
 // The best of the cuts into at most 1 ... 8 parts by what they cost; a forced count (the search's, too) takes the one cut.
 // A count that would need more workgroups than compute units is dealt evenly over those.
 CodesPlan codes_plan_rows(const QgLayout &L, int gps, int M, int mb, int knob_splits, bool by_number)
@@ -985,7 +1004,8 @@ CodesPlan codes_plan_rows(const QgLayout &L, int gps, int M, int mb, int knob_sp
         codes_cut(c, most, room, even);
         if (c.quota == last.quota && c.ranges == last.ranges) continue;        // (priced already)
         codes_price(c, cost);
-        if (most == 1 || c.us < best.us) best = c;
+        if (mb == 2) c.cut_us = codes_cut_us(c, cost);
+        if (most == 1 || (mb == 2 ? c.cut_us < best.cut_us : c.us < best.us)) best = c;
         last = c;
     }
     return best;

@@ -90,6 +90,15 @@ def test_row_block_cases_are_cut_as_stated(tmp, case):
     assert ("add_parts" in names) == (parts > 1 and not fused)
 
 
+# Blocks of 64 rows: whole ranges of K where units dealt evenly measured slower (ranges), and dealt (0) where faster
+@pytest.mark.parametrize("problem,ranges", [
+    ((14611, 6784, 2, 128, 70), 2), ((7614, 20608, 3, 64, 90), 4), ((7702, 10464, 2, 32, 86), 4), ((9374, 17408, 4, 128, 116), 3),
+    ((6991, 8320, 2, 64, 70), 4), ((22016, 8192, 2, 32, 128), 0)])
+def test_blocks_of_64_rows_are_cut_as_measured(tmp, problem, ranges):
+    k, _ = _product(launches(tmp, [{"problem": problem}])[0])
+    assert (k["template"][2], k["args"]["ranges"]) == (2, ranges)
+
+
 @pytest.mark.parametrize("case", SELF_CASES)
 def test_own_operand_cases_are_cut_as_stated(tmp, case):
     *problem, parts = case
