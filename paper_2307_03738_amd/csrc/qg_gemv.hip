@@ -2012,16 +2012,15 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
             size_t most = bits_all == 4 ? 65536 : 49152;
             // (groups of one or two cells: a wavefront holds at most 64 groups, and half of that
             // measured faster than all of it)
-            if (in_step && pl[0].max_spw <= 8) most = (size_t)pl[0].max_spw * pl[0].item_bytes / 2;
+            const bool short_groups = in_step && pl[0].max_spw <= 8;
+            if (short_groups) most = (size_t)pl[0].max_spw * pl[0].item_bytes / 2;
             target = share < 4096 ? 4096 : share > most ? most : share;
-            // 4 bits on int8: six steps a wavefront for several matrices below 64 MB of codes, twelve from 96 MB on (a share of the
-            // launch lay between, which cut short K into chunks of uneven steps): 15 layer sets of 32 to 63 MB 0.93 of the
-            // time, 29 launches from 96 MB on 0.97; 2560 / 6912 g64 10.9 -> 9.6 us.  Between, and for one matrix,
-            // the share is the better or as good: 4096 / 10752 g128, 93 MB, 21.7 | 23.9 with six, gated 2 x 11008 x 4096 10.7 | 10.9.
-            if (bits_all == 4 && mul == MUL_MMA4I && most == 65536) {
-                if (count > 1 && code_bytes < ((size_t)64 << 20)) target = 6 * pl[0].item_bytes;
-                else if (code_bytes >= ((size_t)96 << 20)) target = 12 * pl[0].item_bytes;
-            }
+            // Several 4-bit matrices on int8 below 64 MiB of codes, groups of more than two cells: six steps a wavefront (a share of
+            // the launch lay between, which cut short K into chunks of uneven steps): 24 layer sets of 32 to 64 MiB 0.95 of
+            // the time, the slowest 1.005; 2560 / 6912 g64 10.9 -> 9.6 us.  Beyond, and for one matrix, the share is the better or
+            // as good: 4096 / 10752 g128, 95 MiB, 21.7 | 23.9 with six, gated 2 x 11008 x 4096 10.7 | 10.9; with twelve, 150
+            // launches of 96 to 256 MiB 1.004, 20992 x 17152 g64 40.3 | 44.1.
+            if (bits_all == 4 && mul == MUL_MMA4I && !short_groups && count > 1 && code_bytes < ((size_t)64 << 20)) target = 6 * pl[0].item_bytes;
         }
     }
     if (one_chunk && mma && t_cur.wpb == 0) cap = 8;

@@ -26,7 +26,8 @@ class RowsI8Args(ctypes.Structure):
 class GemvProblem(ctypes.Structure):
     """One problem of a GEMV launch, up to the meeting slots and the cuts of K."""
     _fields_ = [(n, ctypes.c_void_p) for n in ("codes", "scales", "zeros", "x", "y", "slots")] + \
-        [(n, ctypes.c_int32) for n in ("N", "K", "tiles", "steps", "ngroups", "zwords", "group", "chunks")] + [("rest", ctypes.c_ubyte * 176)]
+        [(n, ctypes.c_int32) for n in ("N", "K", "tiles", "steps", "ngroups", "zwords", "group", "chunks", "chunk_shift", "team", "inv_team",
+                                       "team_full", "tiles_per_block", "steps_per_wave")] + [("rest", ctypes.c_ubyte * 152)]
 
 
 class GemvArgs(ctypes.Structure):
@@ -34,6 +35,14 @@ class GemvArgs(ctypes.Structure):
 
 
 WORKSPACE = 1 << 32
+
+
+class GemvDesc(ctypes.Structure):
+    """qg_gemv_desc"""
+    _fields_ = [("packed", ctypes.c_void_p), ("N", ctypes.c_int64), ("K", ctypes.c_int64), ("bits", ctypes.c_int32), ("group", ctypes.c_int32),
+                ("x", ctypes.c_void_p), ("y", ctypes.c_void_p)]
+
+
 SLOTS_PER_TILE = 33 * 64 * 4           # bytes of meeting slots per tile of 64 outputs
 
 
@@ -47,10 +56,17 @@ def _run(stub_path, lib_path, calls):
     L.qg_workspace_bytes.argtypes = [i64, i64, i32, i32, i32]
     L.qg_gemm_autotune.argtypes = [ctypes.POINTER(vp), i32, i64, i64, i32, i32, vp, i32, vp, vp, ctypes.c_size_t, vp, i32, vp, vp, vp]
     L.qg_gemm_small.argtypes = [vp, i64, i64, i32, i32, vp, i32, vp, vp, ctypes.c_size_t, vp]
+    L.qg_gemv_grouped.argtypes = [vp, i32, vp, ctypes.c_size_t, vp]
     out = []
     for c in calls:
         stub.stub_clear()
         stub.stub_device(c.get("device", 0))
+        if "grouped" in c:
+            d = (GemvDesc * len(c["grouped"]))(*[GemvDesc(1 << 20, N, K, bits, group, 1 << 20, 1 << 20) for N, K, bits, group in c["grouped"]])
+            status = L.qg_gemv_grouped(d, len(d), WORKSPACE, 1 << 40, None)
+            problems = [p for i in range(stub.stub_launches()) for a in [GemvArgs.from_address(stub.stub_args(i))] for p in a.p[:a.count]]
+            out.append({"status": status, "cuts": [(p.N, p.K, p.team, p.chunks, p.steps_per_wave) for p in problems]})
+            continue
         N, K, bits, group, M = c["problem"]
         assert L.qg_set_gemm_tuning(c.get("splits", 0), c.get("shape", 0)) == 0
         size = c.get("size") or L.qg_workspace_bytes(N, K, bits, group, M)
@@ -93,7 +109,8 @@ def _run(stub_path, lib_path, calls):
 
 def launches(tmp_path, calls):
     """calls: dicts with problem = (N, K, bits, group, M) of qg_gemm_small and, optionally, splits and shape
-    (qg_set_gemm_tuning), device and the workspace's size, or search = True for qg_gemm_autotune.  Returns per call its status and
+    (qg_set_gemm_tuning), device and the workspace's size, or search = True for qg_gemm_autotune; or grouped = [(N, K, bits, group), ...] of qg_gemv_grouped, which
+    returns (N, K, wavefronts of a team, cuts of K over workgroups, steps of a wavefront) per problem.  Returns per call its status and
     the kernels it launches, or the times of the search's candidates (-1: not timed)."""
     from paper_2307_03738_amd import build
     stub = os.path.join(str(tmp_path), "hip_stub.so")

@@ -165,3 +165,14 @@ def test_int8_operands_stay_out_of_the_meeting_slots(tmp, N, K):
         reads = [s for k in kernels for s in k.get("slots", [])]
         assert results and all(a >= 0 and b <= size for a, b in writes + reads)
         assert not reads or all(a >= max(b for _, b in reads) for a, _ in writes)
+
+
+# 4-bit matrix-vector products: the steps of a wavefront go by the launch's codes beyond 64 MiB and for one matrix; several matrices of
+# 32 to 64 MiB take about six
+@pytest.mark.parametrize("problems,steps", [
+    ([(20992, 17152, 4, 64)], [17]), ([(41856, 9472, 4, 64)], [19]), ([(39424, 11008, 4, 128)], [15]), ([(16384, 8192, 4, 64)], [6]),
+    ([(5120, 5120, 4, 32)] * 4 + [(12032, 5120, 4, 32)] * 2 + [(5120, 12032, 4, 32)], [14, 16]),
+    ([(2560, 2560, 4, 64)] * 4 + [(6912, 2560, 4, 64)] * 2 + [(2560, 6912, 4, 64)], [7])])
+def test_steps_of_a_4_bit_wavefront(tmp, problems, steps):
+    result, = launches(tmp, [{"grouped": problems}])
+    assert result["status"] == 0 and sorted({cut[4] for cut in result["cuts"]}) == steps
