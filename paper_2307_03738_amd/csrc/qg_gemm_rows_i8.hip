@@ -252,16 +252,16 @@ RowsI8Plan rows_i8_plan(const QgLayout &L, int M)
     P.units = (int)((L.K + UNIT_K - 1) / UNIT_K);
     // two wavefronts per SIMD, each with two units of K at least
     const int64_t waves = L.tiles * P.zblocks * SLICES, want = (int64_t)qg_compute_units() * 8;
+    int most = P.units / (2 * SLICES) < 8 ? P.units / (2 * SLICES) : 8;
+    if (most < 1) most = 1;
     int splits = (int)((want + waves - 1) / waves);
-    if (splits > 8) splits = 8;
-    if (splits > P.units / (2 * SLICES)) splits = P.units / (2 * SLICES);
-    if (splits < 1) splits = 1;
+    if (splits > most) splits = most;
     P.per_wave = (P.units + splits * SLICES - 1) / (splits * SLICES);
     P.splits = (P.units + P.per_wave * SLICES - 1) / (P.per_wave * SLICES);
     P.inverse_off = (size_t)P.blocks * P.units * 4 * 1024;
     P.partial_off = qg_round_up(P.inverse_off + (size_t)P.blocks * P.units * 8 * sizeof(float), QG_SECTION_ALIGN);
-    // (as many parts as any device's plan may take)
-    P.total = qg_round_up(P.partial_off + (size_t)8 * M * L.N * sizeof(float), QG_SECTION_ALIGN);
+    // (as many parts as any device's plan may take; a K of up to 1920 is in one)
+    P.total = qg_round_up(P.partial_off + (most > 1 ? (size_t)most * M * L.N * sizeof(float) : 0), QG_SECTION_ALIGN);
     return P;
 }
 

@@ -124,6 +124,16 @@ def test_one_row_is_a_gemv(tmp, case):
     assert filled or not k["slots"] or problem[2] != 4
 
 
+# ... and of as many parts as a K of that length can be cut into
+@pytest.mark.parametrize("N,K,M,parts", [(22016, 1024, 128, 0), (22016, 1920, 128, 0), (22016, 1952, 128, 2), (1000, 2080, 40, 2), (300, 8224, 128, 8)])
+def test_int8_workspace_holds_the_parts_of_a_long_k_alone(tmp, N, K, M, parts):
+    result, = launches(tmp, [{"problem": (N, K, 3, 32, M)}])
+    units, blocks = (K + 127) // 128, (M + 7) // 8
+    operands = blocks * units * (4096 + 32)
+    assert 0 <= result["size"] - 16 * 8448 * ((N + 63) // 64) - operands - 4 * parts * M * N < 1024
+    assert all(b <= result["size"] for k in result["kernels"] for _, b in k.get("writes", []))
+
+
 # 3-bit groups of 32, more rows than one launch of matrix-vector products takes: those where the int8 kernel's chain of units
 # is the longer way
 @pytest.mark.parametrize("problem,names", [(c, ["gemv_mma4i"] * launches_) for *c, launches_ in MANY_ROWS_CASES] + [
