@@ -288,8 +288,8 @@ int qg_set_gemm_tuning(int splits, int shape);
 /* The launch-shape search of qg_gemm_small for one problem (N, K, bits, group, M) -- Section 3,
  * Algorithm 4 with the resource model of eqs. (3)-(5), on this machine's terms.  The 120
  * candidates are the 15 values of `shape` above (0, -1, 1..13) x 1..8 K ranges.  Each is planned
- * without being launched and priced: raw-code cuts as the built-in choice prices them, the dequantizing
- * kernels by the registers per lane and LDS per workgroup of the instance, which give the workgroups the chip
+ * without being launched and priced: raw-code cuts by what the built-in choice expects of their kernels, the
+ * dequantizing kernels by the registers per lane and LDS per workgroup of the instance, which give the workgroups the chip
  * holds at once and so the rounds the launch needs; a round costs a workgroup's fixed time (3.3 us) plus
  * its iterations (2 us each), every further kernel of the call 3 us.  Candidates the planner maps to a plan already seen are skipped, candidates
  * priced above 1.5 times the cheapest are dropped (never the built-in choice), the others run the product `repeats` times,

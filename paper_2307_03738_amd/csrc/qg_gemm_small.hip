@@ -819,7 +819,7 @@ struct CodesPlan {
     int mb, tn, kw, zblocks, blocks, units, ranges, quota, workgroups, parts;
     bool fused, self;
     int kernels;               // of a call
-    double us;                 // what it costs (codes_price)
+    double us, kernels_us;     // what it costs, and what its kernels take of that (codes_price)
     double cut_us;             // ... as blocks of 64 rows are cut by (codes_cut_us)
 };
 
@@ -930,7 +930,7 @@ double codes_self_us(const CodesPlan &P, const CodesCost &C)
     return us;
 }
 constexpr double CODES_LEAST_US = 4.8;       // what no plan's kernels are priced below
-// Sets P.us and, with it, who makes the A operands and who adds the parts.
+// Sets P.us, P.kernels_us and, with them, who makes the A operands and who adds the parts.
 void codes_price(CodesPlan &P, const CodesCost &C)
 {
     P.us = C.call;
@@ -948,12 +948,14 @@ void codes_price(CodesPlan &P, const CodesCost &C)
         P.us += P.fused ? C.last + C.last_mb * mb : C.kernel + C.kernel_mb * mb;
     }
     P.kernels = P.parts > 1 && !P.fused ? 3 : 2;
+    P.kernels_us = P.us;
     P.us = call_us(P.us, P.kernels);
     if (C.self_call > 0.0) {
         const int kernels = P.parts > 1 ? 2 : 1;
-        const double us = call_us(codes_self_us(P, C), kernels);
+        const double kernels_us = codes_self_us(P, C), us = call_us(kernels_us, kernels);
         if (us < P.us) {
             P.us = us;
+            P.kernels_us = kernels_us;
             P.kernels = kernels;
             P.self = true;
             P.fused = false;
@@ -1069,7 +1071,7 @@ struct GemmPrice {
     long iterations;           // barrier-to-barrier iterations one workgroup runs one after the other
     int launches;              // kernels the call enqueues
     KernelInfo kernel;
-    double us;                 // family 0: what the plan says it costs
+    double us;                 // family 0: what the plan says its kernels take
 };
 
 // The built-in plan of the dequantizing kernels: shape (index into SHAPES), workgroups along N and M, K ranges.
@@ -1286,7 +1288,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         const int have = main_kernel(&info);
         if (have != QG_OK) return have;
         if (price) {
-            *price = {0, NSHAPES + (M > 32 && C.mb == 1) + 2 * C.self, C.ranges, (long)C.workgroups, C.quota, C.kernels, info, C.us};
+            *price = {0, NSHAPES + (M > 32 && C.mb == 1) + 2 * C.self, C.ranges, (long)C.workgroups, C.quota, C.kernels, info, C.kernels_us};
             return QG_OK;
         }
         if (!C.self) {
@@ -1441,10 +1443,10 @@ extern "C" int qg_gemm_small(const void *packed, int64_t N, int64_t K, int bits,
 // (Section 3, Algorithm 4, with the resource model of eqs. (3)-(5)) for this call.  Candidates
 // are (kernel family / workgroup shape) x (number of K ranges).  Each is planned without being
 // launched (a shape that does not fit the problem falls back to the built-in one, and a plan
-// seen before is not tried again) and priced: a raw-code cut as the built-in plan prices it, the dequantizing
-// kernels by the registers per lane and the LDS per workgroup of the instance, which give the workgroups the
-// chip holds at once, hence the rounds the launch needs; a round costs a workgroup's fixed time plus its
-// iterations, and every further kernel of the call a launch.
+// seen before is not tried again) and priced by its kernels: a raw-code cut by the built-in plan's estimate of
+// them without the caller's time, the dequantizing kernels by the registers per lane and the LDS per workgroup
+// of the instance, which give the workgroups the chip holds at once, hence the rounds the launch needs; a round
+// costs a workgroup's fixed time plus its iterations, and every further kernel of the call a launch.
 // Candidates priced above 1.5 times the cheapest are dropped, except the plan of the built-in choice, so that
 // the search never records a slower one; the others are timed.
 namespace {

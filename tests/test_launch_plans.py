@@ -59,6 +59,13 @@ def test_search_times_the_built_in_plan(tmp, problem):
     assert results[9]["us"][same[0] - 1] >= 0          # shape 0 (built-in kernel), that many ranges
 
 
+# ... and prices the raw-code cuts on the scale of the others: some of them on the kernel asked for by number are timed
+@pytest.mark.parametrize("problem", [(8192, 8192, 4, 32, 40), (5120, 5120, 4, 128, 64)])
+def test_search_times_raw_code_cuts(tmp, problem):
+    result, = launches(tmp, [{"problem": problem, "search": True}])
+    assert result["status"] == 0 and any(us >= 0 for us in result["us"][14 * 8:])
+
+
 # The GPU test of the cuts of K takes the cuts it names
 @pytest.mark.parametrize("case", [c for c in UNIT_CASES if c[6] is not None])
 def test_unit_cases_are_cut_as_stated(tmp, case):
