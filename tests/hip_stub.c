@@ -58,7 +58,7 @@ int hipLaunchKernel(const void *f, dim3_t g, dim3_t b, void **args, size_t lds, 
     launch[n_launch].kernel = k; launch[n_launch].device = device;
     launch[n_launch].grid = g; launch[n_launch].block = b; launch[n_launch].lds = lds;
     /* the argument struct: QgCodesArgs, QgRowsI8Args, GemvArgs */
-    if (strstr(known[k].name, "gemm_codes")) memcpy(launch[n_launch].args, args[0], 120);
+    if (strstr(known[k].name, "gemm_codes")) memcpy(launch[n_launch].args, args[0], 144);
     if (strstr(known[k].name, "gemm_rows_i8")) memcpy(launch[n_launch].args, args[0], 80);
     if (strstr(known[k].name, "gemv_")) memcpy(launch[n_launch].args, args[3], 4224);
     ++n_launch;

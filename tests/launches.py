@@ -14,7 +14,8 @@ class CodesArgs(ctypes.Structure):
     """Arguments of the raw-code product kernel (QgCodesArgs)."""
     _fields_ = [(n, ctypes.c_void_p) for n in ("codes", "scales", "zeros", "Xop", "Y", "partial", "arrived")] + \
         [(n, ctypes.c_int32) for n in ("M", "N", "tiles", "tile_codes", "tile_scales", "tile_zeros", "steps_padded",
-                                       "group_magic", "zshift", "units", "ranges", "quota", "total", "fused", "kw")]
+                                       "group_magic", "zshift", "units", "ranges", "quota", "total", "fused", "kw", "zblocks", "per_die",
+                                       "self", "K")] + [("X", ctypes.c_void_p)]
 
 
 class RowsI8Args(ctypes.Structure):

@@ -466,6 +466,31 @@ def test_gemv_k_ending_inside_a_step(qg, oracle, N, K, bits, group):
         assert np.all(np.abs(h - ref) <= 1.1 * eg * (np.abs(u) + eu) + np.abs(g) * eu + 1e-6 * np.abs(ref))
 
 
+@pytest.mark.parametrize("outlier", [1e4, 1e9])
+@pytest.mark.parametrize("N,K,bits,group", [(130, 4160, 4, 64), (130, 4160, 3, 32), (70, 1040, 2, 16), (130, 4224, 3, 128)])
+def test_gemv_k_ending_inside_a_step_small_values_beside_large(qg, oracle, N, K, bits, group, outlier):
+    # x goes in as fixed point relative to the largest |x| of each run of 128 (4 bits) or 256 k, and loses 2^-30 of that per
+    # term at most (include/qg.h): shown on outputs whose weights are zero wherever x is large
+    _announce("gemv ragged K, outliers", N, K, bits, group, outlier)
+    run = 128 if bits == 4 else 256
+    W, x = synth.small_case(5310 + N, N, K, 0.02, False)
+    large = np.arange(5, K, run)
+    for k in large:
+        W[:, k // group * group:(k // group + 1) * group] = 0
+    x[large] *= np.float32(outlier)
+    q0, s0, z0 = oracle.quantize(W, bits, group)
+    blob = qg.qg_pack(dev(q0), dev(s0), dev(z0), bits, group)
+    y = host(qg.qg_gemv(blob, N, K, bits, group, dev(x)))
+    assert qg.qg_last_gemv_kernel().endswith(", ragged>")
+    ax = np.abs(x.astype(np.float64))
+    most = np.repeat([ax[k:k + run].max() for k in range(0, K, run)], run)[:K]
+    s, z, q = (np.repeat(s0, group, 1).astype(np.float64), np.repeat(z0, group, 1).astype(np.float64), q0.astype(np.float64))
+    # per output: the fixed point, and fp32 sums of the groups' q x and z x (at most 2^3 roundings deep in lanes, teams and chunks, of
+    # 2^-24 each, around sums of at most 2^5 groups and steps in sequence)
+    bound = (s * q * 2.0 ** -30 * most).sum(1) + 2.0 ** -18 * (s * (q + z) * ax).sum(1)
+    assert np.all(np.abs(y - oracle.matvec(q0, s0, z0, group, x)) <= bound)
+
+
 @pytest.mark.parametrize("tuning", [(1, 4096, 1), (2, 4096, 1), (4, 8192, 1), (8, 4096, 1), (16, 4096, 1), (4, 65536, 1),
                                     (1, 4096, 2), (3, 8192, 2), (8, 4096, 2), (16, 4096, 2), (4, 65536, 2),
                                     (1, 4096, 3), (3, 8192, 3), (8, 4096, 3), (4, 65536, 3),
@@ -1020,8 +1045,8 @@ def test_gemm_small_blocks_of_32_rows(qg, oracle, N, K, bits, group, M, blocks, 
 
 
 # A operands made by the product kernel (tests/test_launch_plans.py looks): N, K, bits, group, M, parts of a sum
-# (0: units dealt evenly).  Every # number of groups per step and width; 2 to 16 rows (one wavefront per step converts), 17 and more (two), several
-# blocks of rows with 1 ... 32 in the last; K of less than a step, ending inside a step and inside a unit; one unit
+# (0: units dealt evenly).  Every number of groups per step and width; up to 16 rows in a block (one wavefront per step
+# converts), 17 and more (two), several blocks of rows with 1 ... 32 in the last; K of less than a step, ending inside a step and inside a unit; one unit
 # and several per workgroup, units dealt evenly
 SELF_CASES = [
     (300, 2304, 4, 128, 17, 5), (70, 1280, 4, 1280, 32, 3), (260, 1024, 2, 64, 31, 2), (330, 1536, 3, 128, 30, 3),

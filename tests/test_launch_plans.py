@@ -73,7 +73,7 @@ def test_unit_cases_are_cut_as_stated(tmp, case):
     k, names = _product(launches(tmp, [{"problem": problem, "splits": splits, "shape": 13}])[0])
     a = k["args"]
     most = a["ranges"] or (a["units"] + a["quota"] - 2) // a["quota"] + 1
-    assert (a["ranges"] == 0, most, a["fused"], 1 << a["zshift"]) == (dealt, parts, fused, row_blocks)
+    assert (a["ranges"] == 0, most, a["fused"], a["zblocks"]) == (dealt, parts, fused, row_blocks)
     assert ("add_parts" in names) == (parts > 1 and not fused)
 
 
@@ -110,7 +110,7 @@ def test_blocks_of_64_rows_are_cut_as_measured(tmp, problem, ranges):
 def test_own_operand_cases_are_cut_as_stated(tmp, case):
     *problem, parts = case
     k, names = _product(launches(tmp, [{"problem": problem}])[0])
-    assert (k["template"][2], k["template"][5]) == (1, 2) and k["args"]["ranges"] == parts
+    assert (k["template"][2], k["template"][5], k["args"]["self"]) == (1, 2, 1) and k["args"]["ranges"] == parts
     assert names == ["gemm_codes"] + ["add_parts"] * (parts != 1)
 
 
