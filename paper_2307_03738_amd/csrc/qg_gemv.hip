@@ -1119,10 +1119,7 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
         }
     const lds_u8 *abase[2] = {&xs[wave][0][lane & 3][0], &xs[wave][1][lane & 3][0]};
 
-    // Fixed point of the step: |x| scale < 2^30 for the largest |x| of the step.  Returns 1 / scale, or, where an infinity has to
-    // make y NaN (rows of qg_gemm_small; a K that ends inside a step, as on gemv_generic), a NaN: the sum of the codes would count
-    // the infinity as 2^31 and -z xhat alone would give y its sign.
-    const uint32_t infinite = RAGGED || P.rows > 0 ? 255u : 256u;
+    // Fixed point of the step: |x| scale < 2^30 for the largest |x| of the step.  Returns 1 / scale.
     auto stage_x = [&](const D &d, int buf) -> float {
         float m = 0.0f;
 #pragma unroll
@@ -1134,7 +1131,6 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
         m = dpp_max<QG_DPP_BCAST15, 0xa>(m);
         m = dpp_max<QG_DPP_BCAST31, 0xc>(m);
         uint32_t eb = (uint32_t)__builtin_amdgcn_readlane(__float_as_int(m), 63) >> 23;   // biased exponent
-        const bool to_nan = eb >= infinite;
         eb = eb < 30u ? 30u : eb > 254u ? 254u : eb;
         const float scale = __uint_as_float((283u - eb) << 23);                             // 2^(156 - eb)
 #pragma unroll
@@ -1152,7 +1148,7 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
                 xs[wave][buf][3][xpos[i][e]] = (uint8_t)(pat >> 24);
             }
         }
-        return __uint_as_float(to_nan ? 0x7fc00000u : (eb - 29u) << 23);                    // 2^(eb - 156)
+        return __uint_as_float((eb - 29u) << 23);                                           // 2^(eb - 156)
     };
 
     float yacc = 0.0f;
@@ -1276,6 +1272,15 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
         compute(db, sb, 1, inv_b);
         close_group(sb);
         inv_a = stage_x(da, 0);
+    }
+    // An infinity has to make y NaN on rows of qg_gemm_small and where K ends inside a step (as on gemv_generic).  The sum of the codes
+    // counts it as 2^31, so y comes out as -z xhat, infinite or NaN: x is looked through again where that has happened.  (Seen in
+    // stage_x instead, it cost registers: 2-bit g32 62 -> 66 of them, seven wavefronts per SIMD for eight, 1.5 % of C4's time.)
+    if ((RAGGED || P.rows > 0) && __any(fabsf(yacc) == __builtin_inff())) {
+        bool infinite = false;
+        const int end = s1 * S < P.K ? s1 * S : P.K;
+        for (int k = s0 * S + lane; k < end; k += QG_WAVE) infinite |= fabsf(P.x[k]) == __builtin_inff();
+        if (__any(infinite)) yacc = __uint_as_float(0x7fc00000u);
     }
     finish_tile(P, job, yacc, red);
 }
