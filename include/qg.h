@@ -185,9 +185,11 @@ int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group
  * 8448); below that whichever the planner's estimates say is the faster (groups of one per output nearly always
  * the second).  At 2 ... 16 rows its estimates choose between the second way, at 4 bits a kernel on codes without a
  * split of K over workgroups, and, for small products, qg_gemv's arithmetic (fp32, X not rounded) once per row in one
- * launch that needs nothing of the workspace.  qg_set_gemm_tuning and qg_gemm_autotune choose otherwise.
+ * launch that needs nothing of the workspace.  (The estimates count the caller's time, 3 us a call and 2 a launch, against that of
+ * the kernels: of two ways a graph may replay the one with more and shorter kernels faster.)  qg_set_gemm_tuning and
+ * qg_gemm_autotune choose otherwise.
  * 3-bit groups of 32: fp32 throughout, X as 32-bit fixed point relative to the largest |x| of each run of 128 k, on int8
- * matrix instructions (two or three kernels) or, for few rows, as below.  (The fixed point keeps its precision while the
+ * matrix instructions (two or three kernels) or, where that is estimated to be faster, as below.  (The fixed point keeps its precision while the
  * largest |x| of a run is at least 2^-96.)
  * Every other layout (odd numbers of cells per group, K % 16 != 0 only with M == 1) runs
  * qg_gemv once per row in fp32, 16 rows per launch; with K % 16 != 0 and M > 1 the call returns

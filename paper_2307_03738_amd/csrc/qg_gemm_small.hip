@@ -1018,7 +1018,9 @@ CodesPlan codes_plan_rows(const QgLayout &L, int gps, int M, int mb, int knob_sp
 // cut into a quarter of the parts, which is more wherever tiles are few.  us per call, blocks of 64 | 32: 5120 x 5120 2-bit
 // g32 M = 48 20.1 | 16.3, 4096 x 4096 3-bit g64 M = 64 17.0 | 13.3, 13824 x 5120 3-bit g64 M = 37 21.5 | 20.6; 22016 x 8192
 // 2-bit g32 M = 128 76 | 90.  Over 504 products of 33 ... 128 rows at 2 and 3 bits the choice takes 0.90 of the time of
-// blocks of 64 alone, the best cut of either kind 0.88.
+// blocks of 64 alone, the best cut of either kind 0.88.  (All on weights that the last-level cache holds.  From memory blocks of 32 lose
+// more, 13824 x 5120 M = 37 23.2 | 24.8, 4096 x 11008 4-bit M = 128 27.2 | 30.0; the choice then takes 0.90 over 120 products.  Where the
+// prices are within 3 % of each other either kind is the faster one, 0.88 ... 1.08.)
 // A forced count on the kernel asked for by number (shape 13) keeps blocks of 64, and that kernel's operands come
 // from prepare_x.
 CodesPlan codes_plan(const QgLayout &L, int gps, int M, int knob_splits, bool by_number)
