@@ -58,7 +58,7 @@ struct alignas(128) GemvProblem {
     int block_begin;       // first block of this problem in the grid
     int pair_tiles;        // > 0: outputs [0, 64 pair_tiles) gate outputs [64 pair_tiles, ...), see emit_output
     float *h;              // gated result (pair_tiles > 0)
-    int rows;              // gemm_rows16: activation rows M (x is X [M][K], y is Y [M][N]); else 1 for a row of a qg_gemm_small call
+    int rows;              // gemm_rows16 only: activation rows M (x is X [M][K], y is Y [M][N])
 };
 
 // Every field of a problem entry in scalar registers at one point: the loads that fetch the
@@ -1066,7 +1066,8 @@ __device__ inline float dpp_max(float v)             // for v >= 0: disabled row
     return fmaxf(v, __int_as_float(moved));
 }
 
-template <int BITS, int CPG, bool RAGGED = false>
+// ROWS: the problems are rows of a qg_gemm_small call (infinities, below).
+template <int BITS, int CPG, bool RAGGED = false, bool ROWS = false>
 __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArgs A)
 {
     static_assert(!RAGGED || CPG > 0, "groups of whole steps end with a step");
@@ -1275,12 +1276,15 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
     }
     // An infinity has to make y NaN on rows of qg_gemm_small and where K ends inside a step (as on gemv_generic).  The sum of the codes
     // counts it as 2^31, so y comes out as -z xhat, infinite or NaN: x is looked through again where that has happened.  (Seen in
-    // stage_x instead, it cost registers: 2-bit g32 62 -> 66 of them, seven wavefronts per SIMD for eight, 1.5 % of C4's time.)
-    if ((RAGGED || P.rows > 0) && __any(fabsf(yacc) == __builtin_inff())) {
-        bool infinite = false;
-        const int end = s1 * S < P.K ? s1 * S : P.K;
-        for (int k = s0 * S + lane; k < end; k += QG_WAVE) infinite |= fabsf(P.x[k]) == __builtin_inff();
-        if (__any(infinite)) yacc = __uint_as_float(0x7fc00000u);
+    // stage_x instead, it cost registers: 2-bit g32 62 -> 66 of them, seven wavefronts per SIMD for eight; and in one instance for rows
+    // and others, 3-bit g64 lost 1 to 2 %.)
+    if constexpr (RAGGED || ROWS) {
+        if (__builtin_expect(__any(fabsf(yacc) == __builtin_inff()), 0)) {
+            bool infinite = false;
+            const int end = s1 * S < P.K ? s1 * S : P.K;
+            for (int k = s0 * S + lane; k < end; k += QG_WAVE) infinite |= fabsf(P.x[k]) == __builtin_inff();
+            if (__any(infinite)) yacc = __uint_as_float(0x7fc00000u);
+        }
     }
     finish_tile(P, job, yacc, red);
 }
@@ -1841,23 +1845,25 @@ GemvKernel pick_mma4(int cpg)
     }
 }
 
-template <int BITS>
-GemvKernel pick_mma4i(int cpg)
+template <int BITS, bool ROWS>
+GemvKernel pick_mma4i_of(int cpg)
 {
     switch (cpg) {
-    case 0: return gemv_mma4i<BITS, 0>;
+    case 0: return gemv_mma4i<BITS, 0, false, ROWS>;
     case 1:
-        if constexpr (BITS != 4) return gemv_mma4i<BITS, 1>;
+        if constexpr (BITS != 4) return gemv_mma4i<BITS, 1, false, ROWS>;
         return nullptr;
-    case 2: return gemv_mma4i<BITS, 2>;
-    case 4: return gemv_mma4i<BITS, 4>;
-    case 8: return gemv_mma4i<BITS, 8>;
+    case 2: return gemv_mma4i<BITS, 2, false, ROWS>;
+    case 4: return gemv_mma4i<BITS, 4, false, ROWS>;
+    case 8: return gemv_mma4i<BITS, 8, false, ROWS>;
     case 16:
-        if constexpr (BITS != 3) return gemv_mma4i<BITS, 16>;
+        if constexpr (BITS != 3) return gemv_mma4i<BITS, 16, false, ROWS>;
         return nullptr;
     default: return nullptr;
     }
 }
+template <int BITS>
+GemvKernel pick_mma4i(int cpg, bool rows) { return rows ? pick_mma4i_of<BITS, true>(cpg) : pick_mma4i_of<BITS, false>(cpg); }
 
 template <int BITS>
 GemvKernel pick_mma4i_ragged(int cpg)
@@ -2130,7 +2136,7 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
         P.tiles_per_block = P.chunks > 1 ? 1 : wpb / P.waves_per_tile;
         P.pair_tiles = gate_rows ? (int)(gate_rows[idx[i]] / QG_WAVE) : 0;
         P.h = gated ? gated[idx[i]] : nullptr;
-        P.rows = rows > 0 ? rows : product_rows;
+        P.rows = rows;
         P.block_begin = blocks;
         A.block_begin[i] = blocks;
         const int64_t nb = P.chunks > 1 ? (int64_t)P.tiles * P.chunks
@@ -2160,7 +2166,7 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
     } else if (kind == KIND_STATIC) {
         if (mul == MUL_MMA4I) {
             family = "gemv_mma4i";
-            fn = bits == 4 ? pick_mma4i<4>(cpg) : bits == 2 ? pick_mma4i<2>(cpg) : pick_mma4i<3>(cpg);
+            fn = bits == 4 ? pick_mma4i<4>(cpg, product_rows) : bits == 2 ? pick_mma4i<2>(cpg, product_rows) : pick_mma4i<3>(cpg, product_rows);
             lds = lds_mma4i(bits, threads);
         } else if (mul == MUL_MMA4) {
             family = "gemv_mma4";
@@ -2178,7 +2184,7 @@ int launch_class(const qg_gemv_desc *descs, const int *idx, int count, const siz
     } else if (kind == KIND_RUNTIME && mul == MUL_MMA4I) {
         family = "gemv_mma4i";
         shown_cpg = 0;
-        fn = bits == 2 ? pick_mma4i<2>(0) : bits == 3 ? pick_mma4i<3>(0) : pick_mma4i<4>(0);
+        fn = bits == 2 ? pick_mma4i<2>(0, product_rows) : bits == 3 ? pick_mma4i<3>(0, product_rows) : pick_mma4i<4>(0, product_rows);
         lds = lds_mma4i(bits, threads);
     } else if (kind == KIND_RUNTIME && mul == MUL_MMA4) {
         family = "gemv_mma4";
