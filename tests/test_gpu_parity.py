@@ -1083,6 +1083,47 @@ def test_gemm_small_own_operands(qg, oracle, N, K, bits, group, M, parts):
         assert np.array_equal(Yv[others], Y[others])
 
 
+# Block-scaled operands, as the plan takes them by itself (tests/test_launch_plans.py looks): N, K, bits, group, M.  Every number
+# of groups per step and width, blocks of 32 and of 64 rows; K of whole units, ending inside a unit, a step and a block of 64;
+# a last block of rows with one row, with 32 and with 64; ragged N; parts by the last workgroup and by a kernel, units dealt evenly
+MX_CASES = [
+    (9001, 4096, 4, 128, 30), (14000, 4096, 4, 64, 32), (12000, 4128, 4, 32, 70), (9517, 6144, 4, 512, 65), (14001, 8192, 2, 128, 31),
+    (20000, 1088, 2, 64, 66), (16001, 1056, 2, 32, 100), (9517, 6144, 2, 512, 97), (4099, 11008, 4, 128, 128), (11008, 4096, 4, 4096, 33),
+    (12000, 4128, 2, 32, 70), (17000, 4160, 4, 32, 32), (12790, 6208, 4, 64, 128), (5000, 18496, 2, 64, 128)]
+
+
+@pytest.mark.parametrize("N,K,bits,group,M", MX_CASES)
+def test_gemm_small_block_scaled_operands(qg, oracle, N, K, bits, group, M):
+    # Against 64 bits no further off than the exact product of X rounded to bf16, for normal X (0.6 of it) and with columns a
+    # hundred times larger
+    _announce("gemm, block-scaled operands", N, K, bits, group, M)
+    W, X = synth.small_case(5300 + N + M, N, K, 0.02, True, m=M)
+    assert _gemm_case(qg, oracle, W, X, bits, group) <= TOL_BF16
+    q, s, z = qg.qg_quantize(dev(W), bits, group)
+    blob = qg.qg_pack(q, s, z, bits, group)
+    What = torch.from_numpy(oracle.dequantize(host(q), host(s), host(z), group)).double()
+    columns = X.copy()
+    columns[:, np.random.default_rng(N).integers(0, K, max(K // 200, 1))] *= 100.0
+    for x in (X, columns):
+        t = torch.from_numpy(x)
+        exact, rounded = t.double() @ What.T, t.bfloat16().double() @ What.T
+        Y = torch.from_numpy(host(qg.qg_gemm_small(blob, N, K, bits, group, dev(x)))).double()
+        assert torch.linalg.norm(Y - exact) <= torch.linalg.norm(rounded - exact)
+    # a value that is no number stays in its row, scales far from one are as good, zero rows are zero
+    Y = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(X)))
+    for value in (np.nan, np.inf, -np.inf):
+        Xv = X.copy()
+        Xv[M // 2, K - 1] = value
+        Yv = host(qg.qg_gemm_small(blob, N, K, bits, group, dev(Xv)))
+        assert np.isnan(Yv[M // 2]).all()
+        others = np.arange(M) != M // 2
+        assert np.array_equal(Yv[others], Y[others])
+    for scale in (2.0 ** -90, 2.0 ** 90):
+        Ys = host(qg.qg_gemm_small(blob, N, K, bits, group, dev((X * np.float32(scale)).astype(np.float32))))
+        assert np.array_equal(Ys, Y * np.float32(scale))
+    assert not host(qg.qg_gemm_small(blob, N, K, bits, group, dev(np.zeros_like(X)))).any()
+
+
 # Products of few rows that run as one fp32 matrix-vector product per row (tests/test_launch_plans.py looks): N, K, bits,
 # group, M; K of whole steps, ending inside one and shorter than one, groups of several steps, 16 rows, one cell per group
 ROWS_CASES = [(512, 512, 4, 64, 2), (2045, 576, 4, 64, 3), (1062, 640, 2, 128, 5), (7803, 2432, 2, 32, 2), (65, 64, 4, 32, 16),

@@ -2,7 +2,7 @@
 import pytest
 
 from tests.launches import launches
-from tests.test_gpu_parity import I8_CASES, M1_CASES, MANY_ROWS_CASES, ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
+from tests.test_gpu_parity import I8_CASES, M1_CASES, MANY_ROWS_CASES, MX_CASES, ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
 
 
 @pytest.fixture(scope="module")
@@ -112,6 +112,17 @@ def test_own_operand_cases_are_cut_as_stated(tmp, case):
     k, names = _product(launches(tmp, [{"problem": problem}])[0])
     assert (k["template"][2], k["template"][5], k["args"]["self"]) == (1, 2, 1) and k["args"]["ranges"] == parts
     assert names == ["gemm_codes"] + ["add_parts"] * (parts != 1)
+
+
+# The GPU tests of block-scaled operands take them, with every number of groups per step, in blocks of 32 and of 64 rows, whole
+# ranges of K and units dealt evenly, parts added either way; the product asked for by number takes the same operands
+def test_block_scaled_cases_take_those_operands(tmp):
+    kernels = [_product(r)[0] for r in launches(tmp, [{"problem": c} for c in MX_CASES])]
+    assert {k["template"][5] for k in kernels} == {3, 4}
+    assert {(*k["template"][:2],) for k in kernels} == {(bits, gps) for bits in (2, 4) for gps in (0, 1, 2, 4)}
+    assert {k["template"][2] for k in kernels} == {1, 2} and {k["args"]["ranges"] == 0 for k in kernels} == {True, False}
+    by_number = [_product(r)[0] for r in launches(tmp, [{"problem": c, "splits": 2, "shape": 13} for c in MX_CASES])]
+    assert {k["template"][5] for k in by_number} <= {3, 4}
 
 
 @pytest.mark.parametrize("problem,name", [(c, "gemv_mma4i") for c in ROWS_CASES] + [
