@@ -1293,16 +1293,24 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
 // Up to 16 activation rows at once (a few prompt tokens): Y = X What^T with the launch
 // structure of the GEMV -- one wavefront per 64 outputs and K range, no workgroup barrier in
 // the loop, K split over the wavefronts of a team -- and the arithmetic of gemv_mma: 4-bit
-// codes become exact bf16 integers 128 + q, the matrix instruction multiplies them with the
-// rows of X (rounded to bf16; rows 16-31 of the A operand are zero), and per group
+// codes become exact bf16 integers 128 + q, v_mfma_f32_16x16x32_bf16 multiplies them with the
+// rows of X (rounded to bf16), and per group
 //     Y[m][n] += s_n (T[m][n] - (128 + z_n) xhat[m]),   xhat[m] = sum_k bf16(X[m][k]),
 // where xhat comes out of one more matrix instruction per operand (X times a column of ones),
 // so it sits in the same registers as T.  Each wavefront converts the X rows of its own step
 // and keeps them in its own LDS region, one 16-byte operand piece per (row, cell).
-// Bound by what a compute unit can load: 8 KB of X per 4 KB of codes (11008 x 4096 at 16 rows 11.2 -> 11.0
-// us, 22016 x 8192 38.9 -> 34.6, 8192 x 8192 g64 19.2 -> 18.2 with the operands below, which need no lane
-// exchange of code words, and X in one register set: 168-184 registers instead of 208-232).
+// The instruction takes 32 k of 16 outputs, lanes 16 j ... holding eight of them each.  Which eight is free as
+// long as X and the codes agree and all are of one group, so lanes load their codes as they need them: of groups
+// of 128 the step's vector j, whose word w meets instruction w; of 64 half of a vector; groups of 32 and 16 want word j of a
+// vector, and words are exchanged between lanes (loaded one by one: 1.2 to 1.3 of the time); of 16 half of the lanes meet zeros.
+// What bounds it: 8 KB of X per 4 KB of codes through a compute unit's load path, and launch and first miss.  The 32 x 32 x 16
+// instruction, which this was written with (24 per step, of 32 cycles, and 24 operand reads from LDS; now 20 of 16 and 4),
+// left half of its rows idle and took as long as all vector instructions.  us per call, 32 x 32 | 16 x 16: 11008 x 4096 g128
+// M = 16 11.4 | 9.5, 4656 x 13184 g128 M = 5 19.9 | 15.8, 5416 x 7936 g64 M = 15 16.7 | 15.0, 18689 x 2304 g32 M = 6 13.4 | 12.3,
+// 9260 x 4352 g16 M = 8 16.4 | 16.0.
 // ---------------------------------------------------------------------------------------
+typedef float mma_floatx4 __attribute__((ext_vector_type(4)));
+
 template <int CPG>
 __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvArgs A)
 {
@@ -1312,14 +1320,15 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
     constexpr int CELLS = cells_per_step<4>();      // 16 cells of 8 codes
     constexpr int GPS = CELLS / CPG;
     constexpr int ZPER = 32 / F::ZBITS;
-    constexpr int ZW = GPS > ZPER ? GPS / ZPER : 1;
     constexpr int PITCH = S + 8;                    // bf16 per LDS row: conflict-free 128-bit reads
     constexpr int XL = 16 * CELLS / QG_WAVE;        // (row, cell) pieces per lane and step: 4
-    static_assert(CPG >= 2 && CPG % 2 == 0, "a group must hold whole pairs of cells");
+    constexpr int PRODUCTS = GPS < 4 ? 4 / GPS : 1; // instructions per group and 16 outputs
+    constexpr bool SPREAD = GPS >= 4;               // scales: a load per group, spread between lanes (else a load per 16 outputs)
+    static_assert(GPS == 1 || GPS == 2 || GPS == 4 || GPS == 8, "whole pairs of cells, a word of zero-points per step");
     // per wavefront: 16 rows of X for one step (reused at the end for the team's partial
-    // results); one row of zeros for rows 16-31 of the A operand
+    // results); groups of 16: one row of zeros
     extern __shared__ __attribute__((aligned(16))) lds_u16 rows_raw[];
-    __shared__ __attribute__((aligned(16))) lds_u16 zero_row[PITCH];
+    __shared__ __attribute__((aligned(16))) lds_u16 zero_row[GPS == 8 ? PITCH : 8];
 
     const int pi = find_problem(fb_a, fb_b, fb_c, A, blockIdx.x);
     const GemvProblem P = A.p[pi];
@@ -1330,121 +1339,160 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
     if (!job.work) return;                      // no work: leave before the barrier
     const int tile = job.tile, s0 = job.item0, s1 = job.item1;
     const int M = P.rows;
+    const int j = lane >> 4, out = lane & 15;       // eight of 32 k; output of sixteen, row of X
 
-    const uint4 *codes = P.codes + (size_t)tile * P.steps * L * QG_WAVE + lane;
-    const float *scales = P.scales + (size_t)tile * P.ngroups * QG_WAVE + lane;
-    const uint32_t *zeros = P.zeros + (size_t)tile * P.zwords * QG_WAVE + lane;
+    const uint4 *codes = P.codes + (size_t)tile * P.steps * L * QG_WAVE + out;
+    const float *scales = P.scales + (size_t)tile * P.ngroups * QG_WAVE;
+    const uint32_t *zeros = P.zeros + (size_t)tile * P.zwords * QG_WAVE + out;
     lds_u16 *xs = rows_raw + (size_t)wave * 16 * PITCH;
 
-#pragma unroll
-    for (int i = lane; i < PITCH; i += QG_WAVE) zero_row[i] = 0;
+    if constexpr (GPS == 8) {
+        for (int i = lane; i < PITCH; i += QG_WAVE) zero_row[i] = 0;
+    }
 
     struct Regs {
-        uint4 v[L];
-        float s[GPS];
-        uint32_t zw[ZW];
+        uint32_t c[4][4];          // of outputs 16 t ...: words in the order of the instructions
+        float s[SPREAD ? 1 : 4][GPS];
+        uint32_t zw[4];
     };
-    float4 x[XL][2];           // pieces (row, cell) = (4 j + lane / 16, lane % 16): 8 consecutive k of X
+    float4 x[XL][2];           // pieces (row, cell) = (4 i + lane / 16, lane % 16): 8 consecutive k of X
     // groups of four rows with no real row are not loaded; other rows past M read row M - 1
-    // again; both are cleared on their way into LDS
+    // again (a row of X reaches its own row of the result alone)
     const int xrow0 = lane >> 4, xcell = lane & 15;
     auto fetch = [&](int step, Regs &r) {
+        const uint4 *at = codes + (size_t)step * L * QG_WAVE;
 #pragma unroll
-        for (int i = 0; i < L; ++i) r.v[i] = codes[((size_t)step * L + i) * QG_WAVE];
+        for (int t = 0; t < 4; ++t) {
+            if constexpr (GPS == 2) {
 #pragma unroll
-        for (int g = 0; g < GPS; ++g) r.s[g] = scales[(size_t)(step * GPS + g) * QG_WAVE];
+                for (int g = 0; g < 2; ++g) {
+                    const uint2 v = ((const uint2 *)(at + (2 * g + (j & 1)) * QG_WAVE + 16 * t))[j >> 1];
+                    r.c[t][2 * g] = v.x, r.c[t][2 * g + 1] = v.y;
+                }
+            } else {
+                const uint4 v = at[j * QG_WAVE + 16 * t];
+                r.c[t][0] = v.x, r.c[t][1] = v.y, r.c[t][2] = v.z, r.c[t][3] = v.w;
+            }
+        }
 #pragma unroll
-        for (int w = 0; w < ZW; ++w) r.zw[w] = zeros[(size_t)((step * GPS) / ZPER + w) * QG_WAVE];
+        for (int g = 0; g < GPS; ++g) {
+            const float *from = scales + (size_t)(step * GPS + g) * QG_WAVE;
+            if constexpr (SPREAD) {
+                r.s[0][g] = from[lane];
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) r.s[t][g] = from[16 * t + out];
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r.zw[t] = zeros[(size_t)((step * GPS) / ZPER) * QG_WAVE + 16 * t];
     };
     auto fetch_x = [&](int step) {
 #pragma unroll
-        for (int j = 0; j < XL; ++j) {
-            if (4 * j >= M) continue;                    // uniform
-            int m = 4 * j + xrow0;
+        for (int i = 0; i < XL; ++i) {
+            if (4 * i >= M) continue;                    // uniform
+            int m = 4 * i + xrow0;
             m = m < M ? m : M - 1;
             const float4 *src = (const float4 *)(P.x + (size_t)m * P.K + (size_t)step * S + xcell * 8);
-            x[j][0] = src[0];
-            x[j][1] = src[1];
+            x[i][0] = src[0];
+            x[i][1] = src[1];
         }
     };
     // X of one step into LDS: per piece the eight values in the order the unpacked codes have
-    // inside an operand (register j = codes j and j + 4)
+    // inside an operand (register n = codes n and n + 4)
     auto stage = [&]() {
 #pragma unroll
-        for (int j = 0; j < XL; ++j) {
-            const int m = 4 * j + xrow0;
+        for (int i = 0; i < XL; ++i) {
+            if (4 * i >= M) continue;
             MmaOperand o;
-            if (4 * j >= M) {                            // uniform: nothing was loaded
-                o.q = make_uint4(0u, 0u, 0u, 0u);
-                *(lds_u128 *)(xs + m * PITCH + xcell * 8) = o.q;
-                continue;
-            }
-            const float4 a = x[j][0], b = x[j][1];
-            const float keep = m < M ? 1.0f : 0.0f;
+            const float4 a = x[i][0], b = x[i][1];
             mma_floatx2 t2;
-            t2[0] = a.x * keep; t2[1] = b.x * keep;
+            t2[0] = a.x; t2[1] = b.x;
             { const mma_bf16x2 h = __builtin_convertvector(t2, mma_bf16x2); o.r[0] = *(const uint32_t *)&h; }
-            t2[0] = a.y * keep; t2[1] = b.y * keep;
+            t2[0] = a.y; t2[1] = b.y;
             { const mma_bf16x2 h = __builtin_convertvector(t2, mma_bf16x2); o.r[1] = *(const uint32_t *)&h; }
-            t2[0] = a.z * keep; t2[1] = b.z * keep;
+            t2[0] = a.z; t2[1] = b.z;
             { const mma_bf16x2 h = __builtin_convertvector(t2, mma_bf16x2); o.r[2] = *(const uint32_t *)&h; }
-            t2[0] = a.w * keep; t2[1] = b.w * keep;
+            t2[0] = a.w; t2[1] = b.w;
             { const mma_bf16x2 h = __builtin_convertvector(t2, mma_bf16x2); o.r[3] = *(const uint32_t *)&h; }
-            *(lds_u128 *)(xs + m * PITCH + xcell * 8) = o.q;
+            *(lds_u128 *)(xs + (4 * i + xrow0) * PITCH + xcell * 8) = o.q;
         }
     };
 
-    // A operands.  A lane's B operand is a cell of its own output, so lanes l and l + 32 hold the same k of
-    // two outputs; with the 16 rows of X against lanes 0-31 in rows 0-15 of A and once more against lanes
-    // 32-63 in rows 16-31 (zeros elsewhere), one instruction multiplies a cell of all 64 outputs with 16
-    // rows, and neither the code words nor the scales have to change lanes.  For xhat: 16 k in rows 0-15.
-    const int row = lane & 31, half = lane >> 5;
-    const lds_u16 *abase = (row < 16) == (half == 0) ? xs + (row & 15) * PITCH : zero_row;
-    const lds_u16 *xbase = xs + (row & 15) * PITCH + half * 8;
+    // A operands: the cells whose codes this lane holds, of row `out`; groups of 16: zeros in the other half of the lanes
+    const int cell0 = GPS == 1 ? 4 * j : GPS == 2 ? 4 * (j & 1) + 2 * (j >> 1) : j;
+    const lds_u16 *arow = xs + out * PITCH + cell0 * 8;
+    const lds_u16 *ahalf[2] = {j < 2 ? arow : zero_row, j < 2 ? zero_row : arow};
     const MmaConst mc = mma_constants<4>();
+    uint32_t zmask = 0x000f0000u, zmagic = 0x43000000u;      // (behind registers, as mma_constants)
+    asm("" : "+s"(zmask));
+    asm("" : "+v"(zmagic));
     MmaOperand ones;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) ones.r[j] = 0x3f803f80u;     // two bf16 1.0
+    for (int n = 0; n < 4; ++n) ones.r[n] = 0x3f803f80u;     // two bf16 1.0
 
-    // results of this wavefront: rows 8 (i / 4) + 4 half + i % 4 (i < 8) of outputs lane % 32 (yp)
-    // and 32 + lane % 32 (yq) of the tile
-    float yp[8], yq[8];
+    // results of this wavefront: rows 4 j + i of outputs 16 t + lane % 16 of the tile
+    float y[4][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { yp[i] = 0.0f; yq[i] = 0.0f; }
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[t][i] = 0.0f;
 
     auto compute = [&](const Regs &r, int step) {
-        const mma_floatx16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        mma_floatx16 acc, accX;
+        const mma_floatx4 zero4 = {0, 0, 0, 0};
+        uint32_t c[4][4], zw[4];
 #pragma unroll
-        for (int cp = 0; cp < CELLS / 2; ++cp) {
-            const int c0 = 2 * cp, u = c0 >> 2, j = c0 & 3;
-            const bool starts = c0 % CPG == 0;
-            uint32_t w0[1] = {word_of(r.v[u], j)}, w1[1] = {word_of(r.v[u], j + 1)};
-            MmaOperand b0[1], b1[1], a0, a1, ax;
-            mma_unpack<4>(w0, mc, b0);
-            mma_unpack<4>(w1, mc, b1);
-            a0.q = *(const lds_u128 *)(abase + cp * 16);
-            a1.q = *(const lds_u128 *)(abase + cp * 16 + 8);
-            ax.q = *(const lds_u128 *)(xbase + cp * 16);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0.v, b0[0].v, starts ? zero16 : acc, 0, 0, 0);
-            accX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ax.v, ones.v, starts ? zero16 : accX, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1.v, b1[0].v, acc, 0, 0, 0);
-            if ((2 * cp + 2) % CPG == 0) {
-                const int gs = (2 * cp + 2) / CPG - 1;
-                const int gabs = step * GPS + gs;
-                const uint32_t zword = r.zw[ZW > 1 ? gs / ZPER : 0];
-                const float s = r.s[gs];
-                const float nzs = -(float)(((zword >> (F::ZBITS * (gabs % ZPER))) & ((1u << F::ZBITS) - 1u)) + 128u) * s;
-                // scale and zero term of the outputs this lane's accumulators belong to
-                const auto ss = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-                const auto zz = __builtin_amdgcn_permlane32_swap(__float_as_uint(nzs), __float_as_uint(nzs), false, false);
-                const float sP = __uint_as_float(ss[0]), sQ = __uint_as_float(ss[1]);
-                const float zP = __uint_as_float(zz[0]), zQ = __uint_as_float(zz[1]);
+        for (int t = 0; t < 4; ++t) {
+            zw[t] = r.zw[t] >> (F::ZBITS * (step * GPS % ZPER));
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    yp[i] += fmaf(sP, acc[i], zP * accX[i]);
-                    yq[i] += fmaf(sQ, acc[8 + i], zQ * accX[i]);
+            for (int n = 0; n < 4; ++n) c[t][n] = r.c[t][n];
+        }
+        if constexpr (SPREAD) {
+            // word w of vector j in lanes 16 j ... becomes word j of vector w
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const auto a = __builtin_amdgcn_permlane32_swap(c[t][0], c[t][2], false, false), b = __builtin_amdgcn_permlane32_swap(c[t][1], c[t][3], false, false);
+                const auto u01 = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false), u23 = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+                c[t][0] = u01[0], c[t][1] = u01[1], c[t][2] = u23[0], c[t][3] = u23[1];
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < GPS; ++g) {
+            mma_floatx4 acc[4], accX;
+#pragma unroll
+            for (int w = 0; w < PRODUCTS; ++w) {
+                MmaOperand a;
+                if constexpr (GPS == 8) a.q = *(const lds_u128 *)(ahalf[g & 1] + (g >> 1) * 32);
+                else a.q = *(const lds_u128 *)(arow + (GPS == 1 ? w : GPS == 2 ? 8 * g + w : 4 * g) * 8);
+                accX = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, ones.v, w == 0 ? zero4 : accX, 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const uint32_t word[1] = {c[t][GPS == 1 ? w : GPS == 2 ? 2 * g + w : GPS == 4 ? g : g >> 1]};
+                    MmaOperand b[1];
+                    mma_unpack<4>(word, mc, b);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b[0].v, w == 0 ? zero4 : acc[t], 0, 0, 0);
                 }
+            }
+            float s[4];
+            if constexpr (SPREAD) {
+                // lanes 16 t ... hold outputs 16 t ...: each sixteen to all lanes
+                const auto lo_hi = __builtin_amdgcn_permlane32_swap(__float_as_uint(r.s[0][g]), __float_as_uint(r.s[0][g]), false, false);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const auto two = __builtin_amdgcn_permlane16_swap(lo_hi[h], lo_hi[h], false, false);
+                    s[2 * h] = __uint_as_float(two[0]);
+                    s[2 * h + 1] = __uint_as_float(two[1]);
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) s[t] = r.s[t][g];
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                // 128 + z as a float: z in bits 16 ... of 128.0
+                const float z128 = __uint_as_float(and_or(g < 4 ? zw[t] << (16 - 4 * g) : zw[t] >> (4 * g - 16), zmask, zmagic));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) y[t][i] = fmaf(s[t], fmaf(-z128, accX[i], acc[t][i]), y[t][i]);
             }
         }
     };
@@ -1477,10 +1525,7 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
     // 17.95 -> 17.4, 4096 x 4096 M = 12 8.91 -> 8.48; teams of four level: 20000 x 4096 M = 16 16.45 -> 16.5, 22016 x 8192 34.1 -> 34.3.)
     float *mine = (float *)(rows_raw + (size_t)wave * 16 * PITCH);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        mine[i * QG_WAVE + lane] = yp[i];
-        mine[(8 + i) * QG_WAVE + lane] = yq[i];
-    }
+    for (int i = 0; i < 16; ++i) mine[i * QG_WAVE + lane] = y[i / 4][i % 4];
     __syncthreads();
     const int team = job.team;
     auto add_and_store = [&](auto most) {                 // teams of up to `most`: all reads at once, of regions the team has
@@ -1492,7 +1537,7 @@ __global__ __launch_bounds__(512) void gemm_rows16(QG_FIRST_BLOCKS, const GemvAr
             float sum = part[0];
 #pragma unroll
             for (int w = 1; w < most; ++w) sum = w < team ? sum + part[w] : sum;
-            const int m = 8 * (i / 4 & 1) + 4 * half + i % 4, n = tile * QG_WAVE + 32 * (i / 8) + (lane & 31);
+            const int m = 4 * j + i % 4, n = tile * QG_WAVE + 16 * (i / 4) + out;
             if (m < M && n < P.N) P.y[(size_t)m * P.N + n] = sum;
         }
     };

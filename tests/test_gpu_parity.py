@@ -1375,6 +1375,27 @@ def test_gemm_small_up_to_16_rows(qg, oracle, N, K, group, M, tuning):
     assert err <= TOL_BF16, err
 
 
+@pytest.mark.parametrize("group", [16, 32, 64, 128])
+@pytest.mark.parametrize("N,K,M", [(65, 128, 2), (130, 384, 4), (3073, 1152, 5), (200, 2176, 12), (4099, 640, 16)])
+def test_gemm_small_up_to_16_rows_every_group(qg, oracle, N, K, M, group):
+    # one step and odd numbers of them, rows that fill four and leave some over, ragged outputs
+    _announce("gemm, up to 16 rows, every group", N, K, M, group)
+    W, X = synth.small_case(5400 + N + M, N, K, 0.02, True, m=M)
+    qg.qg_set_gemm_tuning(0, -1)
+    try:
+        err = _gemm_case(qg, oracle, W, X, 4, group)
+        blob = qg.qg_pack(*qg.qg_quantize(dev(W), 4, group), 4, group)
+        Y = host(qg.qg_gemm_small(blob, N, K, 4, group, dev(X)))
+        for value in (np.nan, np.inf):
+            Xv = X.copy()
+            Xv[M - 1, K - 1] = value
+            Yv = host(qg.qg_gemm_small(blob, N, K, 4, group, dev(Xv)))
+            assert np.isnan(Yv[M - 1]).all() and np.array_equal(Yv[:M - 1], Y[:M - 1])
+    finally:
+        qg.qg_set_gemm_tuning(0, 0)
+    assert err <= TOL_BF16, err
+
+
 @pytest.mark.parametrize("bits,group,cell", [(4, 128, 8), (4, 32, 8), (3, 64, 32), (2, 32, 16)])
 @pytest.mark.parametrize("M", [1, 16, 40, 128])
 def test_gemm_small_single_cell_difference(qg, oracle, bits, group, cell, M):
