@@ -1143,13 +1143,14 @@ double gemv_rows_us(const QgLayout &L, int M)
     return 2.3 + sqrt(one * one + all * all);
 }
 // ... and on gemm_rows16: a workgroup per tile (teams of eight wavefronts, of four beyond one tile per compute unit).
-// Through 171 products of 2 ... 16 rows and 48 and more tiles (6 % off).
+// Through 4600 products of 2 ... 16 rows and 48 and more tiles, two and more steps per wavefront (groups of 16 as before).
 double rows16_us(const QgLayout &L, int M, int cus)
 {
     const int team = L.tiles > cus ? 4 : 8;
     const double rounds = (double)((L.tiles * team / 8 + cus - 1) / cus), spw = (double)((L.steps + team - 1) / team);
     const double full = L.tiles < cus ? (double)L.tiles / cus : 1.0;
-    return 3.0 + rounds * spw * (0.96 + 0.023 * M + 0.168 * (128 / L.group) + 0.3 * full);
+    const double groups = L.group >= 128 ? 0.0 : L.group == 64 ? 0.27 : L.group == 32 ? 0.53 : 1.6;
+    return 3.3 + rounds * spw * (0.73 + 0.023 * M + groups + 0.36 * full);
 }
 
 // Checks, plans and (price == NULL) enqueues one product; knob_*: as qg_set_gemm_tuning.
