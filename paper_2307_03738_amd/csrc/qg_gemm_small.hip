@@ -794,6 +794,14 @@ int codes_gps(const QgLayout &L)       // groups per step of 128 k, 0: groups of
     return L.group >= least && KC % L.group == 0 ? KC / L.group : -1;
 }
 
+// Products that run on block-scaled operands where prepare_x would make bf16 ones.  4-bit groups of 32: where the unpacking, twice
+// that of the others, and the longer conversion of X are paid back, us bf16 | block-scaled: 16000 x 8192 M = 50 39.6 | 38.0, M = 128 64.1 |
+// 61.5, 8192 x 22016 M = 100 77.5 | 76.2; but 17000 x 4160 M = 32 21.0 | 21.7, 12000 x 8320 M = 28 24.8 | 25.1, 12000 x 4128 M = 70 33.0 | 33.8, 15039 x 6208 M = 43 28.2 | 29.2.
+bool codes_mx(const QgLayout &L, int gps, int M)
+{
+    return qg_codes_mx(L.bits, gps) && (L.bits != 4 || gps != 4 || (M > 32 && L.K >= 8192));
+}
+
 // Workspace of the raw-code path: A operands, counters, partial results of the K ranges.
 struct CodesSpace {
     size_t arrived_off, partial_off, total;
@@ -1242,7 +1250,7 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
     if (raw) {
         // (asked for by number: the kind of operand that the built-in plan takes, so that a forced cut changes the order of
         // the sums alone)
-        C.mx = qg_codes_mx(L.bits, gps) && !C.self && (knob_shape == 0 || !codes_plan(L, gps, M, 0, false).self);
+        C.mx = codes_mx(L, gps, M) && !C.self && (knob_shape == 0 || !codes_plan(L, gps, M, 0, false).self);
         const CodesSpace W = codes_space(L, gps, M);
         char *ws = (char *)workspace;
         QgPrepArgs P;

@@ -1087,9 +1087,9 @@ def test_gemm_small_own_operands(qg, oracle, N, K, bits, group, M, parts):
 # of groups per step and width, blocks of 32 and of 64 rows; K of whole units, ending inside a unit, a step and a block of 64;
 # a last block of rows with one row, with 32 and with 64; ragged N; parts by the last workgroup and by a kernel, units dealt evenly
 MX_CASES = [
-    (9001, 4096, 4, 128, 30), (14000, 4096, 4, 64, 32), (12000, 4128, 4, 32, 70), (9517, 6144, 4, 512, 65), (14001, 8192, 2, 128, 31),
+    (9001, 4096, 4, 128, 30), (14000, 4096, 4, 64, 32), (12000, 8224, 4, 32, 70), (9517, 6144, 4, 512, 65), (14001, 8192, 2, 128, 31),
     (20000, 1088, 2, 64, 66), (16001, 1056, 2, 32, 100), (9517, 6144, 2, 512, 97), (4099, 11008, 4, 128, 128), (11008, 4096, 4, 4096, 33),
-    (12000, 4128, 2, 32, 70), (17000, 4160, 4, 32, 32), (12790, 6208, 4, 64, 128), (5000, 18496, 2, 64, 128)]
+    (12000, 4128, 2, 32, 70), (17000, 4160, 2, 32, 32), (12790, 6208, 4, 64, 128), (5000, 18496, 2, 64, 128)]
 
 
 @pytest.mark.parametrize("N,K,bits,group,M", MX_CASES)
