@@ -2,7 +2,7 @@
 // their launch interface.  Included by one source per bit width (qg_gemm_codes_b{2,3,4}.hip), each of
 // which instantiates its width; qg_gemm_small.hip plans and launches.
 //
-// Nothing is dequantized per weight.  A code q becomes the exact bf16 integer 128 + q with a mask
+// Nothing is dequantized per weight.  On bf16 operands (block-scaled ones: see mx_put) a code q becomes the exact bf16 integer 128 + q with a mask
 // and an OR, the matrix instruction accumulates
 //     T[m][n] = sum_{k in group} xb[m][k] (128 + q[n][k]),      xb = X rounded to bf16,
 // in fp32 (the products are exact), and scale and zero-point are applied once per group and
@@ -41,7 +41,7 @@
 // there are 4 matrix instructions and, at groups of 32 k, 32 multiply-adds of the fold plus 16-20 instructions of
 // unpacking (4 cycles each): 2350 cycles per step of 128 k, 2-bit g32, of 2800 measured.  On short problems the
 // launches around it count as much: prepare_x and, where many parts of a sum are better, add_parts.
-// Measured (us per call, passes in sequence, four rotated matrices; before: iterations of KW layout steps,
+// Measured on bf16 operands (us per call, passes in sequence, four rotated matrices; before: iterations of KW layout steps,
 // activations through registers, whole K ranges per block, always a kernel that adds the ranges): 22016 x
 // 8192 2-bit g32 M = 128 104.4 -> 76, 13824 x 5120 3-bit g64 M = 37 27.0 -> 22.1 (in blocks of 32 rows 20.0), 4096 x 11008
 // 4-bit g128 M = 128 28.2 -> 24.9.  Figures further down are differences that one choice made at the time it was taken.
