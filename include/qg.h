@@ -178,10 +178,7 @@ int qg_gemv_swiglu(const void *packed, int64_t I, int64_t K, int bits, int group
  *     32 ... 256; 3 bits: 64 ... 256) or a multiple of a step, K % 16 == 0: the codes enter the
  *     matrix instruction as exact bf16 integers, X is rounded to bf16, and scale and zero-point
  *     are applied in fp32 once per group and element of Y (eq. (2)); X is converted by the
- *     product kernel itself or, on larger products, by a kernel of its own first, so a call enqueues one to three kernels.
- *     On the larger products at 2 and 4 bits (G >= 32) that kernel writes X as the sum of two six-bit numbers with a power of
- *     two per row and 32 k, and the codes enter as four- or six-bit numbers: a value of X is off by at most 2^-8 of the
- *     largest of its 32, Y by half of what bf16(X) gives.  (The sums of (2^7 + q) x over a
+ *     product kernel itself or, on larger products, by a kernel of its own first, so a call enqueues one to three kernels.  (The sums of (2^7 + q) x over a
  *     group, or 128 k of it, are fp32: |x| up to 10^34.)
  * Where both apply (4 bits) the second is used for 17 ... 32 and more than 64 rows on matrices of 4096
  * tile-steps or more (64 outputs x 128 k each) and for 33 ... 64 rows from 8192 on (groups of 32: from

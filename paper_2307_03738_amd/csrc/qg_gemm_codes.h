@@ -2,7 +2,7 @@
 // their launch interface.  Included by one source per bit width (qg_gemm_codes_b{2,3,4}.hip), each of
 // which instantiates its width; qg_gemm_small.hip plans and launches.
 //
-// Nothing is dequantized per weight.  On bf16 operands (block-scaled ones: see mx_put) a code q becomes the exact bf16 integer 128 + q with a mask
+// Nothing is dequantized per weight.  A code q becomes the exact bf16 integer 128 + q with a mask
 // and an OR, the matrix instruction accumulates
 //     T[m][n] = sum_{k in group} xb[m][k] (128 + q[n][k]),      xb = X rounded to bf16,
 // in fp32 (the products are exact), and scale and zero-point are applied once per group and
@@ -36,12 +36,12 @@
 // compute units a workgroup takes a block.  More than 32 rows go in blocks of 64 or of 32 (codes_plan says when); several
 // blocks of 32 rows of the same tiles sit in one die's workgroups, so that its L2 serves their weights.
 //
-// What bounds it on bf16 operands: the issue of a SIMD.  A matrix instruction takes 12 cycles of it (measured: n multiply-adds behind
+// What bounds it: the issue of a SIMD.  A matrix instruction takes 12 cycles of it (measured: n multiply-adds behind
 // each make max(34, 12 + 4 n) cycles, whether one wavefront runs on the SIMD or two).  Per 16 k x 64 outputs x 64 rows
 // there are 4 matrix instructions and, at groups of 32 k, 32 multiply-adds of the fold plus 16-20 instructions of
 // unpacking (4 cycles each): 2350 cycles per step of 128 k, 2-bit g32, of 2800 measured.  On short problems the
 // launches around it count as much: prepare_x and, where many parts of a sum are better, add_parts.
-// Measured on bf16 operands (us per call, passes in sequence, four rotated matrices; before: iterations of KW layout steps,
+// Measured (us per call, passes in sequence, four rotated matrices; before: iterations of KW layout steps,
 // activations through registers, whole K ranges per block, always a kernel that adds the ranges): 22016 x
 // 8192 2-bit g32 M = 128 104.4 -> 76, 13824 x 5120 3-bit g64 M = 37 27.0 -> 22.1 (in blocks of 32 rows 20.0), 4096 x 11008
 // 4-bit g128 M = 128 28.2 -> 24.9.  Figures further down are differences that one choice made at the time it was taken.
@@ -75,7 +75,6 @@ struct QgCodesArgs {
     int self;                  // the A operands are made here, from X
     int K;
     const float *X;            // [M][K] fp32
-    int mx;                    // the A operands are block-scaled
 };
 
 struct QgPrepArgs {
@@ -85,7 +84,6 @@ struct QgPrepArgs {
     int groupk;                // k one xhat covers: the group, or a step for groups of several steps
     uint32_t *arrived;         // counters the product kernel finds at zero
     int counters;
-    int mx;                    // block-scaled
 };
 
 // What a launch would run, for the search that prices candidates before it times them.
@@ -99,30 +97,25 @@ struct QgKernelInfo {
 enum {
     QG_CODES_PREPARED = 0,     // A operands by prepare_x, parts by add_parts
     QG_CODES_FUSED = 1,        // A operands by prepare_x, parts by the workgroup that comes last
-    QG_CODES_SELF = 2,         // A operands by the product kernel itself (blocks of 32 rows), parts by add_parts
-    QG_CODES_MX = 3,           // block-scaled A operands by prepare_mx, parts by add_parts
-    QG_CODES_MX_FUSED = 4      // ... by the workgroup that comes last
+    QG_CODES_SELF = 2          // A operands by the product kernel itself (blocks of 32 rows), parts by add_parts
 };
 
 constexpr size_t QG_LDS_BYTES = 160u << 10;
 constexpr int QG_MAX_SEGMENTS = 8;             // parts the sum of an element of Y is cut into, at most
 constexpr int QG_FUSED_SEGMENTS = 3;           // ... and are added by the workgroup that comes last, at most
 
-// gps: groups per step of 128 k, 0 for groups of several steps.  Layouts that block-scaled operands (mx_put) can serve:
-constexpr bool qg_codes_mx(int bits, int gps) { return bits != 3 && gps <= 4; }
-// KB of A operands per step and block of 32 rows: bf16, an operand for every xhat and sixteen of k; block-scaled, 6 KB of
-// operands, 256 bytes of scales and 256 per xhat
-constexpr int qg_codes_seq(bool mx, int gps) { return mx ? (gps > 3 ? 8 : 7) : 8 + (gps > 0 ? gps : 1); }
+// gps: groups per step of 128 k, 0 for groups of several steps.  A operands per step and block of 32 rows:
+constexpr int qg_codes_seq(int gps) { return 8 + (gps > 0 ? gps : 1); }
 // LDS of an instance: two units of A operands, and 32 rows of the accumulators of k-slices 1 ... KW-1; where
 // those do not fit beside the operands (groups of 16 with four slices) they lie over the unit just multiplied
-constexpr size_t qg_codes_stages(bool mx, int gps, int mb, int kw) { return (size_t)2 * mb * kw * qg_codes_seq(mx, gps) * 1024; }
-constexpr bool qg_codes_slices_apart(bool mx, int gps, int mb, int tn, int kw)
+constexpr size_t qg_codes_stages(int gps, int mb, int kw) { return (size_t)2 * mb * kw * qg_codes_seq(gps) * 1024; }
+constexpr bool qg_codes_slices_apart(int gps, int mb, int tn, int kw)
 {
-    return qg_codes_stages(mx, gps, mb, kw) + (size_t)(kw - 1) * tn * 32 * 256 <= QG_LDS_BYTES;
+    return qg_codes_stages(gps, mb, kw) + (size_t)(kw - 1) * tn * 32 * 256 <= QG_LDS_BYTES;
 }
-constexpr size_t qg_codes_lds(bool mx, int gps, int mb, int tn, int kw)
+constexpr size_t qg_codes_lds(int gps, int mb, int tn, int kw)
 {
-    return qg_codes_stages(mx, gps, mb, kw) + (qg_codes_slices_apart(mx, gps, mb, tn, kw) ? (size_t)(kw - 1) * tn * 32 * 256 : 0);
+    return qg_codes_stages(gps, mb, kw) + (qg_codes_slices_apart(gps, mb, tn, kw) ? (size_t)(kw - 1) * tn * 32 * 256 : 0);
 }
 // k-slices of a workgroup of eight wavefronts: 4 at 32 rows and 2 at 64 (4 there, with half of the tiles, halves
 // the partial sums but doubles the A operands' traffic: 13824 x 5120 3-bit M = 37 +3.0 us, 4096 x
@@ -143,156 +136,6 @@ void qg_codes_prepare_b4(const QgPrepArgs &P, int rows_padded, hipStream_t st);
 
 #ifdef QG_CODES_KERNELS
 namespace {
-
-// ---- block-scaled operands (2 and 4 bits, groups of 32 k and more) ----
-//
-// v_mfma_scale_f32_32x32x64_f8f6f4 multiplies 64 k in the time v_mfma_f32_32x32x16_bf16 takes for 16 if its operands have
-// four or six bits (measured, ns per instruction and SIMD, random operands: bf16 21, six bits by four 21, by six 23, eight
-// by eight 35).  A code is such a number as it stands: the four-bit pattern q (e2m1) is q / 2 for q < 4, the six-bit
-// pattern q (e2m3) is q / 8 for q < 16.  An activation becomes a sum of two e2m3 numbers, the second 2^-5 of the first's
-// scale, with a power of two per row and 32 k that the instruction takes beside them: x = 2^e (hi + lo / 32), e such that
-// the largest of the 32 has 3.75 <= |hi| <= 7.5.  Down to 2^-4 of the largest its largest error is no larger than
-// bf16's, smaller values have the error at that size.  Error of a product against 64 bits (2-norm, Gaussian X):
-// 0.8e-3; X rounded to bf16: 1.7e-3.  The largest exponents end at 2^-121, where fp32 itself is about to lose digits.
-// Measured (us per call, bf16 operands | block-scaled): 22016 x 8192 2-bit g32 M = 128 73.2 | 64.2, 4096 x 11008 4-bit g128
-// M = 128 23.6 | 22.9, 18737 x 3968 2-bit g128 M = 83 27.3 | 24.0, 19596 x 6784 4-bit g64 M = 49 35.6 | 31.9.  Converting X inside
-// the product kernel (SELF) takes 400 ns per 16 rows and step instead of bf16's 190, more than the instructions give back: bf16 stays.
-//
-// A lane of an operand holds 32 consecutive k of one row or output: lanes 0-31 one block of 32, lanes 32-63 another.  Which
-// two blocks of a step of 128 k go together is free as long as X and the codes agree (mx_chunk), so the codes are loaded
-// as the operand wants them -- lanes 0-31 from one place, lanes 32-63 from another, outputs 0-31 and 32-63 of the tile
-// apart, in the same whole lines -- and need no exchange between lanes (which takes the time of four multiply-adds).
-// In groups of 32 lanes 0-31 hold a block's hi, lanes 32-63 its lo, against the same codes in both halves: a group is one
-// instruction; 2-bit codes are then loaded into both halves (4 bits: exchanged, twice the loads would be the longer way).
-// A operands of a step and 32 rows: four operands' first 16 bytes per lane, their last 8, a word of four scales per lane
-// (one per operand), and per group its -xhat in three bf16 parts (8 bytes a row), which a bf16 instruction multiplies by z:
-// T = sum (q - z) x, exact but for fp32.
-typedef uint32_t mx_u6 __attribute__((ext_vector_type(6)));
-typedef int mx_i8 __attribute__((ext_vector_type(8)));
-typedef float mx_f16 __attribute__((ext_vector_type(16)));
-typedef float mx_f32 __attribute__((ext_vector_type(32)));
-constexpr int MX_TAILS = 4096, MX_SCALES = 6144, MX_XHATS = 6400;      // bytes
-constexpr int mx_products(int gps) { return gps == 4 ? 1 : gps == 2 ? 2 : 4; }     // block-scaled instructions per group (gps: 1 or more)
-// Block i of a step's four: chunk (pair of blocks an instruction takes), half of the lanes
-template <int BITS>
-__host__ __device__ constexpr int mx_chunk(int gps, int i) { return BITS == 2 && gps == 1 ? i & 1 : i >> 1; }
-template <int BITS>
-__host__ __device__ constexpr int mx_half(int gps, int i) { return BITS == 2 && gps == 1 ? i >> 1 : i & 1; }
-// Which of a block's 32 codes field f of an operand is: the order compute_mx unpacks them in
-template <int BITS>
-__device__ constexpr int mx_field(int f)
-{
-    if (BITS == 2) return (f & 16) + 2 * (f & 7) + (f >> 3 & 1);
-    constexpr int AT[16] = {0, 1, 3, 4, 6, 7, 9, 2, 12, 5, 15, 8, 10, 11, 13, 14};
-    return (f & 16) + AT[f & 15];
-}
-
-__device__ inline float mx_quad_add(float v, int by)        // of lane ^ 1 (by 0) or lane ^ 2 (by 1)
-{
-    return v + __uint_as_float(by == 0 ? __builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0xb1, 0xf, 0xf, true)
-                                       : __builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x4e, 0xf, 0xf, true));
-}
-
-// Converts block i (= lane & 3) of a row's step and writes it at `to`, the A operands of the step and 32 rows.  All four
-// lanes of a row take part.  value(n): x of the block's k n.
-template <int BITS, int GPS, typename F>
-__device__ inline void mx_put(char *to, int row, int i, F value)
-{
-    mx_f16 p, q;
-    float most = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        p[j] = value(mx_field<BITS>(2 * j));
-        q[j] = value(mx_field<BITS>(2 * j + 1));
-        most = fmaxf(most, fmaxf(fabsf(p[j]), fabsf(q[j])));
-    }
-    // 2^(e - 127) with most / 2^(e - 127) in [3.75, 7.5)
-    uint32_t e = (__float_as_uint(most * (16.0f / 15.0f)) >> 23) & 0xffu;
-    e = (e < 8u ? 8u : e) - 2u;
-    const float scale = __uint_as_float(e << 23), scale_lo = __uint_as_float((e - 5u) << 23);
-    const mx_u6 hi = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(p, q, scale);       // (round to nearest even)
-    const mx_f32 back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(hi, scale);
-    mx_f16 rp, rq;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        rp[j] = p[j] - back[2 * j];
-        rq[j] = q[j] - back[2 * j + 1];
-    }
-    const mx_u6 lo = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(rp, rq, scale_lo);
-    const mx_f32 rest = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(lo, scale_lo);
-    // what the parts stand for, exact: x less what is left; no number if x is none or infinite, which is how the row gets to be NaN
-    float sum = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        sum += p[j] - (rp[j] - rest[2 * j]);
-        sum += q[j] - (rq[j] - rest[2 * j + 1]);
-    }
-    if (GPS <= 2) sum = mx_quad_add(sum, 0);
-    if (GPS <= 1) sum = mx_quad_add(sum, 1);
-    uint32_t part[3];
-    float left = -sum;
-#pragma unroll
-    for (int p3 = 0; p3 < 3; ++p3) {
-        const mma_floatx2 t2 = {left, 0.0f};
-        const mma_bf16x2 hb = __builtin_convertvector(t2, mma_bf16x2);
-        part[p3] = *(const uint32_t *)&hb & 0xffffu;
-        left -= __uint_as_float(part[p3] << 16);
-    }
-    constexpr int PER = GPS == 4 ? 1 : GPS == 2 ? 2 : 4;                     // lanes of a group
-    if (i % PER == 0) *(lds_u64 *)(to + MX_XHATS + i / PER * 256 + row * 8) = make_uint2(part[0] | (part[1] << 16), part[2]);
-    // operands and lanes of the two parts
-    const int chunk = mx_chunk<BITS>(GPS, i), half = mx_half<BITS>(GPS, i);
-    const int at_hi = GPS == 4 ? i : 2 * chunk, at_lo = GPS == 4 ? i : 2 * chunk + 1;
-    const int lane_hi = GPS == 4 ? row : row + 32 * half, lane_lo = GPS == 4 ? row + 32 : lane_hi;
-    *(lds_u128 *)(to + at_hi * 1024 + lane_hi * 16) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    *(lds_u64 *)(to + MX_TAILS + at_hi * 512 + lane_hi * 8) = make_uint2(hi[4], hi[5]);
-    *(lds_u128 *)(to + at_lo * 1024 + lane_lo * 16) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-    *(lds_u64 *)(to + MX_TAILS + at_lo * 512 + lane_lo * 8) = make_uint2(lo[4], lo[5]);
-    // scales: a byte per operand
-    if (GPS == 4) {
-        uint32_t word = e << (8 * i);
-        word |= __builtin_amdgcn_update_dpp(0, word, 0xb1, 0xf, 0xf, true);
-        word |= __builtin_amdgcn_update_dpp(0, word, 0x4e, 0xf, 0xf, true);
-        if (i < 2) *(lds_u32 *)(to + MX_SCALES + (row + 32 * i) * 4) = i == 0 ? word : word - 0x05050505u;
-    } else {
-        uint32_t word = (e | ((e - 5u) << 8)) << (16 * chunk);
-        if (mx_chunk<BITS>(GPS, 1) == 1) word |= __builtin_amdgcn_update_dpp(0, word, 0xb1, 0xf, 0xf, true);
-        else word |= __builtin_amdgcn_update_dpp(0, word, 0x4e, 0xf, 0xf, true);
-        if (chunk == 0) *(lds_u32 *)(to + MX_SCALES + (row + 32 * half) * 4) = word;
-    }
-}
-
-// One block-scaled instruction.  which: the byte of `scales` that is this operand's.
-template <int BITS>
-__device__ inline mma_floatx16 mx_mfma(const uint4 &a, const uint2 &tail, const uint32_t *b, mma_floatx16 c, int which, uint32_t scales)
-{
-    constexpr int FORMAT = BITS == 2 ? 4 : 2, BACK = BITS == 2 ? 128 : 130;       // codes are q / 2, q / 8
-    const mx_i8 av = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, (int)tail.x, (int)tail.y, 0, 0};
-    const mx_i8 bv = {(int)b[0], (int)b[1], (int)b[2], (int)b[3], BITS == 2 ? 0 : (int)b[4], BITS == 2 ? 0 : (int)b[5], 0, 0};
-    switch (which) {
-    case 0: return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 2, FORMAT, 0, (int)scales, 0, BACK);
-    case 1: return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 2, FORMAT, 1, (int)scales, 0, BACK);
-    case 2: return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 2, FORMAT, 2, (int)scales, 0, BACK);
-    default: return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 2, FORMAT, 3, (int)scales, 0, BACK);
-    }
-}
-
-// X as block-scaled A operands; a workgroup takes one step of 32 rows, a lane a block of 32 k.
-template <int BITS, int GPS>
-__global__ __launch_bounds__(128) void prepare_mx(const QgPrepArgs A)
-{
-    const int step = blockIdx.x, row = threadIdx.x >> 2, i = threadIdx.x & 3, m = blockIdx.y * 32 + row;
-    for (int c = (blockIdx.y * gridDim.x + blockIdx.x) * 128 + threadIdx.x; c < A.counters; c += gridDim.x * gridDim.y * 128) A.arrived[c] = 0u;
-    const int k = step * 128 + 32 * i;
-    const float4 *src = (const float4 *)(A.X + (size_t)m * A.K + k);
-    float4 v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = m < A.M && k + 4 * j < A.K ? src[j] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    mx_put<BITS, GPS>(A.Xop + ((size_t)blockIdx.y * A.steps_padded + step) * (qg_codes_seq(true, GPS) * 1024), row, i, [&](int n) {
-        const float4 &f = v[n / 4];
-        return (n & 3) == 0 ? f.x : (n & 3) == 1 ? f.y : (n & 3) == 2 ? f.z : f.w;
-    });
-}
 
 // One item = OCT consecutive k of one row (a cell at 2 bits, a word of a cell otherwise).  A workgroup takes
 // one step of 32 rows and so writes its A operands whole: with a workgroup per row every 128-byte line of
@@ -392,27 +235,22 @@ template <int BITS, int GPS_, int MB, int TN, int KW, int HOW>
 __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs A)
 {
     using F = Fmt<BITS>;
-    constexpr bool FUSED = HOW == QG_CODES_FUSED || HOW == QG_CODES_MX_FUSED, SELF = HOW == QG_CODES_SELF;
+    constexpr bool FUSED = HOW == QG_CODES_FUSED, SELF = HOW == QG_CODES_SELF;
     constexpr bool LONG = GPS_ == 0;                     // groups of several steps
-    constexpr bool MX = HOW >= QG_CODES_MX;              // block-scaled operands: see compute_mx
-    constexpr bool SHORT = !MX && GPS_ >= 2;             // groups of 64 k or less: see compute_short
+    constexpr bool SHORT = GPS_ >= 2;                    // groups of 64 k or less: see compute_short
     constexpr int GPS = LONG ? 1 : GPS_;                 // xhat entries per step
     constexpr int NW = TN * KW;
     constexpr int L = BITS;                              // 128-bit code vectors per lane and step (128 k x 64 outputs)
     constexpr int GK = 8 / GPS;                          // sixteens of k per xhat
-    constexpr int SEQ = qg_codes_seq(MX, GPS_);          // KB of A operands per step and row block
+    constexpr int SEQ = GPS * (GK + 1);                  // A operands per step and row block
     constexpr int ROWS = 32 * MB;
     constexpr int CHUNK = MB * KW * SEQ;                 // KB of A operands per unit
     constexpr int NDMA = SELF ? 0 : (CHUNK + NW - 1) / NW;          // 1 KB copies per wavefront and unit
-    constexpr bool BOTH = MX && GPS == 4;                // hi and lo of a block in one operand
-    constexpr int NV = BOTH && BITS == 2 ? 2 * L : L;    // ... vectors held
-    constexpr int NC = MX && BITS == 2 && GPS == 2 ? 2 * L : NV;    // ... their loads
-    constexpr int PQ = MX ? 2 : 1;                       // scales and zero words: of outputs 0-31 and 32-63 apart
-    constexpr int NLOAD = NC + PQ * (1 + GPS);           // weight loads per wavefront and unit
+    constexpr int NLOAD = L + 1 + GPS;                   // weight loads per wavefront and unit
     constexpr int ZPER = 32 / F::ZBITS;
     constexpr int SLOTS = 2 * MB;                        // matrix instructions per A operand index
-    static_assert(MX || SEQ == GPS * (GK + 1), "operand count");
-    static_assert(MX || NLOAD + NDMA <= SEQ * SLOTS, "a request per slot");
+    static_assert(SEQ == qg_codes_seq(GPS_), "operand count");
+    static_assert(NLOAD + NDMA <= SEQ * SLOTS, "a request per slot");
     static_assert(!SELF || (MB == 1 && NW >= 2 * KW), "a wavefront per 16 rows and step");
     extern __shared__ __attribute__((aligned(16))) char smem[];       // [2][CHUNK KB], then the reduction's
 
@@ -420,7 +258,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tn = wave % TN, kw = wave / TN;
     const int half = lane >> 5, row = lane & 31;
-    const uint32_t lane4 = lane * 4, lane16 = lane * 16, row16 = row * 16;
+    const uint32_t lane4 = lane * 4, lane16 = lane * 16;
 
     // this workgroup's units [u, u1) in the order (block of outputs, block of rows, unit of K)
     int wg = blockIdx.x;
@@ -443,9 +281,9 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     int it = u - b * A.units;
 
     struct StepRegs {
-        uint4 v[NV];
-        float s[PQ * GPS];
-        uint32_t zw, zq;
+        uint4 v[L];
+        float s[GPS];
+        uint32_t zw;
     };
     // Where the next unit's data are (all scalar).  Reads past a tile's codes, scales or zero words (a
     // k-slice past K; the last step of a K that ends inside it) return zeros; the activations there are
@@ -498,26 +336,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     // request t of a unit: codes, zero word, scales, then the wavefront's share of the A operands, which
     // go from memory to LDS without passing through registers
     auto request = [&](int t, StepRegs &r, int stage) {
-        if (MX && t < NLOAD) {
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-            if (t < NC && BITS == 2 && GPS == 2) {       // outputs 32 (t / 2) ..., chunk t % 2: half a vector
-                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(codes_n, row16 + half * 8 + (t >> 1) * 512 + (t & 1) * 1024, 0, 0);
-                if (t & 1) r.v[t >> 1].z = v[0], r.v[t >> 1].w = v[1];
-                else r.v[t >> 1].x = v[0], r.v[t >> 1].y = v[1];
-            } else if (t < NC) {
-                const uint32_t at = BOTH ? (BITS == 2 ? row16 + (t >> 1) * 512 + (t & 1) * 1024 : lane16 + t * 1024)
-                                  : row16 + half * 1024 + (BITS == 2 ? t * 512 : (t >> 1) * 512 + (t & 1) * 2048);
-                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(codes_n, at, 0, 0);
-                r.v[t] = make_uint4(v[0], v[1], v[2], v[3]);
-            } else if (t < NC + 2) {
-                const uint32_t z = __builtin_amdgcn_raw_buffer_load_b32(zeros_n, row * 4 + (t - NC) * 128, 0, 0);
-                if (t == NC) r.zw = z;
-                else r.zq = z;
-            } else {
-                r.s[t - NC - 2] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(scales_n, row * 4 + (t - NC - 2) * 128, 0, 0));
-            }
-        } else if (t < L) {
+        if (t < L) {
             typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
             const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(codes_n, lane16 + t * 1024, 0, 0);
             r.v[t] = make_uint4(v[0], v[1], v[2], v[3]);
@@ -633,12 +452,12 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     };
 
     // ---- accumulators ----
-    constexpr int NT = SHORT || MX ? 2 : 2 * MB;
+    constexpr int NT = SHORT ? 2 : 2 * MB;
     mma_floatx16 acc[NT];                     // T of the running group: [2 mb + (outputs 0-31: 0, 32-63: 1)]; SHORT: of two tiles
     float y[2 * MB][16];
     const mma_floatx16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     float sP = 0.0f, sQ = 0.0f;               // scales of the group the accumulators belong to
-    float sc[2][2];                           // SHORT: [outputs 0-31, 32-63][group parity]; MX: [1][1] of the last tile
+    float sc[2][2];                           // SHORT: [outputs 0-31, 32-63][group parity]
     uint32_t held = ~0u;                      // LONG: that group
     auto reset = [&]() {
         // (an opaque zero: the accumulators must not be cleared ahead of the sums over parts, which want
@@ -881,135 +700,13 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
             }
     };
 
-    // Block-scaled operands.  As compute_short: a group is taken one tile of 32 rows x 32 outputs after the other, each a
-    // chain of instructions (xhat, then the products) into one of two accumulators, with the fold of the tile before under
-    // it, and the operands of outputs 32-63 are unpacked under the chains of outputs 0-31 and the other way round.
-    auto compute_mx = [&](const StepRegs &r, uint32_t step, int stage, StepRegs &req) {
-        constexpr int NX = mx_products(GPS), R = 1 + NX;
-        constexpr int CHUNKS = GPS == 1 ? 2 : 1;           // of a group
-        constexpr int WORDS = BITS == 2 ? 4 : 6;           // of an operand
-        constexpr int PIECES = 1 + 2 * CHUNKS;
-        constexpr int REQUESTS = NLOAD + NDMA, SLOTS_MX = 2 * MB * GPS * R;
-        // few instructions per unit: all requests in front of them
-        constexpr bool AT_START = GPS == 1;
-        constexpr int PER_SLOT = (REQUESTS + SLOTS_MX - 1) / SLOTS_MX;
-        const char *xs = smem + (stage * CHUNK + kw * SEQ) * 1024;
-        const uint32_t g = LONG ? __umulhi(step, A.group_magic) : step * GPS;
-        const uint32_t zshift = F::ZBITS * (g % ZPER);
-        const uint32_t zmask = half ? 0u : (1u << F::ZBITS) - 1u;        // (lanes 32-63: k 8-15 of the bf16 instruction, none)
-        uint32_t bz[2], bo[2][CHUNKS][WORDS], w[4];
-        uint4 a[MB == 1 ? 2 : 1][MB][NX];
-        uint2 tail[MB == 1 ? 2 : 1][MB][NX], xh[MB == 1 ? 2 : 1][MB];
-        uint32_t scales[MB];
-        auto piece = [&](int pq, int grp, int j) {
-            if (j == 0) {
-                const float z = (float)(((pq ? r.zq : r.zw) >> (zshift + F::ZBITS * grp)) & zmask);
-                bz[pq] = __builtin_amdgcn_perm(__float_as_uint(z), __float_as_uint(z), 0x03020302u);
-                asm volatile("" : "+v"(bz[pq]));
-                return;
-            }
-            const int c = (j - 1) >> 1, h = (j - 1) & 1, chunk = grp * CHUNKS + c;
-            uint32_t *o = bo[pq][c] + h * (WORDS / 2);
-            if constexpr (BITS == 2) {
-                const uint32_t x = word_of(r.v[BOTH ? 2 * pq + (grp >> 1) : pq], 2 * (chunk & 1) + h);
-                o[0] = x & 0x33333333u;
-                o[1] = (x >> 2) & 0x33333333u;
-                asm volatile("" : "+v"(o[0]), "+v"(o[1]));
-            } else {
-                // sixteen nibbles to sixteen six-bit fields: each field takes a nibble that is in its place or two bits below
-                uint32_t x, x1;
-                if constexpr (BOTH) {
-                    if (pq == 0) {
-                        const auto s0 = __builtin_amdgcn_permlane32_swap(word_of(r.v[grp], 2 * h), word_of(r.v[grp], 2 * h), false, false);
-                        const auto s1 = __builtin_amdgcn_permlane32_swap(word_of(r.v[grp], 2 * h + 1), word_of(r.v[grp], 2 * h + 1), false, false);
-                        x = s0[0], x1 = s1[0];
-                        w[2 * h] = s0[1], w[2 * h + 1] = s1[1];
-                    } else {
-                        x = w[2 * h], x1 = w[2 * h + 1];
-                    }
-                } else {
-                    x = word_of(r.v[2 * pq + chunk], 2 * h), x1 = word_of(r.v[2 * pq + chunk], 2 * h + 1);
-                }
-                const uint32_t up = x << 2, up1 = x1 << 2;
-                o[0] = (x & 0x0f00f00fu) | (up & 0xc03c03c0u);
-                o[1] = (x1 & 0xf00f00f0u) | (up & 0x03c03c00u) | (x >> 30);
-                o[2] = (x1 & 0x00f00f00u) | (up1 & 0x3c03c03cu);
-                asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]));
-            }
-        };
-        auto read_a = [&](int grp, int mb) {
-            const char *from = xs + mb * KW * SEQ * 1024;
-            const int b = MB == 1 ? grp & 1 : 0;
-            xh[b][mb] = *(const lds_u64 *)(from + MX_XHATS + grp * 256 + row * 8);
-#pragma unroll
-            for (int q = 0; q < NX; ++q) {
-                a[b][mb][q] = *(const lds_u128 *)(from + (grp * NX + q) * 1024 + lane16);
-                tail[b][mb][q] = *(const lds_u64 *)(from + MX_TAILS + (grp * NX + q) * 512 + lane * 8);
-            }
-        };
-        if constexpr (AT_START) {
-#pragma unroll
-            for (int t = 0; t < REQUESTS; ++t) request(t, req, stage ^ 1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            scales[mb] = *(const lds_u32 *)(xs + mb * KW * SEQ * 1024 + MX_SCALES + lane4);
-            read_a(0, mb);
-        }
-#pragma unroll
-        for (int j = 0; j < PIECES; ++j) piece(0, 0, j);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int grp = 0; grp < GPS; ++grp)
-#pragma unroll
-            for (int t = 0; t < 2 * MB; ++t) {
-                const int pq = t / MB, mb = t % MB, ab = MB == 1 ? grp & 1 : 0;
-                const int tp = t == 0 ? 2 * MB - 1 : t - 1;                    // the tile before this one
-                const float s = t > 0 ? r.s[2 * grp + tp / MB] : grp > 0 ? r.s[2 * grp - 1] : sc[1][1];
-                float *yp = y[2 * (tp % MB) + tp / MB];
-#pragma unroll
-                for (int q = 0; q < R; ++q) {
-                    if (q == 0) {
-                        MmaOperand xa, zb;
-                        xa.q = make_uint4(xh[ab][mb].x, xh[ab][mb].y, 0u, 0u);
-                        zb.q = make_uint4(bz[pq], bz[pq], 0u, 0u);
-                        acc[t & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa.v, zb.v, zero16, 0, 0, 0);
-                    } else {
-                        acc[t & 1] = mx_mfma<BITS>(a[ab][mb][q - 1], tail[ab][mb][q - 1], bo[pq][BOTH ? 0 : (q - 1) >> 1], acc[t & 1],
-                                                   (grp * NX + q - 1) & 3, scales[mb]);
-                    }
-                    // rows whose operands nothing of this group needs any more, or (row block 1) needs next
-                    if (MB == 1 && t == 0 && q == 0 && grp + 1 < GPS) read_a(grp + 1, 0);
-                    if (MB == 2 && t == 3 && q == 0 && grp + 1 < GPS) read_a(grp + 1, 0);
-                    if (MB == 2 && t == 0 && q == 0 && grp > 0) read_a(grp, 1);
-                    const int at = mb * R + q;                                 // of MB * R slots per half of a group
-#pragma unroll
-                    for (int j = at * PIECES / (MB * R); j < (at + 1) * PIECES / (MB * R); ++j) {
-                        if (pq == 0) piece(1, grp, j);
-                        else if (grp + 1 < GPS) piece(0, grp + 1, j);
-                    }
-                    if (q > 0) {
-#pragma unroll
-                        for (int i = (q - 1) * 16 / NX; i < q * 16 / NX; ++i) yp[i] = fmaf(s, acc[(t & 1) ^ 1][i], yp[i]);
-                    }
-                    if constexpr (!AT_START) {
-#pragma unroll
-                        for (int n = 0; n < PER_SLOT; ++n) request(((grp * 2 * MB + t) * R + q) * PER_SLOT + n, req, stage ^ 1);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        sc[1][1] = r.s[2 * GPS - 1];
-    };
-
     int stage = 0;                                         // of the A operands of the next unit
-    constexpr bool APART = qg_codes_slices_apart(MX, GPS_, MB, TN, KW);
+    constexpr bool APART = qg_codes_slices_apart(GPS_, MB, TN, KW);
     auto slices_at = [&]() { return APART ? 2 * CHUNK * 1024 : (stage ^ 1) * CHUNK * 1024; };
     // End of a block's units in this workgroup: the whole sum to Y, a part of it to this part's place
     // among the partial results.
     auto finish = [&]() {
-        if constexpr (SHORT || MX) {
+        if constexpr (SHORT) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) y[2 * MB - 1][i] = fmaf(sc[1][1], acc[1][i], y[2 * MB - 1][i]);
         } else {
@@ -1178,11 +875,10 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
     auto arrive = [&](StepRegs &r) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int i = 0; i < NV; ++i) asm volatile("" : "+v"(r.v[i].x), "+v"(r.v[i].y), "+v"(r.v[i].z), "+v"(r.v[i].w));
+        for (int i = 0; i < L; ++i) asm volatile("" : "+v"(r.v[i].x), "+v"(r.v[i].y), "+v"(r.v[i].z), "+v"(r.v[i].w));
 #pragma unroll
-        for (int g = 0; g < PQ * GPS; ++g) asm volatile("" : "+v"(r.s[g]));
+        for (int g = 0; g < GPS; ++g) asm volatile("" : "+v"(r.s[g]));
         asm volatile("" : "+v"(r.zw));
-        if constexpr (MX) asm volatile("" : "+v"(r.zq));
         __syncthreads();
     };
     auto unit = [&](StepRegs &use, StepRegs &req) {
@@ -1196,8 +892,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         if constexpr (SELF) {
             if (!last) load_x();
         }
-        if constexpr (MX) compute_mx(use, step, stage, req);
-        else if constexpr (SHORT) compute_short(use, step, stage, req);
+        if constexpr (SHORT) compute_short(use, step, stage, req);
         else compute(use, step, stage, req);
         stage ^= 1;
         if (ends || last) {
@@ -1227,10 +922,9 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
 template <int BITS, int GPS, int MB, int TN, int KW, int HOW>
 int codes_launch(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKernelInfo *query)
 {
-    constexpr bool MX = HOW >= QG_CODES_MX;
-    static_assert(qg_codes_lds(MX, GPS, MB, TN, KW) <= QG_LDS_BYTES, "LDS of a workgroup");
-    static_assert(qg_codes_slices_apart(MX, GPS, MB, TN, KW) || (KW - 1) * TN * 32 * 256 <= qg_codes_stages(MX, GPS, MB, KW) / 2, "slices in a stage");
-    constexpr size_t lds = qg_codes_lds(MX, GPS, MB, TN, KW);
+    static_assert(qg_codes_lds(GPS, MB, TN, KW) <= QG_LDS_BYTES, "LDS of a workgroup");
+    static_assert(qg_codes_slices_apart(GPS, MB, TN, KW) || (KW - 1) * TN * 32 * 256 <= qg_codes_stages(GPS, MB, KW) / 2, "slices in a stage");
+    constexpr size_t lds = qg_codes_lds(GPS, MB, TN, KW);
     const void *f = (const void *)gemm_codes<BITS, GPS, MB, TN, KW, HOW>;
     if (query) {
         *query = {f, TN * KW * 64, lds};
@@ -1257,12 +951,6 @@ int codes_launch_how(const QgCodesArgs &A, int workgroups, hipStream_t st, QgKer
 {
     if (A.self) {
         if constexpr (MB == 1 && GPS <= 4) return codes_launch<BITS, GPS, MB, 8 / KW, KW, QG_CODES_SELF>(A, workgroups, st, query);
-        return QG_ERR_UNSUPPORTED;
-    }
-    if (A.mx) {
-        if constexpr (qg_codes_mx(BITS, GPS))
-            return A.fused ? codes_launch<BITS, GPS, MB, 8 / KW, KW, QG_CODES_MX_FUSED>(A, workgroups, st, query)
-                           : codes_launch<BITS, GPS, MB, 8 / KW, KW, QG_CODES_MX>(A, workgroups, st, query);
         return QG_ERR_UNSUPPORTED;
     }
     return A.fused ? codes_launch<BITS, GPS, MB, 8 / KW, KW, QG_CODES_FUSED>(A, workgroups, st, query)
@@ -1298,13 +986,6 @@ int codes_launch_any(int gps, int mb, const QgCodesArgs &A, int workgroups, hipS
 template <int BITS>
 void codes_prepare(const QgPrepArgs &P, int rows_padded, hipStream_t st)
 {
-    const dim3 grid((unsigned)P.steps_padded, (unsigned)rows_padded / 32);
-    if constexpr (BITS != 3) if (P.mx) {
-        if (P.groupk == 128) hipLaunchKernelGGL((prepare_mx<BITS, 1>), grid, dim3(128), 0, st, P);
-        if (P.groupk == 64) hipLaunchKernelGGL((prepare_mx<BITS, 2>), grid, dim3(128), 0, st, P);
-        if (P.groupk == 32) hipLaunchKernelGGL((prepare_mx<BITS, 4>), grid, dim3(128), 0, st, P);
-        return;
-    }
     hipLaunchKernelGGL(prepare_x<BITS>, dim3((unsigned)P.steps_padded, (unsigned)rows_padded / 32), dim3(32 * 128 / (BITS == 2 ? 16 : 8)), 0, st, P);
 }
 

@@ -794,14 +794,6 @@ int codes_gps(const QgLayout &L)       // groups per step of 128 k, 0: groups of
     return L.group >= least && KC % L.group == 0 ? KC / L.group : -1;
 }
 
-// Products that run on block-scaled operands where prepare_x would make bf16 ones.  4-bit groups of 32: where the unpacking, twice
-// that of the others, and the longer conversion of X are paid back, us bf16 | block-scaled: 16000 x 8192 M = 50 39.6 | 38.0, M = 128 64.1 |
-// 61.5, 8192 x 22016 M = 100 77.5 | 76.2; but 17000 x 4160 M = 32 21.0 | 21.7, 12000 x 8320 M = 28 24.8 | 25.1, 12000 x 4128 M = 70 33.0 | 33.8, 15039 x 6208 M = 43 28.2 | 29.2.
-bool codes_mx(const QgLayout &L, int gps, int M)
-{
-    return qg_codes_mx(L.bits, gps) && (L.bits != 4 || gps != 4 || (M > 32 && L.K >= 8192));
-}
-
 // Workspace of the raw-code path: A operands, counters, partial results of the K ranges.
 struct CodesSpace {
     size_t arrived_off, partial_off, total;
@@ -814,7 +806,7 @@ CodesSpace codes_space(const QgLayout &L, int gps, int M)
     W.rows_padded = (M + rows_per_block - 1) / rows_per_block * rows_per_block;
     W.steps_padded = (int)((L.K + 4 * KC - 1) / (4 * KC) * 4);
     W.groupk = L.group > KC ? KC : L.group;
-    W.arrived_off = (size_t)W.rows_padded / 32 * W.steps_padded * qg_codes_seq(false, gps) * 1024;
+    W.arrived_off = (size_t)W.rows_padded / 32 * W.steps_padded * qg_codes_seq(gps) * 1024;
     W.partial_off = qg_round_up(W.arrived_off + (size_t)L.tiles * 4 * sizeof(uint32_t), QG_SECTION_ALIGN);
     W.total = qg_round_up(W.partial_off + (size_t)QG_MAX_SEGMENTS * L.tiles * ((M + 7) / 8) * 2048, QG_SECTION_ALIGN);
     return W;
@@ -825,7 +817,7 @@ CodesSpace codes_space(const QgLayout &L, int gps, int M)
 // `quota` consecutive units per workgroup whatever blocks they fall into.
 struct CodesPlan {
     int mb, tn, kw, zblocks, blocks, units, ranges, quota, workgroups, parts;
-    bool fused, self, mx;
+    bool fused, self;
     int kernels;               // of a call
     double us, kernels_us;     // what it costs, and what its kernels take of that (codes_price)
     double cut_us;             // ... as blocks of 64 rows are cut by (codes_cut_us)
@@ -1248,9 +1240,6 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         if (raw && !planned) C = codes_plan(L, gps, M, knob_splits, false);
     }
     if (raw) {
-        // (asked for by number: the kind of operand that the built-in plan takes, so that a forced cut changes the order of
-        // the sums alone)
-        C.mx = codes_mx(L, gps, M) && !C.self && (knob_shape == 0 || !codes_plan(L, gps, M, 0, false).self);
         const CodesSpace W = codes_space(L, gps, M);
         char *ws = (char *)workspace;
         QgPrepArgs P;
@@ -1262,7 +1251,6 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         P.groupk = W.groupk;
         P.arrived = (uint32_t *)(ws + W.arrived_off);
         P.counters = C.fused ? (int)L.tiles * C.zblocks : 0;
-        P.mx = C.mx;
         QgCodesArgs A;
         const char *base = (const char *)packed;
         A.codes = base + L.codes_off;
@@ -1292,7 +1280,6 @@ int gemm_small(const void *packed, int64_t N, int64_t K, int bits, int group, co
         A.X = X;
         A.K = (int)K;
         A.kw = C.kw;
-        A.mx = C.mx;
         auto main_kernel = [&](KernelInfo *query) {
             return bits == 4 ? qg_codes_launch_b4(gps, C.mb, A, C.workgroups, st, query)
                  : bits == 2 ? qg_codes_launch_b2(gps, C.mb, A, C.workgroups, st, query)

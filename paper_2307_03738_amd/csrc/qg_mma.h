@@ -35,8 +35,6 @@ union MmaOperand {
 // both accesses go through types that may alias anything, so that they stay in program order
 typedef uint16_t __attribute__((may_alias)) lds_u16;
 typedef uint4 __attribute__((may_alias)) lds_u128;
-typedef uint2 __attribute__((may_alias)) lds_u64;
-typedef uint32_t __attribute__((may_alias)) lds_u32;
 
 #define QG_MMA_MAGIC 0x43004300u       // two bf16 128.0
 

@@ -1,8 +1,10 @@
 """Launch plans of qg_gemm_small, looked at without a GPU (tests/launches.py; 256 compute units)."""
+import random
+
 import pytest
 
 from tests.launches import launches
-from tests.test_gpu_parity import I8_CASES, M1_CASES, MANY_ROWS_CASES, MX_CASES, ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
+from tests.test_gpu_parity import AHEAD_CASES, I8_CASES, M1_CASES, MANY_ROWS_CASES, ROW_BLOCK_CASES, ROWS_CASES, SELF_CASES, UNIT_CASES
 
 
 @pytest.fixture(scope="module")
@@ -114,15 +116,26 @@ def test_own_operand_cases_are_cut_as_stated(tmp, case):
     assert names == ["gemm_codes"] + ["add_parts"] * (parts != 1)
 
 
-# The GPU tests of block-scaled operands take them, with every number of groups per step, in blocks of 32 and of 64 rows, whole
-# ranges of K and units dealt evenly, parts added either way; the product asked for by number takes the same operands
-def test_block_scaled_cases_take_those_operands(tmp):
-    kernels = [_product(r)[0] for r in launches(tmp, [{"problem": c} for c in MX_CASES])]
-    assert {k["template"][5] for k in kernels} == {3, 4}
-    assert {(*k["template"][:2],) for k in kernels} == {(bits, gps) for bits in (2, 4) for gps in (0, 1, 2, 4)}
-    assert {k["template"][2] for k in kernels} == {1, 2} and {k["args"]["ranges"] == 0 for k in kernels} == {True, False}
-    by_number = [_product(r)[0] for r in launches(tmp, [{"problem": c, "splits": 2, "shape": 13} for c in MX_CASES])]
-    assert {k["template"][5] for k in by_number} <= {3, 4}
+# The GPU tests of operands made ahead take every instance of the kernel (bits, groups per step, blocks of rows, tiles, k-slices, who adds) that
+# the plan takes with them over random products
+def test_cases_of_operands_made_ahead_take_every_instance(tmp):
+    rng = random.Random(1)
+    problems = []
+    while len(problems) < 3000:
+        bits = rng.choice([2, 3, 4])
+        group = rng.choice([32, 64, 128, 256, 512, 0] + [16] * (bits == 4))
+        grain = group or 128
+        K = max(1, round(512 * 43.0 ** rng.random() / grain)) * grain
+        N = round(512 * (min(22016, 22016 * 8192 // K) / 512) ** rng.random())
+        problems.append((N, K, bits, group or K, round(2 * 64.0 ** rng.random())))
+
+    def instances(calls):
+        kernels = [k for r in launches(tmp, [{"problem": c} for c in calls]) for k in r["kernels"] if k["name"] == "gemm_codes"]
+        return [tuple(k["template"]) for k in kernels if not k["args"]["self"]]
+
+    tested = instances(AHEAD_CASES)
+    assert len(tested) == len(AHEAD_CASES)
+    assert set(instances(problems)) <= set(tested) and len(set(tested)) == 50
 
 
 @pytest.mark.parametrize("problem,name", [(c, "gemv_mma4i") for c in ROWS_CASES] + [
