@@ -713,48 +713,66 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
 #pragma unroll
             for (int k = 0; k < 2 * MB; ++k) fold(k);
         }
-        // The k-slices of a tile share its sum: slice o takes OWN quads of every 32 rows (a quad: 8 rows x 32 outputs, four
-        // registers), hands the others theirs and adds its own in slice order.  (Slice 0 adding and storing all: 10135 x 640 3-bit g64
-        // M = 11 6.74 us for 6.34, 6691 x 2112 4-bit g64 M = 92 14.4 for 13.8; 40 products of 5 ... 128 rows 0.98 of the time.)
+        // The sum over the k-slices of a tile, in slice order.  Four slices (blocks of 32 rows) share it: slice o takes OWN quads of the rows (a
+        // quad: 8 rows x 32 outputs, four registers) and is handed the others' parts of those.  Of two slices slice 0 takes all, 32 rows at
+        // a time.  (us, slice 0 | shares.  Four slices: 10135 x 640 3-bit g64 M = 11 6.9 | 6.4, 7146 x 2720 2-bit g32 M = 122 17.4 | 16.3, 13824 x
+        // 5120 3-bit g64 M = 37 20.0 | 19.6, 149 products of 5 ... 128 rows 0.98 of the time.  Two: 24 products 1.006, and registers that the loop
+        // wants: 21663 x 7680 4-bit g64 M = 59, 19 spilled, 40.0 | 43.0, 21060 x 3712 2-bit g64 M = 44 22.3 | 22.9.)
+        constexpr bool SHARED = KW == 4;
         constexpr int OWN = 8 / KW;
-        if constexpr (KW > 1) {
-            if constexpr (!APART) __syncthreads();           // every wavefront has read the unit's operands
+        static_assert(KW == 2 || (SHARED && MB == 1), "slices of a workgroup");
+        if constexpr (!APART) __syncthreads();               // every wavefront has read the unit's operands
+        if constexpr (SHARED) {
             float *red = (float *)(smem + slices_at()) + tn * ((KW - 1) * 32 * 64) + lane;
+#pragma unroll
+            for (int o = 0; o < KW; ++o) {
+                if (o == kw) continue;
+                float *dst = red + (o * (KW - 1) + (kw < o ? kw : kw - 1)) * (OWN * 4 * 64);
+#pragma unroll
+                for (int i = 0; i < OWN * 4; ++i) dst[i * 64] = y[(o * OWN + i / 4) % 2][4 * ((o * OWN + i / 4) / 2) + i % 4];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int o = 0; o < KW; ++o) {
+                if (o != kw) continue;
+                const float *src = red + o * (KW - 1) * (OWN * 4 * 64);
+#pragma unroll
+                for (int i = 0; i < OWN * 4; ++i) {
+                    float &mine = y[(o * OWN + i / 4) % 2][4 * ((o * OWN + i / 4) / 2) + i % 4];
+                    float sum = o == 0 ? mine : src[i * 64];
+#pragma unroll
+                    for (int j = 1; j < KW; ++j) sum += j == o ? mine : src[((j < o ? j : j - 1) * OWN * 4 + i) * 64];
+                    mine = sum;
+                }
+            }
+        } else {
+            float *red = (float *)(smem + slices_at()) + lane;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 if (mb > 0) __syncthreads();
+                if (kw > 0) {
+                    float *dst = red + ((kw - 1) * TN + tn) * (32 * 64);
 #pragma unroll
-                for (int o = 0; o < KW; ++o) {
-                    if (o == kw) continue;
-                    float *dst = red + (o * (KW - 1) + (kw < o ? kw : kw - 1)) * (OWN * 4 * 64);
-#pragma unroll
-                    for (int i = 0; i < OWN * 4; ++i) dst[i * 64] = y[2 * mb + (o * OWN + i / 4) % 2][4 * ((o * OWN + i / 4) / 2) + i % 4];
+                    for (int i = 0; i < 32; ++i) dst[i * 64] = y[2 * mb + i / 16][i % 16];
                 }
                 __syncthreads();
+                if (kw == 0) {
 #pragma unroll
-                for (int o = 0; o < KW; ++o) {
-                    if (o != kw) continue;
-                    const float *src = red + o * (KW - 1) * (OWN * 4 * 64);
+                    for (int j = 1; j < KW; ++j) {
+                        const float *src = red + ((j - 1) * TN + tn) * (32 * 64);
 #pragma unroll
-                    for (int i = 0; i < OWN * 4; ++i) {
-                        float &mine = y[2 * mb + (o * OWN + i / 4) % 2][4 * ((o * OWN + i / 4) / 2) + i % 4];
-                        float sum = o == 0 ? mine : src[i * 64];
-#pragma unroll
-                        for (int j = 1; j < KW; ++j) sum += j == o ? mine : src[((j < o ? j : j - 1) * OWN * 4 + i) * 64];
-                        mine = sum;
+                        for (int i = 0; i < 32; ++i) y[2 * mb + i / 16][i % 16] += src[i * 64];
                     }
                 }
             }
         }
-        // body(qd) for every quad 8 mb + 2 band + pq of the tile that this slice has
+        // SHARED: body(qd) for every quad 2 band + pq of the tile that this slice has
         auto own_quads = [&](auto body) {
 #pragma unroll
             for (int o = 0; o < KW; ++o) {
                 if (o != kw) continue;
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int i = 0; i < OWN; ++i) body(8 * mb + o * OWN + i);
+                for (int i = 0; i < OWN; ++i) body(o * OWN + i);
             }
         };
         const int tb = tiles_of(b), z = b - tb * A.zblocks, m0 = z * ROWS;
@@ -786,11 +804,20 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         };
         constexpr int QUADS = 8 * MB;                          // quad 8 mb + 2 band + pq of a tile
         if (nseg == 1) {
-            if (tile >= A.tiles) return;
-            own_quads([&](int qd) {
-                const int r0 = 8 * (qd / 2), k = 2 * (qd / 8) + qd % 2;
-                if (r0 < rows_left) store_y(r0, qd % 2, &y[k][4 * ((qd / 2) % 4)]);
-            });
+            if constexpr (SHARED) {
+                if (tile >= A.tiles) return;
+                own_quads([&](int qd) {
+                    const int r0 = 8 * (qd / 2);
+                    if (r0 < rows_left) store_y(r0, qd % 2, &y[qd % 2][4 * (qd / 2)]);
+                });
+            } else {
+                if (kw > 0 || tile >= A.tiles) return;
+#pragma unroll
+                for (int qd = 0; qd < QUADS; ++qd) {
+                    const int r0 = 8 * (qd / 2), k = 2 * (qd / 8) + qd % 2;
+                    if (r0 < rows_left) store_y(r0, qd % 2, &y[k][4 * ((qd / 2) % 4)]);
+                }
+            }
             return;
         }
         // A part of the sum, for add_parts or (fused) for the workgroup that comes last: every workgroup
@@ -810,30 +837,41 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
             return u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
         };
         if constexpr (!FUSED) {
-            if (tile >= A.tiles) return;
-            const rsrc_t part = part_of(seg);
-            own_quads([&](int qd) {                            // (bands past M fall outside the buffer and are dropped)
-                __builtin_amdgcn_raw_buffer_store_b128(quad_of(qd), part, lane16 + qd * 1024, 0, 0);
-            });
+            if ((!SHARED && kw > 0) || tile >= A.tiles) return;
+            const rsrc_t part = part_of(seg);                  // (bands past M fall outside the buffer and are dropped)
+            if constexpr (SHARED) {
+                own_quads([&](int qd) { __builtin_amdgcn_raw_buffer_store_b128(quad_of(qd), part, lane16 + qd * 1024, 0, 0); });
+            } else {
+#pragma unroll
+                for (int qd = 0; qd < QUADS; ++qd) __builtin_amdgcn_raw_buffer_store_b128(quad_of(qd), part, lane16 + qd * 1024, 0, 0);
+            }
             return;
         } else {
         bool last = false;
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        if (tile < A.tiles) {
-            const rsrc_t part = part_of(seg);
-            own_quads([&](int qd) { __builtin_amdgcn_raw_buffer_store_b128(quad_of(qd), part, lane16 + qd * 1024, 0, SC1); });
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (SHARED) {
+            if (tile < A.tiles) {
+                const rsrc_t part = part_of(seg);
+                own_quads([&](int qd) { __builtin_amdgcn_raw_buffer_store_b128(quad_of(qd), part, lane16 + qd * 1024, 0, SC1); });
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            __syncthreads();                                   // all slices' quads are written, and the sums have been read
         }
-        if constexpr (KW > 1) __syncthreads();                 // all slices' quads are written, and the sums have been read
         if (kw == 0 && tile < A.tiles) {
+            if constexpr (!SHARED) {
+                const rsrc_t part = part_of(seg);
+#pragma unroll
+                for (int qd = 0; qd < QUADS; ++qd) __builtin_amdgcn_raw_buffer_store_b128(quad_of(qd), part, lane16 + qd * 1024, 0, SC1);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
             uint32_t before = 0;
             if (lane == 0)
                 before = __hip_atomic_fetch_add(A.arrived + (size_t)tile * A.zblocks + z, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             last = (int)__builtin_amdgcn_readfirstlane(before) + 1 == nseg;
         }
-        if constexpr (KW > 1) {
-            // slice 0 tells the others
-            uint32_t *flag = (uint32_t *)(smem + slices_at()) + tn;
+        {
+            // slice 0 tells the others, in a word that is read no more (SHARED: by nobody, else by slice 0 of its own tile alone)
+            uint32_t *flag = (uint32_t *)(smem + slices_at()) + (SHARED ? tn : tn * (32 * 64));
             if (kw == 0 && lane == 0) *flag = last;
             __syncthreads();
             last = __builtin_amdgcn_readfirstlane(*flag) != 0;

@@ -133,3 +133,12 @@ def test_narrow_calls_reject_bad_arguments_without_a_gpu(qg):
     assert L.qg_gemv_narrow(16, 64, 1000, 4, 128, 64, 64, None) == 2        # K % G != 0
     assert L.qg_gemv_grouped_narrow(None, 1, None) == 1
     assert L.qg_set_narrow_tuning(3) == 2 and L.qg_set_narrow_tuning(0) == 0
+
+
+def test_no_raw_code_product_spills_registers(qg):
+    # the loops of gemm_codes hold up to 256 registers, and what spills is stored and loaded again in every unit of K (21663 x 7680 4-bit
+    # groups of 64, M = 59: 40.0 us, with 19 registers spilled 43.0); from the kernels' metadata in the library
+    from paper_2307_03738_amd import build
+    with open(os.environ.get("QG_LIBRARY", build.OUT), "rb") as f:
+        found = re.findall(rb"\.name\xd9.(_ZN12_GLOBAL__N_110gemm_codes\w+)\xbb\.private_segment_fixed_size(.)", f.read(), re.S)
+    assert len(set(found)) == 61 and [name for name, scratch in found if scratch != b"\0"] == []
