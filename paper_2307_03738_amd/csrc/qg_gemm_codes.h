@@ -716,7 +716,7 @@ __global__ __launch_bounds__(TN * KW * 64, 2) void gemm_codes(const QgCodesArgs 
         // The sum over the k-slices of a tile, in slice order.  Four slices (blocks of 32 rows) share it: slice o takes OWN quads of the rows (a
         // quad: 8 rows x 32 outputs, four registers) and is handed the others' parts of those.  Of two slices slice 0 takes all, 32 rows at
         // a time.  (us, slice 0 | shares.  Four slices: 10135 x 640 3-bit g64 M = 11 6.9 | 6.4, 7146 x 2720 2-bit g32 M = 122 17.4 | 16.3, 13824 x
-        // 5120 3-bit g64 M = 37 20.0 | 19.6, 149 products of 5 ... 128 rows 0.98 of the time.  Two: 24 products 1.006, and registers that the loop
+        // 5120 3-bit g64 M = 37 20.0 | 19.7, 149 products of 5 ... 128 rows 0.98 of the time.  Two: 24 products 1.006, and registers that the loop
         // wants: 21663 x 7680 4-bit g64 M = 59, 19 spilled, 40.0 | 43.0, 21060 x 3712 2-bit g64 M = 44 22.3 | 22.9.)
         constexpr bool SHARED = KW == 4;
         constexpr int OWN = 8 / KW;

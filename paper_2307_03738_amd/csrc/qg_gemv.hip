@@ -1305,9 +1305,9 @@ __global__ __launch_bounds__(512) void gemv_mma4i(QG_FIRST_BLOCKS, const GemvArg
 // vector, and words are exchanged between lanes (loaded one by one: 1.2 to 1.3 of the time); of 16 half of the lanes meet zeros.
 // What bounds it: 8 KB of X per 4 KB of codes through a compute unit's load path, and launch and first miss.  The 32 x 32 x 16
 // instruction, which this was written with (24 per step, of 32 cycles, and 24 operand reads from LDS; now 20 of 16 and 4),
-// left half of its rows idle and took as long as all vector instructions.  us per call, 32 x 32 | 16 x 16: 11008 x 4096 g128
-// M = 16 11.4 | 9.5, 4656 x 13184 g128 M = 5 19.9 | 15.8, 5416 x 7936 g64 M = 15 16.7 | 15.0, 18689 x 2304 g32 M = 6 13.4 | 12.3,
-// 9260 x 4352 g16 M = 8 16.4 | 16.0.
+// left half of its rows idle and took as long as all vector instructions.  us per call, 100 calls in sequence, this kernel asked for by number,
+// 32 x 32 | 16 x 16: 11008 x 4096 g128 M = 16 11.0 | 9.3 (among a program's passes 10.5 | 9.1), 4656 x 13184 g128 M = 5 20.0 | 15.8, 5416 x 7936 g64
+// M = 15 16.7 | 15.0, 18689 x 2304 g32 M = 6 13.2 | 12.2, 9260 x 4352 g16 M = 8 16.2 | 15.7.
 // ---------------------------------------------------------------------------------------
 typedef float mma_floatx4 __attribute__((ext_vector_type(4)));
 
